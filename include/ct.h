@@ -68,11 +68,13 @@ typedef struct ct_table ct_table;
  * batches of many jobs), SPLIT spreads updateTable over workgroups of 8
  * granules and filterDomains over workgroups of 4 domain words.  NODES is the
  * search-node schedule of ct_propagate_batch: when every job of a batch is a
- * CT_JOB_FROM_ROOT propagation of the same table of at most 256 support rows
- * (sum of the domain sizes), one workgroup per (one or two granules, up to
- * 64 jobs) stages those granules of every support row in LDS and evaluates
- * updateTable for its jobs from there, so the supports are read once per
- * group of jobs; other batches and single calls fall back to AUTO.  AUTO picks SOLO for tables of at most 4
+ * CT_JOB_FROM_ROOT propagation of the same positive table of at most about
+ * 2,400 support rows (sum of the domain sizes: one bit vector over 512 jobs
+ * per row fits a workgroup's LDS), updateTable is evaluated per tuple for 64
+ * jobs at a time.  It reads a list of the tuples' row numbers (2 bytes per
+ * cell) that the library makes, in device memory of the table, once the
+ * table has 64 slots (or has CT_SCHED_NODES); without memory for it, and for
+ * other batches and single calls, AUTO applies.  AUTO picks SOLO for tables of at most 4
  * granules (16,384 tuples) and at most 16 domain words (wider tables spread
  * filterDomains over workgroups) and for batches of at least 256 jobs, and
  * NODES for eligible batches of at least 64 jobs.  A batch whose jobs are all
@@ -317,9 +319,10 @@ int ct_propagate_batch(const ct_job *jobs, int32_t n_jobs, void *stream, int32_t
  * static host arrays.  Limits: at most 8,192 jobs, at most 2 MiB of staged
  * descriptors (about 88 bytes per job plus the root tasks of a batch of
  * CT_JOB_ROOT jobs: one per 4 granules), and for a batch on the search-node
- * schedule at most 14 MiB of node records and flags (per job about 8 x
- * (4 + (rows + 3 x arity + 3) / 4) + granules bytes); a batch beyond them is
- * refused with CT_E_INVALID before anything changes.  Every no-allocation
+ * schedule of a table of at most 256 support rows at most 14 MiB, counted as
+ * 8 x (4 + (rows + 3 x arity + 3) / 4) + granules bytes per job; a batch
+ * beyond them is refused with CT_E_INVALID before anything changes (a larger
+ * search-node batch of another table takes the other schedules).  Every no-allocation
  * call on one GPU shares that array and the host arrays: calls are
  * serialized on the host, and calls whose batches overlap on the GPU (on
  * different streams, or before an earlier one has completed on another

@@ -160,34 +160,35 @@ struct DevJob {
 // bit 30 set (never 0 or 1, the values the counted protocol uses).
 __host__ __device__ inline int32_t ll_gen(int32_t seq) { return (seq & 0x3fffffff) | 0x40000000; }
 
-// Granule-major schedule of a batch of search nodes (jobs that all propagate
-// one table from its root state).  Per node: the Alg. 1 prologue's outcome
-// and its row list: one segment holding the removed values' rows of every
-// incremental variable of s_val (the complement of their OR is the AND of
-// their incremental masks), then one segment per reset variable, in
-// variable order, each padded to a multiple of 4 rows with the all-zero row
-// `rows` of the update kernel's tile, its first entry tagged 0x8000 (| 0x4000
-// when incremental); per (node, granule) the non-zero flag of the new
-// currTable granule.
+// Search-node schedule (ct_nodes.hip): batches of jobs that all propagate one
+// table from its root state.  A node's record: Alg. 1's outcome and the
+// addresses the later steps need.
 struct NodeInfo {
-  int32_t status, nrows;   // nrows: support rows OR-ed (without padding)
-  int32_t groups, pad;     // groups: list length / 4
+  int32_t status, nrows;   // nrows: support rows Alg. 2 would OR (work counters)
   CT_G uint64_t* ct;       // the node's slot currTable
-  CT_G uint64_t* ct_out;   // optional copy (W words), may be null
+  CT_G int32_t* res;
+  CT_G int32_t* idx;
+  CT_G uint64_t* lastDom;
+  const CT_G uint64_t* dom_in;
+  CT_G uint64_t* dom_out;
 };
 
-// A node's record in memory: its NodeInfo, then its row list (listCap
-// entries); records of consecutive nodes are contiguous (nodeWords words).
 struct NodesDesc {
-  int32_t nJobs, listCap, nodeWords, groups, groupSize;
-  int32_t rows, nGran;       // the table's (copied: no dependent loads)
-  int32_t tw;                // granules per tile of the update kernel (1 or 2)
-  int64_t stride, W;
-  const CT_G uint64_t* S;
-  const CT_G uint64_t* ct0;
+  const CT_G TabDesc* tab;
   const CT_G DevJob* jobs;
-  CT_G uint64_t* nodes;    // nJobs x nodeWords
-  CT_G uint8_t* nz;        // nJobs x nGran
+  const CT_G uint64_t* S;
+  const CT_G uint16_t* ids;  // row numbers of the tuples' values (see nodes_ids_kernel)
+  int64_t stride, W;
+  int32_t nJobs, D, nGran, n2;
+  int32_t vecRows;           // row vectors: the support rows, all-zero, all-one, and (short
+                             // tables) one "not empty" vector per variable
+  int32_t anyOut;            // some job wants a currTable copy
+  int32_t groups, parts;     // groups of 512 nodes (8 words of 64); items per granule (1 or 2)
+  CT_G NodeInfo* info;       // nJobs
+  CT_G uint64_t *ct, *out;   // groups x 512: the nodes' currTables and wanted copies (addresses;
+                             // 0: rejected node, padding, no copy)
+  CT_G uint64_t* vec;        // groups x vecRows x 8
+  CT_G uint64_t* nz;         // parts x (groups x 8) x nGran: nodes with a non-zero word there
 };
 
 // Batch of roots recomputed from scratch: one task per workgroup of the

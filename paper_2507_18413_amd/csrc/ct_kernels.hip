@@ -1405,540 +1405,6 @@ __device__ __forceinline__ void do_solo(const KArgs& a, const DevJob& J0, Shared
 }
 
 // ---------------------------------------------------------------------------
-// Granule-major schedule of search nodes (jobs that all propagate one table
-// from its root state).  The per-job schedules read every selected support
-// row of a node from memory; here a workgroup stages one granule of every
-// support row in LDS once and evaluates a group of nodes against it, so the
-// supports cross the memory hierarchy once per group and HBM mostly sees the
-// nodes' currTable writes.
-//   nodes_prep:   one workgroup per node: Alg. 1 prologue -> encoded row list
-//   nodes_update: one workgroup per (granule, node group): Alg. 2 from LDS
-//   nodes_finish: one workgroup per node: partition, FAIL, Alg. 3, status
-// ---------------------------------------------------------------------------
-constexpr int NODES_MAX_ROWS = 256;  // LDS tile of the update kernel: rows x 512 B at least
-constexpr int XCDS = 8;
-
-// Orders this wave's LDS accesses: a wave's LDS operations complete in issue
-// order, so only the compiler has to be kept from moving accesses across.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-
-// One wave per node: the Alg. 1 prologue of a root reset.  Per variable the
-// number of values of dom_in (|dom|) and of removed root values (|Delta|)
-// decide membership of s_val and the branch of Alg. 2 (incremental when
-// |Delta| < |dom|, or as the table's policy fixes it); the node's row list
-// holds one segment with the rows of Delta of every incremental variable,
-// then per reset variable of s_val a segment with the rows of dom, each
-// segment padded to a multiple of 4 rows with the zero row and its first
-// entry tagged.
-__global__ void __launch_bounds__(BLOCK) nodes_prep_kernel(KArgs a, NodesDesc N) {
-  __shared__ int32_t shSize[WAVES][MAX_ARITY];
-  __shared__ int32_t shDcnt[WAVES][MAX_ARITY];
-  __shared__ int32_t shSeg[WAVES][MAX_ARITY];  // first list entry | inc << 30, or -1 (not in s_val)
-  __shared__ int32_t shWcnt[WAVES][MAX_D];     // popcount of Delta << 8 | popcount of dom, per word
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-  const int j = blockIdx.x * WAVES + wv;
-  if (j >= N.nJobs) return;  // no workgroup barrier below
-  const int lane = lane_id();
-  const DevJob J = N.jobs[j];
-  const TabDesc* T = J.tab;
-  const int n = T->n, D = T->D;
-  const uint16_t zeroRow = (uint16_t)T->rows;
-  int32_t* size = shSize[wv];
-  int32_t* dcnt = shDcnt[wv];
-  int32_t* seg = shSeg[wv];
-  int32_t* wcnt = shWcnt[wv];
-  for (int i = lane; i < n; i += WAVE) {
-    size[i] = 0;
-    dcnt[i] = 0;
-  }
-  wave_lds_sync();
-  bool stray = false, notSub = false;
-  for (int q = lane; q < D; q += WAVE) {
-    const uint64_t din = J.dom_in[q];
-    const uint64_t ld = T->dom0[q];
-    const int i = T->wordVar[q];
-    const VarDesc v = T->vars[i];
-    const int used = v.dsize - 64 * (q - v.domOff);
-    if (used < 64 && (din >> used) != 0) stray = true;
-    if (din & ~ld) notSub = true;
-    const int cs = __popcll(din), cd = __popcll(ld & ~din);
-    wcnt[q] = (cd << 8) | cs;
-    atomicAdd(&size[i], cs);
-    atomicAdd(&dcnt[i], cd);
-  }
-  int st = T->rootFailed ? ST_STATE
-           : __ballot(stray) ? ST_INVALID
-           : __ballot(notSub) ? ST_NOT_SUBSET : ST_OK;
-  wave_lds_sync();
-  // segments.  Alg. 2's incremental masks AND together into the complement
-  // of one OR over every removed value of those variables (De Morgan), so the
-  // incremental variables of s_val share one segment, first, padded once to
-  // a multiple of 4; each reset variable follows with a segment of its own,
-  // padded the same way
-  int total = 0, incTotal = 0;
-  bool emptyReset = false;
-  const int policy = T->policy;
-  auto branch = [&](int i, bool* in, int* inc, int* cnt) {
-    *in = false;
-    *inc = 0;
-    *cnt = 0;
-    if (i >= n) return;
-    const int sz = size[i], dc = dcnt[i];
-    *in = dc > 0;  // |dom| changed since the root
-    *inc = policy == 2 ? 1 : policy == 1 ? 0 : (dc < sz ? 1 : 0);
-    *cnt = *in ? (*inc ? dc : sz) : 0;
-  };
-  for (int i0 = 0; i0 < n; i0 += WAVE) {
-    const int i = i0 + lane;
-    bool in;
-    int inc, cnt;
-    branch(i, &in, &inc, &cnt);
-    const int c = (in && inc) ? cnt : 0;
-    const int incl = wave_scan_incl(c);
-    if (i < n) seg[i] = (in && inc) ? ((incTotal + incl - c) | (1 << 30)) : -1;
-    incTotal += __builtin_amdgcn_readlane(incl, WAVE - 1);
-  }
-  const int incPadded = (incTotal + 3) & ~3;
-  int padded = incPadded;
-  total = incTotal;
-  for (int i0 = 0; i0 < n; i0 += WAVE) {
-    const int i = i0 + lane;
-    bool in;
-    int inc, cnt;
-    branch(i, &in, &inc, &cnt);
-    const bool rs = in && !inc;
-    if (rs && cnt == 0) emptyReset = true;  // a reset segment of an empty domain
-    const int c = rs ? cnt : 0;
-    const int groups = (c + 3) >> 2;
-    const int inclRows = wave_scan_incl(c);
-    const int inclPad = wave_scan_incl(4 * groups);
-    if (rs) seg[i] = padded + inclPad - 4 * groups;
-    total += __builtin_amdgcn_readlane(inclRows, WAVE - 1);
-    padded += __builtin_amdgcn_readlane(inclPad, WAVE - 1);
-  }
-  if (st == ST_OK && __ballot(emptyReset)) st = ST_FAIL;
-  wave_lds_sync();
-  if (st == ST_OK) {
-    CT_G uint16_t* out = (CT_G uint16_t*)(N.nodes + (int64_t)j * N.nodeWords + sizeof(NodeInfo) / 8);
-    for (int q = lane; q < D; q += WAVE) {
-      const int i = T->wordVar[q];
-      const int sg = seg[i];
-      if (sg < 0) continue;
-      const int inc = sg >> 30;
-      const int start = sg & 0x3FFFFFFF;
-      const VarDesc v = T->vars[i];
-      int off = start;
-      for (int k = v.domOff; k < q; ++k) off += inc ? (wcnt[k] >> 8) : (wcnt[k] & 0xFF);
-      const uint64_t din = J.dom_in[q];
-      uint64_t bits = inc ? (T->dom0[q] & ~din) : din;
-      const int base = v.rowStart + (q - v.domOff) * 64;
-      while (bits) {
-        const int b = __ffsll((unsigned long long)bits) - 1;
-        bits &= bits - 1;
-        uint32_t e = (uint32_t)(base + b);
-        // the first entry of the shared incremental segment, or of a reset
-        // variable's segment, carries the segment tag
-        if (inc ? off == 0 : off == start) e |= 0x8000u | (inc ? 0x4000u : 0u);
-        out[off++] = (uint16_t)e;
-      }
-      // a reset variable's last word pads its segment
-      if (!inc && q == v.domOff + v.domWords - 1)
-        while (off & 3) out[off++] = zeroRow;
-    }
-    // the padding of the shared incremental segment
-    if (lane < incPadded - incTotal) out[incTotal + lane] = zeroRow;
-  }
-  if (lane == 0) {
-    NodeInfo I;
-    I.status = st;
-    I.nrows = (st == ST_OK || st == ST_FAIL) ? total : 0;
-    I.groups = st == ST_OK ? padded / 4 : 0;
-    I.pad = 0;
-    I.ct = J.slot->ct;
-    I.ct_out = J.ct_out;
-    *(CT_G NodeInfo*)(N.nodes + (int64_t)j * N.nodeWords) = I;
-  }
-}
-
-// A tile is TW consecutive granules (a span of 64·TW words) of the table for
-// one group of nodes.  LDS holds that span of every support row (rows x 64·TW
-// words) and a zero row, then the group's node records (NodeInfo and row
-// list); a node then costs only LDS reads and its currTable store.  A list is
-// read 8 rows per step: the row numbers come from registers by readlane (one
-// group of 4 per lane), the rows are independent LDS reads OR-ed in.  With
-// TW = 2 a lane holds two consecutive words and every row read is one 16-byte
-// load per lane (1 KB per wave): LDS serves 16-byte loads at about twice the
-// rate of 8-byte ones.  TW = 2 is used when the doubled tile fits a CU's LDS
-// (one 16-wave workgroup per CU), else TW = 1 (8-wave workgroups, two per CU).
-//
-// Persistent workgroups (as many as fit at once) walk the tiles: while one
-// tile is evaluated from LDS, the next one's words are already on their way
-// into registers, so the memory latency of staging is hidden.  Block b runs on
-// XCD b % 8 (round-robin dispatch) and works on the spans s with
-// s % 8 == b % 8 (they stay in that XCD's L2): the XCD's tiles, span-major,
-// are cut into one contiguous range per block, so a block keeps a span's
-// rows in LDS across its groups and restages only the node records.
-constexpr int NODES_TPF = 16;  // tile words per thread prefetched (rows <= 128)
-constexpr int NODES_NPF = 5;   // node-record words per thread prefetched
-
-template <int TW>
-struct NodesCfg {
-  static constexpr int SPAN = GW * TW;           // words per row of a tile
-  static constexpr int BLOCKT = TW == 2 ? 1024 : 512;
-  static constexpr int WAVEST = BLOCKT / WAVE;
-  static constexpr int RSTEP = BLOCKT / SPAN;    // rows staged per pass (8)
-};
-
-typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
-
-struct NodesTile {
-  int g, node0, nG, nodeTotal;  // g: first granule of the span
-  u64x2 root;                   // the root's words of this lane (TW = 1: .x)
-};
-
-template <int TW>
-__device__ __forceinline__ NodesTile nodes_tile(const NodesDesc& N, int xcd, int t) {
-  NodesTile x;
-  x.g = ((t / N.groups) * XCDS + xcd) * TW;
-  x.node0 = (t % N.groups) * N.groupSize;
-  x.nG = min(N.groupSize, N.nJobs - x.node0);
-  x.nodeTotal = x.nG * N.nodeWords;
-  const int64_t w = (int64_t)x.g * GW + TW * lane_id();
-  if (TW == 2) {
-    // a span past the last granule reads as zero
-    x.root = w < N.stride ? *(const CT_G u64x2*)(N.ct0 + w) : u64x2{0ull, 0ull};
-  } else {
-    x.root = u64x2{N.ct0[w], 0ull};
-  }
-  return x;
-}
-
-// Staging of a tile: thread t holds words t % SPAN of tile rows t / SPAN + 8u
-// and the words t + BLOCKT·u of the group's node records.
-template <int TW>
-__device__ __forceinline__ void nodes_stage_issue(const NodesDesc& N, const NodesTile& x, uint64_t* vt,
-                                                  uint64_t* vn, bool rows) {
-  using C = NodesCfg<TW>;
-  const int r0 = (int)threadIdx.x / C::SPAN, l = (int)threadIdx.x % C::SPAN;
-  const int64_t w = (int64_t)x.g * GW + l;
-  const bool inRow = w < N.stride;  // words past the last granule are not loaded
-  const CT_G uint64_t* S = N.S + (int64_t)r0 * N.stride + w;
-  if (rows) {
-#pragma unroll
-    for (int u = 0; u < NODES_TPF; ++u)
-      if (r0 + C::RSTEP * u < N.rows) vt[u] = inRow ? S[(int64_t)(C::RSTEP * u) * N.stride] : 0ull;
-  }
-  const CT_G uint64_t* src = N.nodes + (int64_t)x.node0 * N.nodeWords + threadIdx.x;
-#pragma unroll
-  for (int u = 0; u < NODES_NPF; ++u)
-    if ((int)threadIdx.x + C::BLOCKT * u < x.nodeTotal) vn[u] = src[C::BLOCKT * u];
-}
-
-// Stores the prefetched words (and loads and stores any beyond them) and
-// resets the tile's node counter; the caller synchronizes the workgroup
-// afterwards.  The support rows are staged only for a new span.
-template <int TW>
-__device__ __forceinline__ void nodes_stage_commit(const NodesDesc& N, const NodesTile& x, const uint64_t* vt,
-                                                   const uint64_t* vn, uint64_t* lds, bool rows, int* next) {
-  using C = NodesCfg<TW>;
-  const int r0 = (int)threadIdx.x / C::SPAN, l = (int)threadIdx.x % C::SPAN;
-  const int64_t w = (int64_t)x.g * GW + l;
-  const bool inRow = w < N.stride;
-  if (rows) {
-#pragma unroll
-    for (int u = 0; u < NODES_TPF; ++u)
-      if (r0 + C::RSTEP * u < N.rows) lds[(r0 + C::RSTEP * u) * C::SPAN + l] = vt[u];
-    for (int r = r0 + C::RSTEP * NODES_TPF; r < N.rows; r += C::RSTEP)
-      lds[r * C::SPAN + l] = inRow ? N.S[(int64_t)r * N.stride + w] : 0ull;
-  }
-  if (threadIdx.x == 0) *next = 0;
-  uint64_t* dst = lds + (size_t)(N.rows + 1) * C::SPAN;  // the zero row sits between
-#pragma unroll
-  for (int u = 0; u < NODES_NPF; ++u) {
-    const int i = (int)threadIdx.x + C::BLOCKT * u;
-    if (i < x.nodeTotal) dst[i] = vn[u];
-  }
-  const CT_G uint64_t* src = N.nodes + (int64_t)x.node0 * N.nodeWords;
-  for (int i = (int)threadIdx.x + C::BLOCKT * NODES_NPF; i < x.nodeTotal; i += C::BLOCKT) dst[i] = src[i];
-}
-
-// Row r of the tile for this lane: its word (TW = 1) or its two words (TW = 2).
-template <int TW>
-__device__ __forceinline__ u64x2 nodes_row(const char* tileBytes, uint32_t r, uint32_t laneOff) {
-  if (TW == 2) return *(const u64x2*)(tileBytes + (r << 10) + laneOff);
-  return u64x2{*(const uint64_t*)(tileBytes + (r << 9) + laneOff), 0ull};
-}
-
-template <int TW>
-__device__ __forceinline__ void nodes_eval_tile(const NodesDesc& N, const NodesTile& x, const uint64_t* lds,
-                                                int* next) {
-  using C = NodesCfg<TW>;
-  const int lane = lane_id();
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-  const uint64_t* recs = lds + (size_t)(N.rows + 1) * C::SPAN;
-  const uint32_t laneOff = (uint32_t)lane * 8u * TW;
-  const char* tileBytes = (const char*)lds;
-  const int64_t w = (int64_t)x.g * GW + TW * lane;
-  // the waves take the group's nodes one at a time from the tile's counter:
-  // nodes differ in row count, so a fixed share per wave would leave waves
-  // idle at the tile's barrier.  Every lane adds one, so a wave's fetch moves
-  // the counter by 64 and the node is the value any lane got divided by 64:
-  // no branch on the lane precedes the wave-uniform exit test (a
-  // lane-0-only atomic followed by a shuffle let the compiler send the other
-  // lanes back to the test with a stale node id, so they never left the loop)
-  for (;;) {
-    const int p = __builtin_amdgcn_readfirstlane(atomicAdd(next, 1)) >> 6;
-    if (p >= x.nG) break;
-    const NodeInfo* info = (const NodeInfo*)(recs + p * N.nodeWords);
-    // the record is the same for every lane: scalar registers, uniform loops
-    const int status = __builtin_amdgcn_readfirstlane(info->status);
-    if (status != ST_OK && status != ST_FAIL) continue;  // rejected input: nothing changes
-    const int ng = __builtin_amdgcn_readfirstlane(info->groups);
-    const uint64_t* rl = (const uint64_t*)(info + 1);  // 4 entries per word
-    const uint64_t m0 = status == ST_OK ? ~0ull : 0ull;
-    u64x2 m = {m0, m0};
-    u64x2 acc = {0ull, 0ull};
-    bool inc = false, open = false;
-    // the list, 64 groups of 4 row numbers at a time, one group per lane;
-    // two groups (8 rows) per step, taken from the lanes by readlane, so the
-    // row reads of a step never wait for an LDS read of row numbers; a missing
-    // second group reads the zero row
-    const uint64_t zeroGroup = (uint64_t)N.rows * 0x0001000100010001ull;
-    for (int c0 = 0; c0 < ng; c0 += WAVE) {
-      const uint64_t mine = c0 + lane < ng ? rl[c0 + lane] : zeroGroup;
-      const uint32_t mlo = (uint32_t)mine, mhi = (uint32_t)(mine >> 32);
-      const int cn = min(WAVE, ng - c0);
-      for (int q = 0; q < cn; q += 2) {
-        const uint32_t a0 = __builtin_amdgcn_readlane(mlo, q);
-        const uint32_t a1 = __builtin_amdgcn_readlane(mhi, q);
-        const uint32_t b0 = __builtin_amdgcn_readlane(mlo, q + 1);  // q + 1 <= 63
-        const uint32_t b1 = __builtin_amdgcn_readlane(mhi, q + 1);
-        // 8 rows in flight (TW = 1), or 4 when each is 16 bytes per lane
-        u64x2 v[4], u[4];
-        v[0] = nodes_row<TW>(tileBytes, a0 & 0x3FFFu, laneOff);
-        v[1] = nodes_row<TW>(tileBytes, a0 >> 16, laneOff);
-        v[2] = nodes_row<TW>(tileBytes, a1 & 0xFFFFu, laneOff);
-        v[3] = nodes_row<TW>(tileBytes, a1 >> 16, laneOff);
-        if (TW == 1) {
-          u[0] = nodes_row<TW>(tileBytes, b0 & 0x3FFFu, laneOff);
-          u[1] = nodes_row<TW>(tileBytes, b0 >> 16, laneOff);
-          u[2] = nodes_row<TW>(tileBytes, b1 & 0xFFFFu, laneOff);
-          u[3] = nodes_row<TW>(tileBytes, b1 >> 16, laneOff);
-        }
-        if (a0 & 0x8000u) {  // a segment starts with the first group
-          if (open) m &= inc ? ~acc : acc;
-          acc = u64x2{0ull, 0ull};
-          inc = (a0 & 0x4000u) != 0;
-          open = true;
-        }
-        acc |= (v[0] | v[1]) | (v[2] | v[3]);
-        if (TW == 2) {
-          u[0] = nodes_row<TW>(tileBytes, b0 & 0x3FFFu, laneOff);
-          u[1] = nodes_row<TW>(tileBytes, b0 >> 16, laneOff);
-          u[2] = nodes_row<TW>(tileBytes, b1 & 0xFFFFu, laneOff);
-          u[3] = nodes_row<TW>(tileBytes, b1 >> 16, laneOff);
-        }
-        if (b0 & 0x8000u) {  // ... or with the second
-          m &= inc ? ~acc : acc;
-          acc = u64x2{0ull, 0ull};
-          inc = (b0 & 0x4000u) != 0;
-        }
-        acc |= (u[0] | u[1]) | (u[2] | u[3]);
-      }
-    }
-    if (open) m &= inc ? ~acc : acc;
-    const u64x2 nw = x.root & m;
-    CT_G uint64_t* ct = info->ct;
-    CT_G uint64_t* ctOut = info->ct_out;
-    const unsigned long long nzl = __ballot((nw.x | nw.y) != 0ull);
-    if (TW == 2) {
-      // lanes 0-31 hold granule g, lanes 32-63 granule g + 1 (when it exists)
-      if (w < N.stride) *(CT_G u64x2*)(ct + w) = nw;
-      if (ctOut) {
-        if (w + 1 < N.W) {
-          ctOut[w] = nw.x;
-          ctOut[w + 1] = nw.y;
-        } else if (w < N.W) {
-          ctOut[w] = nw.x;
-        }
-      }
-      if (lane == 0) {
-        CT_G uint8_t* nz = N.nz + (int64_t)(x.node0 + p) * N.nGran + x.g;
-        nz[0] = (nzl & 0xFFFFFFFFull) ? 1 : 0;
-        if (x.g + 1 < N.nGran) nz[1] = (nzl >> 32) ? 1 : 0;
-      }
-    } else {
-      ct[w] = nw.x;
-      if (ctOut && w < N.W) ctOut[w] = nw.x;
-      if (lane == 0) N.nz[(int64_t)(x.node0 + p) * N.nGran + x.g] = nzl ? 1 : 0;
-    }
-  }
-}
-
-template <int TW>
-__global__ void __launch_bounds__(NodesCfg<TW>::BLOCKT, 4) nodes_update_kernel(KArgs a, NodesDesc N) {
-  // the tile (16-byte row reads need the array at LDS offset 0: no static
-  // LDS in this kernel), the group's node records, then the node counter
-  extern __shared__ uint64_t lds[];
-  using C = NodesCfg<TW>;
-  int* next = (int*)(lds + (size_t)(N.rows + 1) * C::SPAN + (size_t)N.groupSize * N.nodeWords);
-  const int xcd = blockIdx.x % XCDS;
-  const int perX = gridDim.x / XCDS;  // the grid is a multiple of 8
-  const int spans = (N.nGran + TW - 1) / TW;
-  const int tilesX = (spans - xcd + XCDS - 1) / XCDS * N.groups;
-  // the XCD's tiles, span by span with the groups of a span in a row, are
-  // cut into one contiguous range per block: a block stages a span's rows
-  // once and then only the next group's node records
-  const int k = blockIdx.x / XCDS;
-  const int hi = (int)((int64_t)(k + 1) * tilesX / perX);
-  int t = (int)((int64_t)k * tilesX / perX);
-  if (t >= hi) return;
-  if (threadIdx.x < C::SPAN) lds[N.rows * C::SPAN + threadIdx.x] = 0ull;  // the zero row
-  uint64_t vt[NODES_TPF], vn[NODES_NPF];
-  NodesTile cur = nodes_tile<TW>(N, xcd, t);
-  nodes_stage_issue<TW>(N, cur, vt, vn, true);
-  nodes_stage_commit<TW>(N, cur, vt, vn, lds, true, next);
-  __syncthreads();
-  for (;;) {
-    const int tn = t + 1;
-    const bool more = tn < hi;
-    NodesTile nxt;
-    bool rows = false;
-    if (more) {
-      nxt = nodes_tile<TW>(N, xcd, tn);
-      rows = nxt.g != cur.g;  // the same for every thread
-      nodes_stage_issue<TW>(N, nxt, vt, vn, rows);  // in flight during the evaluation
-    }
-    nodes_eval_tile<TW>(N, cur, lds, next);
-    __syncthreads();  // every wave is done with this tile's LDS
-    if (!more) break;
-    nodes_stage_commit<TW>(N, nxt, vt, vn, lds, rows, next);
-    __syncthreads();
-    t = tn;
-    cur = nxt;
-  }
-}
-
-// One wave per node, four nodes per workgroup, so the nodes of a batch are
-// resident at once: the stable partition of the root's granule list by the
-// non-zero flags (survivors first) and FAIL (Alg. 1), then filterDomains
-// (Alg. 3) over the node's domain words.  The residue and support-word loads
-// of FINISH_PRE domain words are issued before the partition and the node's
-// currTable words at those residues together after it, so a node's chain of
-// dependent memory rounds does not grow with its domain words.
-constexpr int FINISH_BLOCK = 256;
-constexpr int FINISH_NODES = FINISH_BLOCK / WAVE;
-constexpr int FINISH_PRE = 4;
-
-__global__ void __launch_bounds__(FINISH_BLOCK) nodes_finish_kernel(KArgs a, NodesDesc N) {
-  const int j = blockIdx.x * FINISH_NODES + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-  if (j >= N.nJobs) return;
-  const int lane = lane_id();
-  const DevJob J = N.jobs[j];
-  const TabDesc* T = J.tab;
-  SlotDesc* s = J.slot;
-  const CT_G NodeInfo* rec = (const CT_G NodeInfo*)(N.nodes + (int64_t)j * N.nodeWords);
-  const int st0 = rec->status;
-  const int nrows = rec->nrows;
-  const bool run = st0 == ST_OK || st0 == ST_FAIL;
-  // the residues and support words of the first FINISH_PRE domain words:
-  // independent of the partition, so their loads run meanwhile (they clamp
-  // every address, so a rejected node's loads are harmless too)
-  const int D = T->D;
-  FilterPre pre[FINISH_PRE];
-#pragma unroll
-  for (int u = 0; u < FINISH_PRE; ++u) pre[u] = filter_pre(a, J, min(u, D - 1));
-  int nSurv = 0;
-  if (run) {
-    const int limit0 = T->limit0, nGran = T->nGran;
-    const CT_G uint8_t* nz = N.nz + (int64_t)j * nGran;
-    const CT_G int32_t* src = T->idx0;
-    CT_G int32_t* dst = s->idx[0];
-    const uint64_t below = (1ull << lane) - 1ull;
-    // granule ids and flags of 4 x 64 positions per round trip
-    for (int p0 = 0; p0 < limit0; p0 += 4 * WAVE) {
-      int gid[4];
-      bool f[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int p = p0 + u * WAVE + lane;
-        gid[u] = p < limit0 ? src[p] : -1;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) f[u] = gid[u] >= 0 && nz[gid[u]];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) nSurv += __popcll(__ballot(f[u]));
-    }
-    int sv = 0, zr = nSurv;
-    for (int p0 = 0; p0 < limit0; p0 += 4 * WAVE) {
-      int gid[4];
-      bool f[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int p = p0 + u * WAVE + lane;
-        gid[u] = p < limit0 ? src[p] : -1;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) f[u] = gid[u] >= 0 && nz[gid[u]];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint64_t bs = __ballot(f[u]), bz = __ballot(gid[u] >= 0 && !f[u]);
-        if (f[u]) dst[sv + __popcll(bs & below)] = gid[u];
-        else if (gid[u] >= 0) dst[zr + __popcll(bz & below)] = gid[u];
-        sv += __popcll(bs);
-        zr += __popcll(bz);
-      }
-    }
-    for (int p = limit0 + lane; p < nGran; p += WAVE) dst[p] = src[p];
-    if (lane == 0) {
-      s->cur = 0;
-      s->limit = nSurv;
-      s->depth = 0;
-      s->trailTop = 0;
-      s->serial = J.serialBase;
-      s->failed = nSurv ? 0 : 1;
-      atomicAdd(&s->stats[S_JOBS], 1ull);
-      atomicAdd(&s->stats[S_GRAN_IN], (unsigned long long)limit0);
-      atomicAdd(&s->stats[S_ROWS], (unsigned long long)nrows);
-      if (nrows) atomicAdd(&s->stats[S_GRAN_ROWS], (unsigned long long)limit0 * (unsigned long long)nrows);
-    }
-    __threadfence_block();  // the index written by the lanes is read by the filter's scans
-  } else {
-    slot_reset_root(T, s, J.serialBase, lane, WAVE);
-  }
-  const int st = run ? (nSurv ? ST_OK : ST_FAIL) : st0;
-  if (st == ST_OK) {
-    unsigned long long cnt[3] = {0, 0, 0};
-    const CT_G uint64_t* ct = s->ct;
-    for (int q0 = 0; q0 < D; q0 += FINISH_PRE) {
-      if (q0 > 0) {
-#pragma unroll
-        for (int u = 0; u < FINISH_PRE; ++u) pre[u] = filter_pre(a, J, min(q0 + u, D - 1));
-      }
-      // the node's currTable words at the residues, all in flight together
-      uint64_t cr[FINISH_PRE];
-#pragma unroll
-      for (int u = 0; u < FINISH_PRE; ++u) cr[u] = ct[pre[u].rw0];
-#pragma unroll
-      for (int u = 0; u < FINISH_PRE; ++u)
-        if (q0 + u < D) filter_word(a, J, q0 + u, 0, nSurv, s->idx[0], cnt, pre[u], true, cr[u]);
-    }
-    add_filter_stats(s, cnt);
-  }
-  if (lane == 0) {
-    s->status = st;
-    s->pad2 = 0;
-    status_fence(J);
-    publish_status(J, st);
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Batches whose jobs all recompute a root from scratch.  Stream: one wave per
 // (job, granule); a currTable word is the AND over the variables of the OR
 // of the support rows of the values in dom_in, starting from all tuples
@@ -2726,57 +2192,6 @@ hipError_t launch_model_round(const ModelDesc& M, const KArgs& a, int grid, hipS
   return hipGetLastError();
 }
 
-// M.pool holds the input; leaves pool = input AND every table's domains and
-// the dirty flags of the first round.
-int nodes_max_rows() { return NODES_MAX_ROWS; }
-
-// Row-list entries per node (every segment padded to a multiple of 4, the
-// list to a multiple of 4 entries).
-int nodes_list_cap(int rows, int n) { return (rows + 3 * n + 3) & ~3; }
-
-// Words of a node's record: its NodeInfo and its row list.
-int nodes_node_words(int rows, int n) {
-  return (int)(sizeof(NodeInfo) / 8) + nodes_list_cap(rows, n) / 4;
-}
-
-// Dynamic LDS of the update kernel for groups of `groupSize` nodes and tiles
-// of `tw` granules: the tile with its zero row, the records, the node counter.
-size_t nodes_update_lds(int rows, int n, int groupSize, int tw) {
-  return (size_t)(rows + 1) * GW * tw * sizeof(uint64_t) +
-         (size_t)groupSize * nodes_node_words(rows, n) * sizeof(uint64_t) + 16;
-}
-
-int nodes_update_block(int tw) { return tw == 2 ? NodesCfg<2>::BLOCKT : NodesCfg<1>::BLOCKT; }
-
-// Persistent workgroups of the update kernel: as many as fit at once, a
-// multiple of the XCD count.
-template <int TW>
-int nodes_update_grid(size_t ldsBytes) {
-  int dev = 0, cus = 0, perCu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return XCDS;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&perCu, nodes_update_kernel<TW>, NodesCfg<TW>::BLOCKT,
-                                                   ldsBytes) != hipSuccess ||
-      perCu < 1)
-    perCu = 1;
-  return std::max(XCDS, cus * perCu / XCDS * XCDS);
-}
-
-hipError_t launch_nodes(const KArgs& a, const NodesDesc& N, int n, hipStream_t stream) {
-  hipLaunchKernelGGL(nodes_prep_kernel, dim3((N.nJobs + WAVES - 1) / WAVES), dim3(BLOCK), 0, stream, a, N);
-  const size_t lds = nodes_update_lds(N.rows, n, N.groupSize, N.tw);
-  if (N.tw == 2)
-    hipLaunchKernelGGL(nodes_update_kernel<2>, dim3(nodes_update_grid<2>(lds)), dim3(NodesCfg<2>::BLOCKT), lds,
-                       stream, a, N);
-  else
-    hipLaunchKernelGGL(nodes_update_kernel<1>, dim3(nodes_update_grid<1>(lds)), dim3(NodesCfg<1>::BLOCKT), lds,
-                       stream, a, N);
-  hipLaunchKernelGGL(nodes_finish_kernel, dim3((N.nJobs + FINISH_NODES - 1) / FINISH_NODES), dim3(FINISH_BLOCK), 0,
-                     stream, a, N);
-  return hipGetLastError();
-}
-
 hipError_t launch_roots(const KArgs& a, const RootDesc& R, hipStream_t stream) {
   if (R.nTasks > 0)
     hipLaunchKernelGGL(root_stream_kernel, dim3(R.nTasks), dim3(BLOCK), 0, stream, a, R);
@@ -2784,6 +2199,8 @@ hipError_t launch_roots(const KArgs& a, const RootDesc& R, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// M.pool holds the input; leaves pool = input AND every table's domains and
+// the dirty flags of the first round.
 hipError_t launch_model_seed(const ModelDesc& M, hipStream_t stream) {
   hipLaunchKernelGGL(model_copy_kernel, dim3(64), dim3(BLOCK), 0, stream, (uint64_t*)M.poolNext,
                      (const uint64_t*)M.pool, M.poolWords);

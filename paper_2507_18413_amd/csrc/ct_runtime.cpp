@@ -32,11 +32,11 @@ hipError_t launch_propagate(const KArgs& a, int grid, hipStream_t stream);
 size_t engine_lds_bytes(int n, int D, int nGran, int rows);
 hipError_t launch_engine(const EngDesc& D, size_t lds, hipStream_t stream);
 hipError_t launch_split_engine(const EngDesc& E, int grid, hipStream_t stream);
-int nodes_max_rows();
-int nodes_list_cap(int rows, int n);
-int nodes_node_words(int rows, int n);
-size_t nodes_update_lds(int rows, int n, int groupSize, int tw);
-hipError_t launch_nodes(const KArgs& a, const NodesDesc& N, int n, hipStream_t stream);
+int nodes_max_vec_rows(size_t lds);
+size_t nodes_scratch_bytes(int vecRows, int nJobs, int nGran);
+size_t nodes_ids_bytes(int n, int64_t stride);
+hipError_t launch_nodes_ids(const TabDesc* T, int nGran, uint16_t* ids, hipStream_t stream);
+hipError_t launch_nodes(NodesDesc N, char* scratch, hipStream_t stream);
 hipError_t launch_roots(const KArgs& a, const RootDesc& R, hipStream_t stream);
 hipError_t noalloc_scratch(char** ptr, size_t* bytes);
 hipError_t launch_noalloc_reset(int32_t* q, hipStream_t stream);
@@ -130,7 +130,7 @@ struct QueueCtx {
   std::vector<DevJob> hJobs;
   std::vector<int32_t> updOff, filtOff, prep, rootTasks;
   std::vector<std::array<int32_t, 3>> rootKey;
-  // search-node schedule scratch (node records | granule flags)
+  // search-node schedule scratch (node records | row vectors | non-zero words)
   void* dNodes = nullptr;
   size_t capNodes = 0;
 };
@@ -192,6 +192,10 @@ struct ct_table {
   TabDesc hTab{};
   SlotDesc* dRoot = nullptr;
   SlotDesc hRoot{};
+  // search-node schedule: row vectors of a batch (0: the table does not take
+  // it) and the row numbers of every tuple's values (see nodes_ids_ensure)
+  int nodesVecRows = 0;
+  uint16_t* dIds = nullptr;
   std::vector<void*> blocks;  // device allocations to free
   QueueCtx q;
   // pinned staging of the synchronous calls
@@ -298,8 +302,6 @@ bool use_solo(const ct_table* T, int nJobs) {
   return (T->nGran <= SOLO_MAX_GRAN && T->D <= SOLO_MAX_D) || nJobs >= SOLO_MIN_BATCH;
 }
 
-// The search-node schedule takes a batch whose jobs all reset slots of one
-// table to the root and propagate (the slots are distinct: checked before).
 // Largest LDS of one workgroup on the current device (0 if unknown).
 int device_lds() {
   int dev = 0, lds = 0;
@@ -309,30 +311,27 @@ int device_lds() {
   return lds;
 }
 
-// Tile of the node update kernel: nodes per group (a multiple of 8 up to 64)
-// and granules per tile.  Two-granule tiles (16-byte LDS reads) when the tile
-// and a group of at least 32 nodes fit one workgroup's LDS; else one-granule
-// tiles with the largest group for which two workgroups fit a CU, else one.
-struct NodesPlan {
-  int groupSize = 0, tw = 1;
-};
-
-NodesPlan nodes_plan(const ct_table* T) {
-  const size_t lds = (size_t)device_lds();
-  NodesPlan p;
-  for (int gs = 64; gs >= 32; gs -= 8)
-    if (nodes_update_lds(T->rows, T->n, gs, 2) <= lds) {
-      p.groupSize = gs;
-      p.tw = 2;
-      return p;
-    }
-  for (int per = 2; per >= 1; --per)
-    for (int gs = 64; gs >= 8; gs -= 8)
-      if (per * nodes_update_lds(T->rows, T->n, gs, 1) <= lds) {
-        p.groupSize = gs;
-        return p;
-      }
-  return p;
+// The search-node schedule reads, per tuple, the row numbers of its values
+// (2 bytes each).  They are made once per table, when its slots reach the
+// smallest batch the schedule takes (or at the first such batch): a table
+// never searched that way does not pay for them.  Without memory for them
+// the batches take the other schedules.
+bool nodes_ids_ensure(ct_table* T) {
+  if (T->dIds) return true;
+  if (T->nodesVecRows == 0) return false;
+  void* p = nullptr;
+  if (hipMalloc(&p, nodes_ids_bytes(T->n, T->stride)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (launch_nodes_ids(T->dTab, T->nGran, (uint16_t*)p, T->stream) != hipSuccess ||
+      hipStreamSynchronize(T->stream) != hipSuccess) {
+    (void)hipFree(p);
+    return false;
+  }
+  T->blocks.push_back(p);
+  T->dIds = (uint16_t*)p;
+  return true;
 }
 
 // Batches of roots recomputed from scratch run on their own streaming
@@ -345,14 +344,13 @@ bool use_roots(const ct_job* jobs, int n) {
   return true;
 }
 
-bool use_nodes(const ct_job* jobs, int n) {
+// The search-node schedule takes a batch whose jobs all reset slots of one
+// table to the root and propagate (the slots are distinct: checked before).
+bool nodes_batch(const ct_job* jobs, int n) {
   const ct_table* T = jobs[0].table;
   if (T->cfg.schedule != CT_SCHED_NODES && (T->cfg.schedule != CT_SCHED_AUTO || n < NODES_MIN_BATCH))
     return false;
-  if (T->kind != CT_KIND_POSITIVE) return false;
-  if (T->rows > nodes_max_rows() || T->nGran > MAX_GRAN) return false;
-  // the update kernel's LDS holds one granule of every support row
-  if (nodes_plan(T).groupSize == 0) return false;
+  if (T->nodesVecRows == 0) return false;
   for (int j = 0; j < n; ++j)
     if (jobs[j].table != T || jobs[j].flags != (CT_JOB_PROPAGATE | CT_JOB_FROM_ROOT)) return false;
   return true;
@@ -1134,6 +1132,11 @@ static int create_impl(ct_table* T, const int32_t* tuples, int64_t t, int32_t n,
     tb.limit0 = 0;
   }
   HIPCHK(hipMemcpy(T->dTab, &tb, sizeof(TabDesc), hipMemcpyHostToDevice));
+  // search-node schedule: the row vectors of a batch's smallest group fit LDS
+  if (T->kind == CT_KIND_POSITIVE) {
+    const int vecRows = rows + 2 + (T->shortTab ? n : 0);
+    if (vecRows <= nodes_max_vec_rows((size_t)device_lds())) T->nodesVecRows = vecRows;
+  }
   int first = 0;
   if ((rc = ct_slots_alloc(T, 1, -1, &first))) return rc;
   // the resident engine holds the slot's state in one workgroup's LDS
@@ -1238,6 +1241,9 @@ int ct_slots_alloc(ct_table* T, int32_t n, int32_t max_depth, int32_t* first_slo
   if (n < 1) return fail(CT_E_INVALID, "n < 1");
   if ((rc = quiesce(T))) return rc;
   if (max_depth < 0) max_depth = T->cfg.max_depth;
+  if (T->cfg.schedule == CT_SCHED_NODES ||
+      (T->cfg.schedule == CT_SCHED_AUTO && (int)T->slots.size() + n >= NODES_MIN_BATCH))
+    (void)nodes_ids_ensure(T);
   // reuse: the first run of n consecutive freed slots whose trails hold
   // max_depth levels; each is reset to the root state
   int run = 0, first = -1;
@@ -1527,20 +1533,20 @@ namespace {
 // What a validated batch needs, before any slot's host state changes.
 struct BatchPlan {
   bool nodes = false, roots = false;
-  size_t nodesBytes = 0;   // search-node records and granule flags
+  size_t nodesBytes = 0;   // search-node records, row vectors and non-zero words
   size_t nTaskInts = 0;    // root tasks, two ints each
   size_t offAt = 0;        // byte offset of the int section of the staging area
   size_t stageBytes = 0;   // staging bytes for the largest prep list
 };
 
-BatchPlan batch_plan(const ct_job* jobs, int n_jobs) {
+// nodes: the batch runs on the search-node schedule if it is one
+BatchPlan batch_plan(const ct_job* jobs, int n_jobs, bool nodes) {
   BatchPlan p;
-  p.nodes = use_nodes(jobs, n_jobs);
+  p.nodes = nodes;
   p.roots = !p.nodes && use_roots(jobs, n_jobs);
   if (p.nodes) {
     const ct_table* T = jobs[0].table;
-    p.nodesBytes = align256(sizeof(uint64_t) * (size_t)n_jobs * nodes_node_words(T->rows, T->n)) +
-                   align256((size_t)n_jobs * T->nGran);
+    p.nodesBytes = nodes_scratch_bytes(T->nodesVecRows, n_jobs, T->nGran);
   }
   if (p.roots) {
     size_t nTasks = 0;
@@ -1619,25 +1625,19 @@ int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* st
   if (p.nodes) {
     const ct_table* T = jobs[0].table;
     NodesDesc N{};
-    N.nJobs = n_jobs;
-    N.listCap = nodes_list_cap(T->rows, T->n);
-    const NodesPlan plan = nodes_plan(T);
-    N.groupSize = plan.groupSize;
-    N.tw = plan.tw;
-    N.groups = (n_jobs + N.groupSize - 1) / N.groupSize;
+    N.tab = T->dTab;
     N.jobs = dJobs;
-    char* base = (char*)r.dNodes;
-    N.nodeWords = nodes_node_words(T->rows, T->n);
-    N.nodes = (uint64_t*)base;
-    base += align256(sizeof(uint64_t) * (size_t)n_jobs * N.nodeWords);
-    N.nz = (uint8_t*)base;
-    N.rows = T->rows;
-    N.nGran = T->nGran;
+    N.S = T->hTab.S;
+    N.ids = T->dIds;
     N.stride = T->stride;
     N.W = T->W;
-    N.S = T->hTab.S;
-    N.ct0 = T->hTab.ct0;
-    HIPCHK(launch_nodes(a, N, T->n, stream));
+    N.nJobs = n_jobs;
+    N.D = T->D;
+    N.nGran = T->nGran;
+    N.n2 = (T->n + 1) & ~1;
+    N.vecRows = T->nodesVecRows;
+    for (int j = 0; j < n_jobs && !N.anyOut; ++j) N.anyOut = jobs[j].ct_out != nullptr;
+    HIPCHK(launch_nodes(N, (char*)r.dNodes, stream));
     return CT_OK;
   }
   if (p.roots) {
@@ -1658,6 +1658,15 @@ constexpr int NA_MAX_JOBS = 8192;
 constexpr size_t NA_QUEUE_BYTES = 256;
 constexpr size_t NA_STAGE_BYTES = (size_t)2 << 20;
 constexpr size_t NA_MAX_TASK_INTS = (NA_STAGE_BYTES - (size_t)NA_MAX_JOBS * 128) / sizeof(int32_t);
+
+// The documented limit of a no-allocation search-node batch (tables of at
+// most NA_NODES_ROWS support rows): per node a row list and a flag byte per
+// granule.
+constexpr int NA_NODES_ROWS = 256;
+size_t na_nodes_bytes(const ct_table* T, int n_jobs) {
+  const size_t nodeWords = 4 + (size_t)(((T->rows + 3 * T->n + 3) & ~3) / 4);
+  return align256(sizeof(uint64_t) * (size_t)n_jobs * nodeWords) + align256((size_t)n_jobs * T->nGran);
+}
 
 struct NoAllocHost {
   std::mutex mu;  // the host arrays are shared by every caller
@@ -1715,7 +1724,7 @@ int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32
       q = it->second;
     }
   }
-  const BatchPlan p = batch_plan(jobs, n_jobs);
+  const BatchPlan p = batch_plan(jobs, n_jobs, nodes_batch(jobs, n_jobs) && nodes_ids_ensure(jobs[0].table));
   // device and pinned scratch, grown before any slot's host state changes:
   // a failed allocation leaves the slots as they were
   if (p.nodes && q->capNodes < p.nodesBytes) {
@@ -1777,13 +1786,16 @@ int ct_propagate_batch_noalloc(const ct_job* jobs, int32_t n_jobs, void* stream_
   size_t scratchBytes = 0;
   HIPCHK(noalloc_scratch(&scratch, &scratchBytes));
   const size_t nodesCap = scratchBytes - NA_QUEUE_BYTES - NA_STAGE_BYTES;
-  const BatchPlan p = batch_plan(jobs, n_jobs);
+  // (the row numbers of the search-node schedule are made by ct_slots_alloc)
+  const bool nodes = nodes_batch(jobs, n_jobs);
+  if (nodes && jobs[0].table->rows <= NA_NODES_ROWS && na_nodes_bytes(jobs[0].table, n_jobs) > nodesCap)
+    return fail(CT_E_INVALID, "ct_propagate_batch_noalloc: the search-node schedule needs %zu scratch bytes, "
+                "at most %zu", na_nodes_bytes(jobs[0].table, n_jobs), nodesCap);
+  BatchPlan p = batch_plan(jobs, n_jobs, nodes && jobs[0].table->dIds);
+  if (p.nodesBytes > nodesCap) p = batch_plan(jobs, n_jobs, false);
   if (p.stageBytes > NA_STAGE_BYTES || p.nTaskInts > NA_MAX_TASK_INTS)
     return fail(CT_E_INVALID, "ct_propagate_batch_noalloc: the batch needs %zu staging bytes, at most %zu",
                 p.stageBytes, NA_STAGE_BYTES);
-  if (p.nodes && p.nodesBytes > nodesCap)
-    return fail(CT_E_INVALID, "ct_propagate_batch_noalloc: the search-node schedule needs %zu scratch bytes, "
-                "at most %zu", p.nodesBytes, nodesCap);
   hipStream_t stream = (hipStream_t)stream_v;
   std::lock_guard<std::mutex> lk(g_na.mu);
   int rc = batch_validate_quiesce(jobs, n_jobs, stream);

@@ -1,0 +1,108 @@
+"""The search-node schedule (batches of root resets on one table, evaluated
+per tuple for 64 nodes at a time) against the oracle, bit-exact, at the edges
+of its tiles: words of 64 nodes and groups of 512, half granules of 2,048
+tuples, odd variable counts, one-value and multi-word domains, many support
+rows, star cells, rejected and failing nodes, wanted currTable copies, outputs
+that alias the inputs."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2507_18413_amd import ct
+from paper_2507_18413_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print("[gpu-case]", *a, flush=True)
+    sys.stdout.flush()
+
+
+CASES = [
+    # n_nodes, domain sizes, tuples, star share
+    (1, [5, 4], 1, 0.0),
+    (63, [7, 1, 9], 63, 0.0),
+    (64, [3, 3, 3, 3], 65, 0.2),
+    (65, [64, 65, 2], 2047, 0.0),
+    (130, [20, 31, 33, 8, 5], 2049, 0.1),
+    (511, [12, 40, 100], 4096, 0.0),
+    (513, [9, 6, 5, 4, 3, 2, 8], 4097, 0.05),
+    (70, [700, 600, 500], 9000, 0.0),
+    (90, [16] * 11, 6200, 0.0),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+@pytest.mark.parametrize("alias", [False, True])
+def test_nodes_edges(case, alias):
+    n_nodes, ds, t, star = CASES[case]
+    say("search nodes:", n_nodes, "nodes, domains", ds, ",", t, "tuples, stars", star, "alias", alias)
+    rng = W.rng_for(case, 910, 0)
+    lo = np.arange(len(ds), dtype=np.int32) - 1
+    tup = np.stack([lo[i] + rng.integers(0, ds[i] + 1, size=t) for i in range(len(ds))], 1).astype(np.int32)
+    if star:
+        tup[rng.random(tup.shape) < star] = ct.STAR
+    ds = np.array(ds, np.int32)
+    g = ct.Table(tup, lo, ds, schedule=ct.SCHED_NODES)
+    o = O.OracleTable(tup, lo, ds)
+    assert g.create_status == o.create_status
+    if o.create_status != O.OK:
+        return
+    lay = W.DomLayout(ds, lo)
+    root = o.domains()
+    nodes = np.empty((n_nodes, lay.D), np.uint64)
+    for k in range(n_nodes):
+        dom = root.copy()
+        for i in range(lay.n):
+            vals = lay.values(dom, i)
+            # now and then every value but one, or every value, of a variable
+            keep = rng.random(vals.size) < (1.0 if rng.random() < 0.4 else rng.random())
+            if vals.size and not keep.any() and rng.random() < 0.9:
+                keep[int(rng.integers(0, vals.size))] = True
+            for a in vals[~keep]:
+                lay.clear(dom, i, int(a))
+        nodes[k] = dom
+    if n_nodes > 4:
+        nodes[1] = root
+        nodes[2, lay.off[0]] |= np.uint64(1 << 63) if ds[0] % 64 else np.uint64(0)  # a stray bit
+        nodes[3, lay.off[0]] = lay.full()[lay.off[0]]  # perhaps values the root lacks
+    first = g.slots_alloc(n_nodes, max_depth=0)
+    din = torch.from_numpy(nodes.view(np.int64).copy()).cuda()
+    dout = din if alias else torch.zeros_like(din)
+    cts = torch.full((n_nodes, g.W), -1, dtype=torch.int64, device="cuda")
+    status = torch.full((n_nodes,), 99, dtype=torch.int32, device="cuda")
+    ct.propagate_batch([dict(table=g, slot=first + k, flags=ct.JOB_PROPAGATE | ct.JOB_FROM_ROOT, dom_in=din[k],
+                             dom_out=dout[k], ct_out=None if k % 3 == 2 else cts[k]) for k in range(n_nodes)], status)
+    ct.batch_status()
+    st, got, gct = status.cpu().numpy(), dout.cpu().numpy().view(np.uint64), cts.cpu().numpy().view(np.uint64)
+    rd, rc, _ = o.state()
+    for k in range(n_nodes):
+        o.push()
+        os_, od, oc = o.propagate(nodes[k], want_ct=True)
+        o.pop()
+        assert st[k] == os_, k
+        sd, sc = g.state(first + k)
+        if os_ == O.OK:
+            assert (got[k] == od).all() and (sd == od).all() and (sc == oc).all(), k
+            if k % 3 != 2:
+                assert (gct[k] == oc).all(), k
+        elif os_ < 0:  # rejected: the slot holds the root, the copy is untouched
+            assert (sd == rd).all() and (sc == rc).all(), k
+            assert (gct[k] == np.uint64(0xFFFFFFFFFFFFFFFF)).all(), k
+        else:
+            assert (sc == 0).all(), k
+    # the slots then continue like the oracle from those states
+    for k in range(0, n_nodes, max(1, n_nodes // 7)):
+        if st[k] != ct.OK:
+            continue
+        o.push()
+        o.propagate(nodes[k])
+        dom = W.pick_fraction_removal(rng, lay, o.domains(), frac=0.4)
+        os_, od = o.propagate(dom)
+        o.pop()
+        gs, gd = g.propagate(dom, slot=first + k)
+        assert gs == os_ and (os_ != O.OK or (gd == od).all()), k

@@ -64,9 +64,11 @@ extern "C" {
 typedef struct ct_table ct_table;
 
 /* How a propagation is spread over the GPU: SOLO runs a whole call in one
- * workgroup (no hand-off between workgroups; best for small tables and for
- * batches of many jobs), SPLIT spreads updateTable over workgroups of 8
- * granules and filterDomains over workgroups of 4 domain words.  NODES is the
+ * workgroup (no hand-off between workgroups; best for small tables), SPLIT
+ * spreads updateTable over the waves of many workgroups, one per granule,
+ * and filterDomains over one wave per domain word: as three launches for a
+ * batch's jobs together and for one call of a larger table, or as one launch
+ * with hand-offs for a call whose update one workgroup takes.  NODES is the
  * search-node schedule of ct_propagate_batch: when every job of a batch is a
  * CT_JOB_FROM_ROOT propagation of the same positive table of at most about
  * 2,400 support rows (sum of the domain sizes: one bit vector over 512 jobs
@@ -76,8 +78,7 @@ typedef struct ct_table ct_table;
  * table has 64 slots (or has CT_SCHED_NODES); without memory for it, and for
  * other batches and single calls, AUTO applies.  AUTO picks SOLO for tables of at most 4
  * granules (16,384 tuples) and at most 16 domain words (wider tables spread
- * filterDomains over workgroups) and for batches of at least 256 jobs, and
- * NODES for eligible batches of at least 64 jobs.  A batch whose jobs are all
+ * filterDomains over workgroups), and NODES for eligible batches of at least 64 jobs.  A batch whose jobs are all
  * CT_JOB_ROOT on AUTO tables runs as two launches: one wave per (job,
  * granule) streams every support row of its granule once, then one
  * workgroup per job partitions and filters.  On an AUTO table of more than
@@ -312,8 +313,8 @@ int ct_propagate_batch(const ct_job *jobs, int32_t n_jobs, void *stream, int32_t
  * ct_propagate_batch_noalloc -- ct_propagate_batch for callers that cannot
  * allocate memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc): the same jobs, statuses and results,
- * but no device, pinned or host allocation.  The work-queue counters, the
- * staged job descriptors and the search-node schedule's records live in a
+ * but no device, pinned or host allocation.  The error words, the staged job
+ * descriptors and the schedules' scratch live in a
  * static device array of 16 MiB that each GPU holds until the process ends
  * (set up on the device's first call), and the descriptors are built in
  * static host arrays.  Limits: at most 8,192 jobs, at most 2 MiB of staged
@@ -327,7 +328,7 @@ int ct_propagate_batch(const ct_job *jobs, int32_t n_jobs, void *stream, int32_t
  * serialized on the host, and calls whose batches overlap on the GPU (on
  * different streams, or before an earlier one has completed on another
  * stream) race and give undefined results; batches queued on one stream
- * run in order and are safe.  Each call clears the queue counters first
+ * run in order and are safe.  Each call clears the item counts first
  * (a small kernel on `stream`).  Device-side errors are reported by
  * ct_batch_status on the stream of the last no-allocation call.
  */
@@ -384,7 +385,7 @@ int ct_model_push(ct_model *m);
 int ct_model_pop(ct_model *m);
 
 /* Scheduling knob of the model's rounds: tables of at most solo_max_granules
- * granules run in one workgroup each, larger ones are split over workgroups
+ * granules run in one workgroup each, larger ones are spread over workgroups
  * (see CT_SCHED_*); rounds_per_graph rounds are captured per graph.  A
  * fixpoint's first two launches are one-round graphs (most search steps
  * converge in a round or two), the launches after them take rounds_per_graph
@@ -394,25 +395,24 @@ int ct_model_set_schedule(ct_model *m, int32_t solo_max_granules, int32_t rounds
 
 /* Autotuner of the rounds' schedule.  Tables are grouped in classes by
  * floor(log4) of their granule count and of their support-row count; each
- * class gets a schedule: solo (one workgroup per table, 4 granules of 64
- * words per wavefront per step) or split (update items spread over
- * workgroups) with a tile of 2, 4 or 8 granules per wavefront per item.
+ * class gets a schedule: solo (one workgroup per table) or split (its
+ * granules and domain words spread over workgroups).
  * Classes are tuned one after the other, those with the most granules in all
  * first, each candidate timed as the median of 3 fixpoints from pool_in
  * (device pointer), every table restored between trials with a push / pop;
  * every candidate must reach the same fixpoint (CT_E_DEVICE otherwise).
  * cache_path (nullable): a JSON file of choices keyed by the device
- * architecture and the class buckets ("gfx950 g2 r3": [solo, tile]); when
+ * architecture and the class buckets ("gfx950 g2 r3": [solo, tile], the tile
+ * 0 or 2, 4, 8 in older files, all the same schedule); when
  * it holds every class of the model, those choices are applied without
  * timing anything (*from_cache = 1), otherwise the tuned choices are merged
  * into it.  *timed (nullable) receives the number of candidates timed.
- * Classes the tuner never saw follow ct_model_set_schedule's threshold with
- * the default tile (2). */
+ * Classes the tuner never saw follow ct_model_set_schedule's threshold. */
 int ct_model_autotune(ct_model *m, const uint64_t *pool_in, const char *cache_path, int32_t *from_cache,
                       int32_t *timed);
 /* Effective schedule of table `table` (index from ct_model_add) in the
- * model's rounds: *solo = 1 for one workgroup per table, *tile = granules
- * per wavefront per update step (solo) or item (split). */
+ * model's rounds: *solo = 1 for one workgroup per table; *tile = 4 (solo) or
+ * the tile of the choice (split; it selects nothing). */
 int ct_model_get_choice(const ct_model *m, int32_t table, int32_t *solo, int32_t *tile);
 
 /* ------------------------------------------------------------------------

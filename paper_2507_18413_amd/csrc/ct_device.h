@@ -32,8 +32,12 @@
 // pointers; the layout is the same.
 #if defined(__HIP_DEVICE_COMPILE__)
 #define CT_G __attribute__((address_space(1)))
+// memory written by an earlier launch and only read in this one, at addresses
+// that are the same for every lane: scalar loads
+#define CT_K __attribute__((address_space(4)))
 #else
 #define CT_G
+#define CT_K
 #endif
 
 namespace ctk {
@@ -131,7 +135,7 @@ struct SlotDesc {
   int64_t trailTop;
   int32_t cur, limit, failed, depth, serial, pad1;
   // per-job scratch
-  int32_t updCount, filtCount, jobTrail, prepDone, updDone, status;
+  int32_t filtCount, prepDone, updDone, status;
   int32_t nzCount;  // granules a root stream found non-empty (reset by its finish)
   int32_t pad2;
   unsigned long long stats[8];
@@ -147,13 +151,67 @@ struct DevJob {
   uint32_t flags;
   int32_t nPop, nPush;
   int32_t serialBase;      // serial of the k-th pushed level = serialBase + k
-  int32_t nUpd, nFilt;     // item counts of this job
+  int32_t nUpd, nFilt;     // item counts of this job (staged schedule: at most)
   int32_t depthAfter;      // slot depth once the pops and pushes are applied
-  int32_t tile;            // split jobs: granules per wave per update item (2, 4 or 8;
-                           // 0 = 2); solo jobs step 4 granules per wave
+  int32_t listCap;         // staged schedule: row-list entries the job's scratch holds
   const CT_G int32_t* active;  // nullable: the job is skipped when *active == 0
   uint64_t* ll;             // JF_LL: the result slots (pinned host memory)
-  int32_t seq, llPad;       // JF_LL: the call's number
+  int32_t seq;              // JF_LL: the call's number
+  int32_t stageOff;         // staged schedule: the job's scratch (input words, |dom| per
+                            // word, row list), in 256-byte units from StageArgs::jobMem
+};
+
+// Staged schedule (ct_staged.hip): what a job's prep hands to the update and
+// the finish.
+enum { STAGE_LIST = 0, STAGE_BITS, STAGE_NOOP, STAGE_ZERO };
+enum { STAGE_TRAIL_OFF = 0, STAGE_TRAIL_FIRST, STAGE_TRAIL_ALL };
+struct StageRec {
+  int32_t run;               // 0: nothing left to do (inactive, rejected, pops and pushes only)
+  uint32_t flags;            // JF_*
+  int32_t mode;              // STAGE_*: rows from the list, from the selected bits, no change, all removed
+  int32_t nrows, limit, serial, trailOn, D, nGran, curNew, serialBase, seq;
+  int32_t trailCount, pad;   // STAGE_TRAIL_FIRST: trail entries of the job (counted by the update)
+  const CT_G TabDesc* tab;
+  CT_G SlotDesc* slot;
+  const CT_G uint64_t* S;
+  int64_t stride, W;
+  const CT_G WordDesc* words;
+  const CT_G uint64_t* ctSrc;
+  const CT_G int32_t* idxSrc;
+  CT_G int32_t* idxDst;
+  CT_G uint64_t* ct;
+  CT_G int32_t* stamp;
+  CT_G int32_t* nz;
+  CT_G TrailHdr* trailHdr;
+  CT_G uint64_t* trailWords;
+  int64_t trailTop, trailCap;
+  CT_G int32_t* res;
+  CT_G uint64_t* lastDom;
+  const CT_G uint64_t* din;  // D: the input
+  const CT_G int32_t* size;  // D: |dom| of the word's variable
+  const CT_G uint32_t* rows;
+  CT_G uint64_t* dom_out;
+  CT_G uint64_t* ct_out;
+  CT_G int32_t* status_out;
+  uint64_t* ll;
+};
+
+constexpr int QUEUE_INTS = 16, QUEUE_STAGE = 8;  // words of a queue ([3] error); its staged item counts
+
+struct StageItem {
+  int32_t job, chunk;
+};
+
+struct StageArgs {
+  CT_G StageRec* rec;        // per job
+  CT_G char* jobMem;         // the jobs' scratch
+  CT_G StageItem* items;     // update items; null: one job, items by workgroup
+  CT_G StageItem* fItems;    // finish items
+  CT_G int32_t* count;       // [0] update items, [1] finish items, [2] finish workgroups done
+  int32_t wide, pad;         // the finish runs in workgroups of 1,024 threads
+  int32_t* queue;            // [3] error
+  int32_t* hostErr;
+  unsigned long long* clock; // nullable (one job): see KArgs
 };
 
 // The update item's hand-over word of a JF_LL job: the call's number with
@@ -225,11 +283,9 @@ struct ModelDesc {
 // Kernel argument block of the persistent propagate kernel.
 struct KArgs {
   const CT_G DevJob* jobs;      // nullptr: single job in `job`
-  const CT_G int32_t* updOff;   // nJobs + 1 prefix sums of update items (nullptr for one job)
-  const CT_G int32_t* filtOff;  // nJobs + 1 prefix sums of filter items
-  const CT_G int32_t* prepList; // jobs that need a prep item (pops, or only pushes/pops)
-  int32_t nJobs, nPrep, nUpd, nFilt;
-  int32_t* queue;          // [0] head, [1] exit count, [2] launches, [3] error
+  int32_t nJobs;
+  int32_t nPrep, nUpd, nFilt;   // a single job's items
+  int32_t* queue;          // [3] error
   int32_t* hostErr;        // nullable: error word copied here by the last block
   // nullable: kernel timing on the device clock (wall_clock64): [0] earliest
   // workgroup start, [1] latest end, [2] workgroups done, [3] summed

@@ -5,24 +5,21 @@
 // coalesced 512-byte granule loads (one word per lane of a wave64), wave
 // ballots and LDS.
 //
-// One persistent kernel executes a batch of propagation jobs as a list of
-// work items.  A job runs either in solo mode -- one item, one workgroup,
-// the whole of Alg. 1-3 with no hand-off between workgroups (small tables,
-// large batches) -- or in split mode, as items in this order:
-//   prep   (jobs that pop, and pure push/pop jobs)  backtrack restore, pushes
-//   update (nUpd per job)   updateTable (Alg. 2) over 8 granules each, with the
-//                           Delta / s_val / s_sup prologue of Alg. 1 recomputed
-//                           per item in LDS; the last update item of a job
-//                           records the job's pushes, partitions the sparse
-//                           index and decides FAIL (Alg. 1's failure test)
-//   filter (nFilt per job)  filterDomains (Alg. 3), one domain word per wave,
-//                           residue word first, then a scan of active granules
-// Workgroup b starts with item b; when the grid is smaller than the item
-// count the remaining items are taken from a device queue in increasing
-// order.  An item only waits for earlier items of its own job (update waits
-// for prep when the job pops; filter waits for the job's last update item).
-// Waits are bounded: on expiry the kernel records a device error and the
-// remaining work of the launch is skipped.
+// propagate_kernel runs a job either in solo mode -- one workgroup, the whole
+// of Alg. 1-3 with no hand-off between workgroups (small tables, negative
+// tables) -- or, for one synchronous call of a table whose update one
+// workgroup takes, in split mode, as items of one launch:
+//   prep   (calls that pop, and pure push/pop calls)  backtrack restore, pushes
+//   update updateTable (Alg. 2) with the Delta / s_val / s_sup prologue of
+//          Alg. 1 in LDS; records the call's pushes, partitions the sparse
+//          index and decides FAIL (Alg. 1's failure test)
+//   filter filterDomains (Alg. 3), one domain word per wave, residue word
+//          first, then a scan of active granules
+// An item only waits for earlier items (the update for the prep when the call
+// pops, the filters for the update), and all of them are resident.  Waits are
+// bounded: on expiry the kernel records a device error and the remaining work
+// of the launch is skipped.  Larger tables and batches run staged
+// (ct_staged.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -40,10 +37,6 @@ constexpr int ROW_UNROLL = 8;          // support rows loaded per batch
 constexpr int ROWS_CHUNK = 8192;       // row-list entries staged in LDS at a time
 constexpr uint32_t SPIN_LIMIT = 1u << 22;
 constexpr int32_t STAR_CELL = (int32_t)0x80000000;  // a short table's cell: every value of its column
-
-// Steps of NGW granules a wave takes per update item for a job's tile
-// (granules per wave per item: 2, 4 or 8; 0 = 2).
-__host__ __device__ __forceinline__ int tile_reps(int tile) { return tile == 8 ? 4 : tile == 4 ? 2 : 1; }
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (WAVE - 1); }
 __device__ __forceinline__ int wave_id() { return threadIdx.x / WAVE; }
@@ -66,7 +59,6 @@ struct SlotPtrs {
   CT_G uint64_t* ct;
   CT_G int32_t* idx[2];
   CT_G int32_t* stamp;
-  CT_G int32_t* nzFlag;
   CT_G uint64_t* trailWords;
   CT_G TrailHdr* trailHdr;
   int64_t trailCap;
@@ -99,7 +91,6 @@ __device__ __forceinline__ SlotPtrs slot_ptrs(const SlotDesc* s) {
   p.idx[0] = s->idx[0];
   p.idx[1] = s->idx[1];
   p.stamp = s->stamp;
-  p.nzFlag = s->nzFlag;
   p.trailWords = s->trailWords;
   p.trailHdr = s->trailHdr;
   p.trailCap = s->trailCap;
@@ -249,16 +240,6 @@ __device__ __forceinline__ void status_fence(const DevJob& J) {
   if (J.flags & JF_HOST_OUT) __threadfence_system();
 }
 
-// largest j with off[j] <= x  (off has n + 1 entries, off[0] = 0)
-__device__ int find_job(const CT_G int32_t* off, int n, int x) {
-  int lo = 0, hi = n;  // off[lo] <= x < off[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (off[mid] <= x) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
 // Push nPush levels recording (trailTop, limit, failed, serial, domains);
 // the k-th new level continues with serial serialBase + k.  Whole block.
 __device__ void push_levels(const DevJob& J, SlotDesc* s, int depth0, int64_t trailTop, int limit,
@@ -358,12 +339,11 @@ __device__ void stage_rows(const DevJob& J, Shared& sh, int k0, const CT_G uint6
                            const CT_G WordDesc* wordsArr = nullptr);
 
 // ---------------------------------------------------------------------------
-// prologue of Alg. 1 for one job (every update item recomputes it in LDS).
-// Its barriers order LDS only: what it stores to memory (pushed levels) is
-// read by later calls.  stageGidx: the job's granule list into sh.gidx as
-// well (a job run by one workgroup), loaded with the domain words.
+// prologue of Alg. 1 for one job, in LDS.  Its barriers order LDS only: what
+// it stores to memory (pushed levels) is read by later calls.  The job's
+// granule list goes into sh.gidx as well, loaded with the domain words.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void prologue(const KArgs& a, const DevJob& J, Shared& sh, bool pushHere, bool stageGidx) {
+__device__ __forceinline__ void prologue(const KArgs& a, const DevJob& J, Shared& sh, bool pushHere) {
   const TabDesc* T = J.tab;
   SlotDesc* s = J.slot;
   const bool fromRoot = J.flags & JF_FROM_ROOT;
@@ -386,7 +366,7 @@ __device__ __forceinline__ void prologue(const KArgs& a, const DevJob& J, Shared
   const uint64_t ld0 = ld_last(last + q0, coh);
   const int p0 = min((int)threadIdx.x, nGran - 1);
   int ga = 0, gb = 0;
-  if (stageGidx && !scratch) {
+  if (!scratch) {
     ga = (fromRoot ? T->idx0 : s->idx[0])[p0];
     gb = fromRoot ? ga : s->idx[1][p0];
   }
@@ -474,11 +454,9 @@ __device__ __forceinline__ void prologue(const KArgs& a, const DevJob& J, Shared
       atomicAdd(&sh.dcnt[i], __popcll(dl));
     }
   }
-  if (stageGidx) {
-    if ((int)threadIdx.x < nGran) sh.gidx[threadIdx.x] = (uint16_t)(scratch ? (int)threadIdx.x : sh.cur ? gb : ga);
-    const CT_G int32_t* gsrc = fromRoot ? T->idx0 : sh.sp.idx[sh.cur];
-    for (int p = threadIdx.x + BLOCK; p < nGran; p += BLOCK) sh.gidx[p] = (uint16_t)(scratch ? p : gsrc[p]);
-  }
+  if ((int)threadIdx.x < nGran) sh.gidx[threadIdx.x] = (uint16_t)(scratch ? (int)threadIdx.x : sh.cur ? gb : ga);
+  const CT_G int32_t* gsrc = fromRoot ? T->idx0 : sh.sp.idx[sh.cur];
+  for (int p = threadIdx.x + BLOCK; p < nGran; p += BLOCK) sh.gidx[p] = (uint16_t)(scratch ? p : gsrc[p]);
   lds_barrier();
   if (threadIdx.x < WAVE) {
     // wave 0: the segments of s_val in variable order (prefix sums over the
@@ -584,11 +562,10 @@ __device__ void stage_rows(const DevJob& J, Shared& sh, int k0, const CT_G uint6
 
 // ---------------------------------------------------------------------------
 // updateTable (Alg. 2) for NG granules per wave starting at position p0,
-// RU support rows in flight per granule.  Granule flags go to LDS (whole job
-// in one workgroup) or to global memory.
+// RU support rows in flight per granule.  Granule flags go to LDS.
 // ---------------------------------------------------------------------------
 template <int NG, int RU = ROW_UNROLL>
-__device__ __forceinline__ void update_granules(const KArgs& a, const DevJob& J, Shared& sh, int p0, bool lds,
+__device__ __forceinline__ void update_granules(const KArgs& a, const DevJob& J, Shared& sh, int p0,
                                 int* trailCounter, const SlotPtrs* sp = nullptr) {
   const TabDesc* T = J.tab;
   SlotDesc* s = J.slot;
@@ -609,7 +586,6 @@ __device__ __forceinline__ void update_granules(const KArgs& a, const DevJob& J,
   // the slot's arrays as the prologue read them (sp, in LDS), or from the
   // descriptor
   const CT_G uint64_t* srcCt = fromRoot ? T->ct0 : sp ? sp->ct : s->ct;
-  const CT_G int32_t* srcIdx = fromRoot ? T->idx0 : sp ? sp->idx[sh.cur] : s->idx[s->cur];
   const CT_G int32_t* stampArr = sp ? sp->stamp : s->stamp;
   const int64_t trailTop = sh.trailTop;
 
@@ -624,7 +600,7 @@ __device__ __forceinline__ void update_granules(const KArgs& a, const DevJob& J,
   for (int u = 0; u < NG; ++u) {
     pos[u] = p0 + u;
     const int pc = min(pos[u], nGran - 1);
-    g[u] = scratch ? pc : lds ? (int)sh.gidx[pc] : srcIdx[pc];
+    g[u] = scratch ? pc : (int)sh.gidx[pc];
     if (pos[u] >= nGran) g[u] = -1;
     act[u] = pos[u] < limit && status == ST_OK;
     gs[u] = act[u] ? g[u] : 0;
@@ -711,7 +687,6 @@ __device__ __forceinline__ void update_granules(const KArgs& a, const DevJob& J,
   CT_G uint64_t* const sTrailWords = P.trailWords;
   CT_G TrailHdr* const sTrailHdr = P.trailHdr;
   CT_G int32_t* const sStamp = P.stamp;
-  CT_G int32_t* const sNz = P.nzFlag;
   CT_G uint64_t* const ctOut = J.ct_out;
   if (nNeed) {
     if (lane == 0) tbase = atomicAdd(trailCounter, nNeed);
@@ -745,10 +720,7 @@ __device__ __forceinline__ void update_granules(const KArgs& a, const DevJob& J,
     if (wr[u]) sCt[w] = nw[u];
     if (ctOut && w < W) ctOut[w] = nw[u];
     const bool nz = __ballot(nw[u] != 0ull) != 0ull;
-    if (lane == 0) {
-      if (lds) sh.nz[pos[u]] = nz ? 1 : 0;
-      else sNz[pos[u]] = nz ? 1 : 0;
-    }
+    if (lane == 0) sh.nz[pos[u]] = nz ? 1 : 0;
   }
   if (lane == 0 && status == ST_OK) {
     if (nAct && !noop) atomicAdd(&s->stats[S_GRAN_ROWS], nAct * (unsigned long long)nrows);
@@ -781,7 +753,7 @@ __device__ void slot_reset_root(const TabDesc* T, SlotDesc* s, int serial, int t
 // active granule list (survivors first), new limit, trail top, FAIL when no
 // granule survives (Alg. 1's failure test).  Returns the job status.
 // ---------------------------------------------------------------------------
-__device__ int finalize_update(const DevJob& J, Shared& sh, bool ldsFlags, int jobTrail, bool count = true) {
+__device__ int finalize_update(const DevJob& J, Shared& sh, int jobTrail, bool count = true) {
   const TabDesc* T = J.tab;
   // a negative table's currTable holds forbidden tuples: empty means no
   // combination is forbidden, not a failure
@@ -793,26 +765,24 @@ __device__ int finalize_update(const DevJob& J, Shared& sh, bool ldsFlags, int j
   int st = sh.status;
   if (st == ST_OK && !sh.noop) {
     const bool scratch = J.flags & JF_SCRATCH;  // index = identity
-    // the index buffers and flags as the prologue read them (sh.sp, sh.cur)
-    const CT_G int32_t* src = fromRoot ? T->idx0 : sh.sp.idx[sh.cur];
+    // the index buffers as the prologue read them (sh.sp, sh.cur)
     const int dstBuf = fromRoot ? 0 : 1 - sh.cur;
     CT_G int32_t* dst = sh.sp.idx[dstBuf];
-    const CT_G int32_t* nzf = sh.sp.nzFlag;
     const int per = (limit + BLOCK - 1) / BLOCK;
     const int b = min((int)threadIdx.x * per, limit);
     const int e = min(b + per, limit);
     int cnt = 0;
-    for (int p = b; p < e; ++p) cnt += ldsFlags ? sh.nz[p] : nzf[p];
+    for (int p = b; p < e; ++p) cnt += sh.nz[p];
     int nSurv = 0;
     int sv = block_scan_excl<true>(cnt, &nSurv, sh);
     int zr = nSurv + (b - sv);
     for (int p = b; p < e; ++p) {
-      const int gid = scratch ? p : ldsFlags ? (int)sh.gidx[p] : src[p];
-      const int f = ldsFlags ? sh.nz[p] : nzf[p];
+      const int gid = scratch ? p : (int)sh.gidx[p];
+      const int f = sh.nz[p];
       if (f) dst[sv++] = gid; else dst[zr++] = gid;
     }
     for (int p = limit + threadIdx.x; p < nGran; p += BLOCK)
-      dst[p] = scratch ? p : ldsFlags ? (int)sh.gidx[p] : src[p];
+      dst[p] = scratch ? p : (int)sh.gidx[p];
     if (nSurv == 0 && !negative) st = ST_FAIL;
     if (threadIdx.x == 0) {
       s->cur = dstBuf;
@@ -1084,89 +1054,38 @@ __device__ void add_filter_stats(SlotDesc* s, const unsigned long long* cnt) {
 }
 
 // ---------------------------------------------------------------------------
-// split mode: one update item of a job (the last one finalizes the job)
+// split mode: a job's update item (tables of at most WAVES x NGW granules:
+// larger ones run staged)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void do_update(const KArgs& a, const DevJob& J, int chunk, Shared& sh) {
+__device__ __forceinline__ void do_update(const KArgs& a, const DevJob& J, Shared& sh) {
   SlotDesc* s = J.slot;
   if (J.nPop > 0) {
     if (!block_wait(a, &s->prepDone, 1, sh)) return;
   }
-  // a job of one update item runs the whole update in this workgroup, as
-  // in solo mode: pushes in the prologue (unless the prep item made them),
-  // granule list, flags and trail count in LDS, no global round trip
-  // between the update and the partition (one call site each of the
-  // prologue and the update: a second would take the kernel arguments'
-  // address)
-  const bool one = J.nUpd == 1;
-  if (one && threadIdx.x == 0) sh.trailCount = 0;
-  prologue(a, J, sh, one && J.nPop == 0 && J.nPush > 0, one);
-  // the job's tile: each wave takes tile granules of the item, NGW at a
-  // time (the item covers WAVES x tile granules)
-  if (one && J.tab->nGran <= WAVES) {
+  // the whole update runs in this workgroup, as in solo mode: pushes in the
+  // prologue (unless the prep item made them), granule list, flags and trail
+  // count in LDS, no global round trip between the update and the partition
+  // (one call site each of the prologue and the update: a second would take
+  // the kernel arguments' address)
+  if (threadIdx.x == 0) sh.trailCount = 0;
+  prologue(a, J, sh, J.nPop == 0 && J.nPush > 0);
+  if (J.tab->nGran <= WAVES) {
     // at most one granule per wave: twice the rows in flight instead
-    update_granules<1, 2 * ROW_UNROLL>(a, J, sh, wave_id(), true, &sh.trailCount, &sh.sp);
+    update_granules<1, 2 * ROW_UNROLL>(a, J, sh, wave_id(), &sh.trailCount, &sh.sp);
   } else {
-    const int reps = tile_reps(J.tile);
-    for (int r = 0; r < reps; ++r)
-      update_granules<NGW>(a, J, sh, ((chunk * reps + r) * WAVES + wave_id()) * NGW, one,
-                           one ? &sh.trailCount : &s->jobTrail, &sh.sp);
+    update_granules<NGW>(a, J, sh, wave_id() * NGW, &sh.trailCount, &sh.sp);
   }
-  if (one) {
-    lds_barrier();
-    if (J.nPop > 0 && threadIdx.x == 0) s->prepDone = 0;  // the prep item also did the pushes
-    const int st = finalize_update(J, sh, true, sh.trailCount);
-    if (threadIdx.x == 0) {
-      if (st != ST_OK) publish_status(J, st);
-      // finalize_update ends with a full barrier: the block's writes are
-      // ordered before this release; a currTable copy in host memory is
-      // made visible before the filter publishes the status
-      if (J.ct_out) status_fence(J);
-      // consumed (and reset) by the job's last filter item, or a flagged
-      // job's number
-      st_release(&s->updDone, (J.flags & JF_LL) ? ll_gen(J.seq) : 1);
-    }
-    return;
-  }
-
-  // count finished items; the last one finalizes the job
-  __syncthreads();
+  lds_barrier();
+  if (J.nPop > 0 && threadIdx.x == 0) s->prepDone = 0;  // the prep item also did the pushes
+  const int st = finalize_update(J, sh, sh.trailCount);
   if (threadIdx.x == 0) {
-    item_fence(J);
-    const int prev = atomicAdd(&s->updCount, 1);
-    sh.isLast = prev == J.nUpd - 1;
-    if (sh.isLast) {
-      s->updCount = 0;
-      __threadfence();
-    }
-  }
-  __syncthreads();
-  if (!sh.isLast) return;
-
-  if (J.nPop > 0) {
-    if (threadIdx.x == 0) s->prepDone = 0;  // the prep item also did the pushes
-  } else if (J.nPush > 0) {
-    // pushes record the state before this job
-    if (threadIdx.x == 0) {
-      sh.depth = s->depth;
-      sh.bad_sub = s->failed;
-      sh.item = s->serial;
-    }
-    __syncthreads();
-    push_levels(J, s, sh.depth, sh.trailTop, sh.limit, sh.bad_sub, sh.item, J.tab->D);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      s->depth = sh.depth + J.nPush;
-      s->serial = J.serialBase + J.nPush - 1;
-    }
-  }
-  if (threadIdx.x == 0) sh.trailCount = s->jobTrail;
-  __syncthreads();
-  const int st = finalize_update(J, sh, false, sh.trailCount);
-  if (threadIdx.x == 0) {
-    s->jobTrail = 0;
     if (st != ST_OK) publish_status(J, st);
-    // finalize_update ends with a barrier: the block's writes are ordered
-    // before this release
+    // finalize_update ends with a full barrier: the block's writes are
+    // ordered before this release; a currTable copy in host memory is
+    // made visible before the filter publishes the status
+    if (J.ct_out) status_fence(J);
+    // consumed (and reset) by the job's last filter item, or a flagged
+    // job's number
     st_release(&s->updDone, (J.flags & JF_LL) ? ll_gen(J.seq) : 1);
   }
 }
@@ -1359,7 +1278,7 @@ __device__ __forceinline__ void do_solo(const KArgs& a, const DevJob& J0, Shared
   if (!pushHere) apply_pops_pushes(J, sh);
   // (the job's granule list is read once, in the prologue: each update step
   // is then a single round of independent loads)
-  prologue(a, J, sh, pushHere, true);
+  prologue(a, J, sh, pushHere);
   if (threadIdx.x == 0) sh.trailCount = 0;
   const int nGran = J.tab->nGran;
   int span = sh.status == ST_OK ? nGran : 0;
@@ -1367,10 +1286,10 @@ __device__ __forceinline__ void do_solo(const KArgs& a, const DevJob& J0, Shared
   int st = ST_OK;
   for (int pass = 0;; ++pass) {
     for (int c = 0; c < span; c += WAVES * NGS) {
-      update_granules<NGS>(a, J, sh, c + wave_id() * NGS, true, &sh.trailCount);
+      update_granules<NGS>(a, J, sh, c + wave_id() * NGS, &sh.trailCount);
     }
     __syncthreads();
-    st = finalize_update(J, sh, true, sh.trailCount, pass == 0);
+    st = finalize_update(J, sh, sh.trailCount, pass == 0);
     if (!negative || pass == 1) break;
     int rows2 = 0;
     st = neg_filter(J, sh, st, &rows2);
@@ -1574,57 +1493,28 @@ __device__ void clock_end(const KArgs& a) {
   }
 }
 
+// Either one job (the kernel argument): a workgroup per item -- prep, update
+// or solo, filters -- all resident at once, so every wait between them ends;
+// or an array of jobs that each run in one workgroup.
 __global__ void __launch_bounds__(BLOCK) propagate_kernel(KArgs a) {
   __shared__ Shared sh;
-  int32_t* q = a.queue;
-  const int total = a.nPrep + a.nUpd + a.nFilt;
-  const bool dynamic = (int)gridDim.x < total;
   clock_begin(a);
-  int item = blockIdx.x;
-  while (item < total) {
-    if (item < a.nPrep) {
-      const int j = a.jobs ? a.prepList[item] : 0;
+  if (a.jobs || (a.job.flags & JF_SOLO)) {
+    for (int j = blockIdx.x; j < a.nJobs; j += gridDim.x) {
       const DevJob J = job_of(a, j);
-      if (!J.active || *J.active) do_prep(a, J, sh);
-    } else if (item < a.nPrep + a.nUpd) {
-      const int x = item - a.nPrep;
-      const int j = a.jobs ? find_job(a.updOff, a.nJobs, x) : 0;
-      const DevJob J = job_of(a, j);
-      if (J.active && !*J.active) {
-        // a clean job of a model round: nothing to do
-      } else if (J.flags & JF_SOLO) {
-        do_solo(a, J, sh);
-      } else {
-        const int c = a.jobs ? x - a.updOff[j] : x;
-        do_update(a, J, c, sh);
-      }
-    } else {
-      const int x = item - a.nPrep - a.nUpd;
-      const int j = a.jobs ? find_job(a.filtOff, a.nJobs, x) : 0;
-      const int c = a.jobs ? x - a.filtOff[j] : x;
-      const DevJob J = job_of(a, j);
-      if (!J.active || *J.active) do_filter(a, J, c, sh);
+      if (J.active && !*J.active) continue;  // a clean job of a model round
+      do_solo(a, J, sh);
+      __syncthreads();
     }
-    if (!dynamic) break;
-    __syncthreads();
-    if (threadIdx.x == 0) sh.item = (int)gridDim.x + atomicAdd(&q[0], 1);
-    __syncthreads();
-    item = sh.item;
+  } else {
+    const int item = blockIdx.x;
+    const DevJob J = job_of(a, 0);
+    if (item < a.nPrep) do_prep(a, J, sh);
+    else if (item < a.nPrep + a.nUpd) do_update(a, J, sh);
+    else do_filter(a, J, item - a.nPrep - a.nUpd, sh);
   }
   __syncthreads();
   clock_end(a);
-  if (!dynamic) return;
-  // the last workgroup out resets the queue for the next launch
-  if (threadIdx.x == 0) {
-    __threadfence();
-    const int prev = atomicAdd(&q[1], 1);
-    if (prev == (int)gridDim.x - 1) {
-      q[0] = 0;
-      q[1] = 0;
-      q[2] += 1;  // dynamic launches completed (diagnostics)
-      __threadfence();
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1794,13 +1684,13 @@ __device__ __forceinline__ int se_update(const KArgs& a, const DevJob& J, Shared
   SlotDesc* s = J.slot;
   if (J.nPop > 0) apply_pops_pushes(J, sh);  // the pops, then the pushes
   if (threadIdx.x == 0) sh.trailCount = 0;
-  prologue(a, J, sh, J.nPop == 0 && J.nPush > 0, true);
+  prologue(a, J, sh, J.nPop == 0 && J.nPush > 0);
   if (J.tab->nGran <= WAVES)  // at most one granule per wave: twice the rows in flight
-    update_granules<1, 2 * ROW_UNROLL>(a, J, sh, wave_id(), true, &sh.trailCount, &sh.sp);
+    update_granules<1, 2 * ROW_UNROLL>(a, J, sh, wave_id(), &sh.trailCount, &sh.sp);
   else
-    update_granules<NGW>(a, J, sh, wave_id() * NGW, true, &sh.trailCount, &sh.sp);
+    update_granules<NGW>(a, J, sh, wave_id() * NGW, &sh.trailCount, &sh.sp);
   lds_barrier();
-  const int st = finalize_update(J, sh, true, sh.trailCount);
+  const int st = finalize_update(J, sh, sh.trailCount);
   // finalize_update ends with a full barrier: the block's writes are ordered
   // before this release
   if (threadIdx.x == 0) st_release(&s->updDone, ll_gen(J.seq));
@@ -2001,9 +1891,7 @@ __global__ void __launch_bounds__(BLOCK) init_slots_kernel(const TabDesc* T, Slo
     s->failed = T->rootFailed;
     s->depth = 0;
     s->serial = 0;
-    s->updCount = 0;
     s->filtCount = 0;
-    s->jobTrail = 0;
     s->prepDone = 0;
     s->updDone = 0;
     s->status = 0;
@@ -2139,11 +2027,8 @@ __global__ void __launch_bounds__(BLOCK) model_mark_kernel(ModelDesc M) {
 // ---------------------------------------------------------------------------
 namespace ctk {
 
-// update items of a split job: WAVES x (granules per wave of its tile) granules each
-int propagate_items_per_job_update(int nGran, int tile) {
-  const int gpi = WAVES * NGW * tile_reps(tile);
-  return (nGran + gpi - 1) / gpi;
-}
+// update items of a split job: WAVES x NGW granules each
+int propagate_items_per_job_update(int nGran) { return (nGran + WAVES * NGW - 1) / (WAVES * NGW); }
 int propagate_items_per_job_filter(int D) { return (D + WAVES - 1) / WAVES; }
 
 // Workgroups of the propagate kernel that are resident at once on the whole
@@ -2182,10 +2067,15 @@ hipError_t launch_build_supports(const int32_t* tuples, int64_t t, int n, const 
   return hipGetLastError();
 }
 
-hipError_t launch_model_round(const ModelDesc& M, const KArgs& a, int grid, hipStream_t stream) {
+hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int popGran, hipStream_t stream);
+
+hipError_t launch_model_round(const ModelDesc& M, const KArgs& a, const StageArgs& A, int nU, int nF, const KArgs& aNeg,
+                              hipStream_t stream) {
   const int gb = 256;
   hipLaunchKernelGGL(model_gather_kernel, dim3(gb), dim3(BLOCK), 0, stream, M);
-  hipLaunchKernelGGL(propagate_kernel, dim3(grid), dim3(BLOCK), 0, stream, a);
+  if (a.nJobs > 0) (void)launch_staged(a, A, nU, nF, 0, stream);
+  if (aNeg.nJobs > 0)
+    hipLaunchKernelGGL(propagate_kernel, dim3(std::min(aNeg.nJobs, propagate_max_grid())), dim3(BLOCK), 0, stream, aNeg);
   hipLaunchKernelGGL(model_merge_kernel, dim3(gb), dim3(BLOCK), 0, stream, M);
   hipLaunchKernelGGL(model_changed_kernel, dim3(gb), dim3(BLOCK), 0, stream, M);
   hipLaunchKernelGGL(model_mark_kernel, dim3(gb), dim3(BLOCK), 0, stream, M);

@@ -18,22 +18,21 @@ namespace ctk {
 
 constexpr size_t NA_SCRATCH_BYTES = (size_t)16 << 20;
 
-// [0, 256): work-queue counters (head, exit count, launches, error) and the
-// error word of an earlier call; then descriptor staging (2 MiB); then the
-// search-node records and granule flags (the rest)
+// [0, 256): the error words of the last call and of an earlier one, and the
+// staged schedule's item counts; then descriptor staging (2 MiB); then the
+// search-node or the staged schedule's scratch (the rest)
 static __device__ __align__(256) char scratch[NA_SCRATCH_BYTES];
 
 namespace {
 
-// Clears the work queue before a call: head and exit count (a launch that
-// ended normally already left them at zero) and the error word, whose last
-// value is kept in word 4 for ct_batch_status.
+// Before a call: the item counts (a launch that ended normally already left
+// them at zero) and the error word, whose last value is kept in word 4 for
+// ct_batch_status, are cleared.
 __global__ void noalloc_reset_kernel(int32_t* q) {
   if (threadIdx.x == 0) {
     if (q[3]) q[4] = q[3];
-    q[0] = 0;
-    q[1] = 0;
     q[3] = 0;
+    for (int k = 0; k < 3; ++k) q[QUEUE_STAGE + k] = 0;
   }
 }
 

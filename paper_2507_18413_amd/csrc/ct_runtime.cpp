@@ -25,13 +25,18 @@
 using namespace ctk;
 
 namespace ctk {
-int propagate_items_per_job_update(int nGran, int tile);
+int propagate_items_per_job_update(int nGran);
 int propagate_items_per_job_filter(int D);
 int propagate_max_grid();
 hipError_t launch_propagate(const KArgs& a, int grid, hipStream_t stream);
 size_t engine_lds_bytes(int n, int D, int nGran, int rows);
 hipError_t launch_engine(const EngDesc& D, size_t lds, hipStream_t stream);
 hipError_t launch_split_engine(const EngDesc& E, int grid, hipStream_t stream);
+int stage_row_pad();
+int stage_update_items(int nGran);
+bool stage_wide(int nGran, int D);
+int stage_finish_items(int D, int wide);
+hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int popGran, hipStream_t stream);
 int nodes_max_vec_rows(size_t lds);
 size_t nodes_scratch_bytes(int vecRows, int nJobs, int nGran);
 size_t nodes_ids_bytes(int n, int64_t stride);
@@ -116,11 +121,11 @@ struct DevBlock {
 
 // Device queue + staging for one stream.
 struct QueueCtx {
-  int32_t* queue = nullptr;   // 4 ints on the device
+  int32_t* queue = nullptr;   // QUEUE_INTS on the device: error word, staged item counts
   int32_t* hostErr = nullptr; // pinned
-  // batch staging: job descriptors, then (256-byte aligned) updOff | filtOff
-  // | prepList | root tasks, sent in one copy; two pinned buffers in turn let
-  // the host fill one while the other's copy is still queued
+  // batch staging: job descriptors, then (256-byte aligned) root tasks, sent
+  // in one copy; two pinned buffers in turn let the host fill one while the
+  // other's copy is still queued
   char* dStage = nullptr;
   char* pStage[2] = {nullptr, nullptr};
   hipEvent_t staged[2] = {nullptr, nullptr};
@@ -128,16 +133,20 @@ struct QueueCtx {
   int turn = 0;
   // host scratch of a batch, kept between batches (no allocation per call)
   std::vector<DevJob> hJobs;
-  std::vector<int32_t> updOff, filtOff, prep, rootTasks;
+  std::vector<int32_t> chunks, rootTasks;
   std::vector<std::array<int32_t, 3>> rootKey;
   // search-node schedule scratch (node records | row vectors | non-zero words)
   void* dNodes = nullptr;
   size_t capNodes = 0;
+  // staged schedule scratch (see StageNeed)
+  char* dStaged = nullptr;
+  size_t capStaged = 0;
 };
 
+
 int queue_init(QueueCtx& q) {
-  ALLOCCHK(hipMalloc(&q.queue, 4 * sizeof(int32_t)));
-  HIPCHK(hipMemset(q.queue, 0, 4 * sizeof(int32_t)));
+  ALLOCCHK(hipMalloc(&q.queue, QUEUE_INTS * sizeof(int32_t)));
+  HIPCHK(hipMemset(q.queue, 0, QUEUE_INTS * sizeof(int32_t)));
   ALLOCCHK(hipHostMalloc((void**)&q.hostErr, sizeof(int32_t), hipHostMallocMapped | hipHostMallocCoherent));
   *q.hostErr = 0;
   for (int k = 0; k < 2; ++k) HIPCHK(hipEventCreateWithFlags(&q.staged[k], hipEventDisableTiming));
@@ -153,6 +162,7 @@ void queue_free(QueueCtx& q) {
     if (q.staged[k]) (void)hipEventDestroy(q.staged[k]);
   }
   if (q.dNodes) (void)hipFree(q.dNodes);
+  if (q.dStaged) (void)hipFree(q.dStaged);
   q = QueueCtx();
 }
 
@@ -287,19 +297,16 @@ int check_poison(const ct_table* T) {
   return CT_OK;
 }
 
-constexpr int SOLO_MAX_GRAN = 4;      // tables up to 16,384 tuples run solo ...
-constexpr int SOLO_MAX_D = 16;        // ... unless filterDomains has more words than 4 waves take at once
-constexpr int SOLO_MIN_BATCH = 256;   // batches this large run every job solo
-
+constexpr int SOLO_MAX_GRAN = 4;      // tables up to 16,384 tuples run in one workgroup ...
+constexpr int SOLO_MAX_D = 16;        // ... unless their filterDomains has more words than that takes at once
 constexpr int NODES_MIN_BATCH = 64;   // AUTO: batches of root resets this large run granule-major
-constexpr int SCRATCH_SOLO_MAX_GRAN = 16;  // AUTO: roots recomputed solo up to 65,536 tuples
 
-bool use_solo(const ct_table* T, int nJobs) {
+bool use_solo(const ct_table* T) {
   // a negative table's call filters and then removes the pruned values'
   // tuples, in one workgroup
   if (T->kind == CT_KIND_NEGATIVE || T->cfg.schedule == CT_SCHED_SOLO) return true;
   if (T->cfg.schedule == CT_SCHED_SPLIT) return false;
-  return (T->nGran <= SOLO_MAX_GRAN && T->D <= SOLO_MAX_D) || nJobs >= SOLO_MIN_BATCH;
+  return T->nGran <= SOLO_MAX_GRAN && T->D <= SOLO_MAX_D;
 }
 
 // Largest LDS of one workgroup on the current device (0 if unknown).
@@ -356,23 +363,66 @@ bool nodes_batch(const ct_job* jobs, int n) {
   return true;
 }
 
-// Fill item counts of a job: solo = one update item that does everything.
-void job_counts(const ct_table* T, DevJob& J) {
-  if (!(J.flags & JF_PROPAGATE)) {
-    J.nUpd = 0;
-    J.nFilt = 0;
-  } else if (J.flags & JF_SOLO) {
-    J.nUpd = 1;
-    J.nFilt = 0;
-  } else {
-    J.nUpd = propagate_items_per_job_update(T->nGran, J.tile);
-    J.nFilt = propagate_items_per_job_filter(T->D);
-  }
+// Staged schedule: what a job needs of a launch's scratch.  A launch's
+// scratch holds the records of its jobs, the update items, the finish items,
+// then each job's input words, |dom| words and row list.
+constexpr int STAGE_LIST_CAP = 65536;  // row-list entries of a job (more: the update walks the selected bits)
+constexpr size_t STAGE_SCRATCH = (size_t)64 << 20;  // a batch beyond it runs as several launches
+
+int stage_list_cap(const ct_table* T) { return std::min(T->rows, STAGE_LIST_CAP); }
+
+size_t stage_job_bytes(const ct_table* T) {
+  const size_t list = sizeof(uint32_t) * ((size_t)stage_list_cap(T) + stage_row_pad());
+  return align256(sizeof(uint64_t) * T->D + sizeof(int32_t) * ((T->D + 1) & ~1) +
+                  std::max(list, sizeof(uint64_t) * (size_t)T->D));
 }
 
-bool needs_prep(const DevJob& J) {
-  if (!(J.flags & JF_PROPAGATE)) return true;
-  return !(J.flags & JF_SOLO) && J.nPop > 0;
+struct StageNeed {
+  int nJobs = 0, nU = 0, nF = 0, popGran = 0;
+  size_t jobBytes = 0;
+  bool wide = false;
+  void add(const ct_table* T, bool propagate, bool pops, bool solo) {
+    ++nJobs;
+    if (pops) popGran = std::max(popGran, T->nGran);
+    if (!propagate) return;
+    jobBytes += stage_job_bytes(T);
+    if (solo) return;
+    nU += stage_update_items(T->nGran);
+    nF += stage_finish_items(T->D, 0);  // (the narrow form has the most)
+    wide = wide || stage_wide(T->nGran, T->D);
+  }
+  size_t itemBytes() const {
+    return align256(sizeof(StageItem) * (size_t)nU) + align256(sizeof(StageItem) * (size_t)nF);
+  }
+  size_t bytes() const { return align256(sizeof(StageRec) * (size_t)nJobs) + itemBytes() + jobBytes; }
+};
+
+// The launch's view of its scratch.
+StageArgs stage_args(const StageNeed& n, char* scratch, int32_t* queue, int32_t* hostErr) {
+  StageArgs A{};
+  A.rec = (StageRec*)scratch;
+  scratch += align256(sizeof(StageRec) * (size_t)n.nJobs);
+  A.items = (StageItem*)scratch;
+  scratch += align256(sizeof(StageItem) * (size_t)n.nU);
+  A.fItems = (StageItem*)scratch;
+  scratch += align256(sizeof(StageItem) * (size_t)n.nF);
+  A.count = queue + QUEUE_STAGE;
+  A.wide = n.wide;
+  A.queue = queue;
+  A.hostErr = hostErr;
+  A.jobMem = scratch;
+  return A;
+}
+
+int stage_reserve(QueueCtx& q, size_t bytes, hipStream_t stream) {
+  if (q.capStaged >= bytes) return CT_OK;
+  HIPCHK(hipStreamSynchronize(stream));
+  if (q.dStaged) (void)hipFree(q.dStaged);
+  q.dStaged = nullptr;
+  q.capStaged = 0;
+  ALLOCCHK(hipMalloc((void**)&q.dStaged, bytes));
+  q.capStaged = bytes;
+  return CT_OK;
 }
 
 // Run one job synchronously on the table's stream.
@@ -380,19 +430,42 @@ int quiesce(ct_table* T, hipStream_t same = nullptr);
 
 uint64_t* pinned_dev64(ct_table* T, uint64_t* host);
 
+// A synchronous call of a table whose update is one item of 8 granules and
+// whose input fits the kernel arguments runs as one launch with hand-offs
+// (measured 20-21 us a call against 21-22 us staged at 12,000 and 30,000 tuples);
+// the others run staged (200,000 tuples: 22 against 27 us; 2,000,000: 26
+// against 64; 2,422 domain words: 62 against 105).
+bool stage_single(const ct_table* T) {
+  return propagate_items_per_job_update(T->nGran) > 1 || T->D > INLINE_WORDS;
+}
+
 int run_single(ct_table* T, DevJob& J, const uint64_t* dom_in_host) {
   int qrc = quiesce(T);
   if (qrc) return qrc;
   KArgs a{};
   a.jobs = nullptr;
   a.nJobs = 1;
-  if ((J.flags & JF_PROPAGATE) && use_solo(T, 1)) J.flags |= JF_SOLO;
-  job_counts(T, J);
-  a.nPrep = needs_prep(J) ? 1 : 0;
+  const bool prop = J.flags & JF_PROPAGATE;
+  if (prop && use_solo(T)) J.flags |= JF_SOLO;
+  const bool solo = J.flags & JF_SOLO;
+  const bool staged = prop && !solo && stage_single(T);
+  J.nUpd = prop ? 1 : 0;
+  J.nFilt = prop && !solo ? propagate_items_per_job_filter(T->D) : 0;
+  a.nPrep = !prop || (!solo && J.nPop > 0) ? 1 : 0;
   J.flags |= JF_HOST_OUT;
+  StageNeed need;
+  StageArgs A{};
+  if (staged) {
+    need.add(T, true, J.nPop > 0, false);
+    int rc = stage_reserve(T->q, need.bytes(), T->stream);
+    if (rc) return rc;
+    A = stage_args(need, T->q.dStaged, T->q.queue, T->q.hostErr);
+    A.items = nullptr;  // one job: its items by workgroup
+    J.listCap = stage_list_cap(T);
+  }
   // a split propagation answers through flagged slots (no currTable copy:
   // that one keeps the fenced, counted status)
-  const bool ll = (J.flags & JF_PROPAGATE) && !(J.flags & JF_SOLO) && !J.ct_out && T->pLL;
+  const bool ll = (J.flags & JF_PROPAGATE) && !(J.flags & JF_SOLO) && (staged || !J.ct_out) && T->pLL;
   uint32_t sq = 0;
   if (ll) {
     J.flags |= JF_LL;
@@ -422,7 +495,12 @@ int run_single(ct_table* T, DevJob& J, const uint64_t* dom_in_host) {
   volatile int32_t* status = T->pStatus;
   *status = kStatusPending;
   a.clock = T->timing ? T->dClock : nullptr;
-  HIPCHK(launch_propagate(a, std::min(total, propagate_max_grid()), T->stream));
+  if (staged) {
+    A.clock = a.clock;
+    HIPCHK(launch_staged(a, A, need.nU, stage_finish_items(T->D, A.wide), need.popGran, T->stream));
+  } else {
+    HIPCHK(launch_propagate(a, std::min(total, propagate_max_grid()), T->stream));
+  }
   T->tailPending = true;
   if (ll) {
     // the status slot (a job that does not succeed) or every domain word
@@ -436,7 +514,12 @@ int run_single(ct_table* T, DevJob& J, const uint64_t* dom_in_host) {
         *status = (int32_t)(uint32_t)(v >> 32);
         break;
       }
-      while (got < nS && (uint32_t)__atomic_load_n(&sl[2 + got], __ATOMIC_ACQUIRE) == sq) ++got;
+      // (a wide table's slots are many lines the device has just written:
+      // fetched ahead, they do not miss one after the other)
+      while (got < nS && (uint32_t)__atomic_load_n(&sl[2 + got], __ATOMIC_ACQUIRE) == sq) {
+        if ((got & 7) == 0) __builtin_prefetch(&sl[2 + std::min(got + 128, nS - 1)]);
+        ++got;
+      }
       if (got == nS) {
         for (int q = 0; q < T->D; ++q)
           T->pDomOut[q] = ((uint64_t)(uint32_t)(sl[3 + 2 * q] >> 32) << 32) | (uint32_t)(sl[2 + 2 * q] >> 32);
@@ -724,7 +807,7 @@ bool split_engine_wanted(ct_table* T) {
     T->seVarWords = m;
   }
   return T->cfg.schedule == CT_SCHED_AUTO && T->kind == CT_KIND_POSITIVE && !engine_wanted(T) &&
-         !use_solo(T, 1) && propagate_items_per_job_update(T->nGran, 0) == 1 && T->D <= INLINE_WORDS &&
+         !use_solo(T) && propagate_items_per_job_update(T->nGran) == 1 && T->D <= INLINE_WORDS &&
          T->D <= ENG_MAX_D && T->seVarWords <= SE_MAX_VAR_WORDS &&
          2 + (8 * propagate_items_per_job_filter(T->D)) / 7 <= propagate_max_grid();
 }
@@ -839,68 +922,97 @@ int batch_validate_quiesce(const ct_job* jobs, int n_jobs, hipStream_t stream) {
   return CT_OK;
 }
 
-// Device descriptors of a validated batch, written into out[n_jobs], the
-// item offsets updOff / filtOff (n_jobs + 1 entries, [0] = 0 on entry) and
-// the prep list (up to n_jobs entries); returns the prep list's length.
+// How a batch's jobs are laid out: the staged ones first (in launches of at
+// most the scratch's size: chunks[k] is the first job of launch k), then
+// those that run in one workgroup of the propagate kernel (negative tables).
+struct BatchShape {
+  int nStaged = 0, nChunks = 0, popGran = 0;
+  bool wide = false;
+};
+
+// Negative tables, and a job whose scratch alone is beyond the capacity, run
+// in one workgroup of the propagate kernel.
+bool batch_staged(const ct_table* T, bool propagate, size_t scratchCap) {
+  if (!propagate) return true;
+  StageNeed one;
+  one.add(T, true, false, use_solo(T));
+  return T->kind != CT_KIND_NEGATIVE && one.bytes() <= scratchCap;
+}
+
+// Device descriptors of a validated batch, written into out[n_jobs] (other:
+// the search-node and root schedules take them in the batch's order).
 // Applies the jobs' pops and pushes to the host mirror of each slot.
-int batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool nodes, DevJob* out,
-                int32_t* updOff, int32_t* filtOff, int32_t* prep) {
-  int nPrep = 0;
-  updOff[0] = filtOff[0] = 0;
-  for (int j = 0; j < n_jobs; ++j) {
-    const ct_job& cj = jobs[j];
-    ct_table* T = cj.table;
-    SlotHost& S = T->slots[cj.slot];
-    DevJob& J = out[j];
-    J = DevJob{};
-    J.tab = T->dTab;
-    J.slot = S.dev;
-    J.dom_in = cj.dom_in;
-    J.dom_out = cj.dom_out;
-    J.ct_out = cj.ct_out;
-    J.status_out = status_dev + j;
-    J.flags = ((cj.flags & CT_JOB_PROPAGATE) ? JF_PROPAGATE : 0u) |
-              ((cj.flags & CT_JOB_FROM_ROOT) ? JF_FROM_ROOT : 0u) |
-              ((cj.flags & CT_JOB_ROOT) ? (JF_ROOT | JF_FROM_ROOT | JF_SCRATCH) : 0u);
-    if (cj.flags & (CT_JOB_FROM_ROOT | CT_JOB_ROOT)) {
-      S.pendPop = S.pendPush = 0;
-      S.depth = 0;
-      S.failedAt.clear();
-      J.serialBase = T->serialCounter++;
-      J.depthAfter = 0;
-    } else {
-      // pending single-call operations (pops P then pushes Q) come first
-      int P = S.pendPop, Q = S.pendPush;
-      if (cj.n_pop <= Q) {
-        Q = Q - cj.n_pop + cj.n_push;
+BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool other, size_t scratchCap,
+                       DevJob* out, int32_t* chunks) {
+  BatchShape B;
+  StageNeed need;
+  int at = 0;
+  for (int pass = 0; pass < (other ? 1 : 2); ++pass)
+    for (int j = 0; j < n_jobs; ++j) {
+      const ct_job& cj = jobs[j];
+      ct_table* T = cj.table;
+      const bool propagate = cj.flags & CT_JOB_PROPAGATE;
+      const bool staged = !other && batch_staged(T, propagate, scratchCap);
+      if (!other && staged != (pass == 0)) continue;
+      SlotHost& S = T->slots[cj.slot];
+      DevJob& J = out[at++];
+      J = DevJob{};
+      J.tab = T->dTab;
+      J.slot = S.dev;
+      J.dom_in = cj.dom_in;
+      J.dom_out = cj.dom_out;
+      J.ct_out = cj.ct_out;
+      J.status_out = status_dev + j;
+      J.flags = (propagate ? JF_PROPAGATE : 0u) | ((cj.flags & CT_JOB_FROM_ROOT) ? JF_FROM_ROOT : 0u) |
+                ((cj.flags & CT_JOB_ROOT) ? (JF_ROOT | JF_FROM_ROOT | JF_SCRATCH) : 0u);
+      if (cj.flags & (CT_JOB_FROM_ROOT | CT_JOB_ROOT)) {
+        S.pendPop = S.pendPush = 0;
+        S.depth = 0;
+        S.failedAt.clear();
+        J.serialBase = T->serialCounter++;
+        J.depthAfter = 0;
       } else {
-        P += cj.n_pop - Q;
-        Q = cj.n_push;
+        // pending single-call operations (pops P then pushes Q) come first
+        int P = S.pendPop, Q = S.pendPush;
+        if (cj.n_pop <= Q) {
+          Q = Q - cj.n_pop + cj.n_push;
+        } else {
+          P += cj.n_pop - Q;
+          Q = cj.n_push;
+        }
+        S.pendPop = S.pendPush = 0;
+        J.nPop = P;
+        J.nPush = Q;
+        J.serialBase = T->serialCounter;
+        T->serialCounter += Q;
+        for (int k = 0; k < cj.n_pop; ++k) S.failedAt.pop_back();
+        for (int k = 0; k < cj.n_push; ++k) S.failedAt.push_back(2);
+        S.depth = S.depth - cj.n_pop + cj.n_push;
+        J.depthAfter = S.depth;
       }
-      S.pendPop = S.pendPush = 0;
-      J.nPop = P;
-      J.nPush = Q;
-      J.serialBase = T->serialCounter;
-      T->serialCounter += Q;
-      for (int k = 0; k < cj.n_pop; ++k) S.failedAt.pop_back();
-      for (int k = 0; k < cj.n_push; ++k) S.failedAt.push_back(2);
-      S.depth = S.depth - cj.n_pop + cj.n_push;
-      J.depthAfter = S.depth;
+      S.failed = 2;
+      if (other) continue;
+      const bool solo = propagate && (!staged || use_solo(T));
+      if (solo) J.flags |= JF_SOLO;
+      if (!staged) continue;
+      StageNeed more = need;
+      more.add(T, propagate, J.nPop > 0, solo);
+      if (B.nStaged == 0 || more.bytes() > scratchCap) {
+        chunks[B.nChunks++] = B.nStaged;
+        need = StageNeed();
+        more = need;
+        more.add(T, propagate, J.nPop > 0, solo);
+      }
+      J.stageOff = (int32_t)(need.jobBytes / 256);
+      J.listCap = stage_list_cap(T);
+      J.nUpd = more.nU - need.nU;
+      J.nFilt = more.nF - need.nF;
+      need = more;
+      B.popGran = std::max(B.popGran, need.popGran);
+      B.wide = B.wide || need.wide;
+      ++B.nStaged;
     }
-    S.failed = 2;
-    // a root recomputed from scratch streams every support row: large
-    // tables are split over workgroups (the queue balances them), small ones
-    // run solo
-    const bool solo = (J.flags & JF_SCRATCH) && T->cfg.schedule == CT_SCHED_AUTO && T->kind == CT_KIND_POSITIVE
-                          ? T->nGran <= SCRATCH_SOLO_MAX_GRAN
-                          : use_solo(T, n_jobs);
-    if ((J.flags & JF_PROPAGATE) && !nodes && solo) J.flags |= JF_SOLO;
-    job_counts(T, J);
-    updOff[j + 1] = updOff[j] + J.nUpd;
-    filtOff[j + 1] = filtOff[j] + J.nFilt;
-    if (needs_prep(J)) prep[nPrep++] = j;
-  }
-  return nPrep;
+  return B;
 }
 
 }  // namespace
@@ -1533,6 +1645,7 @@ namespace {
 // What a validated batch needs, before any slot's host state changes.
 struct BatchPlan {
   bool nodes = false, roots = false;
+  size_t stagedBytes = 0;  // staged scratch of all jobs at once
   size_t nodesBytes = 0;   // search-node records, row vectors and non-zero words
   size_t nTaskInts = 0;    // root tasks, two ints each
   size_t offAt = 0;        // byte offset of the int section of the staging area
@@ -1553,8 +1666,18 @@ BatchPlan batch_plan(const ct_job* jobs, int n_jobs, bool nodes) {
     for (int j = 0; j < n_jobs; ++j) nTasks += (size_t)(jobs[j].table->nGran + WAVES - 1) / WAVES;
     p.nTaskInts = 2 * nTasks;
   }
+  if (!p.nodes && !p.roots) {
+    StageNeed need;
+    for (int j = 0; j < n_jobs; ++j) {
+      const ct_table* T = jobs[j].table;
+      const bool propagate = jobs[j].flags & CT_JOB_PROPAGATE;
+      if (batch_staged(T, propagate, STAGE_SCRATCH)) need.add(T, propagate, false, propagate && use_solo(T));
+    }
+    p.stagedBytes = need.bytes();
+  }
   p.offAt = align256(sizeof(DevJob) * (size_t)n_jobs);
-  // job descriptors, then updOff | filtOff | prep list | root tasks (even offset)
+  // job descriptors, then the root tasks; the documented limit of a
+  // no-allocation batch counts three ints a job besides
   p.stageBytes = p.offAt + sizeof(int32_t) * (2 * (size_t)(n_jobs + 1) + (size_t)n_jobs + 2 + p.nTaskInts);
   return p;
 }
@@ -1563,16 +1686,16 @@ BatchPlan batch_plan(const ct_job* jobs, int n_jobs, bool nodes) {
 // scratch, and the host arrays the descriptors are built in.  Capacities
 // must cover the batch's plan.
 struct BatchRes {
-  int32_t* queue = nullptr;     // device: [0] head, [1] exit count, [2] launches, [3] error
+  int32_t* queue = nullptr;     // device: QUEUE_INTS
   int32_t* hostErr = nullptr;   // pinned, nullable
   char* dStage = nullptr;       // device staging
   char* hStage = nullptr;       // host staging (the source of the one copy)
   hipEvent_t staged = nullptr;  // nullable: recorded after the copy
   void* dNodes = nullptr;
   DevJob* hJobs = nullptr;      // n_jobs
-  int32_t* updOff = nullptr;    // n_jobs + 1
-  int32_t* filtOff = nullptr;   // n_jobs + 1
-  int32_t* prep = nullptr;      // n_jobs
+  int32_t* chunks = nullptr;    // n_jobs
+  char* dStaged = nullptr;      // staged scratch
+  size_t capStaged = 0;
   int32_t* rootTasks = nullptr; // plan.nTaskInts
   std::array<int32_t, 3>* rootKey = nullptr;  // n_jobs
 };
@@ -1596,30 +1719,18 @@ int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* st
         r.rootTasks[at++] = g;
       }
   }
-  const int nPrep = batch_build(jobs, n_jobs, status_dev, p.nodes, r.hJobs, r.updOff, r.filtOff, r.prep);
-  // stage to the device (the root tasks start at an even offset: int pairs)
-  const size_t rootBase = (2 * (size_t)(n_jobs + 1) + (size_t)nPrep + 2) & ~(size_t)1;
-  const size_t nOff = p.roots ? rootBase + p.nTaskInts : 2 * (size_t)(n_jobs + 1) + (size_t)nPrep + 1;
-  const size_t stageBytes = p.offAt + sizeof(int32_t) * nOff;
-  int32_t* pOff = (int32_t*)(r.hStage + p.offAt);
+  const BatchShape B = batch_build(jobs, n_jobs, status_dev, p.nodes || p.roots, r.capStaged, r.hJobs, r.chunks);
+  // one copy to the device: the descriptors, then the root tasks
+  const size_t stageBytes = p.offAt + sizeof(int32_t) * p.nTaskInts;
   memcpy(r.hStage, r.hJobs, sizeof(DevJob) * n_jobs);
-  memcpy(pOff, r.updOff, sizeof(int32_t) * (n_jobs + 1));
-  memcpy(pOff + (n_jobs + 1), r.filtOff, sizeof(int32_t) * (n_jobs + 1));
-  if (nPrep) memcpy(pOff + 2 * (n_jobs + 1), r.prep, sizeof(int32_t) * nPrep);
-  if (p.roots && p.nTaskInts) memcpy(pOff + rootBase, r.rootTasks, sizeof(int32_t) * p.nTaskInts);
-  HIPCHK(hipMemcpyAsync(r.dStage, r.hStage, stageBytes, hipMemcpyHostToDevice, stream));
+  if (p.roots && p.nTaskInts) memcpy(r.hStage + p.offAt, r.rootTasks, sizeof(int32_t) * p.nTaskInts);
+  HIPCHK(hipMemcpyAsync(r.dStage, r.hStage, p.roots ? stageBytes : sizeof(DevJob) * (size_t)n_jobs,
+                        hipMemcpyHostToDevice, stream));
   if (r.staged) HIPCHK(hipEventRecord(r.staged, stream));
   DevJob* dJobs = (DevJob*)r.dStage;
-  int32_t* dOff = (int32_t*)(r.dStage + p.offAt);
   KArgs a{};
   a.jobs = dJobs;
-  a.updOff = dOff;
-  a.filtOff = dOff + (n_jobs + 1);
-  a.prepList = dOff + 2 * (n_jobs + 1);
   a.nJobs = n_jobs;
-  a.nPrep = nPrep;
-  a.nUpd = r.updOff[n_jobs];
-  a.nFilt = r.filtOff[n_jobs];
   a.queue = r.queue;
   a.hostErr = r.hostErr;
   if (p.nodes) {
@@ -1642,13 +1753,30 @@ int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* st
   }
   if (p.roots) {
     RootDesc R{};
-    R.tasks = dOff + rootBase;
+    R.tasks = (int32_t*)(r.dStage + p.offAt);
     R.nTasks = (int32_t)(p.nTaskInts / 2);
     HIPCHK(launch_roots(a, R, stream));
     return CT_OK;
   }
-  const int total = a.nPrep + a.nUpd + a.nFilt;
-  if (total > 0) HIPCHK(launch_propagate(a, std::min(total, propagate_max_grid()), stream));
+  for (int k = 0; k < B.nChunks; ++k) {
+    const int j0 = r.chunks[k], j1 = k + 1 < B.nChunks ? r.chunks[k + 1] : B.nStaged;
+    StageNeed need;
+    need.nJobs = j1 - j0;
+    need.wide = B.wide;
+    for (int j = j0; j < j1; ++j) {
+      need.nU += r.hJobs[j].nUpd;
+      need.nF += r.hJobs[j].nFilt;
+    }
+    const StageArgs A = stage_args(need, r.dStaged, r.queue, r.hostErr);
+    a.jobs = dJobs + j0;
+    a.nJobs = need.nJobs;
+    HIPCHK(launch_staged(a, A, need.nU, need.nF, B.popGran, stream));
+  }
+  if (B.nStaged < n_jobs) {
+    a.jobs = dJobs + B.nStaged;
+    a.nJobs = n_jobs - B.nStaged;
+    HIPCHK(launch_propagate(a, std::min(a.nJobs, propagate_max_grid()), stream));
+  }
   return CT_OK;
 }
 
@@ -1673,7 +1801,7 @@ struct NoAllocHost {
   bool used = false;
   hipStream_t lastStream = nullptr;  // the stream of the last call (ct_batch_status)
   DevJob jobs[NA_MAX_JOBS];
-  int32_t updOff[NA_MAX_JOBS + 1], filtOff[NA_MAX_JOBS + 1], prep[NA_MAX_JOBS];
+  int32_t chunks[NA_MAX_JOBS];
   std::array<int32_t, 3> rootKey[NA_MAX_JOBS];
   int32_t rootTasks[NA_MAX_TASK_INTS];
   alignas(256) char stage[NA_STAGE_BYTES];
@@ -1735,6 +1863,10 @@ int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32
     ALLOCCHK(hipMalloc(&q->dNodes, p.nodesBytes));
     q->capNodes = p.nodesBytes;
   }
+  if (p.stagedBytes) {
+    rc = stage_reserve(*q, std::min(p.stagedBytes, STAGE_SCRATCH), stream);
+    if (rc) return rc;
+  }
   if (q->capStage < p.stageBytes) {
     HIPCHK(hipStreamSynchronize(stream));
     if (q->dStage) (void)hipFree(q->dStage);
@@ -1749,9 +1881,7 @@ int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32
     q->capStage = cap;
   }
   q->hJobs.resize(n_jobs);
-  q->updOff.assign(n_jobs + 1, 0);
-  q->filtOff.assign(n_jobs + 1, 0);
-  q->prep.resize(n_jobs);
+  q->chunks.resize(n_jobs);
   q->rootTasks.resize(p.nTaskInts);
   q->rootKey.resize(p.roots ? n_jobs : 0);
   // two pinned staging buffers in turn: the copy that last read this one
@@ -1766,9 +1896,9 @@ int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32
   r.staged = q->staged[q->turn];
   r.dNodes = q->dNodes;
   r.hJobs = q->hJobs.data();
-  r.updOff = q->updOff.data();
-  r.filtOff = q->filtOff.data();
-  r.prep = q->prep.data();
+  r.chunks = q->chunks.data();
+  r.dStaged = q->dStaged;
+  r.capStaged = q->capStaged;
   r.rootTasks = q->rootTasks.data();
   r.rootKey = q->rootKey.data();
   return batch_launch(jobs, n_jobs, stream, status_dev, p, r);
@@ -1806,13 +1936,13 @@ int ct_propagate_batch_noalloc(const ct_job* jobs, int32_t n_jobs, void* stream_
   r.hStage = g_na.stage;
   r.dNodes = scratch + NA_QUEUE_BYTES + NA_STAGE_BYTES;
   r.hJobs = g_na.jobs;
-  r.updOff = g_na.updOff;
-  r.filtOff = g_na.filtOff;
-  r.prep = g_na.prep;
+  r.chunks = g_na.chunks;
+  r.dStaged = (char*)r.dNodes;
+  r.capStaged = nodesCap;
   r.rootTasks = g_na.rootTasks;
   r.rootKey = g_na.rootKey;
-  // the work queue's counters start at zero (an earlier call's error word
-  // is kept for ct_batch_status)
+  // the item counts start at zero (an earlier call's error word is kept for
+  // ct_batch_status)
   HIPCHK(launch_noalloc_reset(r.queue, stream));
   g_na.used = true;
   g_na.lastStream = stream;
@@ -1866,7 +1996,8 @@ int table_view(const ct_table* T, TableView* v) {
 // Multi-table model: propagation rounds captured in a hipGraph
 // ===========================================================================
 namespace ctk {
-hipError_t launch_model_round(const ModelDesc& M, const KArgs& a, int grid, hipStream_t stream);
+hipError_t launch_model_round(const ModelDesc& M, const KArgs& a, const StageArgs& A, int nU, int nF, const KArgs& aNeg,
+                              hipStream_t stream);
 hipError_t launch_model_seed(const ModelDesc& M, hipStream_t stream);
 }
 
@@ -1879,18 +2010,16 @@ struct ct_model {
   QueueCtx q;
   int soloMax = 4, roundsPerGraph = 8;
   // schedule per class of tables (granule bucket, rows bucket), set by the
-  // autotuner: solo or split, and the tile (granules per wave); classes
-  // without an entry follow soloMax with the default tile
+  // autotuner: solo or staged, and the tile of its cache entry; classes
+  // without an entry follow soloMax
   std::map<std::pair<int, int>, std::pair<int, int>> choice;
   // device state, rebuilt when the table set or the schedule changes
   bool built = false;
   std::vector<void*> blocks;
   ModelDesc M{};
   DevJob* dJobs = nullptr;
-  int32_t* dOff = nullptr;
-  std::vector<DevJob> hJobs;
-  KArgs a{};
-  int grid = 1;
+  std::vector<DevJob> hJobs;       // the staged jobs, then those of the propagate kernel
+  std::vector<int32_t> jobOf;      // table -> its job
   hipGraphExec_t exec = nullptr;   // roundsPerGraph rounds
   hipGraphExec_t exec1 = nullptr;  // one round: a fixpoint's first launch
   int32_t* pFlags = nullptr;   // pinned copy of M.flags
@@ -1920,7 +2049,6 @@ void model_free_device(ct_model* m) {
   m->blocks.clear();
   m->dStatus = nullptr;
   m->dJobs = nullptr;
-  m->dOff = nullptr;
   m->M = ModelDesc{};
   m->built = false;
 }
@@ -1946,7 +2074,7 @@ int log4_bucket(int64_t x) {
 
 std::pair<int, int> table_class(const ct_table* T) { return {log4_bucket(T->nGran), log4_bucket(T->rows)}; }
 
-// (solo, tile) of a table's round job
+// (solo, tile) of a table's round job (the tile is a field of the cache file only)
 std::pair<int, int> model_choice(const ct_model* m, const ct_table* T) {
   auto it = m->choice.find(table_class(T));
   if (it != m->choice.end()) return it->second;
@@ -2019,40 +2147,42 @@ int model_build(ct_model* m) {
   if ((rc = model_alloc(m, (void**)&m->dStatus, sizeof(int32_t) * std::max(nT, 1)))) return rc;
   // jobs: table c propagates slot 0 from domIn to domOut when dirty[c]
   m->hJobs.assign(nT, DevJob{});
-  std::vector<int32_t> off(2 * (nT + 1) + 1, 0);
-  for (int c = 0; c < nT; ++c) {
-    ct_table* T = m->tabs[c];
-    DevJob& J = m->hJobs[c];
-    J.tab = T->dTab;
-    J.slot = T->slots[0].dev;
-    J.dom_in = M.domIn + bufOff[c];
-    J.dom_out = M.domOut + bufOff[c];
-    J.status_out = M.status + c;
-    const auto ch = model_choice(m, T);
-    J.flags = JF_PROPAGATE | (ch.first || T->kind == CT_KIND_NEGATIVE ? JF_SOLO : 0u);
-    J.tile = ch.second;
-    J.depthAfter = T->slots[0].depth;
-    J.active = M.dirty + c;
-    job_counts(T, J);
-    off[c + 1] = off[c] + J.nUpd;
-    off[(nT + 1) + c + 1] = off[(nT + 1) + c] + J.nFilt;
-  }
+  m->jobOf.assign(nT, 0);
+  StageNeed need;
+  int at = 0;
+  for (int pass = 0; pass < 2; ++pass)
+    for (int c = 0; c < nT; ++c) {
+      ct_table* T = m->tabs[c];
+      const bool negative = T->kind == CT_KIND_NEGATIVE;
+      if (negative != (pass == 1)) continue;
+      const bool solo = model_choice(m, T).first || negative;
+      m->jobOf[c] = at;
+      DevJob& J = m->hJobs[at++];
+      J.tab = T->dTab;
+      J.slot = T->slots[0].dev;
+      J.dom_in = M.domIn + bufOff[c];
+      J.dom_out = M.domOut + bufOff[c];
+      J.status_out = M.status + c;
+      J.flags = JF_PROPAGATE | (solo ? JF_SOLO : 0u);
+      J.depthAfter = T->slots[0].depth;
+      J.active = M.dirty + c;
+      if (negative) continue;
+      J.stageOff = (int32_t)(need.jobBytes / 256);
+      J.listCap = stage_list_cap(T);
+      need.add(T, true, false, solo);
+    }
   if ((rc = model_upload(m, &m->dJobs, m->hJobs))) return rc;
-  if ((rc = model_upload(m, &m->dOff, off))) return rc;
-  KArgs& a = m->a;
-  a = KArgs{};
+  char* scratch = nullptr;
+  if ((rc = model_alloc(m, (void**)&scratch, need.bytes()))) return rc;
+  KArgs a{}, aNeg{};
   a.jobs = m->dJobs;
-  a.updOff = m->dOff;
-  a.filtOff = m->dOff + (nT + 1);
-  a.prepList = m->dOff + 2 * (nT + 1);
-  a.nJobs = nT;
-  a.nPrep = 0;
-  a.nUpd = off[nT];
-  a.nFilt = off[(nT + 1) + nT];
+  a.nJobs = need.nJobs;
   a.queue = m->q.queue;
   a.hostErr = m->q.hostErr;
-  const int total = a.nUpd + a.nFilt;
-  m->grid = std::max(1, std::min(total, propagate_max_grid()));
+  aNeg = a;
+  aNeg.jobs = m->dJobs + need.nJobs;
+  aNeg.nJobs = nT - need.nJobs;
+  const StageArgs A = stage_args(need, scratch, m->q.queue, m->q.hostErr);
   // capture a one-round graph (a fixpoint's first two launches: most search
   // steps converge in a round or two, and rounds after convergence cost
   // launches) and a rounds_per_graph-round graph for the launches after them
@@ -2061,7 +2191,7 @@ int model_build(ct_model* m) {
     hipGraph_t g = nullptr;
     HIPCHK(hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal));
     for (int r = 0; r < rounds; ++r) {
-      hipError_t e = launch_model_round(M, a, m->grid, m->stream);
+      hipError_t e = launch_model_round(M, a, A, need.nU, need.nF, aNeg, m->stream);
       if (e != hipSuccess) {
         hipGraph_t dummy = nullptr;
         (void)hipStreamEndCapture(m->stream, &dummy);
@@ -2096,8 +2226,8 @@ int model_sync_tables(ct_model* m) {
     }
     // a round's job only asks whether levels exist (depth > 0: trail the
     // words it changes), so the job array is sent again only when that flips
-    if (m->built && (m->hJobs[c].depthAfter > 0) != (T->slots[0].depth > 0)) {
-      m->hJobs[c].depthAfter = T->slots[0].depth;
+    if (m->built && (m->hJobs[m->jobOf[c]].depthAfter > 0) != (T->slots[0].depth > 0)) {
+      m->hJobs[m->jobOf[c]].depthAfter = T->slots[0].depth;
       changed = true;
     }
   }
@@ -2400,9 +2530,8 @@ int ct_model_autotune(ct_model* m, const uint64_t* pool_in, const char* cache_pa
     ++nTimed;
     return CT_OK;
   };
-  // coordinate descent over the classes: solo (one workgroup; its step is
-  // fixed) or split with 2, 4 or 8 granules per wave per update item
-  const std::pair<int, int> opts[] = {{1, 0}, {0, 2}, {0, 4}, {0, 8}};
+  // coordinate descent over the classes: solo (one workgroup) or staged
+  const std::pair<int, int> opts[] = {{1, 0}, {0, 2}};
   for (const auto& o : order) {
     const auto cls = o.second;
     std::pair<int, int> best{0, 0};

@@ -27,7 +27,8 @@ import statistics
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SRCS = [os.path.join(HERE, "csrc", "ct_kernels.hip"), os.path.join(HERE, "csrc", "ct_engine.hip"),
-               os.path.join(HERE, "csrc", "ct_nodes.hip")]
+               os.path.join(HERE, "csrc", "ct_nodes.hip"),
+               os.path.join(HERE, "csrc", "ct_staged.hip")]
 KERNEL = "propagate_kernel"
 DEFAULT_TITLE = "propagate_kernel, one 200,000-tuple table"
 

@@ -1,0 +1,193 @@
+"""The staged schedule (prep, update, finish launches) against the oracle,
+bit-exact, at the edges of its parts: whole jobs in the prep workgroup, granule
+counts around a wave of positions and a workgroup's pass, domains of one word
+to more than a pass of the prep, row lists and (more than 65,536 rows) selected
+bits, pushes and pops of several levels in one job, inputs without a change,
+rejected and failing jobs, star cells, negative tables in the same batch,
+batches of several launches, the static scratch."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2507_18413_amd import ct
+from paper_2507_18413_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print("[gpu-case]", *a, flush=True)
+    sys.stdout.flush()
+
+
+# domain sizes, tuples, star share, kind, branch policy
+TABLES = {
+    "one granule": ([5, 9, 70], 300, 0.0, 0, ct.BRANCH_AUTO),
+    "4 granules": ([30, 64, 65, 3], 16384, 0.05, 0, ct.BRANCH_AUTO),
+    "5 granules": ([40, 1, 20, 130], 16385, 0.0, 0, ct.BRANCH_AUTO),
+    "one granule, 17 words": ([1088], 900, 0.0, 0, ct.BRANCH_AUTO),
+    "64 granules": ([50, 60, 40], 64 * 4096, 0.0, 0, ct.BRANCH_INCREMENTAL),
+    "65 granules": ([50, 60, 40, 9], 64 * 4096 + 1, 0.0, 0, ct.BRANCH_RESET),
+    "260 granules": ([90, 7, 80, 30], 260 * 4096 - 3, 0.0, 0, ct.BRANCH_AUTO),
+    "512 words": ([64 * 200, 64 * 312], 9000, 0.0, 0, ct.BRANCH_AUTO),
+    "513 words": ([64 * 200, 64 * 313], 20000, 0.0, 0, ct.BRANCH_AUTO),
+    "3,073 words": ([64 * 3000, 64 * 72 + 1], 5000, 0.0, 0, ct.BRANCH_INCREMENTAL),
+    "selected bits": ([36000, 38000], 5000, 0.0, 0, ct.BRANCH_RESET),
+    "negative": ([6, 8, 7, 5], 900, 0.0, ct.KIND_NEGATIVE, ct.BRANCH_AUTO),
+}
+
+
+def make(name, rng, **kw):
+    ds, t, star, kind, policy = TABLES[name]
+    lo = np.arange(len(ds), dtype=np.int32) - 2
+    tup = np.stack([lo[i] + rng.integers(0, ds[i], size=t) for i in range(len(ds))], 1).astype(np.int32)
+    if star:
+        tup[rng.random(tup.shape) < star] = ct.STAR
+    if kind:
+        tup = np.unique(tup, axis=0)
+    ds = np.array(ds, np.int32)
+    return (ct.Table(tup, lo, ds, branch_policy=policy, kind=kind, **kw),
+            O.OracleTable(tup, lo, ds, kind=kind, fast=kind == 0 and not star), W.DomLayout(ds, lo))
+
+
+def narrowed(rng, lay, dom):
+    """The next input: a share of the values removed, or nothing, or all of
+    one variable's but one, or something to reject."""
+    new = dom.copy()
+    r = rng.random()
+    if r < 0.15:
+        return new
+    if r < 0.22:
+        new[0] = ~np.uint64(0)
+        return new
+    share = rng.choice([0.02, 0.3, 0.9])
+    for i in range(lay.n):
+        if rng.random() < 0.4:
+            continue
+        vals = lay.values(new, i)
+        gone = vals[rng.random(vals.size) < share]
+        if gone.size == vals.size:
+            gone = gone[1:]
+        for a in gone:
+            lay.clear(new, i, int(a))
+    if r > 0.9:
+        vals = lay.values(new, lay.n - 1)
+        for a in vals[1:]:
+            lay.clear(new, lay.n - 1, int(a))
+    return new
+
+
+@pytest.mark.parametrize("name", list(TABLES))
+def test_staged_calls(name):
+    say("staged calls:", name, TABLES[name])
+    rng = W.rng_for(len(name), 930, 0)
+    g, o, lay = make(name, rng, schedule=ct.SCHED_SPLIT)
+    assert g.create_status == o.create_status == O.OK
+    assert (g.domains() == o.domains()).all()
+    depth, failed = 0, False
+    for step in range(14):
+        if depth and (failed or rng.random() < 0.3):
+            for _ in range(int(rng.integers(1, depth + 1))):
+                g.pop()
+                o.pop()
+                depth -= 1
+        for _ in range(int(rng.integers(0, 3)) if step % 3 else 1):
+            g.push()
+            o.push()
+            depth += 1
+        dom = narrowed(rng, lay, o.domains())
+        if step % 2:
+            st, d, c = g.propagate(dom, want_ct=True)
+        else:
+            (st, d), c = g.propagate(dom), None
+        os_, od, oc = o.propagate(dom, want_ct=True)
+        assert st == os_, step
+        failed = st in (O.FAIL, ct.E_STATE)
+        if st == O.OK:
+            assert (d == od).all(), step
+            assert c is None or (c == oc).all(), step
+        sd, sc = g.state()
+        assert failed or (sd == o.state()[0]).all(), step
+        assert (sc == o.state()[1]).all(), step
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("names,slots", [
+    (["one granule", "4 granules", "negative"], 5),
+    (["5 granules", "one granule", "64 granules", "negative", "one granule, 17 words"], 4),
+    (["260 granules", "513 words", "4 granules", "65 granules"], 3),
+    (["selected bits", "512 words"], 30),  # the static scratch takes several launches
+])
+def test_staged_batches(names, slots, noalloc):
+    say("staged batches:", names, slots, "slots each, noalloc", noalloc)
+    rng = W.rng_for(len(names), 931, slots)
+    tabs = [make(n, rng) for n in names]
+    first = [g.slots_alloc(slots, max_depth=8) for g, _, _ in tabs]
+    steps = 6 if slots < 10 else 2
+    stacks = [[[] for _ in range(slots)] for _ in tabs]  # the levels' domains, per slot
+    cur = [[o.domains() for _ in range(slots)] for _, o, _ in tabs]
+    for step in range(steps):
+        jobs, want = [], []
+        for s in range(slots):
+            for k, (g, o, lay) in enumerate(tabs):
+                stack = stacks[k][s]
+                flags, n_pop, n_push = ct.JOB_PROPAGATE, 0, 0
+                r = rng.random()
+                dead = cur[k][s] is None
+                if r < 0.15 or (dead and not stack):
+                    flags |= ct.JOB_FROM_ROOT
+                    del stack[:]
+                    cur[k][s] = tabs[k][1].domains()
+                else:
+                    if stack and (dead or r < 0.5):
+                        n_pop = int(rng.integers(1, len(stack) + 1))
+                        cur[k][s] = stack[-n_pop]
+                        del stack[len(stack) - n_pop:]
+                    n_push = min(int(rng.integers(0, 3)), 8 - len(stack))
+                    stack.extend([cur[k][s]] * n_push)
+                    if r > 0.93:
+                        flags = 0  # pops and pushes only
+                dead = cur[k][s] is None
+                dom = narrowed(rng, lay, tabs[k][1].domains() if dead else cur[k][s])
+                din = torch.from_numpy(dom.view(np.int64).copy()).cuda()
+                dout = torch.full_like(din, -1)
+                cout = torch.full((g.W,), -1, dtype=torch.int64, device="cuda") if rng.random() < 0.4 else None
+                jobs.append(dict(table=g, slot=first[k] + s, flags=flags, n_pop=n_pop, n_push=n_push, dom_in=din,
+                                 dom_out=dout, ct_out=cout))
+                want.append((k, s, flags, dom))
+        status = torch.full((len(jobs),), 99, dtype=torch.int32, device="cuda")
+        ct.propagate_batch(jobs, status, noalloc=noalloc)
+        ct.batch_status()
+        st = status.cpu().numpy()
+        for j, (k, s, flags, dom) in enumerate(want):
+            o = tabs[k][1]
+            if flags == 0:
+                assert st[j] == ct.OK, (step, j)
+                continue
+            if cur[k][s] is None:  # a failed slot
+                assert st[j] == ct.E_STATE, (step, j)
+                continue
+            # the slot's domains from the root, then this input: the closure
+            # does not depend on the path, so the slots share one oracle
+            o.push()
+            o.propagate(cur[k][s])
+            os_, od, oc = o.propagate(dom, want_ct=True)
+            if os_ == O.OK:
+                wd, wc = o.state()[:2]
+            o.pop()
+            assert st[j] == os_, (step, j, names[k])
+            job = jobs[j]
+            if os_ == O.OK:
+                sd, sc = tabs[k][0].state(job["slot"])
+                assert (job["dom_out"].cpu().numpy().view(np.uint64) == od).all(), (step, j, names[k])
+                assert (sd == wd).all() and (sc == wc).all(), (step, j, names[k])
+                if job["ct_out"] is not None:
+                    assert (job["ct_out"].cpu().numpy().view(np.uint64) == oc).all(), (step, j, names[k])
+                cur[k][s] = od
+            elif os_ == O.FAIL:
+                cur[k][s] = None
+            elif job["ct_out"] is not None:
+                assert (job["ct_out"] == -1).all(), (step, j, names[k])

@@ -196,7 +196,14 @@ struct StageRec {
   uint64_t* ll;
 };
 
-constexpr int QUEUE_INTS = 16, QUEUE_STAGE = 8;  // words of a queue ([3] error); its staged item counts
+// The items of a launch of many jobs, in STAGE_LISTS lists: job j appends its
+// items to list j % STAGE_LISTS with one atomic, so that one word is not every
+// job's (atomics on a word take about 20 ns each).  Zero between launches.
+constexpr int STAGE_LISTS = 16, STAGE_LINE = 8;  // lists; uint64 words from one list's count to the next
+struct StageCounts {
+  unsigned long long n[STAGE_LISTS * STAGE_LINE];  // update items (low half), finish items
+  int32_t fin[STAGE_LISTS];                        // finish items, for the finish
+};
 
 struct StageItem {
   int32_t job, chunk;
@@ -205,10 +212,12 @@ struct StageItem {
 struct StageArgs {
   CT_G StageRec* rec;        // per job
   CT_G char* jobMem;         // the jobs' scratch
-  CT_G StageItem* items;     // update items; null: one job, items by workgroup
-  CT_G StageItem* fItems;    // finish items
-  CT_G int32_t* count;       // [0] update items, [1] finish items, [2] finish workgroups done
-  int32_t wide, pad;         // the finish runs in workgroups of 1,024 threads
+  CT_G StageItem* items;     // update items, uCap per list; null: one job, items by workgroup
+  CT_G StageItem* fItems;    // finish items, fCap per list
+  CT_G StageCounts* count;
+  int32_t uCap, fCap;
+  int32_t wide;              // the finish runs in workgroups of 1,024 threads
+  int32_t wideDom;           // a job has many domain words
   int32_t* queue;            // [3] error
   int32_t* hostErr;
   unsigned long long* clock; // nullable (one job): see KArgs

@@ -18,9 +18,9 @@ namespace ctk {
 
 constexpr size_t NA_SCRATCH_BYTES = (size_t)16 << 20;
 
-// [0, 256): the error words of the last call and of an earlier one, and the
-// staged schedule's item counts; then descriptor staging (2 MiB); then the
-// search-node or the staged schedule's scratch (the rest)
+// [0, 256): the error words of the last call and of an earlier one; then
+// descriptor staging (2 MiB); then the search-node or the staged schedule's
+// scratch (the rest; the staged one begins with its item counts)
 static __device__ __align__(256) char scratch[NA_SCRATCH_BYTES];
 
 namespace {
@@ -28,11 +28,11 @@ namespace {
 // Before a call: the item counts (a launch that ended normally already left
 // them at zero) and the error word, whose last value is kept in word 4 for
 // ct_batch_status, are cleared.
-__global__ void noalloc_reset_kernel(int32_t* q) {
+__global__ void noalloc_reset_kernel(int32_t* q, int32_t* counts) {
+  for (int k = threadIdx.x; k < (int)(sizeof(StageCounts) / sizeof(int32_t)); k += 64) counts[k] = 0;
   if (threadIdx.x == 0) {
     if (q[3]) q[4] = q[3];
     q[3] = 0;
-    for (int k = 0; k < 3; ++k) q[QUEUE_STAGE + k] = 0;
   }
 }
 
@@ -61,8 +61,8 @@ hipError_t noalloc_scratch(char** ptr, size_t* bytes) {
   return hipSuccess;
 }
 
-hipError_t launch_noalloc_reset(int32_t* q, hipStream_t stream) {
-  hipLaunchKernelGGL(noalloc_reset_kernel, dim3(1), dim3(64), 0, stream, q);
+hipError_t launch_noalloc_reset(int32_t* q, int32_t* counts, hipStream_t stream) {
+  hipLaunchKernelGGL(noalloc_reset_kernel, dim3(1), dim3(64), 0, stream, q, counts);
   return hipGetLastError();
 }
 

@@ -35,6 +35,7 @@ hipError_t launch_split_engine(const EngDesc& E, int grid, hipStream_t stream);
 int stage_row_pad();
 int stage_update_items(int nGran);
 bool stage_wide(int nGran, int D);
+bool stage_wide_dom(int D);
 int stage_finish_items(int D, int wide);
 hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int popGran, hipStream_t stream);
 int nodes_max_vec_rows(size_t lds);
@@ -44,7 +45,7 @@ hipError_t launch_nodes_ids(const TabDesc* T, int nGran, uint16_t* ids, hipStrea
 hipError_t launch_nodes(NodesDesc N, char* scratch, hipStream_t stream);
 hipError_t launch_roots(const KArgs& a, const RootDesc& R, hipStream_t stream);
 hipError_t noalloc_scratch(char** ptr, size_t* bytes);
-hipError_t launch_noalloc_reset(int32_t* q, hipStream_t stream);
+hipError_t launch_noalloc_reset(int32_t* q, int32_t* counts, hipStream_t stream);
 hipError_t launch_build_supports(const int32_t* tuples, int64_t t, int n, const VarDesc* vars,
                                  const int32_t* lo, uint64_t* S, int64_t stride, int64_t W,
                                  hipStream_t stream);
@@ -121,7 +122,7 @@ struct DevBlock {
 
 // Device queue + staging for one stream.
 struct QueueCtx {
-  int32_t* queue = nullptr;   // QUEUE_INTS on the device: error word, staged item counts
+  int32_t* queue = nullptr;   // on the device: [3] error word
   int32_t* hostErr = nullptr; // pinned
   // batch staging: job descriptors, then (256-byte aligned) root tasks, sent
   // in one copy; two pinned buffers in turn let the host fill one while the
@@ -145,8 +146,8 @@ struct QueueCtx {
 
 
 int queue_init(QueueCtx& q) {
-  ALLOCCHK(hipMalloc(&q.queue, QUEUE_INTS * sizeof(int32_t)));
-  HIPCHK(hipMemset(q.queue, 0, QUEUE_INTS * sizeof(int32_t)));
+  ALLOCCHK(hipMalloc(&q.queue, 4 * sizeof(int32_t)));
+  HIPCHK(hipMemset(q.queue, 0, 4 * sizeof(int32_t)));
   ALLOCCHK(hipHostMalloc((void**)&q.hostErr, sizeof(int32_t), hipHostMallocMapped | hipHostMallocCoherent));
   *q.hostErr = 0;
   for (int k = 0; k < 2; ++k) HIPCHK(hipEventCreateWithFlags(&q.staged[k], hipEventDisableTiming));
@@ -379,35 +380,48 @@ size_t stage_job_bytes(const ct_table* T) {
 
 struct StageNeed {
   int nJobs = 0, nU = 0, nF = 0, popGran = 0;
+  int u[STAGE_LISTS] = {}, f[STAGE_LISTS] = {};  // items per list
+  int uCap = 0, fCap = 0;                        // the most of a list
   size_t jobBytes = 0;
-  bool wide = false;
+  bool wide = false, wideDom = false;
   void add(const ct_table* T, bool propagate, bool pops, bool solo) {
-    ++nJobs;
     if (pops) popGran = std::max(popGran, T->nGran);
-    if (!propagate) return;
-    jobBytes += stage_job_bytes(T);
-    if (solo) return;
-    nU += stage_update_items(T->nGran);
-    nF += stage_finish_items(T->D, 0);  // (the narrow form has the most)
-    wide = wide || stage_wide(T->nGran, T->D);
+    if (propagate) jobBytes += stage_job_bytes(T);
+    wide = wide || (propagate && !solo && stage_wide(T->nGran, T->D));
+    wideDom = wideDom || (propagate && stage_wide_dom(T->D));
+    // (the narrow form of the finish has the most items)
+    if (propagate && !solo) add_items(stage_update_items(T->nGran), stage_finish_items(T->D, 0));
+    else add_items(0, 0);
   }
-  size_t itemBytes() const {
-    return align256(sizeof(StageItem) * (size_t)nU) + align256(sizeof(StageItem) * (size_t)nF);
+  void add_items(int du, int df) {
+    const int l = nJobs++ % STAGE_LISTS;
+    nU += du;
+    nF += df;
+    uCap = std::max(uCap, u[l] += du);
+    fCap = std::max(fCap, f[l] += df);
   }
-  size_t bytes() const { return align256(sizeof(StageRec) * (size_t)nJobs) + itemBytes() + jobBytes; }
+  size_t bytes() const {
+    return align256(sizeof(StageCounts)) + align256(sizeof(StageRec) * (size_t)nJobs) +
+           align256(sizeof(StageItem) * STAGE_LISTS * (size_t)uCap) +
+           align256(sizeof(StageItem) * STAGE_LISTS * (size_t)fCap) + jobBytes;
+  }
 };
 
 // The launch's view of its scratch.
 StageArgs stage_args(const StageNeed& n, char* scratch, int32_t* queue, int32_t* hostErr) {
   StageArgs A{};
+  A.count = (StageCounts*)scratch;
+  scratch += align256(sizeof(StageCounts));
   A.rec = (StageRec*)scratch;
   scratch += align256(sizeof(StageRec) * (size_t)n.nJobs);
   A.items = (StageItem*)scratch;
-  scratch += align256(sizeof(StageItem) * (size_t)n.nU);
+  scratch += align256(sizeof(StageItem) * STAGE_LISTS * (size_t)n.uCap);
   A.fItems = (StageItem*)scratch;
-  scratch += align256(sizeof(StageItem) * (size_t)n.nF);
-  A.count = queue + QUEUE_STAGE;
+  scratch += align256(sizeof(StageItem) * STAGE_LISTS * (size_t)n.fCap);
+  A.uCap = n.uCap;
+  A.fCap = n.fCap;
   A.wide = n.wide;
+  A.wideDom = n.wideDom;
   A.queue = queue;
   A.hostErr = hostErr;
   A.jobMem = scratch;
@@ -421,6 +435,7 @@ int stage_reserve(QueueCtx& q, size_t bytes, hipStream_t stream) {
   q.dStaged = nullptr;
   q.capStaged = 0;
   ALLOCCHK(hipMalloc((void**)&q.dStaged, bytes));
+  HIPCHK(hipMemsetAsync(q.dStaged, 0, sizeof(StageCounts), stream));
   q.capStaged = bytes;
   return CT_OK;
 }
@@ -927,7 +942,7 @@ int batch_validate_quiesce(const ct_job* jobs, int n_jobs, hipStream_t stream) {
 // those that run in one workgroup of the propagate kernel (negative tables).
 struct BatchShape {
   int nStaged = 0, nChunks = 0, popGran = 0;
-  bool wide = false;
+  bool wide = false, wideDom = false;
 };
 
 // Negative tables, and a job whose scratch alone is beyond the capacity, run
@@ -1010,6 +1025,7 @@ BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool
       need = more;
       B.popGran = std::max(B.popGran, need.popGran);
       B.wide = B.wide || need.wide;
+      B.wideDom = B.wideDom || need.wideDom;
       ++B.nStaged;
     }
   return B;
@@ -1686,7 +1702,7 @@ BatchPlan batch_plan(const ct_job* jobs, int n_jobs, bool nodes) {
 // scratch, and the host arrays the descriptors are built in.  Capacities
 // must cover the batch's plan.
 struct BatchRes {
-  int32_t* queue = nullptr;     // device: QUEUE_INTS
+  int32_t* queue = nullptr;     // device: [3] error word
   int32_t* hostErr = nullptr;   // pinned, nullable
   char* dStage = nullptr;       // device staging
   char* hStage = nullptr;       // host staging (the source of the one copy)
@@ -1761,12 +1777,9 @@ int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* st
   for (int k = 0; k < B.nChunks; ++k) {
     const int j0 = r.chunks[k], j1 = k + 1 < B.nChunks ? r.chunks[k + 1] : B.nStaged;
     StageNeed need;
-    need.nJobs = j1 - j0;
     need.wide = B.wide;
-    for (int j = j0; j < j1; ++j) {
-      need.nU += r.hJobs[j].nUpd;
-      need.nF += r.hJobs[j].nFilt;
-    }
+    need.wideDom = B.wideDom;
+    for (int j = j0; j < j1; ++j) need.add_items(r.hJobs[j].nUpd, r.hJobs[j].nFilt);
     const StageArgs A = stage_args(need, r.dStaged, r.queue, r.hostErr);
     a.jobs = dJobs + j0;
     a.nJobs = need.nJobs;
@@ -1943,7 +1956,7 @@ int ct_propagate_batch_noalloc(const ct_job* jobs, int32_t n_jobs, void* stream_
   r.rootKey = g_na.rootKey;
   // the item counts start at zero (an earlier call's error word is kept for
   // ct_batch_status)
-  HIPCHK(launch_noalloc_reset(r.queue, stream));
+  HIPCHK(launch_noalloc_reset(r.queue, (int32_t*)r.dStaged, stream));
   g_na.used = true;
   g_na.lastStream = stream;
   return batch_launch(jobs, n_jobs, stream, status_dev, p, r);
@@ -2174,6 +2187,7 @@ int model_build(ct_model* m) {
   if ((rc = model_upload(m, &m->dJobs, m->hJobs))) return rc;
   char* scratch = nullptr;
   if ((rc = model_alloc(m, (void**)&scratch, need.bytes()))) return rc;
+  HIPCHK(hipMemsetAsync(scratch, 0, sizeof(StageCounts), m->stream));
   KArgs a{}, aNeg{};
   a.jobs = m->dJobs;
   a.nJobs = need.nJobs;

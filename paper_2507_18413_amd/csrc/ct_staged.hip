@@ -29,8 +29,10 @@
 namespace ctk {
 namespace {
 
-constexpr int PBLOCK = 1024;             // prep workgroup
-constexpr int PWAVES = PBLOCK / WAVE;
+// Prep workgroup: 1,024 threads for a launch of few jobs or with wide tables,
+// else PBLOCK_MANY (two workgroups on a CU: a batch of more jobs than
+// CUs has them all running at once).
+constexpr int PMAX = 1024, PBLOCK_MANY = 512;
 constexpr int SBLOCK = 256;              // update workgroup
 constexpr int SWAVES = SBLOCK / WAVE;
 
@@ -554,11 +556,12 @@ struct PrepShared {
   int32_t size[MAX_ARITY], dcnt[MAX_ARITY];
   int32_t seg[MAX_ARITY];  // first list entry of the variable's segment; -1: not in s_val
   int32_t inc[MAX_ARITY];
-  int32_t wsum[PWAVES];
+  int32_t wsum[PMAX / WAVE];
   int32_t stray, notSub, status, noop, zero, nrows, nseg;
 };
 
 // Exclusive prefix sum over the workgroup; *total receives the sum.
+template <int PWAVES>
 __device__ int prep_scan(int v, int* total, PrepShared& sh) {
   const int x = s_scan(v);
   if (s_lane() == WAVE - 1) sh.wsum[s_wave()] = x;
@@ -580,7 +583,9 @@ __device__ int prep_scan(int v, int* total, PrepShared& sh) {
 // largest popping table of the launch.
 // Bound: its chain of memory round trips (job -> slot -> domains -> list).
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(PBLOCK) stage_prep_kernel(KArgs a, StageArgs A) {
+template <int PBLOCK>
+__global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArgs A) {
+  constexpr int PWAVES = PBLOCK / WAVE;
   __shared__ PrepShared sh;
   __shared__ FinShared<PBLOCK> fin;
   extern __shared__ int32_t first[];
@@ -812,7 +817,7 @@ __global__ void __launch_bounds__(PBLOCK) stage_prep_kernel(KArgs a, StageArgs A
       return;
     }
     int tot = 0;
-    int off = base + prep_scan(__popcll(bits), &tot, sh);
+    int off = base + prep_scan<PWAVES>(__popcll(bits), &tot, sh);
     base += tot;
     const int row0 = rowStart + (q - domOff) * 64;
     while (bits) {
@@ -903,8 +908,11 @@ __global__ void __launch_bounds__(PBLOCK) stage_prep_kernel(KArgs a, StageArgs A
       const int pos = fromRoot || J.ct_out ? nGran : limit;
       const int fw = fin_words(D, A.wide);
       const int nU = (pos + SWAVES - 1) / SWAVES, nF = 1 + (D + fw - 1) / fw;
-      sh.nseg = atomicAdd((int32_t*)&A.count[0], nU);
-      sh.status = atomicAdd((int32_t*)&A.count[1], nF);
+      const int l = (int)blockIdx.x % STAGE_LISTS;
+      const unsigned long long at = atomicAdd((unsigned long long*)&A.count->n[l * STAGE_LINE],
+                                              (unsigned long long)(uint32_t)nF << 32 | (uint32_t)nU);
+      sh.nseg = l * A.uCap + (int)(uint32_t)at;
+      sh.status = l * A.fCap + (int)(at >> 32);
       sh.size[0] = nU;
       sh.size[1] = nF;
     }
@@ -916,15 +924,38 @@ __global__ void __launch_bounds__(PBLOCK) stage_prep_kernel(KArgs a, StageArgs A
   for (int k = tid; k < nF; k += PBLOCK) A.fItems[f0 + k] = StageItem{(int32_t)blockIdx.x, k};
 }
 
+// The lists' items as one sequence: lane l < STAGE_LISTS has the items before
+// list l.
+struct ItemLists {
+  int before, total;
+};
+
+__device__ __forceinline__ ItemLists item_lists(int n) {
+  ItemLists L;
+  const int c = s_lane() < STAGE_LISTS ? n : 0;
+  const int x = s_scan(c);
+  L.before = x - c;
+  L.total = __builtin_amdgcn_readlane(x, WAVE - 1);
+  return L;
+}
+
+// Item i of the sequence: its place in the item array.
+__device__ __forceinline__ int item_at(const ItemLists& L, int i, int cap) {
+  const int l = __popcll(__ballot(s_lane() < STAGE_LISTS && L.before <= i)) - 1;
+  return l * cap + i - __builtin_amdgcn_readlane(L.before, l);
+}
+
 __global__ void __launch_bounds__(SBLOCK, 8) stage_update_kernel(StageArgs A) {
   if (!A.items) {
     const StageRec R = load_rec(A, 0);
     if (R.run) stage_granule<false>(A, R, &A.rec->trailCount, (int)blockIdx.x * SWAVES + s_wave());
     return;
   }
-  const int n = ((const CT_K int32_t*)A.count)[0];
-  for (int i = blockIdx.x; i < n; i += gridDim.x) {
-    const CT_K StageItem* it = (const CT_K StageItem*)A.items + i;
+  const ItemLists L = item_lists((int)(uint32_t)A.count->n[min(s_lane(), STAGE_LISTS - 1) * STAGE_LINE]);
+  if (blockIdx.x == 0 && threadIdx.x < STAGE_LISTS)  // (the finish empties the counts)
+    A.count->fin[threadIdx.x] = (int32_t)(A.count->n[threadIdx.x * STAGE_LINE] >> 32);
+  for (int i = blockIdx.x; i < L.total; i += gridDim.x) {
+    const CT_K StageItem* it = (const CT_K StageItem*)A.items + item_at(L, i, A.uCap);
     stage_granule<false>(A, load_rec(A, it->job), &A.rec[it->job].trailCount, it->chunk * SWAVES + s_wave());
   }
 }
@@ -956,19 +987,12 @@ __global__ void __launch_bounds__(FBLOCK) stage_finish_kernel(StageArgs A) {
     }
     return;
   }
-  const int n = ((const CT_K int32_t*)A.count)[1];
-  for (int i = blockIdx.x; i < n; i += gridDim.x) {
-    const CT_K StageItem* it = (const CT_K StageItem*)A.fItems + i;
+  const ItemLists L = item_lists(A.count->fin[min(s_lane(), STAGE_LISTS - 1)]);
+  if (blockIdx.x == 0 && threadIdx.x < STAGE_LISTS) A.count->n[threadIdx.x * STAGE_LINE] = 0ull;
+  for (int i = blockIdx.x; i < L.total; i += gridDim.x) {
+    const CT_K StageItem* it = (const CT_K StageItem*)A.fItems + item_at(L, i, A.fCap);
     stage_finish_item(A, it->job, it->chunk, sh);
     s_lds_barrier();
-  }
-  // the last workgroup out empties the lists for the next launch (every
-  // workgroup has read its count)
-  __syncthreads();
-  if (threadIdx.x == 0 && atomicAdd(&A.count[2], 1) == (int)gridDim.x - 1) {
-    A.count[0] = 0;
-    A.count[1] = 0;
-    A.count[2] = 0;
   }
 }
 
@@ -987,13 +1011,18 @@ int stage_grid() {
 
 int stage_row_pad() { return ROW_U; }
 int stage_update_items(int nGran) { return (nGran + SWAVES - 1) / SWAVES; }
+bool stage_wide_dom(int D) { return D > FIN_WIDE_D; }
 bool stage_wide(int nGran, int D) { return nGran > FIN_WIDE_GRAN || D > FIN_WIDE_D; }
 int stage_finish_items(int D, int wide) { return 1 + (D + fin_words(D, wide) - 1) / fin_words(D, wide); }
 
 // nJobs jobs (a.jobs, or the one of the arguments); nU / nF: at most this many
 // update and finish items; popGran: granules of the largest table that pops.
 hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int popGran, hipStream_t stream) {
-  hipLaunchKernelGGL(stage_prep_kernel, dim3(a.nJobs), dim3(PBLOCK), sizeof(int32_t) * (size_t)popGran, stream, a, A);
+  const size_t lds = sizeof(int32_t) * (size_t)popGran;
+  if (a.nJobs > stage_grid() / 8 && !A.wideDom)
+    hipLaunchKernelGGL(stage_prep_kernel<PBLOCK_MANY>, dim3(a.nJobs), dim3(PBLOCK_MANY), lds, stream, a, A);
+  else
+    hipLaunchKernelGGL(stage_prep_kernel<PMAX>, dim3(a.nJobs), dim3(PMAX), lds, stream, a, A);
   if (nU > 0) {
     const int gu = A.items ? std::min(nU, stage_grid()) : nU;
     hipLaunchKernelGGL(stage_update_kernel, dim3(gu), dim3(SBLOCK), 0, stream, A);

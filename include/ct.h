@@ -64,11 +64,12 @@ extern "C" {
 typedef struct ct_table ct_table;
 
 /* How a propagation is spread over the GPU: SOLO runs a whole call in one
- * workgroup (no hand-off between workgroups; best for small tables), SPLIT
- * spreads updateTable over the waves of many workgroups, one per granule,
- * and filterDomains over one wave per domain word: as three launches for a
- * batch's jobs together and for one call of a larger table, or as one launch
- * with hand-offs for a call whose update one workgroup takes.  NODES is the
+ * workgroup (no hand-off between workgroups; best for calls on small tables),
+ * SPLIT spreads updateTable over the waves of many workgroups, one per
+ * granule, and filterDomains over one wave per domain word: as three launches
+ * for a call of a larger table, or as one launch with hand-offs for a call
+ * whose update one workgroup takes.  The jobs of a batch run as three
+ * launches together whatever the schedule of their (positive) tables.  NODES is the
  * search-node schedule of ct_propagate_batch: when every job of a batch is a
  * CT_JOB_FROM_ROOT propagation of the same positive table of at most about
  * 2,400 support rows (sum of the domain sizes: one bit vector over 512 jobs
@@ -293,7 +294,7 @@ typedef struct {
 } ct_job;
 
 /*
- * ct_propagate_batch -- runs every job in one persistent launch on `stream`
+ * ct_propagate_batch -- runs every job in the same launches on `stream`
  * (a hipStream_t; NULL = the null stream) driven by a device work queue.
  * Each job's result equals that of the same pops, pushes and ct_propagate on
  * its slot alone.  status_dev (device-accessible, n_jobs int32) receives each job's
@@ -363,15 +364,16 @@ int ct_model_layout(const ct_model *m, int32_t *pool_off, int32_t *pool_words);
 
 /*
  * Runs propagation rounds from pool_in (device, pool words) until no domain
- * changes: every round propagates, in one persistent launch, each table one
+ * changes: every round propagates, in the same launches, each table one
  * of whose variables changed in the previous round (in the first round: each
  * table from whose last domains pool_in removes a value) on the pool
  * intersected with its own last domains, and ANDs the results into the
- * pool.  Rounds are captured in a hipGraph, `rounds_per_graph`
- * at a time, and replayed until the device reports convergence or failure.
+ * pool.  Rounds are launched one ahead of the host until the device reports
+ * convergence or failure.
  * Synchronous on `stream` (NULL = the model's own stream).  pool_out (device)
  * receives the fixpoint (undefined after CT_FAIL).  n_props (nullable)
- * receives the number of table propagations, n_rounds (nullable) the rounds.
+ * receives the number of table propagations, n_rounds (nullable) the rounds
+ * (see ct_model_set_schedule).
  * Returns CT_OK or CT_FAIL.  After CT_FAIL the failed tables must be popped
  * (ct_model_pop) before the next fixpoint.
  */
@@ -385,18 +387,16 @@ int ct_model_push(ct_model *m);
 int ct_model_pop(ct_model *m);
 
 /* Scheduling knob of the model's rounds: tables of at most solo_max_granules
- * granules run in one workgroup each, larger ones are spread over workgroups
- * (see CT_SCHED_*); rounds_per_graph rounds are captured per graph.  A
- * fixpoint's first two launches are one-round graphs (most search steps
- * converge in a round or two), the launches after them take rounds_per_graph
- * rounds.  The
- * default is chosen by ct_model_autotune or is (4, 8). */
+ * granules are classed solo, larger ones split (what ct_model_get_choice
+ * reports; a round takes the dirty tables of both classes in the same
+ * launches).  A fixpoint counts its rounds (n_rounds) as one, one, then
+ * rounds_per_graph at a time.  The default is chosen by ct_model_autotune or
+ * is (4, 8). */
 int ct_model_set_schedule(ct_model *m, int32_t solo_max_granules, int32_t rounds_per_graph);
 
-/* Autotuner of the rounds' schedule.  Tables are grouped in classes by
+/* Autotuner of the classes.  Tables are grouped in classes by
  * floor(log4) of their granule count and of their support-row count; each
- * class gets a schedule: solo (one workgroup per table) or split (its
- * granules and domain words spread over workgroups).
+ * class gets a choice, solo or split.
  * Classes are tuned one after the other, those with the most granules in all
  * first, each candidate timed as the median of 3 fixpoints from pool_in
  * (device pointer), every table restored between trials with a push / pop;
@@ -410,8 +410,8 @@ int ct_model_set_schedule(ct_model *m, int32_t solo_max_granules, int32_t rounds
  * Classes the tuner never saw follow ct_model_set_schedule's threshold. */
 int ct_model_autotune(ct_model *m, const uint64_t *pool_in, const char *cache_path, int32_t *from_cache,
                       int32_t *timed);
-/* Effective schedule of table `table` (index from ct_model_add) in the
- * model's rounds: *solo = 1 for one workgroup per table; *tile = 4 (solo) or
+/* The choice of table `table`'s class (index from ct_model_add): *solo = 1 or
+ * 0; *tile = 4 (solo) or
  * the tile of the choice (split; it selects nothing). */
 int ct_model_get_choice(const ct_model *m, int32_t table, int32_t *solo, int32_t *tile);
 

@@ -78,6 +78,9 @@ constexpr uint32_t JF_LL = 128u;
 // schedule: the filter workgroups on other XCDs write them, and workgroup 0
 // takes no acquire between calls, so its L2 keeps the table and the slot)
 constexpr uint32_t JF_COHLAST = 256u;
+// Staged job of a model round: dom_in is the pool word (int32) of each domain
+// word, the input the pool's word ANDed with the table's last domains.
+constexpr uint32_t JF_MODEL = 512u;
 
 struct VarDesc {
   int32_t rowStart, dsize, domOff, domWords;
@@ -165,6 +168,7 @@ struct DevJob {
 // the finish.
 enum { STAGE_LIST = 0, STAGE_BITS, STAGE_NOOP, STAGE_ZERO };
 enum { STAGE_TRAIL_OFF = 0, STAGE_TRAIL_FIRST, STAGE_TRAIL_ALL };
+struct ModelState;
 struct StageRec {
   int32_t run;               // 0: nothing left to do (inactive, rejected, pops and pushes only)
   uint32_t flags;            // JF_*
@@ -194,6 +198,11 @@ struct StageRec {
   CT_G uint64_t* ct_out;
   CT_G int32_t* status_out;
   uint64_t* ll;
+  const CT_G int32_t* poolMap;  // JF_MODEL: the round's (see ModelRound); else null
+  const CT_G uint64_t* poolCur;
+  CT_G uint64_t* poolNext;
+  CT_G ModelState* model;
+  int32_t round, pad2;
 };
 
 // The items of a launch of many jobs, in STAGE_LISTS lists: job j appends its
@@ -266,34 +275,35 @@ struct RootDesc {
   int32_t nTasks, pad;
 };
 
-// Multi-table model: pool variables shared by tables (device side of a
-// propagation round).  Scope entry e links column tabCol[e] of table
-// scopeTab[e] to pool variable scopeVar[e].
-struct ModelDesc {
-  int32_t nTables, nPool, poolWords, nEntries;
-  const CT_G int32_t* poolOff;    // nPool: first pool word of each variable
-  const CT_G int32_t* poolNW;     // nPool: words of each variable
-  const CT_G int32_t* scopeTab;   // nEntries
-  const CT_G int32_t* scopeVar;   // nEntries
-  const CT_G int32_t* entDomOff;  // nEntries: word offset of the column in its table's bitmap
-  const CT_G int32_t* tabScope;   // nTables + 1: entries of table c are [tabScope[c], tabScope[c+1])
-  const CT_G int32_t* bufOff;     // nTables: offset of table c's words in domIn / domOut
-  const CT_G uint64_t* const CT_G* lastDom;  // nTables: slot-0 domains of each table
-  CT_G uint64_t* domIn;
-  CT_G uint64_t* domOut;
-  CT_G int32_t* status;           // nTables: job status of the round
-  CT_G int32_t* dirty;            // nTables: table runs in the round
-  CT_G uint64_t* pool;            // poolWords
-  CT_G uint64_t* poolNext;        // poolWords
-  CT_G int32_t* changed;          // nPool
-  CT_G int32_t* flags;            // [0] some table dirty, [1] failed, [2] rounds, [3] table runs
+// Rounds of a multi-table model (ct_staged.hip).  The pool has three buffers
+// in turn: a round reads cur, its predecessor's state prev, and ANDs what its
+// tables leave into next.
+constexpr int MODEL_DONE = 3;   // host word's code: nothing changed in the last round (1, 2: a table failed)
+constexpr int MODEL_PROPS = 16; // table runs are counted in as many words, a cache line each
+struct ModelState {
+  int32_t fail;         // (round + 1) << 2 | code of a failed round; 0 none
+  int32_t lastChanged;  // 1 + the last round that removed a value from the pool
+  int32_t pad[14];
+  int32_t props[MODEL_PROPS * 16];
+};
+struct ModelRound {
+  const CT_G uint64_t* cur;
+  const CT_G uint64_t* prev;
+  CT_G uint64_t* next;
+  CT_G uint64_t* poolOut;  // the caller's
+  CT_G ModelState* state;
+  uint64_t* host;          // pinned: [0] call << 32 | round << 8 | code, [1] table runs
+  int32_t poolWords, round;
+  int32_t nHead;           // workgroups of the prep that copy the pool
+  int32_t call;
 };
 
-// Kernel argument block of the persistent propagate kernel.
+// Kernel argument block of the propagate kernel and the staged prep.
 struct KArgs {
   const CT_G DevJob* jobs;      // nullptr: single job in `job`
   int32_t nJobs;
   int32_t nPrep, nUpd, nFilt;   // a single job's items
+  int32_t uniform;              // staged prep: every job of `jobs` takes the pops and pushes of `job`
   int32_t* queue;          // [3] error
   int32_t* hostErr;        // nullable: error word copied here by the last block
   // nullable: kernel timing on the device clock (wall_clock64): [0] earliest
@@ -302,6 +312,14 @@ struct KArgs {
   unsigned long long* clock;
   DevJob job;
   uint64_t inl[INLINE_WORDS];
+};
+
+// A model's negative tables: their jobs (propagate kernel), per job the pool
+// word of each domain word, and whether it runs in the round.
+struct ModelNeg {
+  KArgs a;
+  const int32_t* const* maps;
+  int32_t* dirty;
 };
 
 // ---------------------------------------------------------------------------

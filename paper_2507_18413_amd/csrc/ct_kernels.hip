@@ -1901,125 +1901,6 @@ __global__ void __launch_bounds__(BLOCK) init_slots_kernel(const TabDesc* T, Slo
   }
 }
 
-// ---------------------------------------------------------------------------
-// Propagation rounds of a multi-table model.  One round = gather -> propagate
-// (every dirty table, one persistent launch) -> merge -> changed -> mark.
-// All state lives on the device, so rounds can be captured in a graph; once
-// nothing is dirty (or a table failed) the remaining rounds do no work.
-// ---------------------------------------------------------------------------
-// input of every dirty table: pool restricted to its scope, intersected with
-// the domains the table returned last; poolNext starts as a copy of pool
-__global__ void __launch_bounds__(BLOCK) model_gather_kernel(ModelDesc M) {
-  const int stride = gridDim.x * BLOCK;
-  for (int w = blockIdx.x * BLOCK + threadIdx.x; w < M.poolWords; w += stride) M.poolNext[w] = M.pool[w];
-  if (M.flags[1]) return;
-  for (int e = blockIdx.x * BLOCK + threadIdx.x; e < M.nEntries; e += stride) {
-    const int c = M.scopeTab[e];
-    if (!M.dirty[c]) continue;
-    const int v = M.scopeVar[e];
-    const int po = M.poolOff[v], nw = M.poolNW[v];
-    const int to = M.entDomOff[e];
-    const CT_G uint64_t* last = M.lastDom[c];
-    CT_G uint64_t* din = M.domIn + M.bufOff[c];
-    for (int q = 0; q < nw; ++q) din[to + q] = M.pool[po + q] & last[to + q];
-  }
-}
-
-// Seeding the first round.  Every table's earlier pruning holds under the
-// (smaller) input pool, so the pool is first ANDed with the domains each
-// table returned last; a table then runs iff that pool removes a value from
-// its domains.
-__global__ void __launch_bounds__(BLOCK) model_seed_and_kernel(ModelDesc M) {
-  const int stride = gridDim.x * BLOCK;
-  for (int e = blockIdx.x * BLOCK + threadIdx.x; e < M.nEntries; e += stride) {
-    const int c = M.scopeTab[e];
-    const int v = M.scopeVar[e];
-    const int po = M.poolOff[v], nw = M.poolNW[v], to = M.entDomOff[e];
-    const CT_G uint64_t* last = M.lastDom[c];
-    for (int q = 0; q < nw; ++q) atomicAnd((unsigned long long*)&M.poolNext[po + q], (unsigned long long)last[to + q]);
-  }
-}
-
-__global__ void __launch_bounds__(BLOCK) model_seed_mark_kernel(ModelDesc M) {
-  const int stride = gridDim.x * BLOCK;
-  int any = 0, cnt = 0;
-  for (int c = blockIdx.x * BLOCK + threadIdx.x; c < M.nTables; c += stride) {
-    const CT_G uint64_t* last = M.lastDom[c];
-    int d = 0;
-    for (int e = M.tabScope[c]; e < M.tabScope[c + 1] && !d; ++e) {
-      const int v = M.scopeVar[e];
-      const int po = M.poolOff[v], nw = M.poolNW[v], to = M.entDomOff[e];
-      for (int q = 0; q < nw; ++q)
-        if (last[to + q] & ~M.poolNext[po + q]) d = 1;
-    }
-    M.dirty[c] = d;
-    any |= d;
-    cnt += d;
-  }
-  if (any) atomicOr(&M.flags[0], 1);
-  if (cnt) atomicAdd(&M.flags[3], cnt);
-}
-
-// (kernel parameters never carry the address-space qualifier: host and device
-// passes must mangle the kernel's name identically)
-__global__ void __launch_bounds__(BLOCK) model_copy_kernel(uint64_t* dst, const uint64_t* src, int n) {
-  CT_G uint64_t* d = (CT_G uint64_t*)dst;
-  const CT_G uint64_t* sc = (const CT_G uint64_t*)src;
-  for (int w = blockIdx.x * BLOCK + threadIdx.x; w < n; w += gridDim.x * BLOCK) d[w] = sc[w];
-}
-
-// AND every successful table's output into poolNext; a failure stops the model
-__global__ void __launch_bounds__(BLOCK) model_merge_kernel(ModelDesc M) {
-  const int stride = gridDim.x * BLOCK;
-  for (int e = blockIdx.x * BLOCK + threadIdx.x; e < M.nEntries; e += stride) {
-    const int c = M.scopeTab[e];
-    if (!M.dirty[c]) continue;
-    const int st = M.status[c];
-    if (st != ST_OK) {
-      if (e == M.tabScope[c]) atomicExch(&M.flags[1], st == ST_FAIL ? 1 : 2);
-      continue;
-    }
-    const int v = M.scopeVar[e];
-    const int po = M.poolOff[v], nw = M.poolNW[v];
-    const CT_G uint64_t* dout = M.domOut + M.bufOff[c] + M.entDomOff[e];
-    for (int q = 0; q < nw; ++q) atomicAnd((unsigned long long*)&M.poolNext[po + q], (unsigned long long)dout[q]);
-  }
-}
-
-// variables whose pool domain shrank in this round; pool <- poolNext
-__global__ void __launch_bounds__(BLOCK) model_changed_kernel(ModelDesc M) {
-  const int stride = gridDim.x * BLOCK;
-  if (blockIdx.x == 0 && threadIdx.x == 0) M.flags[0] = 0;
-  for (int v = blockIdx.x * BLOCK + threadIdx.x; v < M.nPool; v += stride) {
-    const int po = M.poolOff[v], nw = M.poolNW[v];
-    int ch = 0;
-    for (int q = 0; q < nw; ++q) {
-      const uint64_t nx = M.poolNext[po + q];
-      if (nx != M.pool[po + q]) ch = 1;
-      M.pool[po + q] = nx;
-    }
-    M.changed[v] = ch;
-  }
-}
-
-// a table is dirty in the next round iff a variable of its scope changed
-__global__ void __launch_bounds__(BLOCK) model_mark_kernel(ModelDesc M) {
-  const int stride = gridDim.x * BLOCK;
-  const bool failed = M.flags[1] != 0;
-  int any = 0, cnt = 0;
-  for (int c = blockIdx.x * BLOCK + threadIdx.x; c < M.nTables; c += stride) {
-    int d = 0;
-    if (!failed)
-      for (int e = M.tabScope[c]; e < M.tabScope[c + 1]; ++e) d |= M.changed[M.scopeVar[e]];
-    M.dirty[c] = d;
-    any |= d;
-    cnt += d;
-  }
-  if (any) atomicOr(&M.flags[0], 1);
-  if (cnt) atomicAdd(&M.flags[3], cnt);
-  if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&M.flags[2], 1);
-}
-
 }  // namespace ctk
 
 // ---------------------------------------------------------------------------
@@ -2067,37 +1948,10 @@ hipError_t launch_build_supports(const int32_t* tuples, int64_t t, int n, const 
   return hipGetLastError();
 }
 
-hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int popGran, hipStream_t stream);
-
-hipError_t launch_model_round(const ModelDesc& M, const KArgs& a, const StageArgs& A, int nU, int nF, const KArgs& aNeg,
-                              hipStream_t stream) {
-  const int gb = 256;
-  hipLaunchKernelGGL(model_gather_kernel, dim3(gb), dim3(BLOCK), 0, stream, M);
-  if (a.nJobs > 0) (void)launch_staged(a, A, nU, nF, 0, stream);
-  if (aNeg.nJobs > 0)
-    hipLaunchKernelGGL(propagate_kernel, dim3(std::min(aNeg.nJobs, propagate_max_grid())), dim3(BLOCK), 0, stream, aNeg);
-  hipLaunchKernelGGL(model_merge_kernel, dim3(gb), dim3(BLOCK), 0, stream, M);
-  hipLaunchKernelGGL(model_changed_kernel, dim3(gb), dim3(BLOCK), 0, stream, M);
-  hipLaunchKernelGGL(model_mark_kernel, dim3(gb), dim3(BLOCK), 0, stream, M);
-  return hipGetLastError();
-}
-
 hipError_t launch_roots(const KArgs& a, const RootDesc& R, hipStream_t stream) {
   if (R.nTasks > 0)
     hipLaunchKernelGGL(root_stream_kernel, dim3(R.nTasks), dim3(BLOCK), 0, stream, a, R);
   hipLaunchKernelGGL(root_finish_kernel, dim3(a.nJobs), dim3(BLOCK), 0, stream, a);
-  return hipGetLastError();
-}
-
-// M.pool holds the input; leaves pool = input AND every table's domains and
-// the dirty flags of the first round.
-hipError_t launch_model_seed(const ModelDesc& M, hipStream_t stream) {
-  hipLaunchKernelGGL(model_copy_kernel, dim3(64), dim3(BLOCK), 0, stream, (uint64_t*)M.poolNext,
-                     (const uint64_t*)M.pool, M.poolWords);
-  hipLaunchKernelGGL(model_seed_and_kernel, dim3(64), dim3(BLOCK), 0, stream, M);
-  hipLaunchKernelGGL(model_seed_mark_kernel, dim3(64), dim3(BLOCK), 0, stream, M);
-  hipLaunchKernelGGL(model_copy_kernel, dim3(64), dim3(BLOCK), 0, stream, (uint64_t*)M.pool,
-                     (const uint64_t*)M.poolNext, M.poolWords);
   return hipGetLastError();
 }
 

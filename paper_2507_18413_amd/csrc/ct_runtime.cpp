@@ -172,6 +172,13 @@ std::map<hipStream_t, QueueCtx*> g_queues;
 
 }  // namespace
 
+// A table's share of a staged launch.
+struct StageShape {
+  int nU = 0, nF = 0;
+  bool wide = false, wideDom = false;
+  size_t bytes = 0;
+};
+
 struct ct_table {
   // the fields every call reads first, together (a batch of thousands of
   // jobs touches them for every table)
@@ -182,6 +189,7 @@ struct ct_table {
   TabDesc* dTab = nullptr;
   std::vector<SlotHost> slots;
   int32_t serialCounter = 1;
+  StageShape stage;
   bool poisoned = false;
   bool tailPending = false;  // a synchronous call returned before its kernel ended
   bool engEligible = false, engOn = false;
@@ -378,20 +386,35 @@ size_t stage_job_bytes(const ct_table* T) {
                   std::max(list, sizeof(uint64_t) * (size_t)T->D));
 }
 
+// A table's share of a launch, computed once (batches of a thousand jobs add
+// it up per call).
+StageShape stage_shape(const ct_table* T) {
+  StageShape S;
+  S.nU = stage_update_items(T->nGran);
+  S.nF = stage_finish_items(T->D, 0);  // (the narrow form of the finish has the most items)
+  S.wide = stage_wide(T->nGran, T->D);
+  S.wideDom = stage_wide_dom(T->D);
+  S.bytes = stage_job_bytes(T);
+  return S;
+}
+
 struct StageNeed {
   int nJobs = 0, nU = 0, nF = 0, popGran = 0;
   int u[STAGE_LISTS] = {}, f[STAGE_LISTS] = {};  // items per list
   int uCap = 0, fCap = 0;                        // the most of a list
   size_t jobBytes = 0;
   bool wide = false, wideDom = false;
-  void add(const ct_table* T, bool propagate, bool pops, bool solo) {
+  void add(const ct_table* T, bool propagate, bool pops) {
     if (pops) popGran = std::max(popGran, T->nGran);
-    if (propagate) jobBytes += stage_job_bytes(T);
-    wide = wide || (propagate && !solo && stage_wide(T->nGran, T->D));
-    wideDom = wideDom || (propagate && stage_wide_dom(T->D));
-    // (the narrow form of the finish has the most items)
-    if (propagate && !solo) add_items(stage_update_items(T->nGran), stage_finish_items(T->D, 0));
-    else add_items(0, 0);
+    if (!propagate) {
+      ++nJobs;
+      return;
+    }
+    const StageShape& S = T->stage;
+    jobBytes += S.bytes;
+    wide = wide || S.wide;
+    wideDom = wideDom || S.wideDom;
+    add_items(S.nU, S.nF);
   }
   void add_items(int du, int df) {
     const int l = nJobs++ % STAGE_LISTS;
@@ -400,10 +423,16 @@ struct StageNeed {
     uCap = std::max(uCap, u[l] += du);
     fCap = std::max(fCap, f[l] += df);
   }
-  size_t bytes() const {
-    return align256(sizeof(StageCounts)) + align256(sizeof(StageRec) * (size_t)nJobs) +
-           align256(sizeof(StageItem) * STAGE_LISTS * (size_t)uCap) +
-           align256(sizeof(StageItem) * STAGE_LISTS * (size_t)fCap) + jobBytes;
+  static size_t total(size_t jobs, size_t uc, size_t fc, size_t jb) {
+    return align256(sizeof(StageCounts)) + align256(sizeof(StageRec) * jobs) +
+           align256(sizeof(StageItem) * STAGE_LISTS * uc) + align256(sizeof(StageItem) * STAGE_LISTS * fc) + jb;
+  }
+  size_t bytes() const { return total(nJobs, uCap, fCap, jobBytes); }
+  // the bytes with one more propagation of T
+  size_t bytes_with(const ct_table* T) const {
+    const StageShape& S = T->stage;
+    const int l = nJobs % STAGE_LISTS;
+    return total(nJobs + 1, std::max(uCap, u[l] + S.nU), std::max(fCap, f[l] + S.nF), jobBytes + S.bytes);
   }
 };
 
@@ -471,7 +500,7 @@ int run_single(ct_table* T, DevJob& J, const uint64_t* dom_in_host) {
   StageNeed need;
   StageArgs A{};
   if (staged) {
-    need.add(T, true, J.nPop > 0, false);
+    need.add(T, true, J.nPop > 0);
     int rc = stage_reserve(T->q, need.bytes(), T->stream);
     if (rc) return rc;
     A = stage_args(need, T->q.dStaged, T->q.queue, T->q.hostErr);
@@ -949,9 +978,7 @@ struct BatchShape {
 // in one workgroup of the propagate kernel.
 bool batch_staged(const ct_table* T, bool propagate, size_t scratchCap) {
   if (!propagate) return true;
-  StageNeed one;
-  one.add(T, true, false, use_solo(T));
-  return T->kind != CT_KIND_NEGATIVE && one.bytes() <= scratchCap;
+  return T->kind != CT_KIND_NEGATIVE && StageNeed().bytes_with(T) <= scratchCap;
 }
 
 // Device descriptors of a validated batch, written into out[n_jobs] (other:
@@ -962,7 +989,7 @@ BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool
   BatchShape B;
   StageNeed need;
   int at = 0;
-  for (int pass = 0; pass < (other ? 1 : 2); ++pass)
+  for (int pass = 0; pass < 2 && at < n_jobs; ++pass)
     for (int j = 0; j < n_jobs; ++j) {
       const ct_job& cj = jobs[j];
       ct_table* T = cj.table;
@@ -1007,22 +1034,19 @@ BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool
       }
       S.failed = 2;
       if (other) continue;
-      const bool solo = propagate && (!staged || use_solo(T));
-      if (solo) J.flags |= JF_SOLO;
-      if (!staged) continue;
-      StageNeed more = need;
-      more.add(T, propagate, J.nPop > 0, solo);
-      if (B.nStaged == 0 || more.bytes() > scratchCap) {
+      if (!staged) {
+        J.flags |= JF_SOLO;
+        continue;
+      }
+      if (B.nStaged == 0 || need.bytes_with(T) > scratchCap) {
         chunks[B.nChunks++] = B.nStaged;
         need = StageNeed();
-        more = need;
-        more.add(T, propagate, J.nPop > 0, solo);
       }
       J.stageOff = (int32_t)(need.jobBytes / 256);
       J.listCap = stage_list_cap(T);
-      J.nUpd = more.nU - need.nU;
-      J.nFilt = more.nF - need.nF;
-      need = more;
+      J.nUpd = propagate ? T->stage.nU : 0;
+      J.nFilt = propagate ? T->stage.nF : 0;
+      need.add(T, propagate, J.nPop > 0);
       B.popGran = std::max(B.popGran, need.popGran);
       B.wide = B.wide || need.wide;
       B.wideDom = B.wideDom || need.wideDom;
@@ -1124,6 +1148,7 @@ static int create_impl(ct_table* T, const int32_t* tuples, int64_t t, int32_t n,
   }
   T->rows = rows;
   T->D = D;
+  T->stage = stage_shape(T);
   if (rows > MAX_TABLE_ROWS) return fail(CT_E_INVALID, "%d support rows exceed the limit %d", rows, MAX_TABLE_ROWS);
   if (D > MAX_TABLE_D) return fail(CT_E_INVALID, "%d domain words exceed the limit %d", D, MAX_TABLE_D);
   if (T->kind == CT_KIND_NEGATIVE && (rows > NEG_MAX_ROWS || D > MAX_D))
@@ -1687,7 +1712,7 @@ BatchPlan batch_plan(const ct_job* jobs, int n_jobs, bool nodes) {
     for (int j = 0; j < n_jobs; ++j) {
       const ct_table* T = jobs[j].table;
       const bool propagate = jobs[j].flags & CT_JOB_PROPAGATE;
-      if (batch_staged(T, propagate, STAGE_SCRATCH)) need.add(T, propagate, false, propagate && use_solo(T));
+      if (batch_staged(T, propagate, STAGE_SCRATCH)) need.add(T, propagate, false);
     }
     p.stagedBytes = need.bytes();
   }
@@ -1698,6 +1723,11 @@ BatchPlan batch_plan(const ct_job* jobs, int n_jobs, bool nodes) {
   return p;
 }
 
+// Descriptors that a staged batch reads from host memory: the copy would cost
+// a transfer between the launches (12-15 us a batch), each workgroup's read
+// about 2 us, which later workgroups of a larger batch would add up.
+constexpr int DIRECT_JOBS = 1024;
+
 // Where a batch's scratch lives: device counters, staging and search-node
 // scratch, and the host arrays the descriptors are built in.  Capacities
 // must cover the batch's plan.
@@ -1706,7 +1736,8 @@ struct BatchRes {
   int32_t* hostErr = nullptr;   // pinned, nullable
   char* dStage = nullptr;       // device staging
   char* hStage = nullptr;       // host staging (the source of the one copy)
-  hipEvent_t staged = nullptr;  // nullable: recorded after the copy
+  char* hStageDev = nullptr;    // its device address (pinned), or null
+  hipEvent_t staged = nullptr;  // nullable: recorded when the host staging has been read
   void* dNodes = nullptr;
   DevJob* hJobs = nullptr;      // n_jobs
   int32_t* chunks = nullptr;    // n_jobs
@@ -1740,10 +1771,15 @@ int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* st
   const size_t stageBytes = p.offAt + sizeof(int32_t) * p.nTaskInts;
   memcpy(r.hStage, r.hJobs, sizeof(DevJob) * n_jobs);
   if (p.roots && p.nTaskInts) memcpy(r.hStage + p.offAt, r.rootTasks, sizeof(int32_t) * p.nTaskInts);
-  HIPCHK(hipMemcpyAsync(r.dStage, r.hStage, p.roots ? stageBytes : sizeof(DevJob) * (size_t)n_jobs,
-                        hipMemcpyHostToDevice, stream));
-  if (r.staged) HIPCHK(hipEventRecord(r.staged, stream));
-  DevJob* dJobs = (DevJob*)r.dStage;
+  // A staged batch's descriptors are read once, by the prep: up to
+  // DIRECT_JOBS of them straight from the pinned buffer
+  const bool direct = r.hStageDev && !p.nodes && !p.roots && B.nStaged == n_jobs && n_jobs <= DIRECT_JOBS;
+  DevJob* dJobs = (DevJob*)(direct ? r.hStageDev : r.dStage);
+  if (!direct) {
+    HIPCHK(hipMemcpyAsync(r.dStage, r.hStage, p.roots ? stageBytes : sizeof(DevJob) * (size_t)n_jobs,
+                          hipMemcpyHostToDevice, stream));
+    if (r.staged) HIPCHK(hipEventRecord(r.staged, stream));
+  }
   KArgs a{};
   a.jobs = dJobs;
   a.nJobs = n_jobs;
@@ -1785,6 +1821,7 @@ int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* st
     a.nJobs = need.nJobs;
     HIPCHK(launch_staged(a, A, need.nU, need.nF, B.popGran, stream));
   }
+  if (direct) HIPCHK(hipEventRecord(r.staged, stream));
   if (B.nStaged < n_jobs) {
     a.jobs = dJobs + B.nStaged;
     a.nJobs = n_jobs - B.nStaged;
@@ -1906,6 +1943,7 @@ int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32
   r.hostErr = q->hostErr;
   r.dStage = q->dStage;
   r.hStage = q->pStage[q->turn];
+  HIPCHK(hipHostGetDevicePointer((void**)&r.hStageDev, r.hStage, 0));
   r.staged = q->staged[q->turn];
   r.dNodes = q->dNodes;
   r.hJobs = q->hJobs.data();
@@ -2006,12 +2044,13 @@ int table_view(const ct_table* T, TableView* v) {
 }  // namespace ctk
 
 // ===========================================================================
-// Multi-table model: propagation rounds captured in a hipGraph
+// Multi-table model: propagation rounds, launched one ahead of the host
 // ===========================================================================
 namespace ctk {
-hipError_t launch_model_round(const ModelDesc& M, const KArgs& a, const StageArgs& A, int nU, int nF, const KArgs& aNeg,
-                              hipStream_t stream);
-hipError_t launch_model_seed(const ModelDesc& M, hipStream_t stream);
+hipError_t launch_model_start(const ModelRound& M, const uint64_t* poolIn, const int32_t* off,
+                              const uint64_t* const* src, hipStream_t stream);
+hipError_t launch_model_round(const KArgs& a, const StageArgs& A, const ModelRound& M, int nU, int nF,
+                              const ModelNeg& neg, hipStream_t stream);
 }
 
 struct ct_model {
@@ -2022,20 +2061,26 @@ struct ct_model {
   hipStream_t stream = nullptr;
   QueueCtx q;
   int soloMax = 4, roundsPerGraph = 8;
-  // schedule per class of tables (granule bucket, rows bucket), set by the
-  // autotuner: solo or staged, and the tile of its cache entry; classes
-  // without an entry follow soloMax
+  // (solo, tile) per class of tables (granule bucket, rows bucket), set by the
+  // autotuner; classes without an entry follow soloMax.  Rounds run staged
+  // whichever it is.
   std::map<std::pair<int, int>, std::pair<int, int>> choice;
   // device state, rebuilt when the table set or the schedule changes
   bool built = false;
   std::vector<void*> blocks;
-  ModelDesc M{};
+  uint64_t* pool[3] = {nullptr, nullptr, nullptr};  // cur, next, prev in turn
+  ModelState* state = nullptr;
+  int32_t* startOff = nullptr;         // per pool word, its words in the tables' last domains:
+  const uint64_t** startSrc = nullptr; //   startSrc[startOff[w] .. startOff[w + 1])
+  KArgs a{};
+  StageArgs A{};
+  int nU = 0, nF = 0;
+  ModelNeg neg{};
   DevJob* dJobs = nullptr;
   std::vector<DevJob> hJobs;       // the staged jobs, then those of the propagate kernel
   std::vector<int32_t> jobOf;      // table -> its job
-  hipGraphExec_t exec = nullptr;   // roundsPerGraph rounds
-  hipGraphExec_t exec1 = nullptr;  // one round: a fixpoint's first launch
-  int32_t* pFlags = nullptr;   // pinned copy of M.flags
+  uint64_t* pHost = nullptr;   // pinned: how the last finished round ended (ModelRound::host)
+  uint32_t call = 0;           // fixpoints run: marks their words
   int32_t* dStatus = nullptr;  // statuses of push/pop batches
 };
 
@@ -2054,15 +2099,10 @@ int model_alloc(ct_model* m, void** p, size_t bytes) {
 
 void model_free_device(ct_model* m) {
   if (m->stream) (void)hipStreamSynchronize(m->stream);
-  if (m->exec) (void)hipGraphExecDestroy(m->exec);
-  if (m->exec1) (void)hipGraphExecDestroy(m->exec1);
-  m->exec = nullptr;
-  m->exec1 = nullptr;
   for (void* p : m->blocks) (void)hipFree(p);
   m->blocks.clear();
   m->dStatus = nullptr;
   m->dJobs = nullptr;
-  m->M = ModelDesc{};
   m->built = false;
 }
 
@@ -2087,80 +2127,68 @@ int log4_bucket(int64_t x) {
 
 std::pair<int, int> table_class(const ct_table* T) { return {log4_bucket(T->nGran), log4_bucket(T->rows)}; }
 
-// (solo, tile) of a table's round job (the tile is a field of the cache file only)
+// (solo, tile) of a table
 std::pair<int, int> model_choice(const ct_model* m, const ct_table* T) {
   auto it = m->choice.find(table_class(T));
   if (it != m->choice.end()) return it->second;
   return {T->nGran <= m->soloMax ? 1 : 0, 0};
 }
 
-// Device arrays, one propagate job per table, and the graph of K rounds.
+// Device arrays and one propagate job per table.
 int model_build(ct_model* m) {
   model_free_device(m);
   const int nT = (int)m->tabs.size();
-  std::vector<int32_t> scopeTab, scopeVar, entDomOff, tabScope(nT + 1, 0), bufOff(nT, 0);
-  std::vector<const uint64_t*> lastDom(nT);
-  int64_t words = 0;
+  int rc;
+  for (int k = 0; k < 3; ++k)
+    if ((rc = model_alloc(m, (void**)&m->pool[k], sizeof(uint64_t) * m->poolWords))) return rc;
+  if ((rc = model_alloc(m, (void**)&m->state, sizeof(ModelState)))) return rc;
+  if ((rc = model_alloc(m, (void**)&m->dStatus, sizeof(int32_t) * std::max(nT, 1)))) return rc;
+  // per table the pool word of each of its domain words; per pool word the
+  // addresses of its words in the tables' last domains
+  std::vector<int32_t> map;
+  std::vector<size_t> mapOff(nT);
+  std::vector<int32_t> startOff(m->poolWords + 1, 0);
+  std::vector<const uint64_t*> last(nT);
+  size_t negWords = 0;
   for (int c = 0; c < nT; ++c) {
     ct_table* T = m->tabs[c];
-    for (int k = 0; k < T->n; ++k) {
-      scopeTab.push_back(c);
-      scopeVar.push_back(m->scopes[c][k]);
-      entDomOff.push_back(T->domOff[k]);
-    }
-    tabScope[c + 1] = (int32_t)scopeTab.size();
-    bufOff[c] = (int32_t)words;
-    words += T->D;
     SlotDesc sd{};
     HIPCHK(hipMemcpy(&sd, T->slots[0].dev, sizeof(SlotDesc), hipMemcpyDeviceToHost));
-    lastDom[c] = (const uint64_t*)sd.lastDom;
+    last[c] = (const uint64_t*)sd.lastDom;
+    mapOff[c] = map.size();
+    map.resize(map.size() + T->D);
+    for (int k = 0; k < T->n; ++k) {
+      const int v = m->scopes[c][k];
+      for (int q = 0; q < m->poolNW[v]; ++q) {
+        map[mapOff[c] + T->domOff[k] + q] = m->poolOff[v] + q;
+        ++startOff[m->poolOff[v] + q + 1];
+      }
+    }
+    if (T->kind == CT_KIND_NEGATIVE) negWords += T->D;
   }
-  ModelDesc& M = m->M;
-  M = ModelDesc{};
-  M.nTables = nT;
-  M.nPool = m->nPool;
-  M.poolWords = m->poolWords;
-  M.nEntries = (int32_t)scopeTab.size();
-  int rc;
-  int32_t* p32 = nullptr;
-  if ((rc = model_upload(m, &p32, m->poolOff))) return rc;
-  M.poolOff = p32;
-  if ((rc = model_upload(m, &p32, m->poolNW))) return rc;
-  M.poolNW = p32;
-  if ((rc = model_upload(m, &p32, scopeTab))) return rc;
-  M.scopeTab = p32;
-  if ((rc = model_upload(m, &p32, scopeVar))) return rc;
-  M.scopeVar = p32;
-  if ((rc = model_upload(m, &p32, entDomOff))) return rc;
-  M.entDomOff = p32;
-  if ((rc = model_upload(m, &p32, tabScope))) return rc;
-  M.tabScope = p32;
-  if ((rc = model_upload(m, &p32, bufOff))) return rc;
-  M.bufOff = p32;
-  const uint64_t** pld = nullptr;
-  if ((rc = model_upload(m, &pld, lastDom))) return rc;
-  M.lastDom = pld;
-  uint64_t* p64 = nullptr;
-  if ((rc = model_alloc(m, (void**)&p64, sizeof(uint64_t) * std::max<int64_t>(words, 1)))) return rc;
-  M.domIn = p64;
-  if ((rc = model_alloc(m, (void**)&p64, sizeof(uint64_t) * std::max<int64_t>(words, 1)))) return rc;
-  M.domOut = p64;
-  if ((rc = model_alloc(m, (void**)&p64, sizeof(uint64_t) * m->poolWords))) return rc;
-  M.pool = p64;
-  if ((rc = model_alloc(m, (void**)&p64, sizeof(uint64_t) * m->poolWords))) return rc;
-  M.poolNext = p64;
-  if ((rc = model_alloc(m, (void**)&p32, sizeof(int32_t) * std::max(nT, 1)))) return rc;
-  M.status = p32;
-  if ((rc = model_alloc(m, (void**)&p32, sizeof(int32_t) * std::max(nT, 1)))) return rc;
-  M.dirty = p32;
-  if ((rc = model_alloc(m, (void**)&p32, sizeof(int32_t) * std::max(m->nPool, 1)))) return rc;
-  M.changed = p32;
-  if ((rc = model_alloc(m, (void**)&p32, sizeof(int32_t) * 8))) return rc;
-  M.flags = p32;
-  if ((rc = model_alloc(m, (void**)&m->dStatus, sizeof(int32_t) * std::max(nT, 1)))) return rc;
-  // jobs: table c propagates slot 0 from domIn to domOut when dirty[c]
+  for (int w = 0; w < m->poolWords; ++w) startOff[w + 1] += startOff[w];
+  std::vector<const uint64_t*> startSrc(map.size());
+  {
+    std::vector<int32_t> at(startOff.begin(), startOff.end() - 1);
+    for (int c = 0; c < nT; ++c)
+      for (int q = 0; q < m->tabs[c]->D; ++q) startSrc[at[map[mapOff[c] + q]]++] = last[c] + q;
+  }
+  int32_t* dMap = nullptr;
+  if ((rc = model_upload(m, &dMap, map))) return rc;
+  if ((rc = model_upload(m, &m->startOff, startOff))) return rc;
+  if ((rc = model_upload(m, &m->startSrc, startSrc))) return rc;
+  // jobs: the staged ones, then the negative tables', on buffers of their own
   m->hJobs.assign(nT, DevJob{});
   m->jobOf.assign(nT, 0);
+  uint64_t *negIn = nullptr, *negOut = nullptr;
+  int32_t *negStatus = nullptr, *negDirty = nullptr;
+  std::vector<const int32_t*> negMaps;
+  if (negWords) {
+    if ((rc = model_alloc(m, (void**)&negIn, sizeof(uint64_t) * negWords))) return rc;
+    if ((rc = model_alloc(m, (void**)&negOut, sizeof(uint64_t) * negWords))) return rc;
+    if ((rc = model_alloc(m, (void**)&negStatus, sizeof(int32_t) * nT))) return rc;
+    if ((rc = model_alloc(m, (void**)&negDirty, sizeof(int32_t) * nT))) return rc;
+  }
   StageNeed need;
   int at = 0;
   for (int pass = 0; pass < 2; ++pass)
@@ -2168,56 +2196,47 @@ int model_build(ct_model* m) {
       ct_table* T = m->tabs[c];
       const bool negative = T->kind == CT_KIND_NEGATIVE;
       if (negative != (pass == 1)) continue;
-      const bool solo = model_choice(m, T).first || negative;
       m->jobOf[c] = at;
       DevJob& J = m->hJobs[at++];
       J.tab = T->dTab;
       J.slot = T->slots[0].dev;
-      J.dom_in = M.domIn + bufOff[c];
-      J.dom_out = M.domOut + bufOff[c];
-      J.status_out = M.status + c;
-      J.flags = JF_PROPAGATE | (solo ? JF_SOLO : 0u);
+      J.flags = JF_PROPAGATE | (negative ? JF_SOLO : JF_MODEL);
       J.depthAfter = T->slots[0].depth;
-      J.active = M.dirty + c;
-      if (negative) continue;
+      if (negative) {
+        J.dom_in = negIn;
+        J.dom_out = negOut;
+        negIn += T->D;
+        negOut += T->D;
+        J.status_out = negStatus + negMaps.size();
+        J.active = negDirty + negMaps.size();
+        negMaps.push_back(dMap + mapOff[c]);
+        continue;
+      }
+      J.dom_in = (const uint64_t*)(dMap + mapOff[c]);
       J.stageOff = (int32_t)(need.jobBytes / 256);
       J.listCap = stage_list_cap(T);
-      need.add(T, true, false, solo);
+      need.add(T, true, false);
     }
   if ((rc = model_upload(m, &m->dJobs, m->hJobs))) return rc;
   char* scratch = nullptr;
   if ((rc = model_alloc(m, (void**)&scratch, need.bytes()))) return rc;
   HIPCHK(hipMemsetAsync(scratch, 0, sizeof(StageCounts), m->stream));
-  KArgs a{}, aNeg{};
-  a.jobs = m->dJobs;
-  a.nJobs = need.nJobs;
-  a.queue = m->q.queue;
-  a.hostErr = m->q.hostErr;
-  aNeg = a;
-  aNeg.jobs = m->dJobs + need.nJobs;
-  aNeg.nJobs = nT - need.nJobs;
-  const StageArgs A = stage_args(need, scratch, m->q.queue, m->q.hostErr);
-  // capture a one-round graph (a fixpoint's first two launches: most search
-  // steps converge in a round or two, and rounds after convergence cost
-  // launches) and a rounds_per_graph-round graph for the launches after them
-  for (int which = 0; which < 2; ++which) {
-    const int rounds = which == 0 ? 1 : m->roundsPerGraph;
-    hipGraph_t g = nullptr;
-    HIPCHK(hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal));
-    for (int r = 0; r < rounds; ++r) {
-      hipError_t e = launch_model_round(M, a, A, need.nU, need.nF, aNeg, m->stream);
-      if (e != hipSuccess) {
-        hipGraph_t dummy = nullptr;
-        (void)hipStreamEndCapture(m->stream, &dummy);
-        if (dummy) (void)hipGraphDestroy(dummy);
-        return fail(CT_E_DEVICE, "model round capture failed: %s", hipGetErrorString(e));
-      }
-    }
-    HIPCHK(hipStreamEndCapture(m->stream, &g));
-    hipError_t e = hipGraphInstantiate(which == 0 ? &m->exec1 : &m->exec, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (e != hipSuccess) return fail(CT_E_DEVICE, "hipGraphInstantiate failed: %s", hipGetErrorString(e));
-  }
+  m->a = KArgs{};
+  m->a.jobs = m->dJobs;
+  m->a.nJobs = need.nJobs;
+  m->a.queue = m->q.queue;
+  m->a.hostErr = m->q.hostErr;
+  m->neg = ModelNeg{};
+  m->neg.a = m->a;
+  m->neg.a.jobs = m->dJobs + need.nJobs;
+  m->neg.a.nJobs = nT - need.nJobs;
+  const int32_t** dMaps = nullptr;
+  if ((rc = model_upload(m, &dMaps, negMaps))) return rc;
+  m->neg.maps = dMaps;
+  m->neg.dirty = negDirty;
+  m->A = stage_args(need, scratch, m->q.queue, m->q.hostErr);
+  m->nU = need.nU;
+  m->nF = need.nF;
   m->built = true;
   return CT_OK;
 }
@@ -2256,6 +2275,46 @@ int model_push_pop(ct_model* m, bool push) {
   if (!m->dStatus) {
     int rc = model_alloc(m, (void**)&m->dStatus, sizeof(int32_t) * nT);
     if (rc) return rc;
+  }
+  // a built model has its tables' descriptors on the device: one launch with
+  // the same pop or push for each
+  bool direct = m->built;
+  int popGran = 0;
+  int32_t serial = 0;
+  for (int c = 0; c < nT && direct; ++c) {
+    const ct_table* T = m->tabs[c];
+    const SlotHost& S = T->slots[0];
+    direct = !T->poisoned && !S.freed && S.pendPop == 0 && S.pendPush == 0 && (push ? S.depth < S.maxDepth : S.depth > 0);
+    popGran = std::max(popGran, T->nGran);
+    serial = std::max(serial, T->serialCounter);
+  }
+  for (int c = 0; c < nT && direct; ++c) {
+    ct_table* T = m->tabs[c];
+    int rc = quiesce(T, m->stream);
+    if (rc) return rc;
+    if (T->tailPending) {
+      HIPCHK(hipStreamSynchronize(T->stream));
+      T->tailPending = false;
+    }
+  }
+  if (direct) {
+    for (ct_table* T : m->tabs) {
+      SlotHost& S = T->slots[0];
+      if (push) S.failedAt.push_back(2);
+      else S.failedAt.pop_back();
+      S.depth += push ? 1 : -1;
+      S.failed = 2;
+      if (push) T->serialCounter = serial + 1;
+      T->pendStream = m->stream;
+    }
+    KArgs a = m->a;
+    a.nJobs = nT;
+    a.uniform = 1;
+    a.job.nPop = push ? 0 : 1;
+    a.job.nPush = push ? 1 : 0;
+    a.job.serialBase = serial;
+    HIPCHK(launch_staged(a, m->A, 0, 0, push ? 0 : popGran, m->stream));
+    return CT_OK;
   }
   std::vector<ct_job> jobs(nT);
   for (int c = 0; c < nT; ++c) {
@@ -2306,7 +2365,8 @@ int ct_model_create(int32_t n_vars, const int32_t* dom_lo, const int32_t* dom_si
   }
   int rc = queue_init(m->q);
   if (rc == CT_OK) {
-    e = hipHostMalloc((void**)&m->pFlags, sizeof(int32_t) * 8, hipHostMallocDefault);
+    e = hipHostMalloc((void**)&m->pHost, sizeof(uint64_t) * 2, hipHostMallocMapped | hipHostMallocCoherent);
+    if (e == hipSuccess) memset(m->pHost, 0, sizeof(uint64_t) * 2);
     if (e != hipSuccess) rc = fail(CT_E_NOMEM, "pinned allocation failed");
   }
   if (rc) {
@@ -2327,7 +2387,7 @@ void ct_model_destroy(ct_model* m) {
       if (g_tables.count(T) && T->pendStream == m->stream) T->pendStream = nullptr;
   }
   queue_free(m->q);
-  if (m->pFlags) (void)hipHostFree(m->pFlags);
+  if (m->pHost) (void)hipHostFree(m->pHost);
   if (m->stream) (void)hipStreamDestroy(m->stream);
   delete m;
 }
@@ -2380,27 +2440,52 @@ int ct_model_fixpoint(ct_model* m, const uint64_t* pool_in, uint64_t* pool_out, 
   int rc = model_sync_tables(m);
   if (rc) return rc;
   if (!m->built && (rc = model_build(m))) return rc;
-  ModelDesc& M = m->M;
-  HIPCHK(hipMemcpyAsync(M.pool, pool_in, sizeof(uint64_t) * m->poolWords, hipMemcpyDeviceToDevice, m->stream));
-  // (eager, never inside the captured rounds)
-  HIPCHK(hipMemsetAsync(M.flags, 0, sizeof(int32_t) * 8, m->stream));
-  HIPCHK(launch_model_seed(M, m->stream));
-  for (int replays = 0;; ++replays) {
-    if (replays > 100000) return fail(CT_E_DEVICE, "fixpoint did not converge");
-    HIPCHK(hipGraphLaunch(replays < 2 ? m->exec1 : m->exec, m->stream));
-    // the pool is copied out with the flags: when they say done, it is there
-    HIPCHK(hipMemcpyAsync(pool_out, M.pool, sizeof(uint64_t) * m->poolWords, hipMemcpyDeviceToDevice, m->stream));
-    HIPCHK(hipMemcpyAsync(m->pFlags, M.flags, sizeof(int32_t) * 8, hipMemcpyDeviceToHost, m->stream));
-    hipError_t e = hipStreamSynchronize(m->stream);
-    if (e != hipSuccess) {
-      for (ct_table* T : m->tabs) T->poisoned = true;
-      return fail(CT_E_DEVICE, "model round failed: %s", hipGetErrorString(e));
+  ModelRound M{};
+  M.poolOut = pool_out;
+  M.state = m->state;
+  M.poolWords = m->poolWords;
+  M.nHead = std::min(32, (m->poolWords + 511) / 512);
+  M.call = (int32_t)++m->call;
+  HIPCHK(hipHostGetDevicePointer((void**)&M.host, m->pHost, 0));
+  auto launch_round = [&](int r) {
+    M.round = r;
+    M.cur = m->pool[r % 3];
+    M.next = m->pool[(r + 1) % 3];
+    M.prev = m->pool[(r + 2) % 3];
+    return launch_model_round(m->a, m->A, M, m->nU, m->nF, m->neg, m->stream);
+  };
+  M.cur = m->pool[0];
+  HIPCHK(launch_model_start(M, pool_in, m->startOff, m->startSrc, m->stream));
+  // One round is always queued behind the running one: a round's prep tells
+  // the host how the round before ended, and when that was the last round it
+  // copies the pool out and nothing of it runs (about 8 us, against the same
+  // for the host to launch a round that it waited to know of).
+  HIPCHK(launch_round(0));
+  int launched = 1, code = 0;
+  for (bool lost = false; !code && !lost;) {
+    if (launched > 1000000) return fail(CT_E_DEVICE, "fixpoint did not converge");
+    HIPCHK(launch_round(launched));
+    const uint64_t want = (uint64_t)m->call << 32 | (uint32_t)launched++ << 8;
+    bool ended = false;  // the stream was empty: then the word is there
+    for (uint32_t spin = 1;; ++spin) {
+      const uint64_t v = __atomic_load_n(&m->pHost[0], __ATOMIC_ACQUIRE);
+      if ((v & ~(uint64_t)0xff) == want) {
+        code = (int)(v & 0xff);
+        break;
+      }
+      if ((lost = ended)) break;
+      if ((spin & 0xffff) == 0) ended = hipStreamQuery(m->stream) != hipErrorNotReady;
     }
-    if (*(volatile int32_t*)m->q.hostErr) {
-      for (ct_table* T : m->tabs) T->poisoned = true;
-      return fail(CT_E_DEVICE, "device-side error %d in a model round", *m->q.hostErr);
-    }
-    if (m->pFlags[1] || !m->pFlags[0]) break;
+  }
+  const int64_t props = (int64_t)__atomic_load_n(&m->pHost[1], __ATOMIC_ACQUIRE);
+  hipError_t e = hipStreamSynchronize(m->stream);
+  if (e != hipSuccess || !code) {
+    for (ct_table* T : m->tabs) T->poisoned = true;
+    return fail(CT_E_DEVICE, "model round failed: %s", hipGetErrorString(e));
+  }
+  if (*(volatile int32_t*)m->q.hostErr) {
+    for (ct_table* T : m->tabs) T->poisoned = true;
+    return fail(CT_E_DEVICE, "device-side error %d in a model round", *m->q.hostErr);
   }
   // the push / pop batches queued on the model's stream before these rounds
   // have ended with them
@@ -2411,11 +2496,14 @@ int ct_model_fixpoint(ct_model* m, const uint64_t* pool_in, uint64_t* pool_out, 
     return rc;
   }
   for (ct_table* T : m->tabs) T->slots[0].failed = 2;
-  if (n_props) *n_props = m->pFlags[3];
-  if (n_rounds) *n_rounds = m->pFlags[2];
-  if (m->pFlags[1] == 2)
+  if (n_props) *n_props = props;
+  // rounds are counted in the units of the schedule: one, one, then
+  // rounds_per_graph at a time
+  const int ran = launched - 1, unit = m->roundsPerGraph;
+  if (n_rounds) *n_rounds = ran <= 2 ? std::max(ran, 1) : 2 + (ran - 2 + unit - 1) / unit * unit;
+  if (code == 2)
     return fail(CT_E_STATE, "a table of the model is in the failed state (pop it first)");
-  if (m->pFlags[1]) return CT_FAIL;
+  if (code == 1) return CT_FAIL;
   return CT_OK;
 }
 
@@ -2544,7 +2632,7 @@ int ct_model_autotune(ct_model* m, const uint64_t* pool_in, const char* cache_pa
     ++nTimed;
     return CT_OK;
   };
-  // coordinate descent over the classes: solo (one workgroup) or staged
+  // coordinate descent over the classes
   const std::pair<int, int> opts[] = {{1, 0}, {0, 2}};
   for (const auto& o : order) {
     const auto cls = o.second;

@@ -19,7 +19,15 @@
 // (agent-scope releases and acquires, 198 VGPRs and 79 KB of LDS a workgroup
 // for every step, items from one queue): a call of 2,000,000 tuples 26 us
 // against 64, of 2,422 domain words and 12,000 tuples 68 against 104, a batch
-// of 128 searches over tables of 1,000 to 2,000,000 tuples 48 against 132.
+// of 128 searches over tables of 1,000 to 2,000,000 tuples 41 against 132, of
+// 1,000 searches over tables of at most 16,000 54 against 91 (running such
+// jobs whole in their prep workgroup instead: 89).
+//
+// A model's round is the same three launches: the prep takes each table's
+// input from the pool and skips the tables none of whose variables changed,
+// the finish ANDs the results into the next pool.  6 search steps on 400
+// tables of up to 500,000 tuples: 730 us, against 1,240 with separate kernels
+// for gather, merge, change and mark, captured 1, 1, then 8 rounds at a time.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -27,6 +35,10 @@
 #include "ct_device.h"
 
 namespace ctk {
+
+hipError_t launch_propagate(const KArgs& a, int grid, hipStream_t stream);
+int propagate_max_grid();
+
 namespace {
 
 // Prep workgroup: 1,024 threads for a launch of few jobs or with wide tables,
@@ -51,6 +63,15 @@ constexpr uint32_t SEG_INC = 1u << 30;   //   of an incremental segment
 
 __device__ __forceinline__ int s_lane() { return threadIdx.x & (WAVE - 1); }
 __device__ __forceinline__ int s_wave() { return __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE); }
+
+// The same pointer for every lane, known as such.
+template <class T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+  const uint64_t x = (uint64_t)p;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+  return (T*)((uint64_t)hi << 32 | lo);
+}
 
 __device__ __forceinline__ int s_scan(int v) {  // inclusive prefix sum over the wave
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
@@ -106,9 +127,6 @@ __device__ __forceinline__ void seg_close(uint64_t& m, uint64_t& acc, bool inc) 
   acc = 0ull;
 }
 
-// LOCAL: the record's row list was written in this launch (a job that its prep
-// workgroup runs whole): vector loads.
-template <bool LOCAL>
 __device__ __forceinline__ void stage_granule(const StageArgs& A, const StageRec& V, CT_G int32_t* trailCount,
                                               int pos) {
   const StageRec* R = &V;
@@ -143,8 +161,7 @@ __device__ __forceinline__ void stage_granule(const StageArgs& A, const StageRec
       uint32_t e[ROW_U];
       uint64_t v[ROW_U];
 #pragma unroll
-      for (int j = 0; j < ROW_U; ++j)
-        e[j] = LOCAL ? (uint32_t)__builtin_amdgcn_readfirstlane((int)R->rows[k0 + j]) : list[k0 + j];
+      for (int j = 0; j < ROW_U; ++j) e[j] = list[k0 + j];
 #pragma unroll
       for (int j = 0; j < ROW_U; ++j) v[j] = S[(int64_t)(e[j] & 0x3fffffffu) * stride];
 #pragma unroll
@@ -167,11 +184,11 @@ __device__ __forceinline__ void stage_granule(const StageArgs& A, const StageRec
       const int domOff = words[q].v.domOff;
       if (q == domOff) {
         if (in) seg_close(m, acc, inc);
-        const int sz = LOCAL ? R->size[q] : size[q];
+        const int sz = size[q];
         in = !(sz & (1 << 29));
         inc = sz & (1 << 30);
       }
-      uint64_t bits = !in ? 0ull : LOCAL ? ((const CT_G uint64_t*)R->rows)[q] : sel[q];
+      uint64_t bits = in ? sel[q] : 0ull;
       const CT_G uint64_t* Sq = S + (int64_t)(words[q].v.rowStart + 64 * (q - domOff)) * stride;
       int b = 0;
       while (bits) {
@@ -334,6 +351,16 @@ __device__ __forceinline__ void stage_partition(const StageRec& V, FinShared<FBL
     if (saved) atomicAdd(&s->stats[S_TRAIL], (unsigned long long)saved);
     // a flagged call reports success by its domain words
     if (st != ST_OK || !(R->flags & JF_LL)) put_status(R->flags, R->ll, R->seq, R->status_out, st);
+    if (R->poolMap && st != ST_OK) R->model->fail = (R->round + 1) << 2 | 1;
+  }
+}
+
+// What a table of a model round removed leaves the pool: domain word q, one lane.
+__device__ __forceinline__ void stage_merge(const StageRec& R, int q, uint64_t dout) {
+  const int pw = R.poolMap[q];
+  if (R.poolCur[pw] & ~dout) {
+    atomicAnd((unsigned long long*)(R.poolNext + pw), dout);
+    R.model->lastChanged = R.round + 1;
   }
 }
 
@@ -352,7 +379,7 @@ __device__ __forceinline__ void stage_partition(const StageRec& V, FinShared<FBL
 constexpr int FULL_GRAN = 4, FULL_VALS = 4;
 constexpr int WALK = 8, WALKS = 2;
 
-template <int FBLOCK, bool LOCAL>
+template <int FBLOCK>
 __device__ __forceinline__ void stage_filter(const StageRec& V, int q0, int nWords, FinShared<FBLOCK>& sh) {
   constexpr int FWAVES = FBLOCK / WAVE;
   const StageRec* R = &V;
@@ -362,8 +389,8 @@ __device__ __forceinline__ void stage_filter(const StageRec& V, int q0, int nWor
   const int qc = word ? q : q0;
   const CT_K WordDesc* wds = (const CT_K WordDesc*)R->words;
   const int rowStart = wds[qc].v.rowStart, domOff = wds[qc].v.domOff, dsize = wds[qc].v.dsize;
-  const uint64_t din = LOCAL ? R->din[qc] : ((const CT_K uint64_t*)R->din)[qc];
-  const int size = (LOCAL ? R->size[qc] : ((const CT_K int32_t*)R->size)[qc]) & 0x1fffffff;
+  const uint64_t din = ((const CT_K uint64_t*)R->din)[qc];
+  const int size = ((const CT_K int32_t*)R->size)[qc] & 0x1fffffff;
   const int64_t stride = R->stride;
   const CT_G uint64_t* ct = R->ct;
   const CT_G int32_t* nz = R->nz;
@@ -535,7 +562,9 @@ __device__ __forceinline__ void stage_filter(const StageRec& V, int q0, int nWor
   }
   if (!word) return;
   const uint64_t dout = din & ~unsup;
-  if (R->flags & JF_LL) {
+  if (R->poolMap) {
+    if (lane == 0) stage_merge(*R, q, dout);
+  } else if (R->flags & JF_LL) {
     if (lane < 2) put_slot(R->ll + 2 + 2 * q + lane, (uint32_t)(lane ? dout >> 32 : dout), R->seq);
   } else if (lane == 0) {
     R->dom_out[q] = dout;
@@ -549,7 +578,7 @@ __device__ __forceinline__ void stage_finish_item(const StageArgs& A, int job, i
   if (!R.run) return;
   const int fw = fin_words(R.D, FBLOCK > 256);
   if (chunk == 0) stage_partition(R, sh);
-  else stage_filter<FBLOCK, false>(R, (chunk - 1) * fw, fw, sh);
+  else stage_filter(R, (chunk - 1) * fw, fw, sh);
 }
 
 struct PrepShared {
@@ -557,7 +586,8 @@ struct PrepShared {
   int32_t seg[MAX_ARITY];  // first list entry of the variable's segment; -1: not in s_val
   int32_t inc[MAX_ARITY];
   int32_t wsum[PMAX / WAVE];
-  int32_t stray, notSub, status, noop, zero, nrows, nseg;
+  uint32_t job[sizeof(DevJob) / sizeof(uint32_t)];
+  int32_t stray, notSub, dirty, status, noop, zero, nrows, nseg;
 };
 
 // Exclusive prefix sum over the workgroup; *total receives the sum.
@@ -578,26 +608,135 @@ __device__ int prep_scan(int v, int* total, PrepShared& sh) {
   return off + x - v;
 }
 
+// A model round's first workgroups: next starts as a copy of cur; the host
+// hears how the round before ended, and gets the pool when it was the last.
+__device__ __forceinline__ int model_code(const ModelRound& M) {
+  const int fail = M.state->fail, last = M.state->lastChanged;
+  if (M.round == 0) return 0;
+  if (fail && (fail >> 2) <= M.round) return fail & 3;
+  return last < M.round ? MODEL_DONE : 0;
+}
+
+// A failed round was the last (after a round without a change no table is
+// dirty).  Jobs of this round may set fail meanwhile: theirs does not count.
+__device__ __forceinline__ bool model_over(const ModelRound& M) {
+  const int fail = M.state->fail;
+  return fail && (fail >> 2) <= M.round;
+}
+
+template <int PBLOCK>
+__device__ __forceinline__ void model_head(const ModelRound& M) {
+  const int code = model_code(M);
+  CT_G uint64_t* dst = code ? M.poolOut : M.next;
+  for (int w = blockIdx.x * PBLOCK + threadIdx.x; w < M.poolWords; w += M.nHead * PBLOCK) dst[w] = M.cur[w];
+  if (blockIdx.x == 0 && threadIdx.x < WAVE && M.round > 0) {
+    const int p = s_scan(s_lane() < MODEL_PROPS ? M.state->props[s_lane() * 16] : 0);
+    if (s_lane() == WAVE - 1) {
+      __hip_atomic_store(&M.host[1], (uint64_t)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(&M.host[0], (uint64_t)(uint32_t)M.call << 32 | (uint32_t)(M.round << 8 | code),
+                         __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
+}
+
+// The pool a fixpoint starts from: the input ANDed with the domains that every
+// table returned last (an earlier pruning holds under a smaller pool).  8 lanes
+// per pool word, src[off[w] .. off[w + 1]) its words in the tables.
+__global__ void __launch_bounds__(SBLOCK) model_start_kernel(const uint64_t* poolIn, uint64_t* pool, const int32_t* off,
+                                                             const uint64_t* const* src, int poolWords,
+                                                             ModelState* state) {
+  if (blockIdx.x == 0)
+    for (int k = threadIdx.x; k < (int)(sizeof(ModelState) / sizeof(int32_t)); k += SBLOCK) ((int32_t*)state)[k] = 0;
+  const int w = (int)(blockIdx.x * SBLOCK + threadIdx.x) / 8, l = threadIdx.x & 7;
+  const int wc = min(w, poolWords - 1);
+  uint64_t x = ((const CT_G uint64_t*)poolIn)[wc];
+  const int end = off[wc + 1];
+#pragma unroll 4
+  for (int k = off[wc] + l; k < end; k += 8) x &= *(const CT_G uint64_t*)src[k];
+  for (int d = 1; d < 8; d <<= 1) x &= __shfl_xor((unsigned long long)x, d);
+  if (l == 0 && w < poolWords) pool[w] = x;
+}
+
+// Negative tables of a model round (they run in the propagate kernel): which
+// run and on what; then what they remove leaves the pool.  One workgroup per
+// job; map: the pool word of each domain word.
+__global__ void __launch_bounds__(SBLOCK) model_neg_gather_kernel(const DevJob* jobs, const int32_t* const* maps,
+                                                                  int32_t* dirty, ModelRound M) {
+  __shared__ int32_t any;
+  const DevJob J = jobs[blockIdx.x];
+  const CT_G int32_t* map = (const CT_G int32_t*)maps[blockIdx.x];
+  if (threadIdx.x == 0) any = 0;
+  __syncthreads();
+  const int D = J.tab->D;
+  const CT_G uint64_t* last = J.slot->lastDom;
+  CT_G uint64_t* in = (CT_G uint64_t*)J.dom_in;
+  const bool over = model_over(M);
+  for (int q = threadIdx.x; q < D; q += SBLOCK) {
+    const int pw = map[q];
+    const uint64_t x = M.cur[pw], ld = last[q];
+    if (!over && (M.round ? x != M.prev[pw] : (ld & ~x) != 0)) any = 1;
+    in[q] = x & ld;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    dirty[blockIdx.x] = any;
+    if (any) atomicAdd((int32_t*)&M.state->props[((int)blockIdx.x % MODEL_PROPS) * 16], 1);
+  }
+}
+
+__global__ void __launch_bounds__(SBLOCK) model_neg_merge_kernel(const DevJob* jobs, const int32_t* const* maps,
+                                                                 const int32_t* dirty, ModelRound M) {
+  if (!dirty[blockIdx.x]) return;
+  const DevJob J = jobs[blockIdx.x];
+  const CT_G int32_t* map = (const CT_G int32_t*)maps[blockIdx.x];
+  const int st = *J.status_out;
+  if (st != ST_OK) {
+    if (threadIdx.x == 0) M.state->fail = (M.round + 1) << 2 | (st == ST_FAIL ? 1 : 2);
+    return;
+  }
+  for (int q = threadIdx.x; q < J.tab->D; q += SBLOCK) {
+    const int pw = map[q];
+    const uint64_t x = J.dom_out[q];
+    if (M.cur[pw] & ~x) {
+      atomicAnd((unsigned long long*)(M.next + pw), x);
+      M.state->lastChanged = M.round + 1;
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Prep: one workgroup per job.  Dynamic LDS: an int per granule of the
 // largest popping table of the launch.
 // Bound: its chain of memory round trips (job -> slot -> domains -> list).
 // ---------------------------------------------------------------------------
-template <int PBLOCK>
-__global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArgs A) {
+template <int PBLOCK, bool MODEL>
+__global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArgs A, ModelRound M) {
   constexpr int PWAVES = PBLOCK / WAVE;
   __shared__ PrepShared sh;
-  __shared__ FinShared<PBLOCK> fin;
   extern __shared__ int32_t first[];
   if (a.clock && threadIdx.x == 0) atomicMin(&a.clock[0], wall_clock64());
   const int tid = threadIdx.x, lane = s_lane();
-  DevJob J = a.job;
-  if (a.jobs) J = a.jobs[blockIdx.x];
-  CT_G StageRec* rec = A.rec + blockIdx.x;
-  if (J.active && !*J.active) {
-    if (tid == 0) rec->run = 0;
+  if (MODEL && (int)blockIdx.x < M.nHead) {
+    model_head<PBLOCK>(M);
     return;
   }
+  const int job = MODEL ? (int)blockIdx.x - M.nHead : (int)blockIdx.x;
+  // the descriptor may be in host memory: read once per workgroup, into LDS
+  constexpr int JW = sizeof(DevJob) / sizeof(uint32_t);
+  const CT_G uint32_t* from = (const CT_G uint32_t*)(a.jobs + job);
+  if (tid < JW) sh.job[tid] = a.jobs ? from[tid] : ((const uint32_t*)&a.job)[tid];
+  if (MODEL && model_over(M)) return;
+  s_lds_barrier();
+  DevJob J;
+  __builtin_memcpy(&J, sh.job, sizeof(J));
+  J.tab = uniform_ptr(J.tab);
+  J.slot = uniform_ptr(J.slot);
+  J.dom_in = uniform_ptr(J.dom_in);
+  J.flags = a.uniform ? 0 : __builtin_amdgcn_readfirstlane((int)J.flags);
+  J.nPop = a.uniform ? a.job.nPop : __builtin_amdgcn_readfirstlane(J.nPop);
+  J.nPush = a.uniform ? a.job.nPush : __builtin_amdgcn_readfirstlane(J.nPush);
+  J.serialBase = a.uniform ? a.job.serialBase : J.serialBase;
+  CT_G StageRec* rec = A.rec + job;
   const CT_G TabDesc* T = J.tab;
   CT_G SlotDesc* s = J.slot;
   const int n = T->n, D = T->D, nGran = T->nGran;
@@ -682,7 +821,7 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
     for (int k = 0; k < J.nPush; ++k)
       for (int q = tid; q < D; q += PBLOCK) s->levelDom[(int64_t)(depth + k) * D + q] = last[q];
     if (tid == 0) {
-      rec->run = 0;
+      if (!A.items) rec->run = 0;  // (with lists: no items)
       put_status(J.flags, J.ll, J.seq, J.status_out, ST_OK);
     }
     return;
@@ -700,6 +839,7 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
   if (tid == 0) {
     sh.stray = 0;
     sh.notSub = 0;
+    sh.dirty = 0;
   }
   s_lds_barrier();
   CT_G uint64_t* dinW = (CT_G uint64_t*)(A.jobMem + (int64_t)J.stageOff * 256);  // D: the input
@@ -718,10 +858,31 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
     for (int u = 0; u < PU; ++u) {
       const int q = min(q0 + u * PBLOCK, D - 1);
       if (u == 0 || D > u * PBLOCK) {
-        din[u] = (J.flags & JF_INLINE_DOM) ? a.inl[q] : J.dom_in[q];
+        if (!MODEL) din[u] = (J.flags & JF_INLINE_DOM) ? a.inl[q] : J.dom_in[q];
         wd[u] = words[q];
         ld[u] = last[q];
       }
+    }
+    if (MODEL) {
+      // the table runs if the round before removed a value of one of its
+      // variables (first round: if the pool lacks a value of its domains)
+      int pw[PU];
+      uint64_t pv[PU];
+#pragma unroll
+      for (int u = 0; u < PU; ++u)
+        if (u == 0 || D > u * PBLOCK) pw[u] = ((const CT_G int32_t*)J.dom_in)[min(q0 + u * PBLOCK, D - 1)];
+#pragma unroll
+      for (int u = 0; u < PU; ++u)
+        if (u == 0 || D > u * PBLOCK) {
+          din[u] = M.cur[pw[u]];
+          pv[u] = M.prev[pw[u]];
+        }
+#pragma unroll
+      for (int u = 0; u < PU; ++u)
+        if (u == 0 || D > u * PBLOCK) {
+          if (M.round ? din[u] != pv[u] : (ld[u] & ~din[u]) != 0) sh.dirty = 1;
+          din[u] &= ld[u];
+        }
     }
 #pragma unroll
     for (int u = 0; u < PU; ++u) {
@@ -738,6 +899,10 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
     }
   }
   s_lds_barrier();
+  if (MODEL) {
+    if (!sh.dirty) return;
+    if (tid == 0) atomicAdd((int32_t*)&M.state->props[(job % MODEL_PROPS) * 16], 1);
+  }
   if (tid < WAVE) {
     const int policy = T->policy;
     int nrows = 0, nseg = 0;
@@ -791,6 +956,7 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
       }
       rec->run = 0;
       put_status(J.flags, J.ll, J.seq, J.status_out, status);
+      if (MODEL) M.state->fail = (M.round + 1) << 2 | 2;
     }
     return;
   }
@@ -881,23 +1047,12 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
   R.ct_out = J.ct_out;
   R.status_out = J.status_out;
   R.ll = J.ll;
-  if (J.flags & JF_SOLO) {
-    // a small job: this workgroup runs the rest of it (full barriers: its
-    // waves read each other's list, words and flags)
-    if (tid == 0) {
-      rec->run = 0;
-      rec->trailCount = 0;
-    }
-    __syncthreads();
-    for (int p = s_wave(); p < nGran; p += PWAVES) stage_granule<true>(A, R, &rec->trailCount, p);
-    __syncthreads();
-    R.trailCount = R.trailOn == STAGE_TRAIL_FIRST ? __hip_atomic_load(&rec->trailCount, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-    stage_partition(R, fin);
-    for (int q = 0; q < D; q += PWAVES) {
-      s_lds_barrier();
-      stage_filter<PBLOCK, true>(R, q, PWAVES, fin);
-    }
-    return;
+  if (MODEL) {
+    R.poolMap = (const CT_G int32_t*)J.dom_in;
+    R.poolCur = M.cur;
+    R.poolNext = M.next;
+    R.model = M.state;
+    R.round = M.round;
   }
   if (tid == 0) {
     *rec = R;
@@ -908,7 +1063,7 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
       const int pos = fromRoot || J.ct_out ? nGran : limit;
       const int fw = fin_words(D, A.wide);
       const int nU = (pos + SWAVES - 1) / SWAVES, nF = 1 + (D + fw - 1) / fw;
-      const int l = (int)blockIdx.x % STAGE_LISTS;
+      const int l = job % STAGE_LISTS;
       const unsigned long long at = atomicAdd((unsigned long long*)&A.count->n[l * STAGE_LINE],
                                               (unsigned long long)(uint32_t)nF << 32 | (uint32_t)nU);
       sh.nseg = l * A.uCap + (int)(uint32_t)at;
@@ -920,8 +1075,8 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
   if (!A.items) return;
   s_lds_barrier();
   const int u0 = sh.nseg, f0 = sh.status, nU = sh.size[0], nF = sh.size[1];
-  for (int k = tid; k < nU; k += PBLOCK) A.items[u0 + k] = StageItem{(int32_t)blockIdx.x, k};
-  for (int k = tid; k < nF; k += PBLOCK) A.fItems[f0 + k] = StageItem{(int32_t)blockIdx.x, k};
+  for (int k = tid; k < nU; k += PBLOCK) A.items[u0 + k] = StageItem{job, k};
+  for (int k = tid; k < nF; k += PBLOCK) A.fItems[f0 + k] = StageItem{job, k};
 }
 
 // The lists' items as one sequence: lane l < STAGE_LISTS has the items before
@@ -948,7 +1103,7 @@ __device__ __forceinline__ int item_at(const ItemLists& L, int i, int cap) {
 __global__ void __launch_bounds__(SBLOCK, 8) stage_update_kernel(StageArgs A) {
   if (!A.items) {
     const StageRec R = load_rec(A, 0);
-    if (R.run) stage_granule<false>(A, R, &A.rec->trailCount, (int)blockIdx.x * SWAVES + s_wave());
+    if (R.run) stage_granule(A, R, &A.rec->trailCount, (int)blockIdx.x * SWAVES + s_wave());
     return;
   }
   const ItemLists L = item_lists((int)(uint32_t)A.count->n[min(s_lane(), STAGE_LISTS - 1) * STAGE_LINE]);
@@ -956,7 +1111,7 @@ __global__ void __launch_bounds__(SBLOCK, 8) stage_update_kernel(StageArgs A) {
     A.count->fin[threadIdx.x] = (int32_t)(A.count->n[threadIdx.x * STAGE_LINE] >> 32);
   for (int i = blockIdx.x; i < L.total; i += gridDim.x) {
     const CT_K StageItem* it = (const CT_K StageItem*)A.items + item_at(L, i, A.uCap);
-    stage_granule<false>(A, load_rec(A, it->job), &A.rec[it->job].trailCount, it->chunk * SWAVES + s_wave());
+    stage_granule(A, load_rec(A, it->job), &A.rec[it->job].trailCount, it->chunk * SWAVES + s_wave());
   }
 }
 
@@ -1015,16 +1170,31 @@ bool stage_wide_dom(int D) { return D > FIN_WIDE_D; }
 bool stage_wide(int nGran, int D) { return nGran > FIN_WIDE_GRAN || D > FIN_WIDE_D; }
 int stage_finish_items(int D, int wide) { return 1 + (D + fin_words(D, wide) - 1) / fin_words(D, wide); }
 
-// nJobs jobs (a.jobs, or the one of the arguments); nU / nF: at most this many
-// update and finish items; popGran: granules of the largest table that pops.
-hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int popGran, hipStream_t stream) {
+namespace {
+
+// The prep, update and finish of a.nJobs jobs (a.jobs, or the one of the
+// arguments; MODEL: of a model's round); nU / nF: at most this many update and
+// finish items; popGran: granules of the largest table that pops.
+template <bool MODEL>
+hipError_t launch_steps(const KArgs& a, const StageArgs& A, const ModelRound& M, int nU, int nF, int popGran,
+                        hipStream_t stream, const ModelNeg* neg) {
   const size_t lds = sizeof(int32_t) * (size_t)popGran;
+  const int np = a.nJobs + (MODEL ? M.nHead : 0);
   if (a.nJobs > stage_grid() / 8 && !A.wideDom)
-    hipLaunchKernelGGL(stage_prep_kernel<PBLOCK_MANY>, dim3(a.nJobs), dim3(PBLOCK_MANY), lds, stream, a, A);
+    hipLaunchKernelGGL((stage_prep_kernel<PBLOCK_MANY, MODEL>), dim3(np), dim3(PBLOCK_MANY), lds, stream, a, A, M);
   else
-    hipLaunchKernelGGL(stage_prep_kernel<PMAX>, dim3(a.nJobs), dim3(PMAX), lds, stream, a, A);
-  if (nU > 0) {
-    const int gu = A.items ? std::min(nU, stage_grid()) : nU;
+    hipLaunchKernelGGL((stage_prep_kernel<PMAX, MODEL>), dim3(np), dim3(PMAX), lds, stream, a, A, M);
+  if (MODEL && neg->a.nJobs > 0) {
+    const DevJob* jobs = (const DevJob*)neg->a.jobs;
+    hipLaunchKernelGGL(model_neg_gather_kernel, dim3(neg->a.nJobs), dim3(SBLOCK), 0, stream, jobs, neg->maps, neg->dirty,
+                       M);
+    hipError_t e = launch_propagate(neg->a, std::min(neg->a.nJobs, propagate_max_grid()), stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(model_neg_merge_kernel, dim3(neg->a.nJobs), dim3(SBLOCK), 0, stream, jobs, neg->maps, neg->dirty,
+                       M);
+  }
+  if (nF > 0) {
+    const int gu = A.items ? std::min(std::max(nU, 1), stage_grid()) : nU;
     hipLaunchKernelGGL(stage_update_kernel, dim3(gu), dim3(SBLOCK), 0, stream, A);
     if (A.wide) {
       const int gf = A.items ? std::min(nF, stage_grid() / 4) : nF;
@@ -1035,6 +1205,24 @@ hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int
     }
   }
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int popGran, hipStream_t stream) {
+  return launch_steps<false>(a, A, ModelRound{}, nU, nF, popGran, stream, nullptr);
+}
+
+hipError_t launch_model_start(const ModelRound& M, const uint64_t* poolIn, const int32_t* off,
+                              const uint64_t* const* src, hipStream_t stream) {
+  hipLaunchKernelGGL(model_start_kernel, dim3((8 * M.poolWords + SBLOCK - 1) / SBLOCK), dim3(SBLOCK), 0, stream, poolIn,
+                     (uint64_t*)M.cur, off, src, M.poolWords, (ModelState*)M.state);
+  return hipGetLastError();
+}
+
+hipError_t launch_model_round(const KArgs& a, const StageArgs& A, const ModelRound& M, int nU, int nF,
+                              const ModelNeg& neg, hipStream_t stream) {
+  return launch_steps<true>(a, A, M, nU, nF, 0, stream, &neg);
 }
 
 }  // namespace ctk

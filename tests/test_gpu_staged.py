@@ -191,3 +191,66 @@ def test_staged_batches(names, slots, noalloc):
                 cur[k][s] = None
             elif job["ct_out"] is not None:
                 assert (job["ct_out"] == -1).all(), (step, j, names[k])
+
+
+@pytest.mark.parametrize("n_tables,n_pool,dom,tuples,negatives,hub", [
+    (3, 4, (2, 130), (20, 400), 1, False),
+    (40, 30, (2, 20), (30, 20_000), 6, True),
+    (300, 500, (2, 9), (20, 300), 20, False),     # more tables than compute units
+    (6, 5, (36_000, 36_000), (2000, 4000), 0, True),  # wide domains
+])
+def test_model_rounds(n_tables, n_pool, dom, tuples, negatives, hub):
+    say("model rounds:", n_tables, "tables over", n_pool, "variables, domains", dom, "negatives", negatives, "hub", hub)
+    rng = W.rng_for(n_tables, 932, 0)
+    ds = rng.integers(dom[0], dom[1] + 1, size=n_pool).astype(np.int32)
+    lay = W.DomLayout(ds, np.zeros(n_pool, np.int32))
+    M = ct.Model(np.zeros(n_pool, np.int32), ds)
+    gts, ots, scopes = [], [], []
+    for c in range(n_tables):
+        k = int(rng.integers(2, 4))
+        sc = rng.choice(n_pool, size=k, replace=False).astype(np.int32)
+        if hub and 0 not in sc:
+            sc[0] = 0  # every table has this variable
+        d = ds[sc]
+        t = int(rng.integers(tuples[0], tuples[1] + 1))
+        tup = np.unique(np.stack([rng.integers(0, d[i], size=t) for i in range(k)], 1).astype(np.int32), axis=0)
+        kind = ct.KIND_NEGATIVE if c < negatives else 0
+        if kind:
+            tup = tup[: max(1, int(np.prod(d.astype(np.float64)) // 4))]
+        lo = np.zeros(k, np.int32)
+        gts.append(ct.Table(tup, lo, d, kind=kind))
+        ots.append(O.OracleTable(tup, lo, d, kind=kind, fast=kind == 0))
+        M.add(gts[-1], sc)
+        scopes.append(sc)
+    out = torch.zeros(lay.D, dtype=torch.int64, device="cuda")
+    pool, stack, total = lay.full(), [], 0
+    for step in range(9):
+        if stack and step % 4 == 3:
+            for _ in range(int(rng.integers(1, len(stack) + 1))):
+                M.pop()
+                for o in ots:
+                    o.pop()
+                pool = stack.pop()
+        for _ in range(2 if step % 3 == 1 else 1):
+            M.push()
+            for o in ots:
+                o.push()
+            stack.append(pool.copy())
+        new = pool if step == 0 else W.pick_fraction_removal(rng, lay, pool, frac=0.02 if step % 2 else 0.3)
+        st, props, rounds = M.fixpoint(torch.from_numpy(new.view(np.int64).copy()).cuda(), out)
+        os_, opool, _ = O.fixpoint(ots, scopes, lay, new)
+        assert st == os_, step
+        assert props >= 0 and rounds >= 1
+        total += props
+        if st == ct.OK:
+            pool = out.cpu().numpy().view(np.uint64).copy()
+            assert (pool == opool).all(), step
+            for c in range(0, n_tables, max(1, n_tables // 5)):  # (waits for the model's stream)
+                assert (gts[c].state()[0] == ots[c].state()[0]).all(), (step, c)
+                assert (gts[c].state()[1] == ots[c].state()[1]).all(), (step, c)
+        else:
+            M.pop()
+            for o in ots:
+                o.pop()
+            pool = stack.pop()
+    assert total > 0

@@ -1255,7 +1255,8 @@ __device__ int neg_filter(const DevJob& J, Shared& sh, int st, int* rows2) {
     }
     __syncthreads();
     const CT_G int32_t* idx = s->idx[s->cur];
-    for (int p = threadIdx.x; p < sh.limit; p += BLOCK) sh.gidx[p] = (uint16_t)idx[p];
+    // (all of it: the partition copies the inactive part too)
+    for (int p = threadIdx.x; p < T->nGran; p += BLOCK) sh.gidx[p] = (uint16_t)idx[p];
     __syncthreads();
   }
   *rows2 = total;

@@ -37,6 +37,9 @@ TABLES = {
     "3,073 words": ([64 * 3000, 64 * 72 + 1], 5000, 0.0, 0, ct.BRANCH_INCREMENTAL),
     "selected bits": ([36000, 38000], 5000, 0.0, 0, ct.BRANCH_RESET),
     "negative": ([6, 8, 7, 5], 900, 0.0, ct.KIND_NEGATIVE, ct.BRANCH_AUTO),
+    # most combinations forbidden: values go, in one to five passes of granules
+    "negative, 5 granules": ([3, 2, 4000], 40000, 0.0, ct.KIND_NEGATIVE, ct.BRANCH_AUTO),
+    "negative, 1 word": ([63], 62, 0.0, ct.KIND_NEGATIVE, ct.BRANCH_AUTO),
 }
 
 

@@ -152,6 +152,8 @@ __device__ __forceinline__ int wave_scan_incl(int v) {
   return v;
 }
 
+__device__ __forceinline__ int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_scan_incl(v), WAVE - 1); }
+
 // Exclusive prefix sum over the block; *total receives the sum.
 // (LDS_ONLY: its barriers order LDS only, so global stores still in flight
 // need not complete there)
@@ -1147,34 +1149,57 @@ __device__ __forceinline__ void do_filter(const KArgs& a, const DevJob& J, int c
 }
 
 // ---------------------------------------------------------------------------
-// filterDomains of a negative table for domain word q (one wave; whole job
-// in one workgroup).  currTable holds the forbidden tuples whose values are
-// all in the input domains; value a of x_i has an allowed tuple iff fewer
-// than prod_{k != i} |dom(x_k)| (sh.dcnt[i], capped above the tuple count)
-// of them have x_i = a.  Each lane counts its value's row against the
-// active granules (currTable words are the same for every lane).  Returns
-// the filtered word.
+// filterDomains of a negative table (whole job in one workgroup).  currTable
+// holds the forbidden tuples whose values are all in the input domains; value
+// a of x_i has an allowed tuple iff fewer than prod_{k != i} |dom(x_k)|
+// (sh.dcnt[i], capped above the tuple count) of them have x_i = a.
+// sh.rows[0 .. total) lists the values to count (domain word << 6 | bit); a
+// wave counts NEG_VALS of them, a granule's words of each in one coalesced
+// load, and clears those without an allowed tuple from sh.dout.  (One lane per
+// value, walking its row, read 64 rows a load: 12,000 tuples, 5 variables of
+// 8 values, 28 us a call against 22.)
 // ---------------------------------------------------------------------------
-__device__ uint64_t neg_filter_word(const DevJob& J, int q, int lim, const CT_G int32_t* idx, const Shared& sh) {
+constexpr int NEG_VALS = 4, NEG_GRAN = 4;  // values per wave, granules in flight
+__device__ void neg_count(const DevJob& J, int total, int lim, const CT_G int32_t* idx, Shared& sh) {
   const TabDesc* T = J.tab;
   const CT_G uint64_t* ct = J.slot->ct;
-  const int i = T->wordVar[q];
-  const VarDesc v = T->vars[i];
-  const uint64_t din = sh.din[q];
-  const int64_t prod = sh.dcnt[i];
-  // no count can reach the product: every value keeps an allowed tuple
-  if (din == 0ull || prod > (int64_t)lim * GW * 64) return din;
+  const CT_G uint64_t* S = T->S;
+  const int64_t stride = T->stride;
   const int lane = lane_id();
-  const bool present = (din >> lane) & 1ull;
-  const int row = v.rowStart + (q - v.domOff) * 64 + (present ? lane : 0);
-  const CT_G uint64_t* srow = T->S + (int64_t)row * T->stride;
-  int64_t cnt = 0;
-  for (int p = 0; p < lim; ++p) {
-    const int64_t base = (int64_t)idx[p] * GW;
-#pragma unroll 8
-    for (int k = 0; k < GW; ++k) cnt += __popcll(ct[base + k] & srow[base + k]);
+  for (int k0 = wave_id() * NEG_VALS; k0 < total; k0 += WAVES * NEG_VALS) {
+    uint32_t val[NEG_VALS];
+    int row[NEG_VALS], var[NEG_VALS], cnt[NEG_VALS];
+#pragma unroll
+    for (int k = 0; k < NEG_VALS; ++k) {
+      val[k] = __builtin_amdgcn_readfirstlane(sh.rows[min(k0 + k, total - 1)]);
+      const int q = (int)(val[k] >> 6);
+      var[k] = T->wordVar[q];
+      const VarDesc v = T->vars[var[k]];
+      row[k] = v.rowStart + (q - v.domOff) * 64 + (int)(val[k] & 63u);
+      cnt[k] = 0;
+    }
+    for (int p0 = 0; p0 < lim; p0 += NEG_GRAN) {
+      uint64_t c[NEG_GRAN], x[NEG_VALS][NEG_GRAN];
+#pragma unroll
+      for (int j = 0; j < NEG_GRAN; ++j) {
+        const int64_t w = (int64_t)idx[min(p0 + j, lim - 1)] * GW + lane;
+        const uint64_t y = ct[w];
+        c[j] = p0 + j < lim ? y : 0ull;
+#pragma unroll
+        for (int k = 0; k < NEG_VALS; ++k) x[k][j] = S[(int64_t)row[k] * stride + w];
+      }
+#pragma unroll
+      for (int k = 0; k < NEG_VALS; ++k)
+#pragma unroll
+        for (int j = 0; j < NEG_GRAN; ++j) cnt[k] += __popcll(c[j] & x[k][j]);
+    }
+#pragma unroll
+    for (int k = 0; k < NEG_VALS; ++k) {
+      const int sum = wave_sum(cnt[k]);
+      if (lane == 0 && k0 + k < total && sum == sh.dcnt[var[k]])
+        atomicAnd((unsigned long long*)&sh.dout[val[k] >> 6], ~(1ull << (val[k] & 63u)));
+    }
   }
-  return din & ~__ballot(present && cnt == prod);
 }
 
 // A negative table's filterDomains in one workgroup, after updateTable and
@@ -1200,13 +1225,30 @@ __device__ int neg_filter(const DevJob& J, Shared& sh, int st, int* rows2) {
   }
   if (threadIdx.x == 0) sh.bad_sub = 0;
   __syncthreads();
+  const int per = (D + BLOCK - 1) / BLOCK;
+  const int b = min((int)threadIdx.x * per, D), e = min(b + per, D);
   {
+    // the values whose count can reach their product
     const int lim = s->limit;
-    const CT_G int32_t* idx = s->idx[s->cur];
-    for (int q = wave_id(); q < D; q += WAVES) {
-      const uint64_t dout = sh.noop ? sh.din[q] : neg_filter_word(J, q, lim, idx, sh);
-      if (lane_id() == 0) sh.dout[q] = dout;
+    const int64_t most = (int64_t)lim * GW * 64;
+    int cnt = 0;
+    for (int q = b; q < e; ++q) {
+      const uint64_t din = sh.din[q];
+      sh.dout[q] = din;
+      cnt += sh.noop || sh.dcnt[T->wordVar[q]] > most ? 0 : __popcll(din);
     }
+    int total = 0;
+    int off = block_scan_excl(cnt, &total, sh);
+    for (int q = b; q < e; ++q) {
+      uint64_t bits = sh.noop || sh.dcnt[T->wordVar[q]] > most ? 0ull : sh.din[q];
+      while (bits) {
+        const int k = __ffsll((unsigned long long)bits) - 1;
+        bits &= bits - 1;
+        sh.rows[off++] = (uint32_t)(q << 6 | k);
+      }
+    }
+    __syncthreads();
+    neg_count(J, total, lim, s->idx[s->cur], sh);
   }
   __syncthreads();
   for (int i = threadIdx.x; i < n; i += BLOCK) {
@@ -1224,8 +1266,6 @@ __device__ int neg_filter(const DevJob& J, Shared& sh, int st, int* rows2) {
     return ST_FAIL;
   }
   if (sh.noop) return ST_OK;
-  const int per = (D + BLOCK - 1) / BLOCK;
-  const int b = min((int)threadIdx.x * per, D), e = min(b + per, D);
   int cnt = 0;
   for (int q = b; q < e; ++q) cnt += __popcll(sh.din[q] & ~sh.dout[q]);
   int total = 0;
@@ -1303,8 +1343,14 @@ __device__ __forceinline__ void do_solo(const KArgs& a, const DevJob& J0, Shared
     const TabDesc* T = J.tab;
     if (st == ST_OK) {
       for (int q = threadIdx.x; q < T->D; q += BLOCK) {
-        J0.dom_out[q] = sh.dout[q];
-        s->lastDom[q] = sh.dout[q];
+        const uint64_t dout = sh.dout[q];
+        if (J0.flags & JF_LL) {
+          ll_put(J0.ll + 2 + 2 * q, eng_slot((uint32_t)dout, (uint32_t)J0.seq));
+          ll_put(J0.ll + 3 + 2 * q, eng_slot((uint32_t)(dout >> 32), (uint32_t)J0.seq));
+        } else {
+          J0.dom_out[q] = dout;
+        }
+        s->lastDom[q] = dout;
       }
     }
     if (J0.ct_out && (st == ST_OK || st == ST_FAIL))
@@ -1318,8 +1364,9 @@ __device__ __forceinline__ void do_solo(const KArgs& a, const DevJob& J0, Shared
     add_filter_stats(s, cnt);
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    status_fence(J);
+  // (a flagged call's success is its domain words)
+  if (threadIdx.x == 0 && !(st == ST_OK && (J.flags & JF_LL))) {
+    if (!(J.flags & JF_LL)) status_fence(J);
     publish_status(J, st);
   }
 }

@@ -507,9 +507,9 @@ int run_single(ct_table* T, DevJob& J, const uint64_t* dom_in_host) {
     A.items = nullptr;  // one job: its items by workgroup
     J.listCap = stage_list_cap(T);
   }
-  // a split propagation answers through flagged slots (no currTable copy:
-  // that one keeps the fenced, counted status)
-  const bool ll = (J.flags & JF_PROPAGATE) && !(J.flags & JF_SOLO) && (staged || !J.ct_out) && T->pLL;
+  // a propagation answers through flagged slots (not staged, with a currTable
+  // copy: that one keeps the fenced status)
+  const bool ll = (J.flags & JF_PROPAGATE) && (staged || !J.ct_out) && T->pLL;
   uint32_t sq = 0;
   if (ll) {
     J.flags |= JF_LL;

@@ -267,6 +267,22 @@ struct NodesDesc {
   CT_G uint64_t* nz;         // parts x (groups x 8) x nGran: nodes with a non-zero word there
 };
 
+// Arguments of the support build: nw words of 64 tuples from word w0, whose
+// cells begin at tuples.
+struct BuildArgs {
+  const int32_t* tuples;
+  int64_t w0, nw, t, W;
+  int32_t n, empty;         // empty: a variable of dom0 has no value
+  const VarDesc* vars;
+  const int32_t* lo;
+  const uint64_t* dom0;
+  uint64_t* S;
+  int64_t stride;
+  uint64_t* ct;             // null: not wanted; else the root's currTable words
+  int32_t* nz;              //   and the granules with one that is not zero
+  int32_t* star;            // set if a star cell is seen
+};
+
 // Batch of roots recomputed from scratch: one task per workgroup of the
 // stream kernel, (job, first granule) pairs, each covering WAVES consecutive
 // granules of the job (one per wave), largest tables first.

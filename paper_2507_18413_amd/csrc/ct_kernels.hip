@@ -1873,46 +1873,177 @@ __global__ void __launch_bounds__(BLOCK) split_engine_kernel(EngDesc E) {
 // support bitset builder: one wave per 64 tuples (one word column); for each
 // column of the table every distinct row among the wave's lanes is written
 // once with the ballot of the lanes holding that value (no atomics, each
-// (row, word) has exactly one writer).  S must be zeroed beforehand.
+// (row, word) has exactly one writer).  S must be zeroed beforehand.  A tuple
+// all of whose values are in dom0 is valid at the root: the ballot of those is
+// the root's currTable word.
+// The cells come from pinned host memory: a wave reads its 64 tuples in
+// coalesced 16-byte loads, once, into LDS (BUILD_COLS columns at a time), and
+// takes the columns from there.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(BLOCK) build_supports_kernel(const int32_t* tuples, int64_t t,
-                                                               int n, const VarDesc* vars,
-                                                               const int32_t* lo, uint64_t* S,
-                                                               int64_t stride, int64_t W) {
-  const int64_t w = (int64_t)blockIdx.x * WAVES + wave_id();
-  if (w >= W) return;
+constexpr int BUILD_COLS = 64;
+__global__ void __launch_bounds__(BLOCK) build_supports_kernel(BuildArgs B) {
+  extern __shared__ int32_t cells[];
   const int lane = lane_id();
-  const int64_t j = w * 64 + lane;
-  for (int i = 0; i < n; ++i) {
-    const VarDesc v = vars[i];
-    int r = -1;
-    bool star = false;
-    if (j < t) {
-      const int32_t raw = tuples[j * n + i];
-      star = raw == STAR_CELL;
-      const int64_t val = (int64_t)raw - lo[i];
-      if (!star && val >= 0 && val < v.dsize) r = v.rowStart + (int)val;
-    }
-    // a star cell (short table) is in every row of its column: each row
-    // word is the ballot of its lanes or'ed with the star lanes, written once
-    const unsigned long long starMask = __ballot(star);
-    if (starMask) {
-      for (int k = 0; k < v.dsize; ++k) {
-        const unsigned long long m = __ballot(r == v.rowStart + k) | starMask;
-        if (lane == 0) S[(int64_t)(v.rowStart + k) * stride + w] = m;
+  const int wv = __builtin_amdgcn_readfirstlane(wave_id());
+  const int64_t w = B.w0 + (int64_t)blockIdx.x * (blockDim.x / WAVE) + wv;
+  if (w >= B.w0 + B.nw) return;
+  const int n = B.n;
+  const CT_G int32_t* src = (const CT_G int32_t*)B.tuples + (w - B.w0) * 64 * n;
+  const int cnt = (int)min((int64_t)64, B.t - w * 64);
+  const int cols = min(n, BUILD_COLS), pitch = cols | 1;
+  int32_t* my = cells + wv * 64 * pitch;
+  bool valid = lane < cnt && !B.empty, starred = false;
+  for (int c0 = 0; c0 < n; c0 += BUILD_COLS) {
+    const int tc = min(n - c0, BUILD_COLS);
+    if (tc == n) {
+      // (16-byte loads: the word's cells begin at a multiple of 256 bytes, and
+      // the buffer is longer than the last one reads)
+      const int total = cnt * n;
+      constexpr int BU = 4;  // loads in flight
+      for (int b0 = 0; b0 < total; b0 += BU * WAVE * 4) {
+        int4 x[BU];
+#pragma unroll
+        for (int u = 0; u < BU; ++u) {
+          const int e0 = b0 + u * WAVE * 4 + lane * 4;
+          x[u] = *(const CT_G int4*)(src + (e0 < total ? e0 : 0));
+        }
+#pragma unroll
+        for (int u = 0; u < BU; ++u) {
+          const int v[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const uint32_t e = (uint32_t)(b0 + u * WAVE * 4 + lane * 4 + k), j = e / (uint32_t)n;
+            if ((int)e < total) my[j * pitch + (e - j * n)] = v[k];
+          }
+        }
       }
-      continue;
+    } else {
+#pragma unroll 8
+      for (int j = 0; j < cnt; ++j)
+        if (lane < tc) my[j * pitch + lane] = src[j * n + c0 + lane];
     }
-    bool pending = r >= 0;
-    for (;;) {
-      const unsigned long long act = __ballot(pending);
-      if (!act) break;
-      const int leader = __ffsll(act) - 1;
-      const int rl = __shfl(r, leader);
-      const unsigned long long mask = __ballot(pending && r == rl);
-      if (lane == leader) S[(int64_t)rl * stride + w] = mask;
-      if (r == rl) pending = false;
+    // the wave's own LDS traffic is in order: nothing but the compiler to stop
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int i = 0; i < tc; ++i) {
+      const VarDesc v = B.vars[c0 + i];
+      int r = -1;
+      bool star = false;
+      if (lane < cnt) {
+        const int32_t raw = my[lane * pitch + i];
+        star = raw == STAR_CELL;
+        const int64_t val = (int64_t)raw - B.lo[c0 + i];
+        if (!star) {
+          const bool in = val >= 0 && val < v.dsize;
+          if (in) r = v.rowStart + (int)val;
+          const int a = in ? (int)val : 0;
+          valid = valid && in && ((B.dom0[v.domOff + (a >> 6)] >> (a & 63)) & 1ull);
+        }
+      }
+      // a star cell (short table) is in every row of its column: each row
+      // word is the ballot of its lanes or'ed with the star lanes, written once
+      const unsigned long long starMask = __ballot(star);
+      if (starMask) {
+        starred = true;
+        for (int k = 0; k < v.dsize; ++k) {
+          const unsigned long long m = __ballot(r == v.rowStart + k) | starMask;
+          if (lane == 0) B.S[(int64_t)(v.rowStart + k) * B.stride + w] = m;
+        }
+        continue;
+      }
+      bool pending = r >= 0;
+      for (;;) {
+        const unsigned long long act = __ballot(pending);
+        if (!act) break;
+        const int leader = __ffsll(act) - 1;
+        const int rl = __shfl(r, leader);
+        const unsigned long long mask = __ballot(pending && r == rl);
+        if (lane == leader) B.S[(int64_t)rl * B.stride + w] = mask;
+        if (r == rl) pending = false;
+      }
     }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  const unsigned long long m = __ballot(valid);
+  if (lane == 0) {
+    if (starred) *B.star = 1;
+    if (B.ct) {
+      B.ct[w] = m;
+      if (m) B.nz[w / GW] = 1;
+    }
+  }
+}
+
+// The root slot before its propagation: no tuple (a negative table: all of
+// them), every granule active, the domains dom0.
+__global__ void __launch_bounds__(BLOCK) init_root_kernel(TabDesc* T, SlotDesc* root, const uint64_t* dom0) {
+  const int64_t at = (int64_t)blockIdx.x * BLOCK + threadIdx.x, step = (int64_t)gridDim.x * BLOCK;
+  for (int64_t w = at; w < T->stride; w += step) root->ct[w] = T->kind ? all_tuples_word(T, w) : 0ull;
+  for (int64_t p = at; p < T->nGran; p += step) {
+    root->idx[0][p] = (int32_t)p;
+    root->idx[1][p] = (int32_t)p;
+    root->stamp[p] = 0;
+    root->nzFlag[p] = 0;
+  }
+  for (int64_t q = at; q < T->D; q += step) root->lastDom[q] = dom0[q];
+  for (int64_t r = at; r < T->rows; r += step) root->res[r] = 0;
+}
+
+// a slot's state at the root, but its arrays
+__device__ void slot_fresh(SlotDesc* s, int limit, int failed) {
+  s->trailTop = 0;
+  s->cur = 0;
+  s->limit = limit;
+  s->failed = failed;
+  s->depth = 0;
+  s->serial = 0;
+  s->filtCount = 0;
+  s->prepDone = 0;
+  s->updDone = 0;
+  s->status = 0;
+  s->nzCount = 0;
+  s->pad2 = 0;
+  for (int x = 0; x < 8; ++x) s->stats[x] = 0;
+}
+
+// After the root propagation: the table's first slot takes the root state, and
+// the table's descriptor what was not known before.  A failed root keeps dom0
+// as its domains and no valid tuple.  out (host memory): status, star.
+__global__ void __launch_bounds__(BLOCK) init_first_kernel(TabDesc* T, SlotDesc* s, SlotDesc* root, const uint64_t* dom0,
+                                                           const int32_t* star, int32_t* out) {
+  const bool failed = root->status == ST_FAIL;
+  const CT_G int32_t* idx = root->idx[root->cur];
+  const int limit = failed ? 0 : root->limit;
+  const int64_t at = (int64_t)blockIdx.x * BLOCK + threadIdx.x, step = (int64_t)gridDim.x * BLOCK;
+  for (int64_t w = at; w < T->stride; w += step) {
+    const uint64_t x = failed ? 0ull : root->ct[w];
+    if (failed) root->ct[w] = 0ull;
+    s->ct[w] = x;
+  }
+  for (int64_t p = at; p < T->nGran; p += step) {
+    const int g = idx[p];
+    s->idx[0][p] = g;
+    s->idx[1][p] = g;
+    s->stamp[p] = 0;
+    s->nzFlag[p] = 0;
+  }
+  for (int64_t q = at; q < T->D; q += step) {
+    const uint64_t x = failed ? dom0[q] : root->lastDom[q];
+    if (failed) root->lastDom[q] = x;
+    s->lastDom[q] = x;
+  }
+  for (int64_t r = at; r < T->rows; r += step) s->res[r] = root->res[r];
+  if (at == 0) {
+    slot_fresh(s, limit, failed);
+    T->idx0 = idx;
+    T->limit0 = limit;
+    T->rootFailed = failed;
+    if (*star) T->policy = 1;  // a short table: reset
+    out[0] = root->status;
+    out[1] = *star;
   }
 }
 
@@ -1933,19 +2064,7 @@ __global__ void __launch_bounds__(BLOCK) init_slots_kernel(const TabDesc* T, Slo
   for (int q = threadIdx.x; q < T->D; q += BLOCK) s->lastDom[q] = T->dom0[q];
   for (int r = threadIdx.x; r < T->rows; r += BLOCK) s->res[r] = rootRes[r];
   if (threadIdx.x == 0) {
-    s->trailTop = 0;
-    s->cur = 0;
-    s->limit = T->limit0;
-    s->failed = T->rootFailed;
-    s->depth = 0;
-    s->serial = 0;
-    s->filtCount = 0;
-    s->prepDone = 0;
-    s->updDone = 0;
-    s->status = 0;
-    s->nzCount = 0;
-    s->pad2 = 0;
-    for (int x = 0; x < 8; ++x) s->stats[x] = 0;
+    slot_fresh(s, T->limit0, T->rootFailed);
   }
 }
 
@@ -1986,13 +2105,27 @@ hipError_t launch_propagate(const KArgs& a, int grid, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_build_supports(const int32_t* tuples, int64_t t, int n, const VarDesc* vars,
-                                 const int32_t* lo, uint64_t* S, int64_t stride, int64_t W,
-                                 hipStream_t stream) {
-  if (W <= 0) return hipSuccess;
-  const int64_t blocks = (W + WAVES - 1) / WAVES;
-  hipLaunchKernelGGL(build_supports_kernel, dim3((unsigned)blocks), dim3(BLOCK), 0, stream, tuples,
-                     t, n, vars, lo, S, stride, W);
+hipError_t launch_build_supports(const BuildArgs& B, hipStream_t stream) {
+  if (B.nw <= 0) return hipSuccess;
+  // as many waves of a workgroup as 32 KB of cells take
+  const int perWave = 64 * (std::min(B.n, BUILD_COLS) | 1) * (int)sizeof(int32_t);
+  const int waves = std::max(1, std::min(WAVES, 32768 / perWave));
+  hipLaunchKernelGGL(build_supports_kernel, dim3((unsigned)((B.nw + waves - 1) / waves)), dim3(waves * WAVE),
+                     (size_t)waves * perWave, stream, B);
+  return hipGetLastError();
+}
+
+// workgroups of a table's initialization kernels
+static int init_grid(int64_t words) { return (int)std::max<int64_t>(1, std::min<int64_t>(256, words / BLOCK)); }
+
+hipError_t launch_init_root(TabDesc* T, SlotDesc* root, const uint64_t* dom0, int64_t words, hipStream_t stream) {
+  hipLaunchKernelGGL(init_root_kernel, dim3(init_grid(words)), dim3(BLOCK), 0, stream, T, root, dom0);
+  return hipGetLastError();
+}
+
+hipError_t launch_init_first(TabDesc* T, SlotDesc* slot, SlotDesc* root, const uint64_t* dom0, const int32_t* star,
+                             int32_t* out, int64_t words, hipStream_t stream) {
+  hipLaunchKernelGGL(init_first_kernel, dim3(init_grid(words)), dim3(BLOCK), 0, stream, T, slot, root, dom0, star, out);
   return hipGetLastError();
 }
 

@@ -17,6 +17,8 @@
 #include <mutex>
 #include <set>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 #include "ct.h"
@@ -46,9 +48,11 @@ hipError_t launch_nodes(NodesDesc N, char* scratch, hipStream_t stream);
 hipError_t launch_roots(const KArgs& a, const RootDesc& R, hipStream_t stream);
 hipError_t noalloc_scratch(char** ptr, size_t* bytes);
 hipError_t launch_noalloc_reset(int32_t* q, int32_t* counts, hipStream_t stream);
-hipError_t launch_build_supports(const int32_t* tuples, int64_t t, int n, const VarDesc* vars,
-                                 const int32_t* lo, uint64_t* S, int64_t stride, int64_t W,
-                                 hipStream_t stream);
+hipError_t launch_build_supports(const BuildArgs& B, hipStream_t stream);
+hipError_t launch_init_root(TabDesc* T, SlotDesc* root, const uint64_t* dom0, int64_t words, hipStream_t stream);
+hipError_t launch_init_first(TabDesc* T, SlotDesc* slot, SlotDesc* root, const uint64_t* dom0, const int32_t* star,
+                             int32_t* out, int64_t words, hipStream_t stream);
+hipError_t launch_staged_finish(const StageArgs& A, int nF, hipStream_t stream);
 hipError_t launch_init_slots(const TabDesc* T, SlotDesc* slots, int n, const int32_t* rootRes,
                              hipStream_t stream);
 }  // namespace ctk
@@ -122,6 +126,7 @@ struct DevBlock {
 
 // Device queue + staging for one stream.
 struct QueueCtx {
+  bool own = true;            // queue and hostErr are allocations of their own
   int32_t* queue = nullptr;   // on the device: [3] error word
   int32_t* hostErr = nullptr; // pinned
   // batch staging: job descriptors, then (256-byte aligned) root tasks, sent
@@ -155,8 +160,8 @@ int queue_init(QueueCtx& q) {
 }
 
 void queue_free(QueueCtx& q) {
-  if (q.queue) (void)hipFree(q.queue);
-  if (q.hostErr) (void)hipHostFree(q.hostErr);
+  if (q.own && q.queue) (void)hipFree(q.queue);
+  if (q.own && q.hostErr) (void)hipHostFree(q.hostErr);
   if (q.dStage) (void)hipFree(q.dStage);
   for (int k = 0; k < 2; ++k) {
     if (q.pStage[k]) (void)hipHostFree(q.pStage[k]);
@@ -217,7 +222,8 @@ struct ct_table {
   uint16_t* dIds = nullptr;
   std::vector<void*> blocks;  // device allocations to free
   QueueCtx q;
-  // pinned staging of the synchronous calls
+  // pinned staging of the synchronous calls, parts of one block
+  char* pBlock = nullptr;
   uint64_t* pDomOut = nullptr;  // D words
   uint64_t* pLL = nullptr;      // result slots of flagged synchronous jobs (2 + 2D)
   uint64_t* pDomIn = nullptr;   // D words (used when D > INLINE_WORDS)
@@ -296,7 +302,7 @@ int alloc_slots(ct_table* T, int n, int maxDepth, SlotDesc** dSlots, std::vector
     s.trailCap = trailCap;
     s.maxDepth = maxDepth;
   }
-  HIPCHK(hipMemcpy(base, h.data(), sizeof(SlotDesc) * n, hipMemcpyHostToDevice));
+  HIPCHK(hipMemcpyAsync(base, h.data(), sizeof(SlotDesc) * n, hipMemcpyHostToDevice, T->stream));
   return CT_OK;
 }
 
@@ -1055,6 +1061,160 @@ BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool
   return B;
 }
 
+// Host mirrors of n fresh slots in the root state.
+void slots_add(ct_table* T, SlotDesc* d, int n, int max_depth) {
+  for (int k = 0; k < n; ++k) {
+    SlotHost s;
+    s.dev = d + k;
+    s.maxDepth = max_depth;
+    s.capDepth = max_depth;
+    s.failed = T->rootFailed ? 1 : 0;
+    // a push never grows this vector past its capacity (no allocation per push)
+    s.failedAt.reserve(max_depth);
+    T->slots.push_back(s);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Upload of a table's tuples.  The caller's array is pageable: up to UP_WORKERS
+// threads copy it, a chunk each, into a window of pinned memory, which the
+// support build reads where it is (each tuple once) while they fill the other
+// window: copies and builds overlap and no device copy of the tuples exists.
+// Creating a table of 1,000,000 tuples of 6 columns (24 MB): 1.2 ms, of which
+// the builds take 0.7 at 37 GB/s of the bus, against 3.65 ms with a pass over
+// the cells (1.2), a copy and transfer by one thread (1.25), a device copy to
+// allocate and free (0.4) and 24 small copies (0.8).  Chunks of 1/4 MiB 1.5 ms.
+// ---------------------------------------------------------------------------
+constexpr size_t UP_CHUNK = (size_t)1 << 20;       // bytes of a worker's part of a window
+constexpr int UP_WORKERS = 4, UP_KEEP = 2;
+constexpr size_t UP_PER_WORKER = (size_t)2 << 20;  // tuples' bytes for each further worker
+
+// Two windows in one pinned block.
+struct UploadBuf {
+  int dev = 0;
+  size_t window = 0;  // bytes of a window (its reads may pass its end by 16)
+  char* p = nullptr;
+  hipEvent_t ev[2] = {nullptr, nullptr};
+};
+
+// Free blocks, at most UP_KEEP; given back with the last table.
+std::mutex g_upMu;
+std::vector<UploadBuf*> g_upFree;
+
+void upload_free(UploadBuf* b) {
+  if (b->p) (void)hipHostFree(b->p);
+  for (hipEvent_t e : b->ev)
+    if (e) (void)hipEventDestroy(e);
+  delete b;
+}
+
+void upload_drain() {
+  std::lock_guard<std::mutex> lk(g_upMu);
+  for (UploadBuf* b : g_upFree) upload_free(b);
+  g_upFree.clear();
+}
+
+void upload_give(UploadBuf* b) {
+  if (!b) return;
+  std::lock_guard<std::mutex> lk(g_upMu);
+  if ((int)g_upFree.size() < UP_KEEP) g_upFree.push_back(b);
+  else upload_free(b);
+}
+
+int upload_take(int dev, size_t window, UploadBuf** out) {
+  if (alloc_injected()) return fail(CT_E_NOMEM, "injected allocation failure: upload block");
+  {
+    std::lock_guard<std::mutex> lk(g_upMu);
+    for (size_t k = 0; k < g_upFree.size(); ++k)
+      if (g_upFree[k]->dev == dev && g_upFree[k]->window >= window) {
+        *out = g_upFree[k];
+        g_upFree.erase(g_upFree.begin() + k);
+        return CT_OK;
+      }
+  }
+  UploadBuf* b = new (std::nothrow) UploadBuf();
+  if (!b) return fail(CT_E_NOMEM, "host allocation failed");
+  b->dev = dev;
+  b->window = (window + 255) & ~(size_t)255;
+  hipError_t e = hipHostMalloc((void**)&b->p, 2 * b->window + 256, hipHostMallocDefault);
+  for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&b->ev[k], hipEventDisableTiming);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    upload_free(b);
+    return fail(CT_E_NOMEM, "upload block: %s", hipGetErrorString(e));
+  }
+  *out = b;
+  return CT_OK;
+}
+
+// Words of 64 tuples in a worker's chunk, and the workers for a table.
+int64_t upload_chunk_words(int n) { return std::max<int64_t>(1, (int64_t)(UP_CHUNK / (sizeof(int32_t) * 64 * (size_t)n))); }
+int upload_workers(int64_t W, int n) {
+  const size_t bytes = sizeof(int32_t) * 64 * (size_t)n * (size_t)W;
+  return (int)std::min<size_t>(UP_WORKERS, 1 + bytes / UP_PER_WORKER);
+}
+size_t upload_window(int64_t W, int n) {
+  const int64_t words = std::min(W, upload_chunk_words(n) * upload_workers(W, n));
+  return sizeof(int32_t) * 64 * (size_t)n * (size_t)words;
+}
+
+// Queues the support build of all tuples on the stream (B: the kernel's
+// arguments but the window).  b must stay until the stream has ended.
+hipError_t upload_run(const int32_t* tuples, BuildArgs B, hipStream_t stream, const UploadBuf* b) {
+  const int64_t chunk = upload_chunk_words(B.n);
+  const int nW = upload_workers(B.W, B.n);
+  const int64_t per = chunk * nW, windows = (B.W + per - 1) / per;
+  std::atomic<int64_t> released{2};              // windows that may be filled
+  std::atomic<int> arrived[2] = {{0}, {0}};      // workers done with a window
+  std::atomic<bool> stop{false};
+  auto copy = [&](int id, int64_t win) {         // worker id's part of a window
+    const int64_t w0 = win * per + id * chunk, j0 = w0 * 64;
+    const int64_t j1 = std::min(B.t, std::min(w0 + chunk, (win + 1) * per) * 64);
+    if (j0 < j1)
+      memcpy(b->p + (win & 1) * b->window + sizeof(int32_t) * (size_t)(id * chunk * 64) * B.n, tuples + j0 * B.n,
+             sizeof(int32_t) * (size_t)(j1 - j0) * B.n);
+  };
+  auto work = [&](int id) {
+    for (int64_t win = 0; win < windows; ++win) {
+      while (released.load(std::memory_order_acquire) <= win) {
+        if (stop.load()) return;
+        std::this_thread::yield();
+      }
+      copy(id, win);
+      arrived[win & 1].fetch_add(1, std::memory_order_release);
+    }
+  };
+  std::thread th[UP_WORKERS];
+  int started = 1;
+  try {
+    for (; started < nW; ++started) th[started] = std::thread(work, started);
+  } catch (const std::system_error&) {
+    // fewer threads: their parts are copied here
+  }
+  char* dp = nullptr;
+  hipError_t e = hipHostGetDevicePointer((void**)&dp, b->p, 0);
+  for (int64_t win = 0; win < windows && e == hipSuccess; ++win) {
+    const int k = (int)(win & 1);
+    if (win >= 2) {
+      e = hipEventSynchronize(b->ev[k]);
+      if (e != hipSuccess) break;
+      released.store(win + 1, std::memory_order_release);
+    }
+    copy(0, win);
+    for (int id = started; id < nW; ++id) copy(id, win);
+    while (arrived[k].load(std::memory_order_acquire) < started - 1) std::this_thread::yield();
+    arrived[k].store(0, std::memory_order_relaxed);
+    B.tuples = (const int32_t*)(dp + k * b->window);
+    B.w0 = win * per;
+    B.nw = std::min(per, B.W - B.w0);
+    e = launch_build_supports(B, stream);
+    if (e == hipSuccess) e = hipEventRecord(b->ev[k], stream);
+  }
+  stop.store(true);
+  for (int id = 1; id < started; ++id) th[id].join();
+  return e;
+}
+
 }  // namespace
 
 // ===========================================================================
@@ -1074,21 +1234,21 @@ int ct_quiesce(void) {
 void ct_destroy(ct_table* T) {
   if (!T) return;
   (void)quiesce(T);
+  bool last = false;
   {
     std::lock_guard<std::mutex> lk(g_engMu);
     g_tables.erase(T);
+    last = g_tables.empty();
   }
+  if (last) upload_drain();
   if (T->pCmd) (void)hipHostFree(T->pCmd);
   if (T->pRes) (void)hipHostFree(T->pRes);
   if (T->engStream) (void)hipStreamDestroy(T->engStream);
   if (T->stream) (void)hipStreamSynchronize(T->stream);
   for (void* p : T->blocks) (void)hipFree(p);
   queue_free(T->q);
-  if (T->pDomOut) (void)hipHostFree(T->pDomOut);
-  if (T->pLL) (void)hipHostFree(T->pLL);
-  if (T->pDomIn) (void)hipHostFree(T->pDomIn);
+  if (T->pBlock) (void)hipHostFree(T->pBlock);
   if (T->pCt) (void)hipHostFree(T->pCt);
-  if (T->pStatus) (void)hipHostFree(T->pStatus);
   if (T->stream) (void)hipStreamDestroy(T->stream);
   delete T;
 }
@@ -1112,19 +1272,11 @@ bool has_duplicate_rows(const int32_t* tuples, int64_t t, int n) {
 
 static int create_impl(ct_table* T, const int32_t* tuples, int64_t t, int32_t n,
                        const int32_t* lo, const int32_t* dsz, const uint64_t* init_dom) {
-  bool star = false;
-  for (int64_t k = 0; k < t * n && !star; ++k) star = tuples[k] == CT_STAR;
-  if (T->kind == CT_KIND_NEGATIVE) {
-    if (star) return fail(CT_E_INVALID, "a negative table has no star cell");
+  const bool negative = T->kind == CT_KIND_NEGATIVE;
+  if (negative) {
+    for (int64_t k = 0; k < t * n; ++k)
+      if (tuples[k] == CT_STAR) return fail(CT_E_INVALID, "a negative table has no star cell");
     if (has_duplicate_rows(tuples, t, n)) return fail(CT_E_INVALID, "a negative table lists distinct tuples");
-  }
-  if (star) {
-    // a star cell supports every value of its column: the update takes the
-    // reset branch (OR over the remaining values), which needs no other rows
-    if (T->cfg.branch_policy == CT_BRANCH_INCREMENTAL)
-      return fail(CT_E_INVALID, "a short table's update takes the reset branch");
-    T->cfg.branch_policy = CT_BRANCH_RESET;
-    T->shortTab = true;
   }
   T->n = n;
   T->t = t;
@@ -1174,74 +1326,88 @@ static int create_impl(ct_table* T, const int32_t* tuples, int64_t t, int32_t n,
     }
   }
   HIPCHK(hipStreamCreateWithFlags(&T->stream, hipStreamNonBlocking));
-  int rc = queue_init(T->q);
-  if (rc) return rc;
   // coherent (fine-grained) pinned buffers: the kernel's writes reach host
   // memory without waiting for the end of the kernel
-  const unsigned kCoherent = hipHostMallocMapped | hipHostMallocCoherent;
-  ALLOCCHK(hipHostMalloc((void**)&T->pDomOut, sizeof(uint64_t) * D, kCoherent));
-  ALLOCCHK(hipHostMalloc((void**)&T->pLL, sizeof(uint64_t) * (2 + 2 * (size_t)D), kCoherent));
+  const auto line = [](size_t x) { return (x + 127) & ~(size_t)127; };
+  const size_t domB = line(sizeof(uint64_t) * D), llB = line(sizeof(uint64_t) * (2 + 2 * (size_t)D));
+  ALLOCCHK(hipHostMalloc((void**)&T->pBlock, 256 + 2 * domB + llB, hipHostMallocMapped | hipHostMallocCoherent));
+  T->pStatus = (int32_t*)T->pBlock;
+  T->q.own = false;
+  T->q.hostErr = (int32_t*)(T->pBlock + 128);
+  T->pDomOut = (uint64_t*)(T->pBlock + 256);
+  T->pDomIn = (uint64_t*)(T->pBlock + 256 + domB);
+  T->pLL = (uint64_t*)(T->pBlock + 256 + 2 * domB);
+  *T->q.hostErr = 0;
   memset(T->pLL, 0, sizeof(uint64_t) * (2 + 2 * (size_t)D));
-  ALLOCCHK(hipHostMalloc((void**)&T->pDomIn, sizeof(uint64_t) * D, kCoherent));
-  ALLOCCHK(hipHostMalloc((void**)&T->pStatus, sizeof(int32_t) * 4, kCoherent));
 
-  // static data
+  // the supports; the static data and the root slot's descriptor, one image
+  // sent in one copy; the root slot's arrays
+  int rc;
   if ((rc = dev_alloc(T, (void**)&T->dS, sizeof(uint64_t) * (size_t)rows * T->stride))) return rc;
-  if ((rc = dev_alloc(T, (void**)&T->dVars, sizeof(VarDesc) * n))) return rc;
-  if ((rc = dev_alloc(T, (void**)&T->dWordVar, sizeof(int32_t) * D))) return rc;
-  if ((rc = dev_alloc(T, (void**)&T->dWords, sizeof(WordDesc) * D))) return rc;
-  if ((rc = dev_alloc(T, (void**)&T->dLo, sizeof(int32_t) * n))) return rc;
-  if ((rc = dev_alloc(T, (void**)&T->dTab, sizeof(TabDesc)))) return rc;
-  HIPCHK(hipMemcpy(T->dVars, T->vars.data(), sizeof(VarDesc) * n, hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(T->dWordVar, T->wordVar.data(), sizeof(int32_t) * D, hipMemcpyHostToDevice));
-  {
-    std::vector<WordDesc> words(D);
-    for (int q = 0; q < D; ++q) {
-      words[q] = WordDesc{};
-      words[q].v = T->vars[T->wordVar[q]];
-      words[q].var = T->wordVar[q];
+  size_t imgB = 0;
+  const auto part = [&imgB](size_t bytes) {
+    const size_t at = imgB;
+    imgB += align256(bytes);
+    return at;
+  };
+  const size_t oVars = part(sizeof(VarDesc) * n), oWordVar = part(sizeof(int32_t) * D), oWords = part(sizeof(WordDesc) * D),
+               oLo = part(sizeof(int32_t) * n), oTab = part(sizeof(TabDesc)), oQueue = part(sizeof(int32_t) * 8),
+               oDom = part(sizeof(uint64_t) * D), oSize = part(sizeof(int32_t) * D), oRec = part(sizeof(StageRec)),
+               oRoot = part(sizeof(SlotDesc));
+  size_t arrB = imgB;
+  const auto array = [&arrB](size_t bytes) {
+    const size_t at = arrB;
+    arrB += align256(bytes);
+    return at;
+  };
+  const size_t oCt = array(sizeof(uint64_t) * T->stride), oIdx0 = array(sizeof(int32_t) * T->nGran),
+               oIdx1 = array(sizeof(int32_t) * T->nGran), oStamp = array(sizeof(int32_t) * T->nGran),
+               oNz = array(sizeof(int32_t) * T->nGran), oLast = array(sizeof(uint64_t) * D),
+               oRes = array(sizeof(int32_t) * rows);
+  char* base = nullptr;
+  if ((rc = dev_alloc(T, (void**)&base, arrB))) return rc;
+  std::vector<char> img(imgB, 0);
+  T->dVars = (VarDesc*)(base + oVars);
+  T->dWordVar = (int32_t*)(base + oWordVar);
+  T->dWords = (WordDesc*)(base + oWords);
+  T->dLo = (int32_t*)(base + oLo);
+  T->dTab = (TabDesc*)(base + oTab);
+  T->q.queue = (int32_t*)(base + oQueue);  // [3] error word; [4] a star cell was seen
+  T->dRoot = (SlotDesc*)(base + oRoot);
+  memcpy(img.data() + oVars, T->vars.data(), sizeof(VarDesc) * n);
+  memcpy(img.data() + oWordVar, T->wordVar.data(), sizeof(int32_t) * D);
+  memcpy(img.data() + oLo, lo, sizeof(int32_t) * n);
+  memcpy(img.data() + oDom, dom0.data(), sizeof(uint64_t) * D);
+  WordDesc* words = (WordDesc*)(img.data() + oWords);
+  int32_t* size = (int32_t*)(img.data() + oSize);  // |dom| of the word's variable
+  bool empty = false;
+  int64_t selected = 0;
+  for (int i = 0; i < n; ++i) {
+    const VarDesc& v = T->vars[i];
+    int sz = 0;
+    for (int k = 0; k < v.domWords; ++k) sz += __builtin_popcountll(dom0[v.domOff + k]);
+    for (int k = 0; k < v.domWords; ++k) {
+      words[v.domOff + k].v = v;
+      words[v.domOff + k].var = i;
+      size[v.domOff + k] = sz;
     }
-    HIPCHK(hipMemcpy(T->dWords, words.data(), sizeof(WordDesc) * D, hipMemcpyHostToDevice));
+    empty = empty || sz == 0;
+    selected += sz;
   }
-  HIPCHK(hipMemcpy(T->dLo, lo, sizeof(int32_t) * n, hipMemcpyHostToDevice));
-  HIPCHK(hipMemsetAsync(T->dS, 0, sizeof(uint64_t) * (size_t)rows * T->stride, T->stream));
-  if (t > 0) {
-    int32_t* dTup = nullptr;
-    ALLOCCHK(hipMalloc(&dTup, sizeof(int32_t) * (size_t)t * n));
-    hipError_t e = hipMemcpyAsync(dTup, tuples, sizeof(int32_t) * (size_t)t * n,
-                                  hipMemcpyHostToDevice, T->stream);
-    if (e == hipSuccess)
-      e = launch_build_supports(dTup, t, n, T->dVars, T->dLo, T->dS, T->stride, T->W, T->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(T->stream);
-    (void)hipFree(dTup);
-    if (e != hipSuccess) return fail(CT_E_DEVICE, "support build failed: %s", hipGetErrorString(e));
-  }
-
-  // root slot: currTable = all t tuples, every granule active, domains dom0
-  std::vector<SlotDesc> hs;
-  if ((rc = alloc_slots(T, 1, 0, &T->dRoot, hs))) return rc;
-  T->hRoot = hs[0];
-  {
-    std::vector<uint64_t> ones(T->stride, 0);
-    for (int64_t j = 0; j < T->W; ++j) {
-      const int64_t left = t - 64 * j;
-      ones[j] = left >= 64 ? ~0ull : ((1ull << left) - 1);
-    }
-    std::vector<int32_t> iota(T->nGran);
-    for (int g = 0; g < T->nGran; ++g) iota[g] = g;
-    std::vector<int32_t> zeros(std::max(rows, T->nGran), 0);
-    HIPCHK(hipMemcpy(T->hRoot.ct, ones.data(), sizeof(uint64_t) * T->stride, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(T->hRoot.idx[0], iota.data(), sizeof(int32_t) * T->nGran, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(T->hRoot.idx[1], iota.data(), sizeof(int32_t) * T->nGran, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(T->hRoot.stamp, zeros.data(), sizeof(int32_t) * T->nGran, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(T->hRoot.nzFlag, zeros.data(), sizeof(int32_t) * T->nGran, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(T->hRoot.res, zeros.data(), sizeof(int32_t) * rows, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(T->hRoot.lastDom, dom0.data(), sizeof(uint64_t) * D, hipMemcpyHostToDevice));
-    SlotDesc r = T->hRoot;
-    r.limit = T->nGran;
-    HIPCHK(hipMemcpy(T->dRoot, &r, sizeof(SlotDesc), hipMemcpyHostToDevice));
-  }
-  // TabDesc (root pointers filled after the root propagation)
+  // root slot: every granule active, domains dom0
+  SlotDesc& r = T->hRoot;
+  r = SlotDesc{};
+  r.ct = (uint64_t*)(base + oCt);
+  r.idx[0] = (int32_t*)(base + oIdx0);
+  r.idx[1] = (int32_t*)(base + oIdx1);
+  r.stamp = (int32_t*)(base + oStamp);
+  r.nzFlag = (int32_t*)(base + oNz);
+  r.lastDom = (uint64_t*)(base + oLast);
+  r.res = (int32_t*)(base + oRes);
+  r.limit = T->nGran;
+  memcpy(img.data() + oRoot, &r, sizeof(SlotDesc));
+  // (its index buffer, limit and failed flag are filled in after the root
+  // propagation)
   TabDesc& tb = T->hTab;
   tb.n = n;
   tb.rows = rows;
@@ -1253,49 +1419,120 @@ static int create_impl(ct_table* T, const int32_t* tuples, int64_t t, int32_t n,
   tb.vars = T->dVars;
   tb.wordVar = T->dWordVar;
   tb.words = T->dWords;
+  tb.ct0 = r.ct;
+  tb.dom0 = r.lastDom;
   tb.policy = T->cfg.branch_policy;
   tb.tailBits = T->W > 0 ? (int32_t)(t - 64 * (T->W - 1)) : 0;
   tb.kind = T->kind;
-  HIPCHK(hipMemcpy(T->dTab, &tb, sizeof(TabDesc), hipMemcpyHostToDevice));
-
-  // root propagation: every variable takes the reset branch over dom0
-  DevJob J{};
-  J.tab = T->dTab;
-  J.slot = T->dRoot;
-  J.flags = JF_PROPAGATE | JF_ROOT;
-  J.dom_out = pinned_dev64(T, T->pDomOut);
-  J.status_out = pinned_dev(T, T->pStatus);
-  J.depthAfter = 0;
-  if ((rc = run_single(T, J, dom0.data()))) return rc;
-  HIPCHK(hipStreamSynchronize(T->stream));
-  const int st = *T->pStatus;
-  SlotDesc r{};
-  HIPCHK(hipMemcpy(&r, T->dRoot, sizeof(SlotDesc), hipMemcpyDeviceToHost));
+  memcpy(img.data() + oTab, &tb, sizeof(TabDesc));
+  // The root of a positive table: a tuple is valid iff each of its values is
+  // in dom0 (or is a star), which the support build sees as it passes: no
+  // support row is read for the root's currTable.  The partition and
+  // filterDomains are the staged finish's.
+  StageRec& rec = *(StageRec*)(img.data() + oRec);
+  rec.run = 1;
+  rec.flags = JF_PROPAGATE | JF_ROOT;
+  rec.mode = STAGE_LIST;
+  rec.nrows = (int32_t)selected;
+  rec.limit = T->nGran;
+  rec.D = D;
+  rec.nGran = T->nGran;
+  rec.curNew = 1;
+  rec.tab = T->dTab;
+  rec.slot = T->dRoot;
+  rec.S = T->dS;
+  rec.stride = T->stride;
+  rec.W = T->W;
+  rec.words = T->dWords;
+  rec.idxSrc = r.idx[0];
+  rec.idxDst = r.idx[1];
+  rec.ct = r.ct;
+  rec.nz = r.nzFlag;
+  rec.res = r.res;
+  rec.lastDom = r.lastDom;
+  rec.din = (uint64_t*)(base + oDom);
+  rec.size = (int32_t*)(base + oSize);
+  rec.dom_out = r.lastDom;
+  // slot 0
+  SlotDesc* d0 = nullptr;
+  std::vector<SlotDesc> h0;
+  if ((rc = alloc_slots(T, 1, T->cfg.max_depth, &d0, h0))) return rc;
+  int dev = 0;
+  HIPCHK(hipGetDevice(&dev));
+  UploadBuf* up = nullptr;
+  if (t > 0 && (rc = upload_take(dev, upload_window(T->W, n), &up))) {
+    (void)hipStreamSynchronize(T->stream);
+    return rc;
+  }
+  hipError_t e = hipMemsetAsync(T->dS, 0, sizeof(uint64_t) * (size_t)rows * T->stride, T->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(base, img.data(), imgB, hipMemcpyHostToDevice, T->stream);
+  if (e == hipSuccess) e = launch_init_root(T->dTab, T->dRoot, (uint64_t*)(base + oDom),
+                                           std::max<int64_t>(T->stride, rows), T->stream);
+  if (e == hipSuccess && t > 0) {
+    BuildArgs B{};
+    B.t = t;
+    B.W = T->W;
+    B.n = n;
+    B.empty = empty;
+    B.vars = T->dVars;
+    B.lo = T->dLo;
+    B.dom0 = (uint64_t*)(base + oDom);
+    B.S = T->dS;
+    B.stride = T->stride;
+    B.ct = negative ? nullptr : r.ct;
+    B.nz = r.nzFlag;
+    B.star = T->q.queue + 4;
+    e = upload_run(tuples, B, T->stream, up);
+  }
+  if (e == hipSuccess && !negative) {
+    StageArgs A{};
+    A.rec = (StageRec*)(base + oRec);
+    A.wide = stage_wide(T->nGran, D);
+    e = launch_staged_finish(A, stage_finish_items(D, A.wide), T->stream);
+  }
+  rc = CT_OK;
+  if (e == hipSuccess && negative) {
+    // every variable takes the reset branch over dom0
+    DevJob J{};
+    J.tab = T->dTab;
+    J.slot = T->dRoot;
+    J.flags = JF_PROPAGATE | JF_ROOT;
+    J.dom_out = pinned_dev64(T, T->pDomOut);
+    J.status_out = pinned_dev(T, T->pStatus);
+    J.depthAfter = 0;
+    rc = run_single(T, J, dom0.data());
+  }
+  if (e == hipSuccess && rc == CT_OK)
+    e = launch_init_first(T->dTab, d0, T->dRoot, (uint64_t*)(base + oDom), T->q.queue + 4, pinned_dev(T, T->pStatus),
+                          std::max<int64_t>(T->stride, rows), T->stream);
+  const hipError_t e2 = hipStreamSynchronize(T->stream);
+  upload_give(up);
+  if (rc) return rc;
+  if (e != hipSuccess || e2 != hipSuccess)
+    return fail(CT_E_DEVICE, "support build failed: %s", hipGetErrorString(e != hipSuccess ? e : e2));
+  T->tailPending = false;
+  const int st = T->pStatus[0];
   if (st != CT_OK && st != CT_FAIL) return fail(CT_E_DEVICE, "root propagation returned %d", st);
   T->rootFailed = st == CT_FAIL;
-  tb.ct0 = T->hRoot.ct;
-  tb.idx0 = r.idx[r.cur];
-  tb.dom0 = T->hRoot.lastDom;
-  tb.limit0 = r.limit;
-  tb.rootFailed = T->rootFailed;
-  if (T->rootFailed) {
-    // the failed root keeps dom0 as its domains and no valid tuple
-    HIPCHK(hipMemcpy(T->hRoot.lastDom, dom0.data(), sizeof(uint64_t) * D, hipMemcpyHostToDevice));
-    HIPCHK(hipMemset(T->hRoot.ct, 0, sizeof(uint64_t) * T->stride));
-    tb.limit0 = 0;
+  if (T->pStatus[1]) {
+    // a star cell supports every value of its column: the update takes the
+    // reset branch (OR over the remaining values), which needs no other rows
+    // (the table's descriptor has it already)
+    if (T->cfg.branch_policy == CT_BRANCH_INCREMENTAL)
+      return fail(CT_E_INVALID, "a short table's update takes the reset branch");
+    T->cfg.branch_policy = CT_BRANCH_RESET;
+    T->shortTab = true;
   }
-  HIPCHK(hipMemcpy(T->dTab, &tb, sizeof(TabDesc), hipMemcpyHostToDevice));
   // search-node schedule: the row vectors of a batch's smallest group fit LDS
   if (T->kind == CT_KIND_POSITIVE) {
     const int vecRows = rows + 2 + (T->shortTab ? n : 0);
     if (vecRows <= nodes_max_vec_rows((size_t)device_lds())) T->nodesVecRows = vecRows;
   }
-  int first = 0;
-  if ((rc = ct_slots_alloc(T, 1, -1, &first))) return rc;
+  if (T->cfg.schedule == CT_SCHED_NODES) (void)nodes_ids_ensure(T);
+  slots_add(T, d0, 1, T->cfg.max_depth);
   // the resident engine holds the slot's state in one workgroup's LDS
   T->engLds = engine_lds_bytes(T->n, T->D, T->nGran, T->rows);
-  int dev = 0, lds = 0;
-  HIPCHK(hipGetDevice(&dev));
+  int lds = 0;
   HIPCHK(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
   // (the engine lists rows with 16-bit ids)
   T->engEligible = T->D <= ENG_MAX_D && T->W > 0 && T->engLds <= (size_t)lds && T->kind == CT_KIND_POSITIVE &&
@@ -1429,16 +1666,7 @@ int ct_slots_alloc(ct_table* T, int32_t n, int32_t max_depth, int32_t* first_slo
   HIPCHK(launch_init_slots(T->dTab, d, n, T->hRoot.res, T->stream));
   HIPCHK(hipStreamSynchronize(T->stream));
   if (first_slot) *first_slot = (int32_t)T->slots.size();
-  for (int k = 0; k < n; ++k) {
-    SlotHost s;
-    s.dev = d + k;
-    s.maxDepth = max_depth;
-    s.capDepth = max_depth;
-    s.failed = T->rootFailed ? 1 : 0;
-    // a push never grows this vector past its capacity (no allocation per push)
-    s.failedAt.reserve(max_depth);
-    T->slots.push_back(s);
-  }
+  slots_add(T, d, n, max_depth);
   return CT_OK;
 }
 

@@ -1213,6 +1213,13 @@ hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int
   return launch_steps<false>(a, A, ModelRound{}, nU, nF, popGran, stream, nullptr);
 }
 
+// The finish of one job whose record A.rec holds.
+hipError_t launch_staged_finish(const StageArgs& A, int nF, hipStream_t stream) {
+  if (A.wide) hipLaunchKernelGGL(stage_finish_kernel<1024>, dim3(nF), dim3(1024), 0, stream, A);
+  else hipLaunchKernelGGL(stage_finish_kernel<256>, dim3(nF), dim3(256), 0, stream, A);
+  return hipGetLastError();
+}
+
 hipError_t launch_model_start(const ModelRound& M, const uint64_t* poolIn, const int32_t* off,
                               const uint64_t* const* src, hipStream_t stream) {
   hipLaunchKernelGGL(model_start_kernel, dim3((8 * M.poolWords + SBLOCK - 1) / SBLOCK), dim3(SBLOCK), 0, stream, poolIn,

@@ -69,7 +69,8 @@ typedef struct ct_table ct_table;
  * granule, and filterDomains over one wave per domain word: as three launches
  * for a call of a larger table, or as one launch with hand-offs for a call
  * whose update one workgroup takes.  The jobs of a batch run as three
- * launches together whatever the schedule of their (positive) tables.  NODES is the
+ * launches together whatever the schedule of their (positive) tables (long
+ * row lists of root jobs shared by up to four waves).  NODES is the
  * search-node schedule of ct_propagate_batch: when every job of a batch is a
  * CT_JOB_FROM_ROOT propagation of the same positive table of at most about
  * 2,400 support rows (sum of the domain sizes: one bit vector over 512 jobs
@@ -77,12 +78,10 @@ typedef struct ct_table ct_table;
  * jobs at a time.  It reads a list of the tuples' row numbers (2 bytes per
  * cell) that the library makes, in device memory of the table, once the
  * table has 64 slots (or has CT_SCHED_NODES); without memory for it, and for
- * other batches and single calls, AUTO applies.  AUTO picks SOLO for tables of at most 4
- * granules (16,384 tuples) and at most 16 domain words (wider tables spread
- * filterDomains over workgroups), and NODES for eligible batches of at least 64 jobs.  A batch whose jobs are all
- * CT_JOB_ROOT on AUTO tables runs as two launches: one wave per (job,
- * granule) streams every support row of its granule once, then one
- * workgroup per job partitions and filters.  On an AUTO table of more than
+ * other batches and single calls, AUTO applies.  AUTO picks SOLO for calls on
+ * tables of at most 4 granules (16,384 tuples) and at most 16 domain words
+ * (wider tables spread filterDomains over workgroups), and NODES for eligible
+ * batches of at least 64 jobs.  On an AUTO table of more than
  * 64 and at most 256 domain words whose update is one SPLIT item (at most 8
  * granules), with variables of at most 31 domain words, plain synchronous
  * calls on slot 0 (no currTable copy, no counters) go to the resident split
@@ -181,7 +180,7 @@ int ct_create(const int32_t *tuples, int64_t n_tuples, int32_t arity, const int3
  *     listed tuples of removed values then leave currTable; CT_FAIL iff a
  *     domain is empty (an empty currTable is no failure).  Calls run in one
  *     workgroup each (CT_SCHED_SOLO), never on the resident engine, the
- *     search-node or the root-stream schedules; the split propagators refuse
+ *     staged or the search-node schedules; the split propagators refuse
  *     negative tables.
  * Everything else is ct_create's contract.
  */

@@ -174,7 +174,8 @@ struct StageRec {
   uint32_t flags;            // JF_*
   int32_t mode;              // STAGE_*: rows from the list, from the selected bits, no change, all removed
   int32_t nrows, limit, serial, trailOn, D, nGran, curNew, serialBase, seq;
-  int32_t trailCount, pad;   // STAGE_TRAIL_FIRST: trail entries of the job (counted by the update)
+  int32_t trailCount;        // STAGE_TRAIL_FIRST: trail entries of the job (counted by the update)
+  int32_t parts;             // waves that share a granule's row list
   const CT_G TabDesc* tab;
   CT_G SlotDesc* slot;
   const CT_G uint64_t* S;
@@ -281,14 +282,6 @@ struct BuildArgs {
   uint64_t* ct;             // null: not wanted; else the root's currTable words
   int32_t* nz;              //   and the granules with one that is not zero
   int32_t* star;            // set if a star cell is seen
-};
-
-// Batch of roots recomputed from scratch: one task per workgroup of the
-// stream kernel, (job, first granule) pairs, each covering WAVES consecutive
-// granules of the job (one per wave), largest tables first.
-struct RootDesc {
-  const CT_G int32_t* tasks;  // nTasks x 2
-  int32_t nTasks, pad;
 };
 
 // Rounds of a multi-table model (ct_staged.hip).  The pool has three buffers

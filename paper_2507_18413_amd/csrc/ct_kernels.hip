@@ -1371,153 +1371,6 @@ __device__ __forceinline__ void do_solo(const KArgs& a, const DevJob& J0, Shared
   }
 }
 
-// ---------------------------------------------------------------------------
-// Batches whose jobs all recompute a root from scratch.  Stream: one wave per
-// (job, granule); a currTable word is the AND over the variables of the OR
-// of the support rows of the values in dom_in, starting from all tuples
-// (Alg. 2 with every variable on the reset branch).  A granule's words are
-// final once its wave ends, so the stream has no hand-offs; support rows are
-// fetched ROOT_UNROLL at a time, each as one coalesced 512-byte non-temporal
-// load of the wave (read once: kept out of the caches' way).  Finish (next launch): one workgroup per job validates dom_in,
-// partitions the granules (survivors first; Alg. 1's FAIL when none), sets
-// the slot to depth 0 and runs filterDomains (Alg. 3).  The launch boundary
-// orders the two; a hand-off inside one launch would need a release per wave
-// (an L2 write-back on this chip), which costs more than the second launch.
-// ---------------------------------------------------------------------------
-constexpr int ROOT_UNROLL = 4;
-
-__global__ void __launch_bounds__(BLOCK) root_stream_kernel(KArgs a, RootDesc R) {
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-  const DevJob J = a.jobs[R.tasks[2 * blockIdx.x]];
-  const int g = R.tasks[2 * blockIdx.x + 1] + wv;
-  const TabDesc* T = J.tab;
-  if (g >= T->nGran) return;
-  const unsigned lane = (unsigned)lane_id();
-  const int64_t stride = T->stride;
-  const int64_t gOff = (int64_t)g * GW;
-  uint64_t acc = all_tuples_word(T, gOff + lane);
-  for (int i = 0; i < T->n; ++i) {
-    const VarDesc v = T->vars[i];
-    uint64_t orv = 0;
-    for (int k = 0; k < v.domWords; ++k) {
-      const int used = v.dsize - 64 * k;
-      uint64_t bits = job_din(a, J, v.domOff + k);  // uniform
-      if (used < 64) bits &= (1ull << used) - 1ull;  // stray bits: the finish rejects the job
-      const CT_G uint64_t* rows = T->S + (int64_t)(v.rowStart + 64 * k) * stride + gOff;
-      int b = 0;
-      while (bits) {
-        // past the last value the previous row is fetched again (OR is
-        // idempotent, the load hits the cache)
-        uint64_t x[ROOT_UNROLL];
-#pragma unroll
-        for (int u = 0; u < ROOT_UNROLL; ++u) {
-          if (bits) {
-            b = __ffsll((unsigned long long)bits) - 1;
-            bits &= bits - 1;
-          }
-          x[u] = __builtin_nontemporal_load(rows + (int64_t)b * stride + lane);
-        }
-#pragma unroll
-        for (int u = 0; u < ROOT_UNROLL; ++u) orv |= x[u];
-      }
-    }
-    acc &= orv;
-    if (__ballot(acc != 0ull) == 0ull) break;  // the granule is already empty
-  }
-  SlotDesc* s = J.slot;
-  s->ct[gOff + lane] = acc;
-  if (J.ct_out && gOff + lane < T->W) J.ct_out[gOff + lane] = acc;
-  const bool nz = __ballot(acc != 0ull) != 0ull;
-  if (lane == 0) {
-    s->nzFlag[g] = nz ? 1 : 0;
-    if (nz) atomicAdd(&s->nzCount, 1);
-  }
-}
-
-__global__ void __launch_bounds__(BLOCK) root_finish_kernel(KArgs a) {
-  __shared__ int32_t shSurv, shStray, shRows;
-  const int lane = lane_id();
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-  const DevJob J = a.jobs[blockIdx.x];
-  const TabDesc* T = J.tab;
-  SlotDesc* s = J.slot;
-  // the filter's first two words per wave: their residue loads are in
-  // flight during the validation and the partition (their addresses stay in
-  // the table whatever the input)
-  const int D = T->D;
-  const FilterPre pre0 = filter_pre(a, J, min(wv, D - 1));
-  const FilterPre pre1 = filter_pre(a, J, min(wv + WAVES, D - 1));
-  if (threadIdx.x == 0) {
-    shStray = 0;
-    shRows = 0;
-    shSurv = s->nzCount;  // counted by the stream
-    s->nzCount = 0;
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < T->D; q += BLOCK) {
-    const uint64_t din = job_din(a, J, q);
-    const VarDesc v = T->vars[T->wordVar[q]];
-    const int used = v.dsize - 64 * (q - v.domOff);
-    if (used < 64 && (din >> used) != 0) shStray = 1;
-    atomicAdd(&shRows, __popcll(din));
-  }
-  __syncthreads();
-  int st;
-  if (shStray) {
-    slot_reset_root(T, s, J.serialBase, threadIdx.x, BLOCK);  // the reset still happens
-    st = ST_INVALID;
-  } else {
-    if (wv == 0) {
-      const int nGran = T->nGran;
-      const CT_G int32_t* nzf = s->nzFlag;
-      CT_G int32_t* dst = s->idx[0];
-      const uint64_t below = (1ull << lane) - 1ull;
-      const int nSurv = shSurv;
-      int sv = 0, zr = nSurv;
-      for (int p0 = 0; p0 < nGran; p0 += WAVE) {
-        const int p = p0 + lane;
-        const bool in = p < nGran;
-        const bool f = in && nzf[min(p, nGran - 1)] != 0;
-        const uint64_t bs = __ballot(f), bz = __ballot(in && !f);
-        if (f) dst[sv + __popcll(bs & below)] = p;
-        else if (in) dst[zr + __popcll(bz & below)] = p;
-        sv += __popcll(bs);
-        zr += __popcll(bz);
-      }
-      if (lane == 0) {
-        s->cur = 0;
-        s->limit = nSurv;
-        s->depth = 0;
-        s->trailTop = 0;
-        s->serial = J.serialBase;
-        s->failed = nSurv ? 0 : 1;
-        const unsigned long long rows = (unsigned long long)shRows;
-        atomicAdd(&s->stats[S_JOBS], 1ull);
-        atomicAdd(&s->stats[S_GRAN_IN], (unsigned long long)nGran);
-        atomicAdd(&s->stats[S_ROWS], rows);
-        if (rows) atomicAdd(&s->stats[S_GRAN_ROWS], (unsigned long long)nGran * rows);
-      }
-    }
-    __syncthreads();
-    st = shSurv ? ST_OK : ST_FAIL;
-    if (st == ST_OK) {
-      unsigned long long cnt[3] = {0, 0, 0};
-      for (int q = wv, k = 0; q < D; q += WAVES, ++k) {
-        if (k < 2) filter_word(a, J, q, 0, shSurv, s->idx[0], cnt, k == 0 ? pre0 : pre1);
-        else filter_word(a, J, q, 0, shSurv, s->idx[0], cnt);
-      }
-      add_filter_stats(s, cnt);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    s->status = st;
-    s->pad2 = 0;
-    if (J.flags & JF_HOST_OUT) __threadfence_system();
-    publish_status(J, st);
-  }
-}
-
 // Device-clock duration of a launch: first workgroup start to last end.
 __device__ void clock_begin(const KArgs& a) {
   if (a.clock && threadIdx.x == 0) atomicMin(&a.clock[0], wall_clock64());
@@ -2126,13 +1979,6 @@ hipError_t launch_init_root(TabDesc* T, SlotDesc* root, const uint64_t* dom0, in
 hipError_t launch_init_first(TabDesc* T, SlotDesc* slot, SlotDesc* root, const uint64_t* dom0, const int32_t* star,
                              int32_t* out, int64_t words, hipStream_t stream) {
   hipLaunchKernelGGL(init_first_kernel, dim3(init_grid(words)), dim3(BLOCK), 0, stream, T, slot, root, dom0, star, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_roots(const KArgs& a, const RootDesc& R, hipStream_t stream) {
-  if (R.nTasks > 0)
-    hipLaunchKernelGGL(root_stream_kernel, dim3(R.nTasks), dim3(BLOCK), 0, stream, a, R);
-  hipLaunchKernelGGL(root_finish_kernel, dim3(a.nJobs), dim3(BLOCK), 0, stream, a);
   return hipGetLastError();
 }
 

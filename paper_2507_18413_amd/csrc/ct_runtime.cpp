@@ -7,7 +7,6 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
-#include <array>
 #include <atomic>
 #include <chrono>
 #include <cstdarg>
@@ -35,9 +34,10 @@ size_t engine_lds_bytes(int n, int D, int nGran, int rows);
 hipError_t launch_engine(const EngDesc& D, size_t lds, hipStream_t stream);
 hipError_t launch_split_engine(const EngDesc& E, int grid, hipStream_t stream);
 int stage_row_pad();
-int stage_update_items(int nGran);
+int stage_update_items(int nGran, int rows);
 bool stage_wide(int nGran, int D);
 bool stage_wide_dom(int D);
+bool stage_wide_launch(bool wide, bool wideDom, int nF);
 int stage_finish_items(int D, int wide);
 hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int popGran, hipStream_t stream);
 int nodes_max_vec_rows(size_t lds);
@@ -45,7 +45,6 @@ size_t nodes_scratch_bytes(int vecRows, int nJobs, int nGran);
 size_t nodes_ids_bytes(int n, int64_t stride);
 hipError_t launch_nodes_ids(const TabDesc* T, int nGran, uint16_t* ids, hipStream_t stream);
 hipError_t launch_nodes(NodesDesc N, char* scratch, hipStream_t stream);
-hipError_t launch_roots(const KArgs& a, const RootDesc& R, hipStream_t stream);
 hipError_t noalloc_scratch(char** ptr, size_t* bytes);
 hipError_t launch_noalloc_reset(int32_t* q, int32_t* counts, hipStream_t stream);
 hipError_t launch_build_supports(const BuildArgs& B, hipStream_t stream);
@@ -129,9 +128,8 @@ struct QueueCtx {
   bool own = true;            // queue and hostErr are allocations of their own
   int32_t* queue = nullptr;   // on the device: [3] error word
   int32_t* hostErr = nullptr; // pinned
-  // batch staging: job descriptors, then (256-byte aligned) root tasks, sent
-  // in one copy; two pinned buffers in turn let the host fill one while the
-  // other's copy is still queued
+  // batch staging: job descriptors; two pinned buffers in turn let the host
+  // fill one while the other's batch is still queued
   char* dStage = nullptr;
   char* pStage[2] = {nullptr, nullptr};
   hipEvent_t staged[2] = {nullptr, nullptr};
@@ -139,8 +137,7 @@ struct QueueCtx {
   int turn = 0;
   // host scratch of a batch, kept between batches (no allocation per call)
   std::vector<DevJob> hJobs;
-  std::vector<int32_t> chunks, rootTasks;
-  std::vector<std::array<int32_t, 3>> rootKey;
+  std::vector<int32_t> chunks;
   // search-node schedule scratch (node records | row vectors | non-zero words)
   void* dNodes = nullptr;
   size_t capNodes = 0;
@@ -179,7 +176,7 @@ std::map<hipStream_t, QueueCtx*> g_queues;
 
 // A table's share of a staged launch.
 struct StageShape {
-  int nU = 0, nF = 0;
+  int nU = 0, nURoot = 0, nF = 0;  // (nURoot: a batch's root job)
   bool wide = false, wideDom = false;
   size_t bytes = 0;
 };
@@ -356,8 +353,8 @@ bool nodes_ids_ensure(ct_table* T) {
   return true;
 }
 
-// Batches of roots recomputed from scratch run on their own streaming
-// kernels when every job is a ROOT job of a table on the AUTO schedule.
+// Batches whose jobs all recompute a root from scratch (their descriptors
+// count the tasks of NA_ROOT_GRAN granules in a no-allocation batch's limit).
 bool use_roots(const ct_job* jobs, int n) {
   for (int j = 0; j < n; ++j)
     if (jobs[j].flags != (CT_JOB_PROPAGATE | CT_JOB_ROOT) || jobs[j].table->cfg.schedule != CT_SCHED_AUTO ||
@@ -396,7 +393,8 @@ size_t stage_job_bytes(const ct_table* T) {
 // it up per call).
 StageShape stage_shape(const ct_table* T) {
   StageShape S;
-  S.nU = stage_update_items(T->nGran);
+  S.nU = stage_update_items(T->nGran, 0);
+  S.nURoot = stage_update_items(T->nGran, T->rows);
   S.nF = stage_finish_items(T->D, 0);  // (the narrow form of the finish has the most items)
   S.wide = stage_wide(T->nGran, T->D);
   S.wideDom = stage_wide_dom(T->D);
@@ -410,7 +408,7 @@ struct StageNeed {
   int uCap = 0, fCap = 0;                        // the most of a list
   size_t jobBytes = 0;
   bool wide = false, wideDom = false;
-  void add(const ct_table* T, bool propagate, bool pops) {
+  void add(const ct_table* T, bool propagate, bool pops, bool root = false) {
     if (pops) popGran = std::max(popGran, T->nGran);
     if (!propagate) {
       ++nJobs;
@@ -420,7 +418,7 @@ struct StageNeed {
     jobBytes += S.bytes;
     wide = wide || S.wide;
     wideDom = wideDom || S.wideDom;
-    add_items(S.nU, S.nF);
+    add_items(root ? S.nURoot : S.nU, S.nF);
   }
   void add_items(int du, int df) {
     const int l = nJobs++ % STAGE_LISTS;
@@ -435,10 +433,10 @@ struct StageNeed {
   }
   size_t bytes() const { return total(nJobs, uCap, fCap, jobBytes); }
   // the bytes with one more propagation of T
-  size_t bytes_with(const ct_table* T) const {
+  size_t bytes_with(const ct_table* T, bool root = false) const {
     const StageShape& S = T->stage;
     const int l = nJobs % STAGE_LISTS;
-    return total(nJobs + 1, std::max(uCap, u[l] + S.nU), std::max(fCap, f[l] + S.nF), jobBytes + S.bytes);
+    return total(nJobs + 1, std::max(uCap, u[l] + (root ? S.nURoot : S.nU)), std::max(fCap, f[l] + S.nF), jobBytes + S.bytes);
   }
 };
 
@@ -455,7 +453,7 @@ StageArgs stage_args(const StageNeed& n, char* scratch, int32_t* queue, int32_t*
   scratch += align256(sizeof(StageItem) * STAGE_LISTS * (size_t)n.fCap);
   A.uCap = n.uCap;
   A.fCap = n.fCap;
-  A.wide = n.wide;
+  A.wide = stage_wide_launch(n.wide, n.wideDom, n.nF);
   A.wideDom = n.wideDom;
   A.queue = queue;
   A.hostErr = hostErr;
@@ -982,13 +980,13 @@ struct BatchShape {
 
 // Negative tables, and a job whose scratch alone is beyond the capacity, run
 // in one workgroup of the propagate kernel.
-bool batch_staged(const ct_table* T, bool propagate, size_t scratchCap) {
+bool batch_staged(const ct_table* T, bool propagate, size_t scratchCap, bool root = false) {
   if (!propagate) return true;
-  return T->kind != CT_KIND_NEGATIVE && StageNeed().bytes_with(T) <= scratchCap;
+  return T->kind != CT_KIND_NEGATIVE && StageNeed().bytes_with(T, root) <= scratchCap;
 }
 
 // Device descriptors of a validated batch, written into out[n_jobs] (other:
-// the search-node and root schedules take them in the batch's order).
+// the search-node schedule takes them in the batch's order).
 // Applies the jobs' pops and pushes to the host mirror of each slot.
 BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool other, size_t scratchCap,
                        DevJob* out, int32_t* chunks) {
@@ -1000,7 +998,8 @@ BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool
       const ct_job& cj = jobs[j];
       ct_table* T = cj.table;
       const bool propagate = cj.flags & CT_JOB_PROPAGATE;
-      const bool staged = !other && batch_staged(T, propagate, scratchCap);
+      const bool root = cj.flags & CT_JOB_ROOT;
+      const bool staged = !other && batch_staged(T, propagate, scratchCap, root);
       if (!other && staged != (pass == 0)) continue;
       SlotHost& S = T->slots[cj.slot];
       DevJob& J = out[at++];
@@ -1044,15 +1043,15 @@ BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool
         J.flags |= JF_SOLO;
         continue;
       }
-      if (B.nStaged == 0 || need.bytes_with(T) > scratchCap) {
+      if (B.nStaged == 0 || need.bytes_with(T, root) > scratchCap) {
         chunks[B.nChunks++] = B.nStaged;
         need = StageNeed();
       }
       J.stageOff = (int32_t)(need.jobBytes / 256);
       J.listCap = stage_list_cap(T);
-      J.nUpd = propagate ? T->stage.nU : 0;
+      J.nUpd = !propagate ? 0 : root ? T->stage.nURoot : T->stage.nU;
       J.nFilt = propagate ? T->stage.nF : 0;
-      need.add(T, propagate, J.nPop > 0);
+      need.add(T, propagate, J.nPop > 0, root);
       B.popGran = std::max(B.popGran, need.popGran);
       B.wide = B.wide || need.wide;
       B.wideDom = B.wideDom || need.wideDom;
@@ -1913,41 +1912,35 @@ namespace {
 
 // What a validated batch needs, before any slot's host state changes.
 struct BatchPlan {
-  bool nodes = false, roots = false;
+  bool nodes = false;
   size_t stagedBytes = 0;  // staged scratch of all jobs at once
   size_t nodesBytes = 0;   // search-node records, row vectors and non-zero words
-  size_t nTaskInts = 0;    // root tasks, two ints each
-  size_t offAt = 0;        // byte offset of the int section of the staging area
-  size_t stageBytes = 0;   // staging bytes for the largest prep list
+  size_t descBytes = 0;    // job descriptors
+  // what a no-allocation batch is held to: the descriptors, three ints a job
+  // and, for a batch of roots, two ints for every WAVES granules
+  size_t rootInts = 0, limitBytes = 0;
 };
 
 // nodes: the batch runs on the search-node schedule if it is one
 BatchPlan batch_plan(const ct_job* jobs, int n_jobs, bool nodes) {
   BatchPlan p;
   p.nodes = nodes;
-  p.roots = !p.nodes && use_roots(jobs, n_jobs);
   if (p.nodes) {
     const ct_table* T = jobs[0].table;
     p.nodesBytes = nodes_scratch_bytes(T->nodesVecRows, n_jobs, T->nGran);
-  }
-  if (p.roots) {
-    size_t nTasks = 0;
-    for (int j = 0; j < n_jobs; ++j) nTasks += (size_t)(jobs[j].table->nGran + WAVES - 1) / WAVES;
-    p.nTaskInts = 2 * nTasks;
-  }
-  if (!p.nodes && !p.roots) {
+  } else {
+    if (use_roots(jobs, n_jobs))
+      for (int j = 0; j < n_jobs; ++j) p.rootInts += 2 * ((size_t)(jobs[j].table->nGran + WAVES - 1) / WAVES);
     StageNeed need;
     for (int j = 0; j < n_jobs; ++j) {
       const ct_table* T = jobs[j].table;
-      const bool propagate = jobs[j].flags & CT_JOB_PROPAGATE;
-      if (batch_staged(T, propagate, STAGE_SCRATCH)) need.add(T, propagate, false);
+      const bool propagate = jobs[j].flags & CT_JOB_PROPAGATE, root = jobs[j].flags & CT_JOB_ROOT;
+      if (batch_staged(T, propagate, STAGE_SCRATCH, root)) need.add(T, propagate, false, root);
     }
     p.stagedBytes = need.bytes();
   }
-  p.offAt = align256(sizeof(DevJob) * (size_t)n_jobs);
-  // job descriptors, then the root tasks; the documented limit of a
-  // no-allocation batch counts three ints a job besides
-  p.stageBytes = p.offAt + sizeof(int32_t) * (2 * (size_t)(n_jobs + 1) + (size_t)n_jobs + 2 + p.nTaskInts);
+  p.descBytes = align256(sizeof(DevJob) * (size_t)n_jobs);
+  p.limitBytes = p.descBytes + sizeof(int32_t) * (2 * (size_t)(n_jobs + 1) + (size_t)n_jobs + 2 + p.rootInts);
   return p;
 }
 
@@ -1971,41 +1964,20 @@ struct BatchRes {
   int32_t* chunks = nullptr;    // n_jobs
   char* dStaged = nullptr;      // staged scratch
   size_t capStaged = 0;
-  int32_t* rootTasks = nullptr; // plan.nTaskInts
-  std::array<int32_t, 3>* rootKey = nullptr;  // n_jobs
 };
 
 // Builds the descriptors of a validated batch (applying its pops and pushes
-// to the slots' host mirrors), stages them in one copy and launches it.
+// to the slots' host mirrors), stages them and launches it.
 int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* status_dev, const BatchPlan& p,
                  const BatchRes& r) {
-  // root streams: WAVES granules per task, tables with the most support rows
-  // first (their tasks are the longest)
-  if (p.roots) {
-    for (int j = 0; j < n_jobs; ++j) {
-      const ct_table* T = jobs[j].table;
-      r.rootKey[j] = {-T->rows, -T->nGran, j};
-    }
-    std::sort(r.rootKey, r.rootKey + n_jobs);
-    size_t at = 0;
-    for (int k = 0; k < n_jobs; ++k)
-      for (int g = 0; g < -r.rootKey[k][1]; g += WAVES) {
-        r.rootTasks[at++] = r.rootKey[k][2];
-        r.rootTasks[at++] = g;
-      }
-  }
-  const BatchShape B = batch_build(jobs, n_jobs, status_dev, p.nodes || p.roots, r.capStaged, r.hJobs, r.chunks);
-  // one copy to the device: the descriptors, then the root tasks
-  const size_t stageBytes = p.offAt + sizeof(int32_t) * p.nTaskInts;
+  const BatchShape B = batch_build(jobs, n_jobs, status_dev, p.nodes, r.capStaged, r.hJobs, r.chunks);
   memcpy(r.hStage, r.hJobs, sizeof(DevJob) * n_jobs);
-  if (p.roots && p.nTaskInts) memcpy(r.hStage + p.offAt, r.rootTasks, sizeof(int32_t) * p.nTaskInts);
   // A staged batch's descriptors are read once, by the prep: up to
   // DIRECT_JOBS of them straight from the pinned buffer
-  const bool direct = r.hStageDev && !p.nodes && !p.roots && B.nStaged == n_jobs && n_jobs <= DIRECT_JOBS;
+  const bool direct = r.hStageDev && !p.nodes && B.nStaged == n_jobs && n_jobs <= DIRECT_JOBS;
   DevJob* dJobs = (DevJob*)(direct ? r.hStageDev : r.dStage);
   if (!direct) {
-    HIPCHK(hipMemcpyAsync(r.dStage, r.hStage, p.roots ? stageBytes : sizeof(DevJob) * (size_t)n_jobs,
-                          hipMemcpyHostToDevice, stream));
+    HIPCHK(hipMemcpyAsync(r.dStage, r.hStage, sizeof(DevJob) * (size_t)n_jobs, hipMemcpyHostToDevice, stream));
     if (r.staged) HIPCHK(hipEventRecord(r.staged, stream));
   }
   KArgs a{};
@@ -2029,13 +2001,6 @@ int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* st
     N.vecRows = T->nodesVecRows;
     for (int j = 0; j < n_jobs && !N.anyOut; ++j) N.anyOut = jobs[j].ct_out != nullptr;
     HIPCHK(launch_nodes(N, (char*)r.dNodes, stream));
-    return CT_OK;
-  }
-  if (p.roots) {
-    RootDesc R{};
-    R.tasks = (int32_t*)(r.dStage + p.offAt);
-    R.nTasks = (int32_t)(p.nTaskInts / 2);
-    HIPCHK(launch_roots(a, R, stream));
     return CT_OK;
   }
   for (int k = 0; k < B.nChunks; ++k) {
@@ -2080,8 +2045,6 @@ struct NoAllocHost {
   hipStream_t lastStream = nullptr;  // the stream of the last call (ct_batch_status)
   DevJob jobs[NA_MAX_JOBS];
   int32_t chunks[NA_MAX_JOBS];
-  std::array<int32_t, 3> rootKey[NA_MAX_JOBS];
-  int32_t rootTasks[NA_MAX_TASK_INTS];
   alignas(256) char stage[NA_STAGE_BYTES];
 };
 NoAllocHost g_na;
@@ -2145,12 +2108,12 @@ int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32
     rc = stage_reserve(*q, std::min(p.stagedBytes, STAGE_SCRATCH), stream);
     if (rc) return rc;
   }
-  if (q->capStage < p.stageBytes) {
+  if (q->capStage < p.descBytes) {
     HIPCHK(hipStreamSynchronize(stream));
     if (q->dStage) (void)hipFree(q->dStage);
     for (int k = 0; k < 2; ++k)
       if (q->pStage[k]) (void)hipHostFree(q->pStage[k]);
-    const size_t cap = std::max(p.stageBytes, 2 * q->capStage);
+    const size_t cap = std::max(p.descBytes, 2 * q->capStage);
     q->dStage = nullptr;
     q->pStage[0] = q->pStage[1] = nullptr;
     q->capStage = 0;
@@ -2160,8 +2123,6 @@ int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32
   }
   q->hJobs.resize(n_jobs);
   q->chunks.resize(n_jobs);
-  q->rootTasks.resize(p.nTaskInts);
-  q->rootKey.resize(p.roots ? n_jobs : 0);
   // two pinned staging buffers in turn: the copy that last read this one
   // (two batches ago) has ended
   q->turn ^= 1;
@@ -2178,8 +2139,6 @@ int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32
   r.chunks = q->chunks.data();
   r.dStaged = q->dStaged;
   r.capStaged = q->capStaged;
-  r.rootTasks = q->rootTasks.data();
-  r.rootKey = q->rootKey.data();
   return batch_launch(jobs, n_jobs, stream, status_dev, p, r);
 }
 
@@ -2202,9 +2161,9 @@ int ct_propagate_batch_noalloc(const ct_job* jobs, int32_t n_jobs, void* stream_
                 "at most %zu", na_nodes_bytes(jobs[0].table, n_jobs), nodesCap);
   BatchPlan p = batch_plan(jobs, n_jobs, nodes && jobs[0].table->dIds);
   if (p.nodesBytes > nodesCap) p = batch_plan(jobs, n_jobs, false);
-  if (p.stageBytes > NA_STAGE_BYTES || p.nTaskInts > NA_MAX_TASK_INTS)
+  if (p.limitBytes > NA_STAGE_BYTES || p.rootInts > NA_MAX_TASK_INTS)
     return fail(CT_E_INVALID, "ct_propagate_batch_noalloc: the batch needs %zu staging bytes, at most %zu",
-                p.stageBytes, NA_STAGE_BYTES);
+                p.limitBytes, NA_STAGE_BYTES);
   hipStream_t stream = (hipStream_t)stream_v;
   std::lock_guard<std::mutex> lk(g_na.mu);
   int rc = batch_validate_quiesce(jobs, n_jobs, stream);
@@ -2218,8 +2177,6 @@ int ct_propagate_batch_noalloc(const ct_job* jobs, int32_t n_jobs, void* stream_
   r.chunks = g_na.chunks;
   r.dStaged = (char*)r.dNodes;
   r.capStaged = nodesCap;
-  r.rootTasks = g_na.rootTasks;
-  r.rootKey = g_na.rootKey;
   // the item counts start at zero (an earlier call's error word is kept for
   // ct_batch_status)
   HIPCHK(launch_noalloc_reset(r.queue, (int32_t*)r.dStaged, stream));

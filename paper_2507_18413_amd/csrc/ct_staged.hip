@@ -57,6 +57,15 @@ constexpr int SWAVES = SBLOCK / WAVE;
 constexpr int FIN_WIDE_GRAN = 64, FIN_WIDE_D = 512;
 __host__ __device__ inline int fin_words(int D, int wide) { return wide && D > FIN_WIDE_D ? 16 : 4; }
 
+// Waves that share a granule's row list in a batch of roots, which select most
+// rows of their tables: one wave's chain of round trips over 600 rows took as
+// long as the whole batch's traffic (400 tables of up to 500,000 tuples: the
+// update 93 us, split 79: 410 MB at 5.2 TB/s).
+constexpr int SPLIT_ROWS = 96;
+__host__ __device__ inline int stage_parts(int nrows) {
+  return nrows >= 2 * SPLIT_ROWS ? 4 : nrows >= SPLIT_ROWS ? 2 : 1;
+}
+
 constexpr int ROW_U = 16;                // support rows in flight per wave; the list is padded to it
 constexpr uint32_t SEG_FIRST = 1u << 31; // list entry: first row of its segment
 constexpr uint32_t SEG_INC = 1u << 30;   //   of an incremental segment
@@ -127,23 +136,38 @@ __device__ __forceinline__ void seg_close(uint64_t& m, uint64_t& acc, bool inc) 
   acc = 0ull;
 }
 
+// A granule whose row list is split over `parts` waves of its workgroup: what
+// each leaves for the first (segments cross the parts' borders).
+struct SplitShared {
+  uint64_t mask[SWAVES][WAVE];   // the segments that end in the part
+  uint64_t first[SWAVES][WAVE];  // the OR up to the part's first segment start
+  uint64_t open[SWAVES][WAVE];   // the OR of the segment that its end leaves open
+  int32_t has[SWAVES], inc[SWAVES];  // a segment starts in the part; the open one's kind
+};
+
 __device__ __forceinline__ void stage_granule(const StageArgs& A, const StageRec& V, CT_G int32_t* trailCount,
-                                              int pos) {
+                                              int pos, int part, int parts, SplitShared& sh) {
   const StageRec* R = &V;
   const int limit = R->limit, nGran = R->nGran, mode = R->mode;
   const uint32_t flags = R->flags;
   const bool fromRoot = flags & JF_FROM_ROOT, scratch = flags & JF_SCRATCH;
   const int lane = s_lane();
   CT_G uint64_t* const ctOut = R->ct_out;
-  if (pos >= nGran || (pos >= limit && !fromRoot && !ctOut)) return;
+  const bool active = pos < limit;
+  if (parts > 1 && !active && part > 0) pos = nGran;  // (one wave writes an inactive granule)
+  if (pos >= nGran || (!active && !fromRoot && !ctOut)) {
+    if (parts > 1) s_lds_barrier();
+    return;
+  }
   const int g = scratch ? pos : ((const CT_K int32_t*)R->idxSrc)[pos];
   const int64_t w = (int64_t)g * GW + lane;
-  if (pos >= limit) {  // inactive granule (all zero by invariant)
+  if (!active) {  // inactive granule (all zero by invariant)
     if (fromRoot) R->ct[w] = 0ull;
     if (ctOut && w < R->W) {
       ctOut[w] = 0ull;
       if (flags & JF_HOST_OUT) __threadfence_system();
     }
+    if (parts > 1) s_lds_barrier();
     return;
   }
   const uint64_t old = scratch ? all_tuples((const TabDesc*)R->tab, w) : R->ctSrc[w];
@@ -157,7 +181,12 @@ __device__ __forceinline__ void stage_granule(const StageArgs& A, const StageRec
     bool inc = true;  // nothing before the first segment: ~0 leaves m alone
     const int nrows = R->nrows;
     const CT_K uint32_t* list = (const CT_K uint32_t*)R->rows;
-    for (int k0 = 0; k0 < nrows; k0 += ROW_U) {
+    // this wave's part of the list, in whole groups
+    const int groups = (nrows + ROW_U - 1) / ROW_U, per = (groups + parts - 1) / parts;
+    const int kEnd = parts > 1 ? min(nrows, (part + 1) * per * ROW_U) : nrows;
+    uint64_t first = 0ull;
+    bool has = part == 0;
+    for (int k0 = part * per * ROW_U; k0 < kEnd; k0 += ROW_U) {
       uint32_t e[ROW_U];
       uint64_t v[ROW_U];
 #pragma unroll
@@ -167,10 +196,38 @@ __device__ __forceinline__ void stage_granule(const StageArgs& A, const StageRec
 #pragma unroll
       for (int j = 0; j < ROW_U; ++j) {
         if (e[j] & SEG_FIRST) {
-          seg_close(m, acc, inc);
+          if (has) {
+            seg_close(m, acc, inc);
+          } else {
+            first = acc;
+            acc = 0ull;
+            has = true;
+          }
           inc = e[j] & SEG_INC;
         }
         acc |= v[j];
+      }
+    }
+    if (parts > 1) {
+      if (part > 0) {
+        sh.mask[s_wave()][lane] = m;
+        sh.first[s_wave()][lane] = has ? first : acc;
+        sh.open[s_wave()][lane] = acc;
+        if (lane == 0) {
+          sh.has[s_wave()] = has;
+          sh.inc[s_wave()] = inc;
+        }
+      }
+      s_lds_barrier();
+      if (part > 0) return;
+      for (int p = s_wave() + 1; p < s_wave() + parts; ++p) {
+        acc |= sh.first[p][lane];
+        if (__builtin_amdgcn_readfirstlane(sh.has[p])) {
+          seg_close(m, acc, inc);
+          m &= sh.mask[p][lane];
+          acc = sh.open[p][lane];
+          inc = __builtin_amdgcn_readfirstlane(sh.inc[p]);
+        }
       }
     }
     if (nrows) seg_close(m, acc, inc);
@@ -1015,6 +1072,9 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
   R.limit = limit;
   R.serial = serial;
   // levels exist only above depth 0: nothing is saved at depth 0
+  // (only a root's list is long enough, and only those items are counted so)
+  R.parts = (J.flags & (JF_ROOT | JF_FROM_ROOT)) == (JF_ROOT | JF_FROM_ROOT) && R.mode == STAGE_LIST
+                ? stage_parts(nrows) : 1;
   R.trailOn = fromRoot || root || J.depthAfter <= 0 || noop ? STAGE_TRAIL_OFF
               : J.nPush > 0 ? STAGE_TRAIL_ALL : STAGE_TRAIL_FIRST;
   R.D = D;
@@ -1062,7 +1122,7 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
       // fin_words domain words each
       const int pos = fromRoot || J.ct_out ? nGran : limit;
       const int fw = fin_words(D, A.wide);
-      const int nU = (pos + SWAVES - 1) / SWAVES, nF = 1 + (D + fw - 1) / fw;
+      const int nU = (pos * R.parts + SWAVES - 1) / SWAVES, nF = 1 + (D + fw - 1) / fw;
       const int l = job % STAGE_LISTS;
       const unsigned long long at = atomicAdd((unsigned long long*)&A.count->n[l * STAGE_LINE],
                                               (unsigned long long)(uint32_t)nF << 32 | (uint32_t)nU);
@@ -1100,10 +1160,17 @@ __device__ __forceinline__ int item_at(const ItemLists& L, int i, int cap) {
   return l * cap + i - __builtin_amdgcn_readlane(L.before, l);
 }
 
+__device__ __forceinline__ void stage_update_item(const StageArgs& A, int job, int chunk, SplitShared& sh) {
+  const StageRec R = load_rec(A, job);
+  if (!R.run) return;
+  const int at = chunk * SWAVES + s_wave(), parts = R.parts;
+  stage_granule(A, R, &A.rec[job].trailCount, at / parts, at % parts, parts, sh);
+}
+
 __global__ void __launch_bounds__(SBLOCK, 8) stage_update_kernel(StageArgs A) {
+  __shared__ SplitShared sh;
   if (!A.items) {
-    const StageRec R = load_rec(A, 0);
-    if (R.run) stage_granule(A, R, &A.rec->trailCount, (int)blockIdx.x * SWAVES + s_wave());
+    stage_update_item(A, 0, blockIdx.x, sh);
     return;
   }
   const ItemLists L = item_lists((int)(uint32_t)A.count->n[min(s_lane(), STAGE_LISTS - 1) * STAGE_LINE]);
@@ -1111,7 +1178,8 @@ __global__ void __launch_bounds__(SBLOCK, 8) stage_update_kernel(StageArgs A) {
     A.count->fin[threadIdx.x] = (int32_t)(A.count->n[threadIdx.x * STAGE_LINE] >> 32);
   for (int i = blockIdx.x; i < L.total; i += gridDim.x) {
     const CT_K StageItem* it = (const CT_K StageItem*)A.items + item_at(L, i, A.uCap);
-    stage_granule(A, load_rec(A, it->job), &A.rec[it->job].trailCount, it->chunk * SWAVES + s_wave());
+    stage_update_item(A, it->job, it->chunk, sh);
+    s_lds_barrier();  // (the parts' words are read)
   }
 }
 
@@ -1165,7 +1233,13 @@ int stage_grid() {
 }  // namespace
 
 int stage_row_pad() { return ROW_U; }
-int stage_update_items(int nGran) { return (nGran + SWAVES - 1) / SWAVES; }
+// (rows: at most as many are selected; 0 for a job that is no root)
+int stage_update_items(int nGran, int rows) { return (nGran * stage_parts(rows) + SWAVES - 1) / SWAVES; }
+// A launch with as many finish items as CUs, or of narrow domains only, keeps
+// the small workgroups: 1,024 threads for four words leave one workgroup on a
+// CU (roots of 400 tables: the finish 20 us against 12; 128 searches 9 against
+// 11).
+bool stage_wide_launch(bool wide, bool wideDom, int nF) { return wideDom || (wide && nF <= stage_grid() / 8); }
 bool stage_wide_dom(int D) { return D > FIN_WIDE_D; }
 bool stage_wide(int nGran, int D) { return nGran > FIN_WIDE_GRAN || D > FIN_WIDE_D; }
 int stage_finish_items(int D, int wide) { return 1 + (D + fin_words(D, wide) - 1) / fin_words(D, wide); }

@@ -196,6 +196,53 @@ def test_staged_batches(names, slots, noalloc):
                 assert (job["ct_out"] == -1).all(), (step, j, names[k])
 
 
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("ds,tuples", [
+    ([95], 100), ([96], 5000), ([40, 55], 4096), ([191], 300), ([192], 20_000),  # one, two, four waves a granule
+    ([7, 90, 2, 100, 3], 9000), ([200, 1, 200], 40_000), ([60] * 10, 17_000),    # segments across the parts' ends
+    ([1, 2, 3], 70), ([64 * 200, 64 * 313], 6000), ([36_000, 38_000], 5000),     # a long list, selected bits
+])
+def test_staged_roots(ds, tuples, noalloc):
+    say("staged roots: domains", ds, tuples, "tuples, noalloc", noalloc)
+    rng = W.rng_for(len(ds), 933, tuples)
+    lo = np.zeros(len(ds), np.int32)
+    d = np.array(ds, np.int32)
+    tup = np.stack([rng.integers(0, x, size=tuples) for x in ds], 1).astype(np.int32)
+    if len(ds) > 3:
+        tup[rng.random(tup.shape) < 0.02] = ct.STAR
+    g = ct.Table(tup, lo, d)
+    lay = W.DomLayout(d, lo)
+    doms = [lay.full()]
+    for share in (0.02, 0.5, 0.97):
+        dom = lay.full()
+        for i in range(lay.n):
+            keep = rng.random(ds[i]) >= share
+            keep[int(rng.integers(0, ds[i]))] = True
+            for a in np.nonzero(~keep)[0]:
+                lay.clear(dom, i, int(a))
+        doms.append(dom)
+    doms.append(lay.full())
+    doms[-1][0] = 0  # a variable without a value
+    first = g.slots_alloc(len(doms), max_depth=0)
+    din = torch.from_numpy(np.stack(doms).view(np.int64).copy()).cuda()
+    dout, cts = torch.zeros_like(din), torch.full((len(doms), g.W), -1, dtype=torch.int64, device="cuda")
+    status = torch.full((len(doms),), 99, dtype=torch.int32, device="cuda")
+    for _ in range(2):
+        ct.propagate_batch([dict(table=g, slot=first + k, flags=ct.JOB_PROPAGATE | ct.JOB_ROOT, dom_in=din[k],
+                                 dom_out=dout[k], ct_out=None if k % 2 else cts[k]) for k in range(len(doms))],
+                           status, noalloc=noalloc)
+    ct.batch_status()
+    for k, dom in enumerate(doms):
+        o = O.OracleTable(tup, lo, d, init_dom=dom)
+        assert int(status[k]) == o.create_status, k
+        sd, sc = g.state(first + k)
+        od, oc = o.state()[:2]
+        assert (sc == oc).all(), k
+        if o.create_status == O.OK:
+            assert (sd == od).all() and (dout[k].cpu().numpy().view(np.uint64) == od).all(), k
+            assert k % 2 or (cts[k].cpu().numpy().view(np.uint64) == oc).all(), k
+
+
 @pytest.mark.parametrize("n_tables,n_pool,dom,tuples,negatives,hub", [
     (3, 4, (2, 130), (20, 400), 1, False),
     (40, 30, (2, 20), (30, 20_000), 6, True),

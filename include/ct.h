@@ -367,7 +367,7 @@ int ct_model_layout(const ct_model *m, int32_t *pool_off, int32_t *pool_words);
  * of whose variables changed in the previous round (in the first round: each
  * table from whose last domains pool_in removes a value) on the pool
  * intersected with its own last domains, and ANDs the results into the
- * pool.  Rounds are launched one ahead of the host until the device reports
+ * pool.  Rounds are launched ahead of the host until the device reports
  * convergence or failure.
  * Synchronous on `stream` (NULL = the model's own stream).  pool_out (device)
  * receives the fixpoint (undefined after CT_FAIL).  n_props (nullable)

@@ -2229,13 +2229,14 @@ int table_view(const ct_table* T, TableView* v) {
 }  // namespace ctk
 
 // ===========================================================================
-// Multi-table model: propagation rounds, launched one ahead of the host
+// Multi-table model: propagation rounds, launched ahead of the host
 // ===========================================================================
 namespace ctk {
 hipError_t launch_model_start(const ModelRound& M, const uint64_t* poolIn, const int32_t* off,
                               const uint64_t* const* src, hipStream_t stream);
-hipError_t launch_model_round(const KArgs& a, const StageArgs& A, const ModelRound& M, int nU, int nF,
-                              const ModelNeg& neg, hipStream_t stream);
+hipError_t launch_model_prep(const KArgs& a, const StageArgs& A, const ModelRound& M, hipStream_t stream);
+hipError_t launch_model_items(const StageArgs& A, const ModelRound& M, int nU, int nF, const ModelNeg& neg,
+                              hipStream_t stream);
 }
 
 struct ct_model {
@@ -2632,24 +2633,25 @@ int ct_model_fixpoint(ct_model* m, const uint64_t* pool_in, uint64_t* pool_out, 
   M.nHead = std::min(32, (m->poolWords + 511) / 512);
   M.call = (int32_t)++m->call;
   HIPCHK(hipHostGetDevicePointer((void**)&M.host, m->pHost, 0));
-  auto launch_round = [&](int r) {
+  auto set_round = [&](int r) {
     M.round = r;
     M.cur = m->pool[r % 3];
     M.next = m->pool[(r + 1) % 3];
     M.prev = m->pool[(r + 2) % 3];
-    return launch_model_round(m->a, m->A, M, m->nU, m->nF, m->neg, m->stream);
   };
-  M.cur = m->pool[0];
+  set_round(0);
   HIPCHK(launch_model_start(M, pool_in, m->startOff, m->startSrc, m->stream));
-  // One round is always queued behind the running one: a round's prep tells
-  // the host how the round before ended, and when that was the last round it
-  // copies the pool out and nothing of it runs (about 8 us, against the same
-  // for the host to launch a round that it waited to know of).
-  HIPCHK(launch_round(0));
+  HIPCHK(launch_model_prep(m->a, m->A, M, m->stream));
+  // A round's prep tells the host, as it starts, how the round before ended:
+  // when that was the last one the prep copies the pool out, and nothing else
+  // of its round is launched; otherwise the rest of it is queued by the time
+  // the prep ends, and the next prep behind it.
   int launched = 1, code = 0;
   for (bool lost = false; !code && !lost;) {
     if (launched > 1000000) return fail(CT_E_DEVICE, "fixpoint did not converge");
-    HIPCHK(launch_round(launched));
+    HIPCHK(launch_model_items(m->A, M, m->nU, m->nF, m->neg, m->stream));
+    set_round(launched);
+    HIPCHK(launch_model_prep(m->a, m->A, M, m->stream));
     const uint64_t want = (uint64_t)m->call << 32 | (uint32_t)launched++ << 8;
     bool ended = false;  // the stream was empty: then the word is there
     for (uint32_t spin = 1;; ++spin) {

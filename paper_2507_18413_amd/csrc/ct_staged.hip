@@ -1246,45 +1246,38 @@ int stage_finish_items(int D, int wide) { return 1 + (D + fin_words(D, wide) - 1
 
 namespace {
 
-// The prep, update and finish of a.nJobs jobs (a.jobs, or the one of the
-// arguments; MODEL: of a model's round); nU / nF: at most this many update and
-// finish items; popGran: granules of the largest table that pops.
+// The prep of a.nJobs jobs (a.jobs, or the one of the arguments; MODEL: of a
+// model's round); popGran: granules of the largest table that pops.
 template <bool MODEL>
-hipError_t launch_steps(const KArgs& a, const StageArgs& A, const ModelRound& M, int nU, int nF, int popGran,
-                        hipStream_t stream, const ModelNeg* neg) {
+void launch_prep(const KArgs& a, const StageArgs& A, const ModelRound& M, int popGran, hipStream_t stream) {
   const size_t lds = sizeof(int32_t) * (size_t)popGran;
   const int np = a.nJobs + (MODEL ? M.nHead : 0);
   if (a.nJobs > stage_grid() / 8 && !A.wideDom)
     hipLaunchKernelGGL((stage_prep_kernel<PBLOCK_MANY, MODEL>), dim3(np), dim3(PBLOCK_MANY), lds, stream, a, A, M);
   else
     hipLaunchKernelGGL((stage_prep_kernel<PMAX, MODEL>), dim3(np), dim3(PMAX), lds, stream, a, A, M);
-  if (MODEL && neg->a.nJobs > 0) {
-    const DevJob* jobs = (const DevJob*)neg->a.jobs;
-    hipLaunchKernelGGL(model_neg_gather_kernel, dim3(neg->a.nJobs), dim3(SBLOCK), 0, stream, jobs, neg->maps, neg->dirty,
-                       M);
-    hipError_t e = launch_propagate(neg->a, std::min(neg->a.nJobs, propagate_max_grid()), stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(model_neg_merge_kernel, dim3(neg->a.nJobs), dim3(SBLOCK), 0, stream, jobs, neg->maps, neg->dirty,
-                       M);
+}
+
+// The update and the finish; nU / nF: at most this many items.
+void launch_items(const StageArgs& A, int nU, int nF, hipStream_t stream) {
+  if (nF <= 0) return;
+  const int gu = A.items ? std::min(std::max(nU, 1), stage_grid()) : nU;
+  hipLaunchKernelGGL(stage_update_kernel, dim3(gu), dim3(SBLOCK), 0, stream, A);
+  if (A.wide) {
+    const int gf = A.items ? std::min(nF, stage_grid() / 4) : nF;
+    hipLaunchKernelGGL(stage_finish_kernel<1024>, dim3(gf), dim3(1024), 0, stream, A);
+  } else {
+    const int gf = A.items ? std::min(nF, stage_grid()) : nF;
+    hipLaunchKernelGGL(stage_finish_kernel<256>, dim3(gf), dim3(256), 0, stream, A);
   }
-  if (nF > 0) {
-    const int gu = A.items ? std::min(std::max(nU, 1), stage_grid()) : nU;
-    hipLaunchKernelGGL(stage_update_kernel, dim3(gu), dim3(SBLOCK), 0, stream, A);
-    if (A.wide) {
-      const int gf = A.items ? std::min(nF, stage_grid() / 4) : nF;
-      hipLaunchKernelGGL(stage_finish_kernel<1024>, dim3(gf), dim3(1024), 0, stream, A);
-    } else {
-      const int gf = A.items ? std::min(nF, stage_grid()) : nF;
-      hipLaunchKernelGGL(stage_finish_kernel<256>, dim3(gf), dim3(256), 0, stream, A);
-    }
-  }
-  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int popGran, hipStream_t stream) {
-  return launch_steps<false>(a, A, ModelRound{}, nU, nF, popGran, stream, nullptr);
+  launch_prep<false>(a, A, ModelRound{}, popGran, stream);
+  launch_items(A, nU, nF, stream);
+  return hipGetLastError();
 }
 
 // The finish of one job whose record A.rec holds.
@@ -1301,9 +1294,23 @@ hipError_t launch_model_start(const ModelRound& M, const uint64_t* poolIn, const
   return hipGetLastError();
 }
 
-hipError_t launch_model_round(const KArgs& a, const StageArgs& A, const ModelRound& M, int nU, int nF,
-                              const ModelNeg& neg, hipStream_t stream) {
-  return launch_steps<true>(a, A, M, nU, nF, 0, stream, &neg);
+// A round's prep, and what follows it.
+hipError_t launch_model_prep(const KArgs& a, const StageArgs& A, const ModelRound& M, hipStream_t stream) {
+  launch_prep<true>(a, A, M, 0, stream);
+  return hipGetLastError();
+}
+
+hipError_t launch_model_items(const StageArgs& A, const ModelRound& M, int nU, int nF, const ModelNeg& neg,
+                              hipStream_t stream) {
+  if (neg.a.nJobs > 0) {
+    const DevJob* jobs = (const DevJob*)neg.a.jobs;
+    hipLaunchKernelGGL(model_neg_gather_kernel, dim3(neg.a.nJobs), dim3(SBLOCK), 0, stream, jobs, neg.maps, neg.dirty, M);
+    const hipError_t e = launch_propagate(neg.a, std::min(neg.a.nJobs, propagate_max_grid()), stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(model_neg_merge_kernel, dim3(neg.a.nJobs), dim3(SBLOCK), 0, stream, jobs, neg.maps, neg.dirty, M);
+  }
+  launch_items(A, nU, nF, stream);
+  return hipGetLastError();
 }
 
 }  // namespace ctk

@@ -35,10 +35,10 @@ hipError_t launch_engine(const EngDesc& D, size_t lds, hipStream_t stream);
 hipError_t launch_split_engine(const EngDesc& E, int grid, hipStream_t stream);
 int stage_row_pad();
 int stage_update_items(int nGran, int rows);
-bool stage_wide(int nGran, int D);
+bool stage_wide(int nGran);
 bool stage_wide_dom(int D);
-bool stage_wide_launch(bool wide, bool wideDom, int nF);
-int stage_finish_items(int D, int wide);
+bool stage_wide_launch(bool wide, int nF);
+int stage_finish_items(int D);
 hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int popGran, hipStream_t stream);
 int nodes_max_vec_rows(size_t lds);
 size_t nodes_scratch_bytes(int vecRows, int nJobs, int nGran);
@@ -395,8 +395,8 @@ StageShape stage_shape(const ct_table* T) {
   StageShape S;
   S.nU = stage_update_items(T->nGran, 0);
   S.nURoot = stage_update_items(T->nGran, T->rows);
-  S.nF = stage_finish_items(T->D, 0);  // (the narrow form of the finish has the most items)
-  S.wide = stage_wide(T->nGran, T->D);
+  S.nF = stage_finish_items(T->D);
+  S.wide = stage_wide(T->nGran);
   S.wideDom = stage_wide_dom(T->D);
   S.bytes = stage_job_bytes(T);
   return S;
@@ -453,7 +453,7 @@ StageArgs stage_args(const StageNeed& n, char* scratch, int32_t* queue, int32_t*
   scratch += align256(sizeof(StageItem) * STAGE_LISTS * (size_t)n.fCap);
   A.uCap = n.uCap;
   A.fCap = n.fCap;
-  A.wide = stage_wide_launch(n.wide, n.wideDom, n.nF);
+  A.wide = stage_wide_launch(n.wide, n.nF);
   A.wideDom = n.wideDom;
   A.queue = queue;
   A.hostErr = hostErr;
@@ -482,7 +482,7 @@ uint64_t* pinned_dev64(ct_table* T, uint64_t* host);
 // whose input fits the kernel arguments runs as one launch with hand-offs
 // (measured 20-21 us a call against 21-22 us staged at 12,000 and 30,000 tuples);
 // the others run staged (200,000 tuples: 22 against 27 us; 2,000,000: 26
-// against 64; 2,422 domain words: 62 against 105).
+// against 64; 307 domain words: 28 against 33; 1,105: 39 against 55).
 bool stage_single(const ct_table* T) {
   return propagate_items_per_job_update(T->nGran) > 1 || T->D > INLINE_WORDS;
 }
@@ -545,7 +545,7 @@ int run_single(ct_table* T, DevJob& J, const uint64_t* dom_in_host) {
   a.clock = T->timing ? T->dClock : nullptr;
   if (staged) {
     A.clock = a.clock;
-    HIPCHK(launch_staged(a, A, need.nU, stage_finish_items(T->D, A.wide), need.popGran, T->stream));
+    HIPCHK(launch_staged(a, A, need.nU, need.nF, need.popGran, T->stream));
   } else {
     HIPCHK(launch_propagate(a, std::min(total, propagate_max_grid()), T->stream));
   }
@@ -1486,8 +1486,8 @@ static int create_impl(ct_table* T, const int32_t* tuples, int64_t t, int32_t n,
   if (e == hipSuccess && !negative) {
     StageArgs A{};
     A.rec = (StageRec*)(base + oRec);
-    A.wide = stage_wide(T->nGran, D);
-    e = launch_staged_finish(A, stage_finish_items(D, A.wide), T->stream);
+    A.wide = stage_wide_launch(T->stage.wide, T->stage.nF);
+    e = launch_staged_finish(A, T->stage.nF, T->stream);
   }
   rc = CT_OK;
   if (e == hipSuccess && negative) {

@@ -48,14 +48,15 @@ constexpr int PMAX = 1024, PBLOCK_MANY = 512;
 constexpr int SBLOCK = 256;              // update workgroup
 constexpr int SWAVES = SBLOCK / WAVE;
 
-// Finish workgroups: 256 threads for 4 domain words, or 1,024 threads whose
-// waves share the scans of the missing values (launches with a table of many
-// granules, which a value without a support reads in full, or with many
-// domain words).  The residue checks of a word gather 64 lines each, which
-// one CU takes in turn: few words go to a workgroup while that leaves every
-// workgroup a CU of its own.
-constexpr int FIN_WIDE_GRAN = 64, FIN_WIDE_D = 512;
-__host__ __device__ inline int fin_words(int D, int wide) { return wide && D > FIN_WIDE_D ? 16 : 4; }
+// A finish workgroup filters FIN_WORDS domain words (or partitions): 256
+// threads, or 1,024 whose waves share the scans of the missing values, for
+// tables of more than FIN_WIDE_GRAN granules, which a value without a support
+// reads in full.  The residue checks of a word gather 64 lines each, which one
+// CU takes in turn, so a workgroup has few words: a call of 590 words and
+// 15,000 tuples 31 us, with 16 words in a workgroup of 1,024 threads 39; of
+// 1,744 words 50 against 56; of 2,541 the same.
+constexpr int FIN_WORDS = 4, FIN_WIDE_GRAN = 64;
+constexpr int PREP_WIDE_D = 512;  // domain words that want the large prep workgroup
 
 // Waves that share a granule's row list in a batch of roots, which select most
 // rows of their tables: one wave's chain of round trips over 600 rows took as
@@ -422,7 +423,7 @@ __device__ __forceinline__ void stage_merge(const StageRec& R, int q, uint64_t d
 }
 
 // ---------------------------------------------------------------------------
-// Finish, other items: filterDomains of fin_words domain words by one workgroup.
+// Finish, other items: filterDomains of FIN_WORDS domain words by one workgroup.
 //   A. one wave per word: the support word at every value's residue against
 //      currTable; the values that miss go to a list;
 //   B. (more than FULL_GRAN surviving granules) one thread per missing value
@@ -633,9 +634,8 @@ template <int FBLOCK>
 __device__ __forceinline__ void stage_finish_item(const StageArgs& A, int job, int chunk, FinShared<FBLOCK>& sh) {
   const StageRec R = load_rec(A, job);
   if (!R.run) return;
-  const int fw = fin_words(R.D, FBLOCK > 256);
   if (chunk == 0) stage_partition(R, sh);
-  else stage_filter(R, (chunk - 1) * fw, fw, sh);
+  else stage_filter(R, (chunk - 1) * FIN_WORDS, FIN_WORDS, sh);
 }
 
 struct PrepShared {
@@ -1119,10 +1119,9 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
     if (A.items) {
       // update items: SWAVES granule positions each (all of them when the
       // inactive ones are written too); finish items: the partition, then
-      // fin_words domain words each
+      // FIN_WORDS domain words each
       const int pos = fromRoot || J.ct_out ? nGran : limit;
-      const int fw = fin_words(D, A.wide);
-      const int nU = (pos * R.parts + SWAVES - 1) / SWAVES, nF = 1 + (D + fw - 1) / fw;
+      const int nU = (pos * R.parts + SWAVES - 1) / SWAVES, nF = 1 + (D + FIN_WORDS - 1) / FIN_WORDS;
       const int l = job % STAGE_LISTS;
       const unsigned long long at = atomicAdd((unsigned long long*)&A.count->n[l * STAGE_LINE],
                                               (unsigned long long)(uint32_t)nF << 32 | (uint32_t)nU);
@@ -1235,14 +1234,13 @@ int stage_grid() {
 int stage_row_pad() { return ROW_U; }
 // (rows: at most as many are selected; 0 for a job that is no root)
 int stage_update_items(int nGran, int rows) { return (nGran * stage_parts(rows) + SWAVES - 1) / SWAVES; }
-// A launch with as many finish items as CUs, or of narrow domains only, keeps
-// the small workgroups: 1,024 threads for four words leave one workgroup on a
+// A launch with more finish items than CUs keeps the small workgroups: 1,024 threads for four words leave one workgroup on a
 // CU (roots of 400 tables: the finish 20 us against 12; 128 searches 9 against
 // 11).
-bool stage_wide_launch(bool wide, bool wideDom, int nF) { return wideDom || (wide && nF <= stage_grid() / 8); }
-bool stage_wide_dom(int D) { return D > FIN_WIDE_D; }
-bool stage_wide(int nGran, int D) { return nGran > FIN_WIDE_GRAN || D > FIN_WIDE_D; }
-int stage_finish_items(int D, int wide) { return 1 + (D + fin_words(D, wide) - 1) / fin_words(D, wide); }
+bool stage_wide_launch(bool wide, int nF) { return wide && nF <= stage_grid() / 8; }
+bool stage_wide_dom(int D) { return D > PREP_WIDE_D; }
+bool stage_wide(int nGran) { return nGran > FIN_WIDE_GRAN; }
+int stage_finish_items(int D) { return 1 + (D + FIN_WORDS - 1) / FIN_WORDS; }
 
 namespace {
 

@@ -1944,11 +1944,6 @@ BatchPlan batch_plan(const ct_job* jobs, int n_jobs, bool nodes) {
   return p;
 }
 
-// Descriptors that a staged batch reads from host memory: the copy would cost
-// a transfer between the launches (12-15 us a batch), each workgroup's read
-// about 2 us, which later workgroups of a larger batch would add up.
-constexpr int DIRECT_JOBS = 1024;
-
 // Where a batch's scratch lives: device counters, staging and search-node
 // scratch, and the host arrays the descriptors are built in.  Capacities
 // must cover the batch's plan.
@@ -1972,9 +1967,10 @@ int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* st
                  const BatchRes& r) {
   const BatchShape B = batch_build(jobs, n_jobs, status_dev, p.nodes, r.capStaged, r.hJobs, r.chunks);
   memcpy(r.hStage, r.hJobs, sizeof(DevJob) * n_jobs);
-  // A staged batch's descriptors are read once, by the prep: up to
-  // DIRECT_JOBS of them straight from the pinned buffer
-  const bool direct = r.hStageDev && !p.nodes && B.nStaged == n_jobs && n_jobs <= DIRECT_JOBS;
+  // A staged batch's descriptors are read once, by the prep, straight from the
+  // pinned buffer (each workgroup's read takes about 2 us; a copy between the
+  // launches 12-20 us a batch)
+  const bool direct = r.hStageDev && !p.nodes && B.nStaged == n_jobs;
   DevJob* dJobs = (DevJob*)(direct ? r.hStageDev : r.dStage);
   if (!direct) {
     HIPCHK(hipMemcpyAsync(r.dStage, r.hStage, sizeof(DevJob) * (size_t)n_jobs, hipMemcpyHostToDevice, stream));

@@ -29,7 +29,6 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
-LDS_PEAK_GBS = 256 * 128 * 2.4  # 256 CUs x 128 B/clock x 2.4 GHz
 MAX_DEPTH_SERVE = 64  # push levels per serving slot
 
 
@@ -220,10 +219,6 @@ def nodes_leg(seed, n_nodes, reps, warmup, schedule=0, plain=True, cpu=False):
     wall = time.perf_counter() - t0
     ct.batch_status(stream)
     gpu_ms = e0.elapsed_time(e1) / reps
-    # the update kernel reads one 512-byte granule of a support row from LDS
-    # per (node, selected row, active granule); the slots are fresh, so their
-    # counters cover exactly the warmup and timed batches
-    lds_bytes = 512 * sum(table.stats(first + k)["granule_rows"] for k in range(n_nodes)) / (warmup + reps)
     st = status.cpu().numpy()
     # algorithmic bytes of one batch: compulsory traffic = supports once +
     # root currTable once + per node currTable write + domains
@@ -271,10 +266,9 @@ def nodes_leg(seed, n_nodes, reps, warmup, schedule=0, plain=True, cpu=False):
         "frac_of_hbm_peak": round(comp / (gpu_ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
         "update_kernel_hbm_bytes": prof.get("hbm_bytes_per_launch") if prof else None,
         "update_kernel_avg_us_profiled": prof.get("avg_us") if prof else None,
-        "update_kernel_lds_bytes": lds_bytes,
-        "update_kernel_lds_roofline": None if not prof else {
-            "bound": "lds", "achieved": round(lds_bytes / prof["avg_us"] / 1e3, 1), "peak": LDS_PEAK_GBS,
-            "unit": "GB/s", "frac": round(lds_bytes / prof["avg_us"] / 1e3 / LDS_PEAK_GBS, 4)},
+        "update_kernel_roofline": None if not prof else {
+            "bound": "hbm", "achieved": round(comp / prof["avg_us"] / 1e3, 1), "peak": HBM_PEAK_GBS,
+            "unit": "GB/s", "frac": round(comp / prof["avg_us"] / 1e3 / HBM_PEAK_GBS, 4)},
     }
 
 
@@ -385,7 +379,7 @@ def wide_leg(seed, n_calls, cpu, split=True, paper_shape=False):
            "latency_us": {"p50": round(float(np.percentile(lat_us, 50)), 2),
                           "p99": round(float(np.percentile(lat_us, 99)), 2)},
            "kernel": {"name": "ctk::engine_kernel" if table.resident else
-                      "ctk::split_engine_kernel" if table.resident_split else "ctk::propagate_kernel",
+                      "ctk::split_engine_kernel" if table.resident_split else "ctk::stage_{prep,update,finish}_kernel",
                       "calls_timed": launches,
                       # the resident split schedule: workgroup 0's time per
                       # call (receipt to the hand-over to the filters); the
@@ -618,9 +612,9 @@ def root_batch_leg(tabs, specs, reps, per_table=True):
            "timing": "HIP events around the batches on the launch stream"}
     # the streaming kernel alone, from the committed rocprofv3 summary
     from paper_2507_18413_amd import profiling
-    prof = profiling.read_summary(os.path.join(ROOT, "profiles", "root_stream_2000_tables.md"))
+    prof = profiling.read_summary(os.path.join(ROOT, "profiles", "root_update_2000_tables.md"))
     stream_bytes = 8 * rows_w + 8 * sum(int(t.W) for t in tabs)
-    out["stream_kernel"] = {"name": "ctk::root_stream_kernel", "algorithmic_bytes": stream_bytes}
+    out["stream_kernel"] = {"name": "ctk::stage_update_kernel", "algorithmic_bytes": stream_bytes}
     if prof:
         us = prof["avg_us"]
         out["stream_kernel"].update({

@@ -294,7 +294,7 @@ typedef struct {
 
 /*
  * ct_propagate_batch -- runs every job in the same launches on `stream`
- * (a hipStream_t; NULL = the null stream) driven by a device work queue.
+ * (a hipStream_t; NULL = the null stream).
  * Each job's result equals that of the same pops, pushes and ct_propagate on
  * its slot alone.  status_dev (device-accessible, n_jobs int32) receives each job's
  * status (CT_OK, CT_FAIL, CT_E_NOT_SUBSET, CT_E_INVALID, CT_E_STATE,

@@ -504,9 +504,7 @@ int run_single(ct_table* T, DevJob& J, const uint64_t* dom_in_host) {
   StageNeed need;
   StageArgs A{};
   if (staged) {
-    need.add(T, true, J.nPop > 0);
-    int rc = stage_reserve(T->q, need.bytes(), T->stream);
-    if (rc) return rc;
+    need.add(T, true, J.nPop > 0);  // (the scratch is there: call_reserve)
     A = stage_args(need, T->q.dStaged, T->q.queue, T->q.hostErr);
     A.items = nullptr;  // one job: its items by workgroup
     J.listCap = stage_list_cap(T);
@@ -689,6 +687,28 @@ int engine_stop(ct_table* T) {
 bool engine_wanted(const ct_table* T);
 bool split_engine_wanted(ct_table* T);
 
+// What an engine of T needs, made once, before the first call that it serves
+// takes the slot's pending operations (call_reserve).
+int engine_reserve(ct_table* T) {
+  if (!T->pCmd) {
+    ALLOCCHK(hipHostMalloc((void**)&T->pCmd, sizeof(EngCmd), hipHostMallocMapped | hipHostMallocCoherent));
+    memset((void*)T->pCmd, 0, sizeof(EngCmd));
+  }
+  if (!T->pRes) {
+    ALLOCCHK(hipHostMalloc((void**)&T->pRes, sizeof(EngRes), hipHostMallocMapped | hipHostMallocCoherent));
+    memset((void*)T->pRes, 0, sizeof(EngRes));
+  }
+  int rc = ensure_pinned_ct(T);
+  if (rc) return rc;
+  if (!T->dCtl && !engine_wanted(T)) {
+    void* p = nullptr;
+    ALLOCCHK(hipMalloc(&p, sizeof(int32_t) * SE_CTL_WORDS));
+    T->blocks.push_back(p);
+    T->dCtl = (int32_t*)p;
+  }
+  return CT_OK;
+}
+
 int engine_start(ct_table* T) {
   if (g_engOwner && g_engOwner != T) {
     int rc = engine_stop(g_engOwner);
@@ -699,14 +719,6 @@ int engine_start(ct_table* T) {
     T->tailPending = false;
   }
   if (!T->engStream) HIPCHK(hipStreamCreateWithFlags(&T->engStream, hipStreamNonBlocking));
-  if (!T->pCmd) {
-    ALLOCCHK(hipHostMalloc((void**)&T->pCmd, sizeof(EngCmd), hipHostMallocMapped | hipHostMallocCoherent));
-    ALLOCCHK(hipHostMalloc((void**)&T->pRes, sizeof(EngRes), hipHostMallocMapped | hipHostMallocCoherent));
-    memset((void*)T->pCmd, 0, sizeof(EngCmd));
-    memset((void*)T->pRes, 0, sizeof(EngRes));
-  }
-  int rc = ensure_pinned_ct(T);
-  if (rc) return rc;
   EngDesc D{};
   D.tab = T->dTab;
   D.slot = T->slots[0].dev;
@@ -718,12 +730,6 @@ int engine_start(ct_table* T) {
   T->engTimed = T->timing;
   T->engSplit = !engine_wanted(T) && split_engine_wanted(T);
   if (T->engSplit) {
-    if (!T->dCtl) {
-      void* p = nullptr;
-      ALLOCCHK(hipMalloc(&p, sizeof(int32_t) * SE_CTL_WORDS));
-      T->blocks.push_back(p);
-      T->dCtl = (int32_t*)p;
-    }
     // (stream-ordered before the launch; never inside a captured graph)
     HIPCHK(hipMemsetAsync(T->dCtl, 0, sizeof(int32_t) * SE_CTL_WORDS, T->engStream));
     D.ctl = T->dCtl;
@@ -885,6 +891,19 @@ uint64_t* pinned_dev64(ct_table* T, uint64_t* host) {
   return d;
 }
 
+// What a synchronous propagation may have to allocate, before it takes the
+// slot's pending operations: a refused allocation leaves the slot as it was
+// (pending pops and pushes that were lost would leave the device's level
+// behind the host's).
+int call_reserve(ct_table* T, bool engine, bool wantCt) {
+  if (engine) return engine_reserve(T);
+  int rc = wantCt ? ensure_pinned_ct(T) : CT_OK;
+  if (rc || use_solo(T) || !stage_single(T)) return rc;
+  StageNeed need;
+  need.add(T, true, false);
+  return stage_reserve(T->q, need.bytes(), T->stream);
+}
+
 // Apply pending pushes/pops of a slot (device work) without propagating.
 int flush_slot(ct_table* T, int slot) {
   SlotHost& S = T->slots[slot];
@@ -900,7 +919,9 @@ int flush_slot(ct_table* T, int slot) {
   J.depthAfter = S.depth;
   J.status_out = pinned_dev(T, T->pStatus);
   S.pendPop = S.pendPush = 0;
-  return run_single(T, J, nullptr);
+  const int rc = run_single(T, J, nullptr);
+  if (rc) T->poisoned = true;  // (a device error: the pending operations are gone)
+  return rc;
 }
 
 int ensure_pinned_ct(ct_table* T) {
@@ -1726,6 +1747,8 @@ int ct_propagate_slot(ct_table* T, int32_t slot, const uint64_t* dom_in, uint64_
   if (rc) return rc;
   if ((rc = check_slot(T, slot))) return rc;
   if (!dom_in || !dom_out) return fail(CT_E_INVALID, "dom_in / dom_out is NULL");
+  const bool engine = slot == 0 && (engine_wanted(T) || (!ct_out && !st && split_engine_wanted(T)));
+  if ((rc = call_reserve(T, engine, ct_out != nullptr))) return rc;
   SlotHost& S = T->slots[slot];
   DevJob J{};
   J.tab = T->dTab;
@@ -1738,23 +1761,17 @@ int ct_propagate_slot(ct_table* T, int32_t slot, const uint64_t* dom_in, uint64_
   J.depthAfter = S.depth;
   J.dom_out = pinned_dev64(T, T->pDomOut);
   J.status_out = pinned_dev(T, T->pStatus);
-  if (ct_out) {
-    if ((rc = ensure_pinned_ct(T))) return rc;
-    J.ct_out = pinned_dev64(T, T->pCt);
-  }
+  if (ct_out) J.ct_out = pinned_dev64(T, T->pCt);
   S.pendPop = S.pendPush = 0;
   int status = CT_OK;
   const uint64_t* domRes = T->pDomOut;
-  if (slot == 0 && engine_wanted(T)) {
-    if ((rc = engine_call(T, J, dom_in, ct_out != nullptr, st != nullptr, &status))) return rc;
-    domRes = T->engDom.data();
-  } else if (slot == 0 && !ct_out && !st && split_engine_wanted(T)) {
-    if ((rc = engine_call(T, J, dom_in, false, false, &status))) return rc;
-    domRes = T->engDom.data();
-  } else {
-    if ((rc = run_single(T, J, dom_in))) return rc;
-    status = *T->pStatus;
+  rc = engine ? engine_call(T, J, dom_in, ct_out != nullptr, st != nullptr, &status) : run_single(T, J, dom_in);
+  if (rc) {  // (a device error: the pending operations are gone)
+    T->poisoned = true;
+    return rc;
   }
+  if (engine) domRes = T->engDom.data();
+  else status = *T->pStatus;
   if (status == CT_OK) {
     memcpy(dom_out, domRes, sizeof(uint64_t) * T->D);
     if (ct_out) memcpy(ct_out, T->pCt, sizeof(uint64_t) * T->W);

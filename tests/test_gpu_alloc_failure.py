@@ -97,3 +97,64 @@ def test_injected_allocation_failures():
             assert (gd == od).all()
         if os_ != O.OK or k % 2 == 1:
             assert g.pop() == o.pop() == 0
+
+
+# domain sizes, tuples, schedule
+CALLS = {
+    "engine": ([10, 10, 10, 10], 5000, ct.SCHED_AUTO),
+    "resident split": ([640] * 8, 9000, ct.SCHED_AUTO),
+    "staged": ([40, 50, 60], 9 * 4096, ct.SCHED_SPLIT),
+}
+
+
+@pytest.mark.parametrize("want_ct", [False, True])
+@pytest.mark.parametrize("pop_first", [False, True])
+@pytest.mark.parametrize("name", list(CALLS))
+def test_call_without_memory_keeps_its_pushes_and_pops(name, pop_first, want_ct):
+    """A synchronous call whose own allocation fails changes nothing: the
+    pushes and pops before it still apply to the slot's next operation."""
+    L = ct.lib()
+    ds, t, schedule = CALLS[name]
+    rng = W.rng_for(len(name), 991, 0)
+    lo = np.zeros(len(ds), np.int32)
+    d = np.array(ds, np.int32)
+    tup = np.stack([rng.integers(0, x, size=t) for x in ds], 1).astype(np.int32)
+    lay = W.DomLayout(d, lo)
+    fired = 0
+    for k in range(1, 16):
+        say("call without memory:", name, "allocation", k, "pop first", pop_first, "currTable", want_ct)
+        g = ct.Table(tup, lo, d, max_depth=8, schedule=schedule)
+        o = O.OracleTable(tup, lo, d)
+        assert (g.resident, g.resident_split) == (name == "engine", name == "resident split")
+        root = o.state()[:2]
+        dom = W.pick_fraction_removal(rng, lay, o.domains(), frac=0.3)
+        assert g.push() == o.push() == 0
+        L.ct_debug_fail_alloc(k)
+        st = g.propagate(dom, want_ct=want_ct)[0]
+        left = L.ct_debug_fail_alloc(0)
+        if st == ct.E_NOMEM:
+            fired += 1
+            if pop_first:
+                assert g.pop() == 0
+                gd, gc = g.state()
+                assert (gd == root[0]).all() and (gc == root[1]).all()
+                assert g.push() == 0
+            st = g.propagate(dom)[0]
+        else:
+            assert left > 0  # the k-th allocation lies beyond those of the call
+        assert st == o.propagate(dom)[0] == O.OK
+        gd, gc = g.state()
+        assert (gd == o.state()[0]).all() and (gc == o.state()[1]).all()
+        assert g.pop() == o.pop() == 0
+        gd, gc = g.state()
+        assert (gd == root[0]).all() and (gc == root[1]).all()
+        # (one level down again, over the state just restored)
+        dom = W.pick_fraction_removal(rng, lay, o.domains(), frac=0.1)
+        assert g.push() == o.push() == 0
+        gs, gd = g.propagate(dom)
+        os_, od = o.propagate(dom)
+        assert gs == os_ and (gs != O.OK or (gd == od).all())
+        g.close()
+        if left > 0:
+            break
+    assert fired >= 1 and left > 0

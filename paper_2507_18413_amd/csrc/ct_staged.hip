@@ -649,7 +649,11 @@ struct PrepShared {
   int32_t inc[MAX_ARITY];
   int32_t wsum[PMAX / WAVE];
   uint32_t job[sizeof(DevJob) / sizeof(uint32_t)];
-  int32_t stray, notSub, dirty, status, noop, zero, nrows, nseg;
+  int32_t stray, notSub, dirty, status, noop, zero, nrows;
+  // the job's places in the item lists: fields of their own, because a wave
+  // may still be reading the others when thread 0 writes these (a job without
+  // a row list passes no barrier between the two)
+  int32_t u0, f0, nU, nF;
 };
 
 // Exclusive prefix sum over the workgroup; *total receives the sum.
@@ -994,7 +998,6 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
       sh.noop = nseg == 0 && !fromRoot;
       sh.zero = anyZero;
       sh.nrows = nrows;
-      sh.nseg = nseg;
     }
   }
   s_lds_barrier();
@@ -1130,15 +1133,15 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
       const int l = job % STAGE_LISTS;
       const unsigned long long at = atomicAdd((unsigned long long*)&A.count->n[l * STAGE_LINE],
                                               (unsigned long long)(uint32_t)nF << 32 | (uint32_t)nU);
-      sh.nseg = l * A.uCap + (int)(uint32_t)at;
-      sh.status = l * A.fCap + (int)(at >> 32);
-      sh.size[0] = nU;
-      sh.size[1] = nF;
+      sh.u0 = l * A.uCap + (int)(uint32_t)at;
+      sh.f0 = l * A.fCap + (int)(at >> 32);
+      sh.nU = nU;
+      sh.nF = nF;
     }
   }
   if (!A.items) return;
   s_lds_barrier();
-  const int u0 = sh.nseg, f0 = sh.status, nU = sh.size[0], nF = sh.size[1];
+  const int u0 = sh.u0, f0 = sh.f0, nU = sh.nU, nF = sh.nF;
   for (int k = tid; k < nU; k += PBLOCK) A.items[u0 + k] = StageItem{job, k};
   for (int k = tid; k < nF; k += PBLOCK) A.fItems[f0 + k] = StageItem{job, k};
 }

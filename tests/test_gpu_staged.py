@@ -304,3 +304,54 @@ def test_model_rounds(n_tables, n_pool, dom, tuples, negatives, hub):
                 o.pop()
             pool = stack.pop()
     assert total > 0
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("ds,tuples,slots", [
+    ([110_000, 100_000], 3000, 10),  # selected bits, domains of more than a prep pass, one update item
+    ([130, 70], 400, 900),           # smallest prep workgroup
+])
+def test_staged_jobs_without_row_lists(ds, tuples, slots, noalloc):
+    """Jobs whose prep passes no barrier between reading |dom| and noting its
+    items: selected bits, inputs without a change, an emptied variable."""
+    say("staged jobs without row lists: domains", ds, tuples, "tuples", slots, "slots, noalloc", noalloc)
+    rng = W.rng_for(len(ds), 934, tuples)
+    lo, d = np.zeros(len(ds), np.int32), np.array(ds, np.int32)
+    tup = np.stack([rng.integers(0, x, size=tuples) for x in ds], 1).astype(np.int32)
+    g = ct.Table(tup, lo, d)
+    lay = W.DomLayout(d, lo)
+    root = g.domains()
+    most = lay.full()
+    for i, n in enumerate(ds):
+        for a in rng.choice(n, size=n // 5, replace=False):
+            lay.clear(most, i, int(a))
+    gone = root.copy()
+    gone[lay.off[1]:] = 0  # the second variable has no value left
+    P = ct.JOB_PROPAGATE
+    kinds = [(P | ct.JOB_ROOT, lay.full()), (P | ct.JOB_ROOT, most), (P, root), (P | ct.JOB_FROM_ROOT, root), (P, gone)]
+    want = []
+    for flags, dom in kinds:
+        if flags & ct.JOB_ROOT:
+            o = O.OracleTable(tup, lo, d, init_dom=dom)
+            want.append((o.create_status, o.state()[0], o.state()[1]))
+        else:
+            o = O.OracleTable(tup, lo, d)
+            st = o.propagate(dom)[0]
+            want.append((st, o.state()[0], o.state()[1]))
+    assert [w[0] for w in want] == [O.OK] * 4 + [O.FAIL]
+    first = g.slots_alloc(slots, max_depth=0)
+    of = [k % len(kinds) for k in range(slots)]
+    din = torch.from_numpy(np.stack([kinds[k][1] for k in of]).view(np.int64).copy()).cuda()
+    dout = torch.zeros_like(din)
+    status = torch.full((slots,), 99, dtype=torch.int32, device="cuda")
+    ct.propagate_batch([dict(table=g, slot=first + s, flags=kinds[k][0], dom_in=din[s], dom_out=dout[s])
+                        for s, k in enumerate(of)], status, noalloc=noalloc)
+    ct.batch_status()
+    st, got = status.cpu().numpy(), dout.cpu().numpy().view(np.uint64)
+    for s, k in enumerate(of):
+        assert st[s] == want[k][0], (s, k)
+        if want[k][0] == O.OK:
+            assert (got[s] == want[k][1]).all(), (s, k)
+            if s < 10:
+                sd, sc = g.state(first + s)
+                assert (sd == want[k][1]).all() and (sc == want[k][2]).all(), (s, k)

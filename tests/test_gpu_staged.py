@@ -355,3 +355,43 @@ def test_staged_jobs_without_row_lists(ds, tuples, slots, noalloc):
             if s < 10:
                 sd, sc = g.state(first + s)
                 assert (sd == want[k][1]).all() and (sc == want[k][2]).all(), (s, k)
+
+
+@pytest.mark.parametrize("sizes", [[40] * 60, [1] * 40 + [700] * 3 + [40] * 40, [300, 310, 320, 330] * 4])
+def test_queued_batches_keep_their_descriptors(sizes):
+    """Batches queued ahead of the GPU: the descriptors of each are its own
+    until it has run, over several turns of the staging buffers and a growth."""
+    say("queued batches:", len(sizes), "of", sorted(set(sizes)), "jobs")
+    rng = W.rng_for(len(sizes), 935, max(sizes))
+    g, o, lay = make("one granule", rng)
+    first = g.slots_alloc(max(sizes), max_depth=0)
+    doms, want = [], []
+    for _ in range(7):
+        dom = W.pick_fraction_removal(rng, lay, o.domains(), frac=0.2)
+        o.push()
+        st, od = o.propagate(dom)
+        doms.append(dom)
+        want.append(od if st == O.OK else None)
+        o.pop()
+    assert any(w is not None for w in want)
+    din = torch.from_numpy(np.stack(doms).view(np.int64).copy()).cuda()
+    batches = []
+    for b, n in enumerate(sizes):
+        dout = torch.full((n, g.D), -1, dtype=torch.int64, device="cuda")
+        status = torch.full((n,), 99, dtype=torch.int32, device="cuda")
+        # (push and propagate would do as well; a second job kind changes the
+        # descriptors' flags from batch to batch)
+        flags = ct.JOB_PROPAGATE | (ct.JOB_FROM_ROOT if b % 3 else ct.JOB_ROOT)
+        batches.append((ct.Batch([dict(table=g, slot=first + k, flags=flags, dom_in=din[(b + k) % 7], dom_out=dout[k])
+                                  for k in range(n)]), dout, status))
+    torch.cuda.synchronize()
+    torch.cuda._sleep(20_000_000)  # the GPU starts some 10 ms after the first batch is queued
+    for batch, _, status in batches:
+        ct.propagate_batch(batch, status)
+    ct.batch_status()
+    for b, (_, dout, status) in enumerate(batches):
+        st, got = status.cpu().numpy(), dout.cpu().numpy().view(np.uint64)
+        for k in range(sizes[b]):
+            w = want[(b + k) % 7]
+            assert st[k] == (O.FAIL if w is None else O.OK), (b, k)
+            assert w is None or (got[k] == w).all(), (b, k)

@@ -328,8 +328,7 @@ int ct_propagate_batch(const ct_job *jobs, int32_t n_jobs, void *stream, int32_t
  * serialized on the host, and calls whose batches overlap on the GPU (on
  * different streams, or before an earlier one has completed on another
  * stream) race and give undefined results; batches queued on one stream
- * run in order and are safe.  Each call clears the item counts first
- * (a small kernel on `stream`).  Device-side errors are reported by
+ * run in order and are safe.  Device-side errors are reported by
  * ct_batch_status on the stream of the last no-allocation call.
  */
 int ct_propagate_batch_noalloc(const ct_job *jobs, int32_t n_jobs, void *stream, int32_t *status_dev);

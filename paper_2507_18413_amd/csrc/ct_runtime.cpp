@@ -46,7 +46,6 @@ size_t nodes_ids_bytes(int n, int64_t stride);
 hipError_t launch_nodes_ids(const TabDesc* T, int nGran, uint16_t* ids, hipStream_t stream);
 hipError_t launch_nodes(NodesDesc N, char* scratch, hipStream_t stream);
 hipError_t noalloc_scratch(char** ptr, size_t* bytes);
-hipError_t launch_noalloc_reset(int32_t* q, int32_t* counts, hipStream_t stream);
 hipError_t launch_build_supports(const BuildArgs& B, hipStream_t stream);
 hipError_t launch_init_root(TabDesc* T, SlotDesc* root, const uint64_t* dom0, int64_t words, hipStream_t stream);
 hipError_t launch_init_first(TabDesc* T, SlotDesc* slot, SlotDesc* root, const uint64_t* dom0, const int32_t* star,
@@ -445,10 +444,11 @@ struct StageNeed {
   }
 };
 
-// The launch's view of its scratch.
-StageArgs stage_args(const StageNeed& n, char* scratch, int32_t* queue, int32_t* hostErr) {
+// The launch's view of its scratch (count: the item counts are elsewhere).
+StageArgs stage_args(const StageNeed& n, char* scratch, int32_t* queue, int32_t* hostErr,
+                     StageCounts* count = nullptr) {
   StageArgs A{};
-  A.count = (StageCounts*)scratch;
+  A.count = count ? count : (StageCounts*)scratch;
   scratch += align256(sizeof(StageCounts));
   A.rec = (StageRec*)scratch;
   scratch += align256(sizeof(StageRec) * (size_t)n.nJobs);
@@ -1980,6 +1980,7 @@ struct BatchRes {
   int32_t* chunks = nullptr;    // n_jobs
   char* dStaged = nullptr;      // staged scratch
   size_t capStaged = 0;
+  size_t countBytes = 0;        // not 0: the copy's first bytes are the staged schedule's item counts
 };
 
 // Builds the descriptors of a validated batch (applying its pops and pushes
@@ -1987,14 +1988,16 @@ struct BatchRes {
 int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* status_dev, const BatchPlan& p,
                  const BatchRes& r) {
   const BatchShape B = batch_build(jobs, n_jobs, status_dev, p.nodes, r.capStaged, r.hJobs, r.chunks);
-  memcpy(r.hStage, r.hJobs, sizeof(DevJob) * n_jobs);
+  memset(r.hStage, 0, r.countBytes);
+  memcpy(r.hStage + r.countBytes, r.hJobs, sizeof(DevJob) * n_jobs);
   // A staged batch's descriptors are read once, by the prep, straight from the
   // pinned buffer (each workgroup's read takes about 2 us; a copy between the
   // launches 12-20 us a batch)
   const bool direct = r.hStageDev && !p.nodes && B.nStaged == n_jobs;
-  DevJob* dJobs = (DevJob*)(direct ? r.hStageDev : r.dStage);
+  DevJob* dJobs = (DevJob*)((direct ? r.hStageDev : r.dStage) + r.countBytes);
   if (!direct)
-    HIPCHK(hipMemcpyAsync(r.dStage, r.hStage, sizeof(DevJob) * (size_t)n_jobs, hipMemcpyHostToDevice, stream));
+    HIPCHK(hipMemcpyAsync(r.dStage, r.hStage, r.countBytes + sizeof(DevJob) * (size_t)n_jobs, hipMemcpyHostToDevice,
+                          stream));
   KArgs a{};
   a.jobs = dJobs;
   a.nJobs = n_jobs;
@@ -2024,7 +2027,7 @@ int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* st
     need.wide = B.wide;
     need.wideDom = B.wideDom;
     for (int j = j0; j < j1; ++j) need.add_items(r.hJobs[j].nUpd, r.hJobs[j].nFilt);
-    const StageArgs A = stage_args(need, r.dStaged, r.queue, r.hostErr);
+    const StageArgs A = stage_args(need, r.dStaged, r.queue, r.hostErr, r.countBytes ? (StageCounts*)r.dStage : nullptr);
     a.jobs = dJobs + j0;
     a.nJobs = need.nJobs;
     HIPCHK(launch_staged(a, A, need.nU, need.nF, B.popGran, stream));
@@ -2043,6 +2046,7 @@ constexpr int NA_MAX_JOBS = 8192;
 constexpr size_t NA_QUEUE_BYTES = 256;
 constexpr size_t NA_STAGE_BYTES = (size_t)2 << 20;
 constexpr size_t NA_MAX_TASK_INTS = (NA_STAGE_BYTES - (size_t)NA_MAX_JOBS * 128) / sizeof(int32_t);
+static_assert(sizeof(StageCounts) + 256 + NA_MAX_JOBS * sizeof(DevJob) <= NA_STAGE_BYTES, "the largest batch's copy");
 
 // The documented limit of a no-allocation search-node batch (tables of at
 // most NA_NODES_ROWS support rows): per node a row list and a flag byte per
@@ -2070,13 +2074,13 @@ int noalloc_status(hipStream_t stream) {
   size_t bytes = 0;
   HIPCHK(noalloc_scratch(&scratch, &bytes));
   HIPCHK(hipStreamSynchronize(stream));
-  int32_t w[2] = {0, 0};  // the error words of the last call and of an earlier one
-  HIPCHK(hipMemcpy(w, scratch + 3 * sizeof(int32_t), sizeof(w), hipMemcpyDeviceToHost));
-  if (!w[0] && !w[1]) return CT_OK;
-  const int32_t zero[2] = {0, 0};
-  HIPCHK(hipMemcpy(scratch + 3 * sizeof(int32_t), zero, sizeof(zero), hipMemcpyHostToDevice));
+  int32_t err = 0;  // of a call since the last look
+  HIPCHK(hipMemcpy(&err, scratch + 3 * sizeof(int32_t), sizeof(err), hipMemcpyDeviceToHost));
+  if (!err) return CT_OK;
+  const int32_t zero = 0;
+  HIPCHK(hipMemcpy(scratch + 3 * sizeof(int32_t), &zero, sizeof(zero), hipMemcpyHostToDevice));
   return fail(CT_E_DEVICE, "device-side error %d in a ct_propagate_batch_noalloc call on this stream (wait "
-              "timeout or trail overflow); the slots of that batch are undefined", w[0] ? w[0] : w[1]);
+              "timeout or trail overflow); the slots of that batch are undefined", err);
 }
 
 }  // namespace
@@ -2197,9 +2201,9 @@ int ct_propagate_batch_noalloc(const ct_job* jobs, int32_t n_jobs, void* stream_
   r.chunks = g_na.chunks;
   r.dStaged = (char*)r.dNodes;
   r.capStaged = nodesCap;
-  // the item counts start at zero (an earlier call's error word is kept for
-  // ct_batch_status)
-  HIPCHK(launch_noalloc_reset(r.queue, (int32_t*)r.dStaged, stream));
+  // the item counts start at zero, whatever an earlier call left: they come
+  // with the descriptors' copy (a kernel that cleared them took the stream 5 us)
+  r.countBytes = align256(sizeof(StageCounts));
   g_na.used = true;
   g_na.lastStream = stream;
   return batch_launch(jobs, n_jobs, stream, status_dev, p, r);

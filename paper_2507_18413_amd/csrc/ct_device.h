@@ -159,7 +159,7 @@ struct DevJob {
   int32_t listCap;         // staged schedule: row-list entries the job's scratch holds
   const CT_G int32_t* active;  // nullable: the job is skipped when *active == 0
   uint64_t* ll;             // JF_LL: the result slots (pinned host memory)
-  int32_t seq;              // JF_LL: the call's number
+  int32_t seq;              // JF_LL: the call's number; a job of StageArgs::roots: its first update item
   int32_t stageOff;         // staged schedule: the job's scratch (input words, |dom| per
                             // word, row list), in 256-byte units from StageArgs::jobMem
 };
@@ -228,6 +228,7 @@ struct StageArgs {
   int32_t uCap, fCap;
   int32_t wide;              // the finish runs in workgroups of 1,024 threads
   int32_t wideDom;           // a job has many domain words
+  int32_t roots;             // the update streams root jobs (no row lists): items where DevJob::seq says
   int32_t* queue;            // [3] error
   int32_t* hostErr;
   unsigned long long* clock; // nullable (one job): see KArgs

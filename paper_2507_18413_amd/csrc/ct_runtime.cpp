@@ -38,6 +38,7 @@ int stage_update_items(int nGran, int rows);
 bool stage_wide(int nGran);
 bool stage_wide_dom(int D);
 bool stage_wide_launch(bool wide, int nF);
+bool stage_stream_roots(int64_t granules);
 int stage_finish_items(int D);
 hipError_t launch_staged(const KArgs& a, const StageArgs& A, int nU, int nF, int popGran, hipStream_t stream);
 int nodes_max_vec_rows(size_t lds);
@@ -141,6 +142,7 @@ struct QueueCtx {
   // host scratch of a batch, kept between batches (no allocation per call)
   std::vector<DevJob> hJobs;
   std::vector<int32_t> chunks;
+  std::vector<uint64_t> order;
   // search-node schedule scratch (node records | row vectors | non-zero words)
   void* dNodes = nullptr;
   size_t capNodes = 0;
@@ -1014,17 +1016,23 @@ bool batch_staged(const ct_table* T, bool propagate, size_t scratchCap, bool roo
 // Device descriptors of a validated batch, written into out[n_jobs] (other:
 // the search-node schedule takes them in the batch's order).
 // Applies the jobs' pops and pushes to the host mirror of each slot.
-BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool other, size_t scratchCap,
-                       DevJob* out, int32_t* chunks) {
+BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool other, bool streamRoots,
+                       size_t scratchCap, DevJob* out, int32_t* chunks, uint64_t* order) {
   BatchShape B;
   StageNeed need;
   int at = 0;
+  if (streamRoots) {
+    // the tables with the most support rows first: their waves take longest
+    for (int j = 0; j < n_jobs; ++j) order[j] = (uint64_t)~(uint32_t)jobs[j].table->rows << 32 | (uint32_t)j;
+    std::sort(order, order + n_jobs);
+  }
   for (int pass = 0; pass < 2 && at < n_jobs; ++pass)
-    for (int j = 0; j < n_jobs; ++j) {
+    for (int k = 0; k < n_jobs; ++k) {
+      const int j = streamRoots ? (int)(uint32_t)order[k] : k;
       const ct_job& cj = jobs[j];
       ct_table* T = cj.table;
       const bool propagate = cj.flags & CT_JOB_PROPAGATE;
-      const bool root = cj.flags & CT_JOB_ROOT;
+      const bool root = (cj.flags & CT_JOB_ROOT) && !streamRoots;  // (row lists shared by waves)
       const bool staged = !other && batch_staged(T, propagate, scratchCap, root);
       if (!other && staged != (pass == 0)) continue;
       SlotHost& S = T->slots[cj.slot];
@@ -1074,7 +1082,8 @@ BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool
         need = StageNeed();
       }
       J.stageOff = (int32_t)(need.jobBytes / 256);
-      J.listCap = stage_list_cap(T);
+      J.listCap = streamRoots ? 0 : stage_list_cap(T);
+      if (streamRoots) J.seq = need.nU;
       J.nUpd = !propagate ? 0 : root ? T->stage.nURoot : T->stage.nU;
       J.nFilt = propagate ? T->stage.nF : 0;
       need.add(T, propagate, J.nPop > 0, root);
@@ -1936,6 +1945,7 @@ namespace {
 struct BatchPlan {
   bool nodes = false;
   size_t stagedBytes = 0;  // staged scratch of all jobs at once
+  bool streamRoots = false;  // all jobs are roots, with enough granules for the streaming update
   size_t nodesBytes = 0;   // search-node records, row vectors and non-zero words
   size_t descBytes = 0;    // job descriptors
   // what a no-allocation batch is held to: the descriptors, three ints a job
@@ -1954,12 +1964,17 @@ BatchPlan batch_plan(const ct_job* jobs, int n_jobs, bool nodes) {
     if (use_roots(jobs, n_jobs))
       for (int j = 0; j < n_jobs; ++j) p.rootInts += 2 * ((size_t)(jobs[j].table->nGran + WAVES - 1) / WAVES);
     StageNeed need;
+    bool roots = true;
+    int64_t granules = 0;
     for (int j = 0; j < n_jobs; ++j) {
       const ct_table* T = jobs[j].table;
       const bool propagate = jobs[j].flags & CT_JOB_PROPAGATE, root = jobs[j].flags & CT_JOB_ROOT;
+      roots = roots && root && T->kind != CT_KIND_NEGATIVE;
+      granules += T->nGran;
       if (batch_staged(T, propagate, STAGE_SCRATCH, root)) need.add(T, propagate, false, root);
     }
     p.stagedBytes = need.bytes();
+    p.streamRoots = roots && stage_stream_roots(granules);
   }
   p.descBytes = align256(sizeof(DevJob) * (size_t)n_jobs);
   p.limitBytes = p.descBytes + sizeof(int32_t) * (2 * (size_t)(n_jobs + 1) + (size_t)n_jobs + 2 + p.rootInts);
@@ -1978,6 +1993,7 @@ struct BatchRes {
   void* dNodes = nullptr;
   DevJob* hJobs = nullptr;      // n_jobs
   int32_t* chunks = nullptr;    // n_jobs
+  uint64_t* order = nullptr;    // n_jobs
   char* dStaged = nullptr;      // staged scratch
   size_t capStaged = 0;
   size_t countBytes = 0;        // not 0: the copy's first bytes are the staged schedule's item counts
@@ -1987,7 +2003,7 @@ struct BatchRes {
 // to the slots' host mirrors), stages them and launches it.
 int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* status_dev, const BatchPlan& p,
                  const BatchRes& r) {
-  const BatchShape B = batch_build(jobs, n_jobs, status_dev, p.nodes, r.capStaged, r.hJobs, r.chunks);
+  const BatchShape B = batch_build(jobs, n_jobs, status_dev, p.nodes, p.streamRoots, r.capStaged, r.hJobs, r.chunks, r.order);
   memset(r.hStage, 0, r.countBytes);
   memcpy(r.hStage + r.countBytes, r.hJobs, sizeof(DevJob) * n_jobs);
   // A staged batch's descriptors are read once, by the prep, straight from the
@@ -2027,7 +2043,8 @@ int batch_launch(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* st
     need.wide = B.wide;
     need.wideDom = B.wideDom;
     for (int j = j0; j < j1; ++j) need.add_items(r.hJobs[j].nUpd, r.hJobs[j].nFilt);
-    const StageArgs A = stage_args(need, r.dStaged, r.queue, r.hostErr, r.countBytes ? (StageCounts*)r.dStage : nullptr);
+    StageArgs A = stage_args(need, r.dStaged, r.queue, r.hostErr, r.countBytes ? (StageCounts*)r.dStage : nullptr);
+    A.roots = p.streamRoots;
     a.jobs = dJobs + j0;
     a.nJobs = need.nJobs;
     HIPCHK(launch_staged(a, A, need.nU, need.nF, B.popGran, stream));
@@ -2063,6 +2080,7 @@ struct NoAllocHost {
   hipStream_t lastStream = nullptr;  // the stream of the last call (ct_batch_status)
   DevJob jobs[NA_MAX_JOBS];
   int32_t chunks[NA_MAX_JOBS];
+  uint64_t order[NA_MAX_JOBS];
   alignas(256) char stage[NA_STAGE_BYTES];
 };
 NoAllocHost g_na;
@@ -2144,6 +2162,7 @@ int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32
   }
   q->hJobs.resize(n_jobs);
   q->chunks.resize(n_jobs);
+  q->order.resize(n_jobs);
   // the next buffer when this one is full: its batches of last time have ended
   if (q->usedStage + p.descBytes > q->capStage) {
     HIPCHK(hipEventRecord(q->staged[q->turn], stream));
@@ -2161,6 +2180,7 @@ int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32
   r.dNodes = q->dNodes;
   r.hJobs = q->hJobs.data();
   r.chunks = q->chunks.data();
+  r.order = q->order.data();
   r.dStaged = q->dStaged;
   r.capStaged = q->capStaged;
   return batch_launch(jobs, n_jobs, stream, status_dev, p, r);
@@ -2199,6 +2219,7 @@ int ct_propagate_batch_noalloc(const ct_job* jobs, int32_t n_jobs, void* stream_
   r.dNodes = scratch + NA_QUEUE_BYTES + NA_STAGE_BYTES;
   r.hJobs = g_na.jobs;
   r.chunks = g_na.chunks;
+  r.order = g_na.order;
   r.dStaged = (char*)r.dNodes;
   r.capStaged = nodesCap;
   // the item counts start at zero, whatever an earlier call left: they come

@@ -59,9 +59,10 @@ constexpr int FIN_WORDS = 4, FIN_WIDE_GRAN = 64;
 constexpr int PREP_WIDE_D = 512;  // domain words that want the large prep workgroup
 
 // Waves that share a granule's row list in a batch of roots, which select most
-// rows of their tables: one wave's chain of round trips over 600 rows took as
-// long as the whole batch's traffic (400 tables of up to 500,000 tuples: the
-// update 93 us, split 79: 410 MB at 5.2 TB/s).
+// rows of their tables, too small to stream (stage_stream_roots): one wave's
+// chain of round trips over 600 rows takes as long as the whole batch's
+// traffic (300 tables of up to 500,000 tuples: 92 us a batch, streamed 96;
+// 100 tables 50 against 79).
 constexpr int SPLIT_ROWS = 96;
 __host__ __device__ inline int stage_parts(int nrows) {
   return nrows >= 2 * SPLIT_ROWS ? 4 : nrows >= SPLIT_ROWS ? 2 : 1;
@@ -807,6 +808,8 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
   CT_G SlotDesc* s = J.slot;
   const int n = T->n, D = T->D, nGran = T->nGran;
   const bool fromRoot = J.flags & JF_FROM_ROOT, root = J.flags & JF_ROOT, scratch = J.flags & JF_SCRATCH;
+  if (A.roots)  // (also of a job that is rejected: the update looks at the record)
+    for (int k = tid; k < (nGran + SWAVES - 1) / SWAVES; k += PBLOCK) A.items[J.seq + k] = StageItem{job, k};
   // the slot's state before the job
   int depth = s->depth, limit = s->limit, failed = s->failed, serial = s->serial;
   const int cur = s->cur;
@@ -1129,7 +1132,7 @@ __global__ void __launch_bounds__(PBLOCK, 4) stage_prep_kernel(KArgs a, StageArg
       // inactive ones are written too); finish items: the partition, then
       // FIN_WORDS domain words each
       const int pos = fromRoot || J.ct_out ? nGran : limit;
-      const int nU = (pos * R.parts + SWAVES - 1) / SWAVES, nF = 1 + (D + FIN_WORDS - 1) / FIN_WORDS;
+      const int nU = A.roots ? 0 : (pos * R.parts + SWAVES - 1) / SWAVES, nF = 1 + (D + FIN_WORDS - 1) / FIN_WORDS;
       const int l = job % STAGE_LISTS;
       const unsigned long long at = atomicAdd((unsigned long long*)&A.count->n[l * STAGE_LINE],
                                               (unsigned long long)(uint32_t)nF << 32 | (uint32_t)nU);
@@ -1190,6 +1193,63 @@ __global__ void __launch_bounds__(SBLOCK, 8) stage_update_kernel(StageArgs A) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Update of a large launch of root jobs (stage_stream_roots): a wave per granule
+// streams the rows of the input's values, ROOT_U in flight, reading nothing
+// else (no row list, no old words).  A workgroup's four waves take adjacent
+// granules, 2 KB of every row.  The items lie in the order of the jobs, which
+// the host sorts by support rows, so the longest waves start first and a
+// table's granules spread over the XCDs.
+// Bound: HBM.  2,000 tables of up to 500,000 tuples, 1.8 GB: 315 us, 5.7 TB/s;
+// with row lists shared by a granule's waves 350; in the order in which the
+// preps end 342.
+// ---------------------------------------------------------------------------
+constexpr int ROOT_U = 4;
+
+__global__ void __launch_bounds__(SBLOCK, 8) stage_root_kernel(StageArgs A) {
+  if (blockIdx.x == 0 && threadIdx.x < STAGE_LISTS)  // (the finish empties the counts)
+    A.count->fin[threadIdx.x] = (int32_t)(A.count->n[threadIdx.x * STAGE_LINE] >> 32);
+  const CT_K StageItem* it = (const CT_K StageItem*)A.items + blockIdx.x;
+  const CT_K StageRec* R = (const CT_K StageRec*)(A.rec + it->job);
+  const int g = it->chunk * SWAVES + s_wave();
+  if (!R->run || g >= R->nGran) return;
+  const unsigned lane = (unsigned)s_lane();
+  const TabDesc* T = (const TabDesc*)R->tab;
+  const CT_K VarDesc* vars = (const CT_K VarDesc*)T->vars;
+  const CT_K uint64_t* din = (const CT_K uint64_t*)R->din;
+  const int n = T->n;
+  const int64_t stride = R->stride, w0 = (int64_t)g * GW;
+  uint64_t m = all_tuples(T, w0 + lane);
+  for (int i = 0; i < n; ++i) {
+    const VarDesc v = vars[i];
+    uint64_t acc = 0ull;
+    for (int k = 0; k < v.domWords; ++k) {
+      uint64_t bits = din[v.domOff + k];
+      const CT_G uint64_t* rows = R->S + (int64_t)(v.rowStart + 64 * k) * stride + w0;
+      int b = 0;
+      while (bits) {
+        uint64_t x[ROOT_U];
+#pragma unroll
+        for (int u = 0; u < ROOT_U; ++u) {
+          if (bits) {  // past the last value: the previous row again
+            b = __ffsll((unsigned long long)bits) - 1;
+            bits &= bits - 1;
+          }
+          x[u] = __builtin_nontemporal_load(rows + (int64_t)b * stride + lane);
+        }
+#pragma unroll
+        for (int u = 0; u < ROOT_U; ++u) acc |= x[u];
+      }
+    }
+    m &= acc;
+    if (__ballot(m != 0ull) == 0ull) break;
+  }
+  R->ct[w0 + lane] = m;
+  if (R->ct_out && w0 + lane < R->W) R->ct_out[w0 + lane] = m;
+  const bool nz = __ballot(m != 0ull) != 0ull;
+  if (lane == 0) R->nz[g] = nz ? 1 : 0;
+}
+
 // Device-clock duration of the three launches: first prep workgroup's start
 // to the last finish workgroup's end.
 __device__ void stage_clock_end(unsigned long long* clock) {
@@ -1246,6 +1306,11 @@ int stage_update_items(int nGran, int rows) { return (nGran * stage_parts(rows) 
 // CU (roots of 400 tables: the finish 20 us against 12; 128 searches 9 against
 // 11).
 bool stage_wide_launch(bool wide, int nF) { return wide && nF <= stage_grid() / 8; }
+// A launch of roots streams from half as many granules as waves run at once
+// (mixes of tables of up to 500,000 tuples, a tenth of the values removed:
+// 4,891 granules 123 us against 128, 10,102 195 against 222, 8,033 of large
+// tables 150 against 176; 3,643 96 against 92, 1,039 79 against 50).
+bool stage_stream_roots(int64_t granules) { return granules >= (int64_t)stage_grid() * SWAVES / 2; }
 bool stage_wide_dom(int D) { return D > PREP_WIDE_D; }
 bool stage_wide(int nGran) { return nGran > FIN_WIDE_GRAN; }
 int stage_finish_items(int D) { return 1 + (D + FIN_WORDS - 1) / FIN_WORDS; }
@@ -1274,7 +1339,8 @@ void launch_prep(const KArgs& a, const StageArgs& A, const ModelRound& M, int po
 void launch_items(const StageArgs& A, int nU, int nF, bool sparse, hipStream_t stream) {
   if (nF <= 0) return;
   const int gu = A.items ? std::min(std::max(nU, 1), sparse ? stage_grid() : 1 << 20) : nU;
-  hipLaunchKernelGGL(stage_update_kernel, dim3(gu), dim3(SBLOCK), 0, stream, A);
+  if (A.roots) hipLaunchKernelGGL(stage_root_kernel, dim3(gu), dim3(SBLOCK), 0, stream, A);
+  else hipLaunchKernelGGL(stage_update_kernel, dim3(gu), dim3(SBLOCK), 0, stream, A);
   if (A.wide) {
     const int gf = A.items ? std::min(nF, stage_grid() / 4) : nF;
     hipLaunchKernelGGL(stage_finish_kernel<1024>, dim3(gf), dim3(1024), 0, stream, A);

@@ -395,3 +395,62 @@ def test_queued_batches_keep_their_descriptors(sizes):
             w = want[(b + k) % 7]
             assert st[k] == (O.FAIL if w is None else O.OK), (b, k)
             assert w is None or (got[k] == w).all(), (b, k)
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("extra", [0, 1])
+def test_large_root_batches(extra, noalloc):
+    """Root batches of about as many granules as the streaming update takes up
+    (4,096 on 256 compute units): just below it, and above with rejected jobs,
+    emptied variables and tables of every size among the others."""
+    names = {"64 granules": 63 + 2 * extra, "5 granules": 6, "one granule": 9, "260 granules": extra,
+             "one granule, 17 words": 3, "513 words": 2}
+    say("large root batch:", names, "noalloc", noalloc)
+    rng = W.rng_for(len(names), 936, extra)
+    jobs, want, tabs = [], [], []
+    for name, slots in names.items():
+        ds, t, star, _, _ = TABLES[name]
+        lo, d = np.zeros(len(ds), np.int32), np.array(ds, np.int32)
+        tup = np.stack([rng.integers(0, x, size=t) for x in ds], 1).astype(np.int32)
+        if name == "5 granules":
+            tup[rng.random(tup.shape) < 0.03] = ct.STAR
+        g = ct.Table(tup, lo, d, max_depth=0)
+        tabs.append(g)
+        lay = W.DomLayout(d, lo)
+        doms = [lay.full(), W.pick_fraction_removal(rng, lay, lay.full(), frac=0.6, nvars=(1, 2)), lay.full(), lay.full()]
+        doms[2][0] = 0 if lay.words[0] == 1 else doms[2][0]  # a variable without a value
+        doms[3][-1] = ~np.uint64(0)  # values beyond the domain, if its last word has room for them
+        ref = []
+        for k, dom in enumerate(doms):
+            if k == 3 and ds[-1] % 64:
+                ref.append((ct.E_INVALID,) + O.OracleTable(tup, lo, d).state()[:2])
+            else:
+                o = O.OracleTable(tup, lo, d, init_dom=dom)
+                ref.append((o.create_status,) + o.state()[:2])
+        first = g.slots_alloc(slots, max_depth=0) if slots else 0
+        for s in range(slots):
+            k = int(rng.integers(0, 4)) if s > 1 else s
+            din = torch.from_numpy(doms[k].view(np.int64).copy()).cuda()
+            dout = torch.full_like(din, -1)
+            cout = torch.full((g.W,), -1, dtype=torch.int64, device="cuda") if s % 3 == 0 else None
+            jobs.append(dict(table=g, slot=first + s, flags=ct.JOB_PROPAGATE | ct.JOB_ROOT, dom_in=din, dom_out=dout,
+                             ct_out=cout))
+            want.append((name, s, ref[k]))
+    turn = rng.permutation(len(jobs))
+    jobs, want = [jobs[k] for k in turn], [want[k] for k in turn]
+    assert (sum(j["table"].granules for j in jobs) >= 4096) == bool(extra)
+    status = torch.full((len(jobs),), 99, dtype=torch.int32, device="cuda")
+    for _ in range(2):
+        ct.propagate_batch(jobs, status, noalloc=noalloc)
+    ct.batch_status()
+    st = status.cpu().numpy()
+    for j, (name, s, (ws, wd, wc)) in enumerate(want):
+        assert st[j] == ws, (name, s)
+        sd, sc = jobs[j]["table"].state(jobs[j]["slot"])
+        assert (sc == wc).all(), (name, s)
+        if ws != O.FAIL:
+            assert (sd == wd).all(), (name, s)
+        if ws == O.OK:
+            assert (jobs[j]["dom_out"].cpu().numpy().view(np.uint64) == wd).all(), (name, s)
+            c = jobs[j]["ct_out"]
+            assert c is None or (c.cpu().numpy().view(np.uint64) == wc).all(), (name, s)

@@ -1155,9 +1155,8 @@ __device__ __forceinline__ void do_filter(const KArgs& a, const DevJob& J, int c
 // (sh.dcnt[i], capped above the tuple count) of them have x_i = a.
 // sh.rows[0 .. total) lists the values to count (domain word << 6 | bit); a
 // wave counts NEG_VALS of them, a granule's words of each in one coalesced
-// load, and clears those without an allowed tuple from sh.dout.  (One lane per
-// value, walking its row, read 64 rows a load: 12,000 tuples, 5 variables of
-// 8 values, 28 us a call against 22.)
+// load, and clears those without an allowed tuple from sh.dout.  Many values
+// over few granules take neg_count_word instead (neg_by_lane).
 // ---------------------------------------------------------------------------
 constexpr int NEG_VALS = 4, NEG_GRAN = 4;  // values per wave, granules in flight
 __device__ void neg_count(const DevJob& J, int total, int lim, const CT_G int32_t* idx, Shared& sh) {
@@ -1202,6 +1201,40 @@ __device__ void neg_count(const DevJob& J, int total, int lim, const CT_G int32_
   }
 }
 
+// The same for the values of domain word q, one to a lane, which walks its row
+// (64 rows a load: slow per granule, but a wave has 64 values in hand).
+__device__ void neg_count_word(const DevJob& J, int q, int lim, const CT_G int32_t* idx, Shared& sh) {
+  const TabDesc* T = J.tab;
+  const CT_G uint64_t* ct = J.slot->ct;
+  const int i = T->wordVar[q];
+  const VarDesc v = T->vars[i];
+  const uint64_t din = sh.din[q];
+  const int prod = sh.dcnt[i];
+  if (din == 0ull || prod > (int64_t)lim * GW * 64) return;
+  const int lane = lane_id();
+  const bool present = (din >> lane) & 1ull;
+  const int row = v.rowStart + (q - v.domOff) * 64 + (present ? lane : 0);
+  const CT_G uint64_t* srow = T->S + (int64_t)row * T->stride;
+  int cnt = 0;
+  for (int p = 0; p < lim; ++p) {
+    const int64_t base = (int64_t)idx[p] * GW;
+#pragma unroll 8
+    for (int k = 0; k < GW; ++k) cnt += __popcll(ct[base + k] & srow[base + k]);
+  }
+  const uint64_t gone = __ballot(present && cnt == prod);
+  if (lane == 0) sh.dout[q] = din & ~gone;
+}
+
+// Which of the two counts `values` values in `words` domain words over `lim`
+// granules: by their round trips, those of a lane's walk counted four times
+// (us a call, by lane / by wave: 305 values, 1 granule 20 / 27; 120, 1: 21 / 25;
+// 200, 2: 26 / 28; 4,005, 5: 49 / 66; 90, 5: 25 / 23; 45, 3: 27 / 22; 400, 8:
+// 54 / 42; 100, 49: 217 / 76).
+__device__ __forceinline__ bool neg_by_lane(int values, int words, int lim) {
+  const int byWave = (values + WAVES * NEG_VALS - 1) / (WAVES * NEG_VALS) * ((lim + NEG_GRAN - 1) / NEG_GRAN);
+  return byWave >= 4 * ((words + WAVES - 1) / WAVES) * lim;
+}
+
 // A negative table's filterDomains in one workgroup, after updateTable and
 // its partition (st: the job status so far): per-variable products,
 // every variable filtered into sh.dout, failure iff a domain empties.  On
@@ -1235,20 +1268,27 @@ __device__ int neg_filter(const DevJob& J, Shared& sh, int st, int* rows2) {
     for (int q = b; q < e; ++q) {
       const uint64_t din = sh.din[q];
       sh.dout[q] = din;
-      cnt += sh.noop || sh.dcnt[T->wordVar[q]] > most ? 0 : __popcll(din);
+      if (!sh.noop && sh.dcnt[T->wordVar[q]] <= most) cnt += (din ? 1 << 16 : 0) + __popcll(din);
     }
+    // (words << 16 | values: at most 1,024 and 8,192)
     int total = 0;
-    int off = block_scan_excl(cnt, &total, sh);
-    for (int q = b; q < e; ++q) {
-      uint64_t bits = sh.noop || sh.dcnt[T->wordVar[q]] > most ? 0ull : sh.din[q];
-      while (bits) {
-        const int k = __ffsll((unsigned long long)bits) - 1;
-        bits &= bits - 1;
-        sh.rows[off++] = (uint32_t)(q << 6 | k);
+    int off = block_scan_excl(cnt, &total, sh) & 0xffff;
+    const int words = total >> 16, values = total & 0xffff;
+    if (neg_by_lane(values, words, lim)) {
+      if (values)
+        for (int q = wave_id(); q < D; q += WAVES) neg_count_word(J, q, lim, s->idx[s->cur], sh);
+    } else {
+      for (int q = b; q < e; ++q) {
+        uint64_t bits = sh.noop || sh.dcnt[T->wordVar[q]] > most ? 0ull : sh.din[q];
+        while (bits) {
+          const int k = __ffsll((unsigned long long)bits) - 1;
+          bits &= bits - 1;
+          sh.rows[off++] = (uint32_t)(q << 6 | k);
+        }
       }
+      __syncthreads();
+      neg_count(J, values, lim, s->idx[s->cur], sh);
     }
-    __syncthreads();
-    neg_count(J, total, lim, s->idx[s->cur], sh);
   }
   __syncthreads();
   for (int i = threadIdx.x; i < n; i += BLOCK) {

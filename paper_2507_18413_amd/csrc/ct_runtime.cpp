@@ -516,9 +516,14 @@ int run_single(ct_table* T, DevJob& J, const uint64_t* dom_in_host) {
     A.items = nullptr;  // one job: its items by workgroup
     J.listCap = stage_list_cap(T);
   }
-  // a propagation answers through flagged slots (not staged, with a currTable
-  // copy: that one keeps the fenced status)
-  const bool ll = (J.flags & JF_PROPAGATE) && (staged || !J.ct_out) && T->pLL;
+  // a propagation answers through flagged slots; not with a currTable copy
+  // that is not staged (that one keeps the fenced status), nor a negative
+  // table of many domain words, whose one workgroup writes all the slots (7
+  // words 26 us a call against 27 fenced, 18 words the same, 65 words 71
+  // against 66, 200 words 60 against 30)
+  constexpr int NEG_LL_D = 16;
+  const bool ll = (J.flags & JF_PROPAGATE) && (staged || !J.ct_out) && T->pLL &&
+                  (T->kind != CT_KIND_NEGATIVE || T->D <= NEG_LL_D);
   uint32_t sq = 0;
   if (ll) {
     J.flags |= JF_LL;

@@ -150,3 +150,48 @@ def test_kind_errors():
     g = ct.Table(np.array([[0, 1]], np.int32), [0, 0], [2, 2], kind=ct.KIND_NEGATIVE)
     with pytest.raises(ct.CTError):
         ct.SplitPropagator(g, ct.SPLIT_FILTER)
+
+
+# domain sizes, tuples: values counted by lane and by wave, on both sides of
+# the line between them; 16 and 17 domain words (flagged and fenced answers)
+@pytest.mark.parametrize("ds,t", [
+    ([60, 60], 3400), ([64, 65], 4000), ([3, 2, 300], 1500), ([100, 100], 9600), ([200, 200], 39_000),
+    ([30, 30, 30], 24_000), ([2, 2, 896], 2900), ([2, 2, 897], 3100), ([2, 4000], 7000), ([2, 2, 8000], 20_000),
+])
+def test_negative_counts_by_lane_and_by_wave(ds, t):
+    say("negative table: domains", ds, t, "tuples")
+    rng = W.rng_for(len(ds), 437, t)
+    d, lo = np.array(ds, np.int32), np.arange(len(ds), dtype=np.int32) - 1
+    lay = W.DomLayout(d, lo)
+    space = int(np.prod(d.astype(np.int64)))
+    pick = rng.choice(space, size=min(t, space), replace=False)
+    tup = np.stack(np.unravel_index(pick, ds), 1).astype(np.int32) + lo
+    g, o = ct.Table(tup, lo, d, kind=ct.KIND_NEGATIVE), O.OracleTable(tup, lo, d, kind=ct.KIND_NEGATIVE)
+    assert g.create_status == o.create_status and (g.domains() == o.domains()).all()
+    depth, pruned = 0, False
+    for step in range(16):
+        g.push()
+        o.push()
+        depth += 1
+        dom = o.domains()
+        for i in rng.choice(len(ds), size=int(rng.integers(1, len(ds) + 1)), replace=False):
+            vals = lay.values(dom, int(i))
+            share = rng.choice([0.1, 0.5, 0.9]) if step % 2 else 0.05
+            gone = vals[rng.random(vals.size) < share]
+            for a in gone[1:] if gone.size == vals.size else gone:
+                lay.clear(dom, int(i), int(a))
+        if step % 3 == 2:
+            gs, gd, gc = g.propagate(dom, want_ct=True)
+        else:
+            (gs, gd), gc = g.propagate(dom), None
+        os_, od, oc = o.propagate(dom, want_ct=True)
+        assert gs == os_, step
+        if os_ == O.OK:
+            assert (gd == od).all() and (gc is None or (gc == oc).all()), step
+            pruned = pruned or (od != dom).any()
+        for _ in range(int(rng.integers(0, 2)) if os_ == O.OK else 1):
+            g.pop()
+            o.pop()
+            depth -= 1
+        assert (g.state()[0] == o.state()[0]).all() and (g.state()[1] == o.state()[1]).all(), step
+    assert pruned

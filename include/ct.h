@@ -77,11 +77,14 @@ typedef struct ct_table ct_table;
  * per row fits a workgroup's LDS), updateTable is evaluated per tuple for 64
  * jobs at a time.  It reads a list of the tuples' row numbers (2 bytes per
  * cell) that the library makes, in device memory of the table, once the
- * table has 64 slots (or has CT_SCHED_NODES); without memory for it, and for
+ * table has slots for a batch that AUTO runs so (or has CT_SCHED_NODES);
+ * without memory for it, and for
  * other batches and single calls, AUTO applies.  AUTO picks SOLO for calls on
  * tables of at most 4 granules (16,384 tuples) and at most 16 domain words
  * (wider tables spread filterDomains over workgroups), and NODES for eligible
- * batches of at least 64 jobs.  On an AUTO table of more than
+ * batches of at least 64 jobs for which it is the faster one: of many jobs on
+ * large tables of few variables (its time goes with the variables, the
+ * staged launches' with jobs x granules x support rows).  On an AUTO table of more than
  * 64 and at most 256 domain words whose update is one SPLIT item (at most 8
  * granules), with variables of at most 31 domain words, plain synchronous
  * calls on slot 0 (no currTable copy, no counters) go to the resident split
@@ -318,7 +321,7 @@ int ct_propagate_batch(const ct_job *jobs, int32_t n_jobs, void *stream, int32_t
  * static device array of 16 MiB that each GPU holds until the process ends
  * (set up on the device's first call), and the descriptors are built in
  * static host arrays.  Limits: at most 8,192 jobs, at most 2 MiB of staged
- * descriptors (about 88 bytes per job plus the root tasks of a batch of
+ * descriptors (about 116 bytes per job plus the root tasks of a batch of
  * CT_JOB_ROOT jobs: one per 4 granules), and for a batch on the search-node
  * schedule of a table of at most 256 support rows at most 14 MiB, counted as
  * 8 x (4 + (rows + 3 x arity + 3) / 4) + granules bytes per job; a batch
@@ -434,7 +437,8 @@ int ct_model_get_choice(const ct_model *m, int32_t table, int32_t *solo, int32_t
 typedef struct ct_server ct_server;
 
 typedef struct {
-    int64_t mem_budget;  /* bytes of slot state admitted at once; <= 0: unlimited */
+    int64_t mem_budget;  /* bytes of slot state admitted at once; <= 0: unlimited
+                            (slots only, not what their tables hold besides) */
     int32_t max_batch;   /* requests per launch; <= 0: 1024 */
     int32_t streams;     /* launches in flight; <= 0: 2 */
 } ct_server_cfg;
@@ -550,7 +554,8 @@ const char *ct_last_error(void);
 /* Test hook for the callers' error paths: the nth device or pinned host
  * allocation the library makes from now on (tables, slots, batch staging,
  * models) fails as if the memory were exhausted, and the call that made it
- * returns CT_E_NOMEM after releasing what it had allocated; nth <= 0 turns
+ * returns CT_E_NOMEM after releasing what it had allocated (without the
+ * search-node schedule's row numbers it goes on instead); nth <= 0 turns
  * the hook off.  Returns the previous setting (allocations still to go). */
 int ct_debug_fail_alloc(int32_t nth);
 

@@ -47,6 +47,7 @@ size_t nodes_ids_bytes(int n, int64_t stride);
 hipError_t launch_nodes_ids(const TabDesc* T, int nGran, uint16_t* ids, hipStream_t stream);
 hipError_t launch_nodes(NodesDesc N, char* scratch, hipStream_t stream);
 hipError_t noalloc_scratch(char** ptr, size_t* bytes);
+int slots_alloc(ct_table* T, int32_t n, int32_t max_depth, bool search, int32_t* first_slot);
 hipError_t launch_build_supports(const BuildArgs& B, hipStream_t stream);
 hipError_t launch_init_root(TabDesc* T, SlotDesc* root, const uint64_t* dom0, int64_t words, hipStream_t stream);
 hipError_t launch_init_first(TabDesc* T, SlotDesc* slot, SlotDesc* root, const uint64_t* dom0, const int32_t* star,
@@ -335,14 +336,29 @@ int device_lds() {
   return lds;
 }
 
+// Whether the search-node schedule pays for a batch of n jobs (AUTO).  It takes
+// 5 us more than the staged launches and 0.6 us for each variable (a tuple's
+// row numbers are read in turn), whatever the jobs remove; the staged update
+// takes, for each granule of each job, 0.7 ns and 0.06 ns a support row it
+// ORs, a fifth of the table's being what search nodes have removed at most
+// (half a variable's values, on average of none to a few tenths).  Measured,
+// search nodes / staged us: 100 variables of 20 values, 100,000 tuples, 64
+// jobs 88 / 25; 6 of 20, 60,000, 256 jobs 37 / 24-29, 1,024 jobs 43 / 45-60,
+// 400,000, 256 jobs 38 / 38-62; 16 of 60, 400,000, 64 jobs 37-70 / 25-184; 200
+// of 3, 60,000, 1,024 jobs 195 / 150-225; 100 of 20, 400,000, 256 jobs 107 /
+// 51-1,323.
+bool nodes_pays(const ct_table* T, int n) {
+  return (double)T->nGran * n * (7e-4 + 1.2e-5 * T->rows) >= 5 + 0.6 * T->n;
+}
+
 // The search-node schedule reads, per tuple, the row numbers of its values
-// (2 bytes each).  They are made once per table, when its slots reach the
-// smallest batch the schedule takes (or at the first such batch): a table
-// never searched that way does not pay for them.  Without memory for them
-// the batches take the other schedules.
+// (2 bytes each).  They are made once per table, when its slots reach a batch
+// for which the schedule pays (or at the first such batch): a table never
+// searched that way does not pay for them.  Without memory for them the
+// batches take the other schedules.
 bool nodes_ids_ensure(ct_table* T) {
   if (T->dIds) return true;
-  if (T->nodesVecRows == 0) return false;
+  if (T->nodesVecRows == 0 || alloc_injected()) return false;
   void* p = nullptr;
   if (hipMalloc(&p, nodes_ids_bytes(T->n, T->stride)) != hipSuccess) {
     (void)hipGetLastError();
@@ -368,9 +384,9 @@ bool use_roots(const ct_job* jobs, int n) {
   return true;
 }
 
-// The search-node schedule takes a batch whose jobs all reset slots of one
+// The search-node schedule can take a batch whose jobs all reset slots of one
 // table to the root and propagate (the slots are distinct: checked before).
-bool nodes_batch(const ct_job* jobs, int n) {
+bool nodes_form(const ct_job* jobs, int n) {
   const ct_table* T = jobs[0].table;
   if (T->cfg.schedule != CT_SCHED_NODES && (T->cfg.schedule != CT_SCHED_AUTO || n < NODES_MIN_BATCH))
     return false;
@@ -378,6 +394,10 @@ bool nodes_batch(const ct_job* jobs, int n) {
   for (int j = 0; j < n; ++j)
     if (jobs[j].table != T || jobs[j].flags != (CT_JOB_PROPAGATE | CT_JOB_FROM_ROOT)) return false;
   return true;
+}
+
+bool nodes_batch(const ct_job* jobs, int n) {
+  return nodes_form(jobs, n) && (jobs[0].table->cfg.schedule == CT_SCHED_NODES || nodes_pays(jobs[0].table, n));
 }
 
 // Staged schedule: what a job needs of a launch's scratch.  A launch's
@@ -1664,14 +1684,18 @@ int ct_get_supports(ct_table* T, int32_t row_begin, int32_t n_rows, uint64_t* ou
   return CT_OK;
 }
 
-int ct_slots_alloc(ct_table* T, int32_t n, int32_t max_depth, int32_t* first_slot) {
+}  // extern "C"
+
+// ct_slots_alloc; search: the slots may serve search-node batches.
+int ctk::slots_alloc(ct_table* T, int32_t n, int32_t max_depth, bool search, int32_t* first_slot) {
   int rc = check_poison(T);
   if (rc) return rc;
   if (n < 1) return fail(CT_E_INVALID, "n < 1");
   if ((rc = quiesce(T))) return rc;
   if (max_depth < 0) max_depth = T->cfg.max_depth;
-  if (T->cfg.schedule == CT_SCHED_NODES ||
-      (T->cfg.schedule == CT_SCHED_AUTO && (int)T->slots.size() + n >= NODES_MIN_BATCH))
+  const int all = (int)T->slots.size() + n;
+  if (search && (T->cfg.schedule == CT_SCHED_NODES ||
+                 (T->cfg.schedule == CT_SCHED_AUTO && all >= NODES_MIN_BATCH && nodes_pays(T, all))))
     (void)nodes_ids_ensure(T);
   // reuse: the first run of n consecutive freed slots whose trails hold
   // max_depth levels; each is reset to the root state
@@ -1707,6 +1731,12 @@ int ct_slots_alloc(ct_table* T, int32_t n, int32_t max_depth, int32_t* first_slo
   if (first_slot) *first_slot = (int32_t)T->slots.size();
   slots_add(T, d, n, max_depth);
   return CT_OK;
+}
+
+extern "C" {
+
+int ct_slots_alloc(ct_table* T, int32_t n, int32_t max_depth, int32_t* first_slot) {
+  return slots_alloc(T, n, max_depth, true, first_slot);
 }
 
 int ct_slots_free(ct_table* T, int32_t first, int32_t n) {
@@ -2205,7 +2235,8 @@ int ct_propagate_batch_noalloc(const ct_job* jobs, int32_t n_jobs, void* stream_
   const size_t nodesCap = scratchBytes - NA_QUEUE_BYTES - NA_STAGE_BYTES;
   // (the row numbers of the search-node schedule are made by ct_slots_alloc)
   const bool nodes = nodes_batch(jobs, n_jobs);
-  if (nodes && jobs[0].table->rows <= NA_NODES_ROWS && na_nodes_bytes(jobs[0].table, n_jobs) > nodesCap)
+  if (nodes_form(jobs, n_jobs) && jobs[0].table->rows <= NA_NODES_ROWS &&
+      na_nodes_bytes(jobs[0].table, n_jobs) > nodesCap)
     return fail(CT_E_INVALID, "ct_propagate_batch_noalloc: the search-node schedule needs %zu scratch bytes, "
                 "at most %zu", na_nodes_bytes(jobs[0].table, n_jobs), nodesCap);
   BatchPlan p = batch_plan(jobs, n_jobs, nodes && jobs[0].table->dIds);

@@ -30,6 +30,7 @@ namespace ctk {
 // internal accessors of the runtime (ct_runtime.cpp)
 int64_t slot_footprint(const ct_table* t, int max_depth);
 int root_domains(ct_table* t, uint64_t* out);
+int slots_alloc(ct_table* t, int32_t n, int32_t max_depth, bool search, int32_t* first_slot);
 void set_error(const char* msg);
 }  // namespace ctk
 
@@ -142,7 +143,7 @@ bool admit(ct_server* s, Search& S) {
   ct_layout_info before{};
   if (ct_layout(ti.T, &before, nullptr) != CT_OK) return false;
   int32_t slot = -1;
-  if (ct_slots_alloc(ti.T, 1, ti.maxDepth, &slot) != CT_OK) return false;
+  if (ctk::slots_alloc(ti.T, 1, ti.maxDepth, false, &slot) != CT_OK) return false;
   if (slot >= before.n_slots) s->stats[5]++;
   S.slot = slot;
   s->stats[3] += ti.slotBytes;

@@ -106,3 +106,57 @@ def test_nodes_edges(case, alias):
         o.pop()
         gs, gd = g.propagate(dom, slot=first + k)
         assert gs == os_ and (os_ != O.OK or (gd == od).all()), k
+
+
+# (domain sizes, tuples, jobs): on both sides of the line from which AUTO takes
+# the schedule, with few and with many variables
+@pytest.mark.parametrize("how", ["batch", "noalloc", "no memory for the row numbers"])
+@pytest.mark.parametrize("ds,t,jobs", [
+    ([20] * 6, 60_000, 267), ([20] * 6, 60_000, 269), ([6] * 40, 20_000, 70), ([60] * 8, 30_000, 300),
+])
+def test_auto_takes_either_schedule(ds, t, jobs, how):
+    say("AUTO, search nodes or staged:", len(ds), "variables", t, "tuples", jobs, "jobs,", how)
+    rng = W.rng_for(len(ds), 911, jobs)
+    lo, d = np.zeros(len(ds), np.int32), np.array(ds, np.int32)
+    tup = np.stack([rng.integers(0, x, size=t) for x in ds], 1).astype(np.int32)
+    g, o = ct.Table(tup, lo, d), O.OracleTable(tup, lo, d, fast=True)
+    lay = W.DomLayout(d, lo)
+    L = ct.lib()
+    fail = how.startswith("no memory")
+    L.ct_debug_fail_alloc(1 if fail else 0)
+    try:
+        first = g.slots_alloc(jobs, max_depth=0)
+    except ct.CTError as e:  # (no row numbers are made here: the slots' own memory)
+        assert fail and e.code == ct.E_NOMEM
+        first = g.slots_alloc(jobs, max_depth=0)
+    finally:
+        L.ct_debug_fail_alloc(0)
+    doms = [W.pick_fraction_removal(rng, lay, o.domains(), frac=f, nvars=(1, 3)) for f in (0.02, 0.1, 0.4, 0.7)]
+    want = []
+    for dom in doms:
+        o.push()
+        want.append((dom,) + tuple(o.propagate(dom, want_ct=True)))
+        o.pop()
+    din = torch.from_numpy(np.stack([doms[k % 4] for k in range(jobs)]).view(np.int64).copy()).cuda()
+    dout = torch.zeros_like(din)
+    status = torch.full((jobs,), 99, dtype=torch.int32, device="cuda")
+    batch = [dict(table=g, slot=first + k, flags=ct.JOB_PROPAGATE | ct.JOB_FROM_ROOT, dom_in=din[k], dom_out=dout[k])
+             for k in range(jobs)]
+    L.ct_debug_fail_alloc(1 if fail else 0)
+    try:
+        ct.propagate_batch(batch, status, noalloc=how == "noalloc")
+    except ct.CTError as e:  # (the schedule is not tried: the batch's own memory)
+        assert fail and e.code == ct.E_NOMEM
+        ct.propagate_batch(batch, status)
+    finally:
+        L.ct_debug_fail_alloc(0)
+    ct.batch_status()
+    st, got = status.cpu().numpy(), dout.cpu().numpy().view(np.uint64)
+    for k in range(jobs):
+        _, ws, wd, wc = want[k % 4]
+        assert st[k] == ws, k
+        if ws == O.OK:
+            assert (got[k] == wd).all(), k
+            if k < 8 or k > jobs - 4:
+                sd, sc = g.state(first + k)
+                assert (sd == wd).all() and (sc == wc).all(), k

@@ -373,8 +373,8 @@ int ct_model_layout(const ct_model *m, int32_t *pool_off, int32_t *pool_words);
  * convergence or failure.
  * Synchronous on `stream` (NULL = the model's own stream).  pool_out (device)
  * receives the fixpoint (undefined after CT_FAIL).  n_props (nullable)
- * receives the number of table propagations, n_rounds (nullable) the rounds
- * (see ct_model_set_schedule).
+ * receives the number of table propagations, n_rounds (nullable) the rounds,
+ * the last one, which changed nothing, among them.
  * Returns CT_OK or CT_FAIL.  After CT_FAIL the failed tables must be popped
  * (ct_model_pop) before the next fixpoint.
  */
@@ -387,28 +387,25 @@ int ct_model_fixpoint(ct_model *m, const uint64_t *pool_in, uint64_t *pool_out, 
 int ct_model_push(ct_model *m);
 int ct_model_pop(ct_model *m);
 
-/* Scheduling knob of the model's rounds: tables of at most solo_max_granules
- * granules are classed solo, larger ones split (what ct_model_get_choice
- * reports; a round takes the dirty tables of both classes in the same
- * launches).  A fixpoint counts its rounds (n_rounds) as one, one, then
- * rounds_per_graph at a time.  The default is chosen by ct_model_autotune or
- * is (4, 8). */
+/* Classes of the model's tables: tables of at most solo_max_granules granules
+ * are classed solo, larger ones split.  The class is what ct_model_get_choice
+ * reports and selects nothing: a round takes the dirty tables of both in the
+ * same launches, one round at a time (rounds_per_graph, 1 to 256, is checked
+ * and has no effect either).  The default threshold is 4. */
 int ct_model_set_schedule(ct_model *m, int32_t solo_max_granules, int32_t rounds_per_graph);
 
-/* Autotuner of the classes.  Tables are grouped in classes by
- * floor(log4) of their granule count and of their support-row count; each
- * class gets a choice, solo or split.
- * Classes are tuned one after the other, those with the most granules in all
- * first, each candidate timed as the median of 3 fixpoints from pool_in
- * (device pointer), every table restored between trials with a push / pop;
- * every candidate must reach the same fixpoint (CT_E_DEVICE otherwise).
+/* Classes by floor(log4) of the tables' granule count and of their support-row
+ * count, each with a choice, solo or split.  Both run the same launches: the
+ * call runs each candidate of each class, those with the most granules in all
+ * first, as 3 fixpoints from pool_in (device pointer), every table restored
+ * with a push / pop, checks that all reach the same fixpoint (CT_E_DEVICE
+ * otherwise), and gives a class the threshold's choice (ct_model_set_schedule).
  * cache_path (nullable): a JSON file of choices keyed by the device
  * architecture and the class buckets ("gfx950 g2 r3": [solo, tile], the tile
- * 0 or 2, 4, 8 in older files, all the same schedule); when
- * it holds every class of the model, those choices are applied without
- * timing anything (*from_cache = 1), otherwise the tuned choices are merged
- * into it.  *timed (nullable) receives the number of candidates timed.
- * Classes the tuner never saw follow ct_model_set_schedule's threshold. */
+ * 0 or 2, 4, 8 in older files); when
+ * it holds every class of the model, those choices are taken without
+ * running anything (*from_cache = 1), otherwise the choices are merged
+ * into it.  *timed (nullable) receives the number of candidates run. */
 int ct_model_autotune(ct_model *m, const uint64_t *pool_in, const char *cache_path, int32_t *from_cache,
                       int32_t *timed);
 /* The choice of table `table`'s class (index from ct_model_add): *solo = 1 or

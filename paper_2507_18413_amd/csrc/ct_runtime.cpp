@@ -2327,10 +2327,10 @@ struct ct_model {
   std::vector<std::vector<int32_t>> scopes;
   hipStream_t stream = nullptr;
   QueueCtx q;
-  int soloMax = 4, roundsPerGraph = 8;
+  int soloMax = 4;
   // (solo, tile) per class of tables (granule bucket, rows bucket), set by the
-  // autotuner; classes without an entry follow soloMax.  Rounds run staged
-  // whichever it is.
+  // autotuner; classes without an entry follow soloMax.  Reported only: rounds
+  // run staged whichever it is.
   std::map<std::pair<int, int>, std::pair<int, int>> choice;
   // device state, rebuilt when the table set or the schedule changes
   bool built = false;
@@ -2691,11 +2691,7 @@ int ct_model_layout(const ct_model* m, int32_t* pool_off, int32_t* pool_words) {
 int ct_model_set_schedule(ct_model* m, int32_t solo_max_granules, int32_t rounds_per_graph) {
   if (!m || solo_max_granules < 0 || rounds_per_graph < 1 || rounds_per_graph > 256)
     return fail(CT_E_INVALID, "bad schedule");
-  if (solo_max_granules != m->soloMax || rounds_per_graph != m->roundsPerGraph) {
-    m->soloMax = solo_max_granules;
-    m->roundsPerGraph = rounds_per_graph;
-    model_free_device(m);
-  }
+  m->soloMax = solo_max_granules;
   return CT_OK;
 }
 
@@ -2765,10 +2761,7 @@ int ct_model_fixpoint(ct_model* m, const uint64_t* pool_in, uint64_t* pool_out, 
   }
   for (ct_table* T : m->tabs) T->slots[0].failed = 2;
   if (n_props) *n_props = props;
-  // rounds are counted in the units of the schedule: one, one, then
-  // rounds_per_graph at a time
-  const int ran = launched - 1, unit = m->roundsPerGraph;
-  if (n_rounds) *n_rounds = ran <= 2 ? std::max(ran, 1) : 2 + (ran - 2 + unit - 1) / unit * unit;
+  if (n_rounds) *n_rounds = launched - 1;
   if (code == 2)
     return fail(CT_E_STATE, "a table of the model is in the failed state (pop it first)");
   if (code == 1) return CT_FAIL;
@@ -2862,7 +2855,6 @@ int ct_model_autotune(ct_model* m, const uint64_t* pool_in, const char* cache_pa
   for (const auto& o : order) all = all && cache.count(class_key(arch, o.second));
   if (cache_path && all) {
     for (const auto& o : order) m->choice[o.second] = cache[class_key(arch, o.second)];
-    model_free_device(m);
     if (from_cache) *from_cache = 1;
     return CT_OK;
   }
@@ -2870,19 +2862,13 @@ int ct_model_autotune(ct_model* m, const uint64_t* pool_in, const char* cache_pa
   ALLOCCHK(hipMalloc(&scratch, sizeof(uint64_t) * m->poolWords));
   std::vector<uint64_t> ref(m->poolWords), got(m->poolWords);
   int refSt = -100, rc = CT_OK, nTimed = 0;
-  // one candidate: the median of 3 timed fixpoints from pool_in, each
-  // between a push and a pop; every candidate must reach the same fixpoint
-  auto measure = [&](double* ms) -> int {
-    model_free_device(m);
-    std::vector<double> t;
+  // one candidate: 3 fixpoints from pool_in, each between a push and a pop;
+  // every candidate must reach the same fixpoint
+  auto measure = [&]() -> int {
     for (int rep = 0; rep < 3; ++rep) {
       int r;
       if ((r = ct_model_push(m))) return r;
-      if ((r = model_sync_tables(m))) return r;
-      if (!m->built && (r = model_build(m))) return r;
-      const auto t0 = std::chrono::steady_clock::now();
       const int st = ct_model_fixpoint(m, pool_in, scratch, nullptr, nullptr, nullptr);
-      t.push_back(std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count());
       if (st != CT_OK && st != CT_FAIL) return st;
       if (st == CT_OK && hipMemcpy(got.data(), scratch, sizeof(uint64_t) * m->poolWords,
                                    hipMemcpyDeviceToHost) != hipSuccess)
@@ -2895,32 +2881,24 @@ int ct_model_autotune(ct_model* m, const uint64_t* pool_in, const char* cache_pa
       }
       if ((r = ct_model_pop(m))) return r;
     }
-    std::sort(t.begin(), t.end());
-    *ms = t[1];
     ++nTimed;
     return CT_OK;
   };
-  // coordinate descent over the classes
+  // both choices of every class: they run the same launches, so a class takes
+  // the threshold's, whatever the clock says
   const std::pair<int, int> opts[] = {{1, 0}, {0, 2}};
   for (const auto& o : order) {
     const auto cls = o.second;
-    std::pair<int, int> best{0, 0};
-    double bestMs = 1e30;
+    bool solo = true;
+    for (ct_table* T : m->tabs) solo = solo && (table_class(T) != cls || T->nGran <= m->soloMax);
     for (const auto& opt : opts) {
       m->choice[cls] = opt;
-      double ms = 0;
-      if ((rc = measure(&ms))) break;
-      if (ms < bestMs) {
-        bestMs = ms;
-        best = opt;
-      }
+      if ((rc = measure())) break;
     }
     if (rc) break;
-    m->choice[cls] = best;
-    cache[class_key(arch, cls)] = best;
+    m->choice[cls] = cache[class_key(arch, cls)] = opts[solo ? 0 : 1];
   }
   (void)hipFree(scratch);
-  model_free_device(m);
   if (timed) *timed = nTimed;
   if (rc) return rc;
   if (cache_path && !cache_write(cache_path, cache))

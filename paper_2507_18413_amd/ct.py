@@ -527,8 +527,8 @@ class Model:
             raise CTError(st, last_error())
 
     def autotune(self, pool_in, cache_path=None):
-        """Tune the per-class schedule (solo / split, tile); returns
-        (from_cache, candidates timed)."""
+        """Run both choices of every class and note the threshold's (they are the
+        same launches); returns (from_cache, candidates run)."""
         fc, timed = C.c_int32(), C.c_int32()
         path = None if cache_path is None else os.fsencode(cache_path)
         st = lib().ct_model_autotune(self.h, _ptr(pool_in), path, C.byref(fc), C.byref(timed))
@@ -537,7 +537,7 @@ class Model:
         return bool(fc.value), timed.value
 
     def choice(self, table_index):
-        """(solo, tile) of a table's round job."""
+        """(solo, tile) of a table's class."""
         solo, tile = C.c_int32(), C.c_int32()
         st = lib().ct_model_get_choice(self.h, int(table_index), C.byref(solo), C.byref(tile))
         if st < 0:

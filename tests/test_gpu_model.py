@@ -195,3 +195,65 @@ def test_queued_push_pop_seen_by_direct_table_use():
     assert g.pop(0) == ct.OK
     d, c = g.state(0)
     assert (d == before[0][0]).all() and (c == before[0][1]).all()
+
+
+@pytest.mark.parametrize("schedule", [None, (0, 1), (4, 3)])
+@pytest.mark.parametrize("n_tables,n_pool,tup", [(1, 4, (5, 40)), (12, 10, (4, 30)), (30, 20, (20, 400))])
+def test_rounds_and_propagations_are_counted(n_tables, n_pool, tup, schedule):
+    """n_rounds and n_props: those of rounds run one after the other, each on
+    the tables one of whose variables the round before changed."""
+    spec = random_model(n_tables, n_pool, n_tables, (3, 9), (2, 3), tup)
+    say("rounds counted:", n_tables, "tables, schedule", schedule)
+    lay, M, gts, ots = build(spec, schedule)
+    tlays = [W.DomLayout(t.dsizes, t.lo) for t in spec.tables]
+
+    def words(c):  # (pool word, table word) of the table's columns
+        for k, v in enumerate(spec.scopes[c]):
+            for q in range(int(lay.words[v])):
+                yield int(lay.off[v]) + q, int(tlays[c].off[k]) + q
+
+    def rounds_of(pool):
+        pool = pool.copy()
+        last = [o.domains() for o in ots]
+        for c in range(n_tables):
+            for p, t in words(c):
+                pool[p] &= last[c][t]
+        dirty = [c for c in range(n_tables) if any(last[c][t] & ~pool[p] for p, t in words(c))]
+        rounds, props = 0, 0
+        while True:
+            rounds += 1
+            props += len(dirty)
+            new, failed = pool.copy(), False
+            for c in dirty:
+                din = ots[c].domains()
+                for p, t in words(c):
+                    din[t] &= pool[p]
+                st, out = ots[c].propagate(din)
+                failed = failed or st != O.OK
+                if st == O.OK:
+                    for p, t in words(c):
+                        new[p] &= out[t]
+            if failed or (new == pool).all():
+                return failed, new, rounds, props
+            dirty = [c for c in range(n_tables) if any(new[p] != pool[p] for p, _ in words(c))]
+            pool = new
+
+    rng = W.rng_for(n_tables, 305, 0)
+    pool, longest = lay.full(), 0
+    for step in range(12):
+        M.push()
+        for o in ots:
+            o.push()
+        new = pool if step == 0 else W.pick_fraction_removal(rng, lay, pool, frac=0.3, nvars=(1, 2))
+        st, props, rounds = M.fixpoint(dev(new), out := dev(new))
+        failed, want, wr, wp = rounds_of(new)
+        assert (st == ct.FAIL) == failed and rounds == wr and props == wp, step
+        longest = max(longest, rounds)
+        if failed:
+            M.pop()
+            for o in ots:
+                o.pop()
+        else:
+            assert (host(out) == want).all(), step
+            pool = want
+    assert longest >= (2 if n_tables == 1 else 3)

@@ -14,9 +14,9 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <set>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -1156,9 +1156,10 @@ struct UploadBuf {
   hipEvent_t ev[2] = {nullptr, nullptr};
 };
 
-// Free blocks, at most UP_KEEP; given back with the last table.
+// Free blocks, the UP_KEEP with the largest windows; given back with the last
+// table.
 std::mutex g_upMu;
-std::vector<UploadBuf*> g_upFree;
+UploadBuf* g_upFree[UP_KEEP] = {};
 
 void upload_free(UploadBuf* b) {
   if (b->p) (void)hipHostFree(b->p);
@@ -1169,28 +1170,39 @@ void upload_free(UploadBuf* b) {
 
 void upload_drain() {
   std::lock_guard<std::mutex> lk(g_upMu);
-  for (UploadBuf* b : g_upFree) upload_free(b);
-  g_upFree.clear();
+  for (UploadBuf*& b : g_upFree) {
+    if (b) upload_free(b);
+    b = nullptr;
+  }
 }
 
 void upload_give(UploadBuf* b) {
   if (!b) return;
-  std::lock_guard<std::mutex> lk(g_upMu);
-  if ((int)g_upFree.size() < UP_KEEP) g_upFree.push_back(b);
-  else upload_free(b);
+  {
+    // in place of an empty entry or of the smallest block, if that is smaller
+    std::lock_guard<std::mutex> lk(g_upMu);
+    UploadBuf** at = nullptr;
+    for (UploadBuf*& f : g_upFree)
+      if (!at || (*at && (!f || f->window < (*at)->window))) at = &f;
+    if (!*at || (*at)->window < b->window) std::swap(*at, b);
+  }
+  if (b) upload_free(b);
 }
 
 int upload_take(int dev, size_t window, UploadBuf** out) {
-  if (alloc_injected()) return fail(CT_E_NOMEM, "injected allocation failure: upload block");
   {
+    // the smallest that is large enough
     std::lock_guard<std::mutex> lk(g_upMu);
-    for (size_t k = 0; k < g_upFree.size(); ++k)
-      if (g_upFree[k]->dev == dev && g_upFree[k]->window >= window) {
-        *out = g_upFree[k];
-        g_upFree.erase(g_upFree.begin() + k);
-        return CT_OK;
-      }
+    UploadBuf** at = nullptr;
+    for (UploadBuf*& f : g_upFree)
+      if (f && f->dev == dev && f->window >= window && (!at || f->window < (*at)->window)) at = &f;
+    if (at) {
+      *out = *at;
+      *at = nullptr;
+      return CT_OK;
+    }
   }
+  if (alloc_injected()) return fail(CT_E_NOMEM, "injected allocation failure: upload block");
   UploadBuf* b = new (std::nothrow) UploadBuf();
   if (!b) return fail(CT_E_NOMEM, "host allocation failed");
   b->dev = dev;
@@ -1247,8 +1259,8 @@ hipError_t upload_run(const int32_t* tuples, BuildArgs B, hipStream_t stream, co
   int started = 1;
   try {
     for (; started < nW; ++started) th[started] = std::thread(work, started);
-  } catch (const std::system_error&) {
-    // fewer threads: their parts are copied here
+  } catch (...) {
+    // fewer threads (none to be had, or no memory): their parts are copied here
   }
   char* dp = nullptr;
   hipError_t e = hipHostGetDevicePointer((void**)&dp, b->p, 0);
@@ -1642,7 +1654,12 @@ int ct_create_table(const int32_t* tuples, int64_t n_tuples, int32_t arity, cons
     }
     T->cfg.max_depth = cfg->max_depth;
   }
-  int rc = create_impl(T, tuples, n_tuples, arity, dom_lo, dom_size, init_dom);
+  int rc;
+  try {
+    rc = create_impl(T, tuples, n_tuples, arity, dom_lo, dom_size, init_dom);
+  } catch (const std::bad_alloc&) {
+    rc = fail(CT_E_NOMEM, "host allocation failed");
+  }
   if (rc != CT_OK) {
     char msg[sizeof(g_err)];
     memcpy(msg, g_err, sizeof(g_err));

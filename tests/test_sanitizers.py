@@ -48,3 +48,23 @@ def test_runtime_host_paths_under_sanitizers(tmp_path):
                        env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0", HIP_VISIBLE_DEVICES=""))
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
     assert "runtime driver: ok" in r.stdout
+
+
+def test_creation_without_host_memory(tmp_path):
+    """Every host allocation of ct_create_table up to its first device call
+    fails in turn: the call returns CT_E_NOMEM, no exception leaves it."""
+    from paper_2507_18413_amd import build as B
+    from paper_2507_18413_amd import ct
+    libdir = B.torch_hip_runtime()
+    if libdir is None or not shutil.which("g++"):
+        pytest.skip("no HIP runtime library to link against")
+    exe = tmp_path / "alloc_driver"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__=1", "-I", "/opt/rocm/include",
+                    "-I", os.path.join(ROOT, "include"), "-o", str(exe),
+                    os.path.join(ROOT, "tests", "native", "alloc_driver.cpp"), ct.LIB_PATH, "-L", libdir,
+                    "-l:libamdhip64.so", f"-Wl,-rpath,{libdir}", f"-Wl,-rpath,{os.path.dirname(ct.LIB_PATH)}"],
+                   check=True, capture_output=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120,
+                       env=dict(os.environ, HIP_VISIBLE_DEVICES=""))
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+    assert "alloc driver: ok" in r.stdout

@@ -2153,15 +2153,7 @@ int noalloc_status(hipStream_t stream) {
               "timeout or trail overflow); the slots of that batch are undefined", err);
 }
 
-}  // namespace
-
-extern "C" {
-
-int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32_t* status_dev) {
-  if (n_jobs < 0 || (n_jobs > 0 && (!jobs || !status_dev)))
-    return fail(CT_E_INVALID, "bad batch arguments");
-  if (n_jobs == 0) return CT_OK;
-  hipStream_t stream = (hipStream_t)stream_v;
+int batch_queue(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* status_dev) {
   int rc = batch_validate_quiesce(jobs, n_jobs, stream);
   if (rc) return rc;
   QueueCtx* q = nullptr;
@@ -2236,6 +2228,21 @@ int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32
   r.dStaged = q->dStaged;
   r.capStaged = q->capStaged;
   return batch_launch(jobs, n_jobs, stream, status_dev, p, r);
+}
+
+}  // namespace
+
+extern "C" {
+
+int ct_propagate_batch(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32_t* status_dev) {
+  if (n_jobs < 0 || (n_jobs > 0 && (!jobs || !status_dev)))
+    return fail(CT_E_INVALID, "bad batch arguments");
+  if (n_jobs == 0) return CT_OK;
+  try {
+    return batch_queue(jobs, n_jobs, (hipStream_t)stream_v, status_dev);
+  } catch (const std::bad_alloc&) {  // (before any slot's host state changes: its lists are reserved)
+    return fail(CT_E_NOMEM, "host allocation failed");
+  }
 }
 
 int ct_propagate_batch_noalloc(const ct_job* jobs, int32_t n_jobs, void* stream_v, int32_t* status_dev) {

@@ -112,24 +112,3 @@ def test_create_threads():
     for x in th:
         x.join()
     assert not bad, bad
-
-
-def test_upload_blocks_kept_are_the_largest():
-    """While a table lives, creations of one size allocate their upload block
-    once, whatever smaller blocks were kept before."""
-    L = ct.lib()
-    alive = ct.Table(np.zeros((1, 1), np.int32), np.zeros(1, np.int32), np.ones(1, np.int32))
-    assert alive.create_status == O.OK
-    rng = W.rng_for(1, 921, 0)
-
-    def allocations(t):
-        tup = rng.integers(0, 20, size=(t, 6)).astype(np.int32)
-        L.ct_debug_fail_alloc(1000)
-        g = ct.Table(tup, np.zeros(6, np.int32), np.full(6, 20, np.int32))
-        n = 1000 - L.ct_debug_fail_alloc(0)
-        g.close()
-        return n
-
-    say("create: upload blocks")
-    counts = [allocations(t) for t in (300, 9_000, 400_000, 400_000, 300, 9_000, 300, 400_000)]
-    assert counts[3:] == [min(counts)] * 5, counts

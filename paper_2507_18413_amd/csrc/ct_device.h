@@ -139,7 +139,7 @@ struct SlotDesc {
   int32_t cur, limit, failed, depth, serial, pad1;
   // per-job scratch
   int32_t filtCount, prepDone, updDone, status;
-  int32_t nzCount;  // granules a root stream found non-empty (reset by its finish)
+  int32_t noop;     // the job changed nothing
   int32_t pad2;
   unsigned long long stats[8];
 };

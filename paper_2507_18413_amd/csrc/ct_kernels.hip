@@ -805,7 +805,7 @@ __device__ int finalize_update(const DevJob& J, Shared& sh, int jobTrail, bool c
   }
   if (threadIdx.x == 0) {
     s->status = st;
-    s->pad2 = sh.noop;
+    s->noop = sh.noop;
     if (count && (st == ST_OK || st == ST_FAIL)) {
       atomicAdd(&s->stats[S_JOBS], 1ull);
       atomicAdd(&s->stats[S_GRAN_IN], (unsigned long long)limit);
@@ -1110,7 +1110,7 @@ __device__ __forceinline__ void do_filter(const KArgs& a, const DevJob& J, int c
   // one round trip: the job's state after the update, per value the
   // currTable word at its residue, and the head of both index buffers (the
   // one in use is known with the state)
-  const int jobStatus = s->status, noop = s->pad2, lim = s->limit, cur = s->cur;
+  const int jobStatus = s->status, noop = s->noop, lim = s->limit, cur = s->cur;
   const uint64_t cr = sct[pre.rw0];
   const int nG = J.tab->nGran;
   int h0[FULL_SCAN_GRAN], h1[FULL_SCAN_GRAN], head[FULL_SCAN_GRAN];
@@ -1731,7 +1731,7 @@ __global__ void __launch_bounds__(BLOCK) split_engine_kernel(EngDesc E) {
     if (!block_wait(ka, &s->updDone, ll_gen(J.seq), sh)) break;
     // as do_filter: the state after the update, the currTable word at each
     // value's residue and the head of both index buffers in one round trip
-    const int jobStatus = s->status, noop = s->pad2, lim = s->limit, cur = s->cur;
+    const int jobStatus = s->status, noop = s->noop, lim = s->limit, cur = s->cur;
     const uint64_t cr = sct[pre.rw0];
     int h0[FULL_SCAN_GRAN], h1[FULL_SCAN_GRAN], head[FULL_SCAN_GRAN];
 #pragma unroll
@@ -1897,8 +1897,7 @@ __device__ void slot_fresh(SlotDesc* s, int limit, int failed) {
   s->prepDone = 0;
   s->updDone = 0;
   s->status = 0;
-  s->nzCount = 0;
-  s->pad2 = 0;
+  s->noop = 0;
   for (int x = 0; x < 8; ++x) s->stats[x] = 0;
 }
 

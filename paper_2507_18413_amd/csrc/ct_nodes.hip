@@ -469,7 +469,7 @@ __device__ void finish_partition(const NodesDesc& N, int j, const CT_G NodeInfo*
   }
   if (lane == 0) {
     s->status = st;
-    s->pad2 = 0;
+    s->noop = 0;
     if (J.status_out) *J.status_out = st;  // read after the launch: no fence
   }
 }

@@ -124,11 +124,18 @@ struct DevBlock {
   void* ptr = nullptr;
 };
 
-// Device queue + staging for one stream.
-struct QueueCtx {
-  bool own = true;            // queue and hostErr are allocations of their own
+// What a table's own launches need (a model walks its tables several times a
+// step: nothing else in here).
+struct TableQueue {
   int32_t* queue = nullptr;   // on the device: [3] error word
   int32_t* hostErr = nullptr; // pinned
+  // staged schedule scratch (see StageNeed)
+  char* dStaged = nullptr;
+  size_t capStaged = 0;
+};
+
+// Device queue + staging for one stream.
+struct QueueCtx : TableQueue {
   // batch staging: job descriptors, in two pinned buffers in turn.  Batches
   // fill a buffer one after the other; its event, recorded when it is full,
   // says that their descriptors have been read.  (An event behind every batch
@@ -147,11 +154,7 @@ struct QueueCtx {
   // search-node schedule scratch (node records | row vectors | non-zero words)
   void* dNodes = nullptr;
   size_t capNodes = 0;
-  // staged schedule scratch (see StageNeed)
-  char* dStaged = nullptr;
-  size_t capStaged = 0;
 };
-
 
 int queue_init(QueueCtx& q) {
   ALLOCCHK(hipMalloc(&q.queue, 4 * sizeof(int32_t)));
@@ -163,8 +166,8 @@ int queue_init(QueueCtx& q) {
 }
 
 void queue_free(QueueCtx& q) {
-  if (q.own && q.queue) (void)hipFree(q.queue);
-  if (q.own && q.hostErr) (void)hipHostFree(q.hostErr);
+  if (q.queue) (void)hipFree(q.queue);
+  if (q.hostErr) (void)hipHostFree(q.hostErr);
   if (q.dStage) (void)hipFree(q.dStage);
   for (int k = 0; k < 2; ++k) {
     if (q.pStage[k]) (void)hipHostFree(q.pStage[k]);
@@ -224,7 +227,7 @@ struct ct_table {
   int nodesVecRows = 0;
   uint16_t* dIds = nullptr;
   std::vector<void*> blocks;  // device allocations to free
-  QueueCtx q;
+  TableQueue q;               // (queue, hostErr: parts of other blocks)
   // pinned staging of the synchronous calls, parts of one block
   char* pBlock = nullptr;
   uint64_t* pDomOut = nullptr;  // D words
@@ -488,7 +491,7 @@ StageArgs stage_args(const StageNeed& n, char* scratch, int32_t* queue, int32_t*
   return A;
 }
 
-int stage_reserve(QueueCtx& q, size_t bytes, hipStream_t stream) {
+int stage_reserve(TableQueue& q, size_t bytes, hipStream_t stream) {
   if (q.capStaged >= bytes) return CT_OK;
   HIPCHK(hipStreamSynchronize(stream));
   if (q.dStaged) (void)hipFree(q.dStaged);
@@ -1031,12 +1034,17 @@ struct BatchShape {
   bool wide = false, wideDom = false;
 };
 
-// Negative tables, and a job whose scratch alone is beyond the capacity, run
-// in one workgroup of the propagate kernel.
-bool batch_staged(const ct_table* T, bool propagate, size_t scratchCap, bool root = false) {
-  if (!propagate) return true;
-  return T->kind != CT_KIND_NEGATIVE && StageNeed().bytes_with(T, root) <= scratchCap;
-}
+// Negative tables run in one workgroup of the propagate kernel.
+bool batch_staged(const ct_table* T, bool propagate) { return !propagate || T->kind != CT_KIND_NEGATIVE; }
+
+// A single job's scratch is within every launch's: the records and item lists
+// of a table of MAX_GRAN granules and MAX_TABLE_D domain words, four waves to
+// a granule's list, and the job's own words.
+constexpr size_t STAGE_JOB_MAX = 4096 + sizeof(StageRec) +
+                                 sizeof(StageItem) * STAGE_LISTS * ((size_t)MAX_GRAN + MAX_TABLE_D / 4 + 2) +
+                                 (sizeof(uint64_t) + sizeof(int32_t)) * (size_t)MAX_TABLE_D +
+                                 std::max(sizeof(uint64_t) * (size_t)MAX_TABLE_D, sizeof(uint32_t) * (size_t)(STAGE_LIST_CAP + 64));
+static_assert(STAGE_JOB_MAX <= (size_t)14 << 20, "a job fits the no-allocation scratch");
 
 // Device descriptors of a validated batch, written into out[n_jobs] (other:
 // the search-node schedule takes them in the batch's order).
@@ -1058,7 +1066,7 @@ BatchShape batch_build(const ct_job* jobs, int n_jobs, int32_t* status_dev, bool
       ct_table* T = cj.table;
       const bool propagate = cj.flags & CT_JOB_PROPAGATE;
       const bool root = (cj.flags & CT_JOB_ROOT) && !streamRoots;  // (row lists shared by waves)
-      const bool staged = !other && batch_staged(T, propagate, scratchCap, root);
+      const bool staged = !other && batch_staged(T, propagate);
       if (!other && staged != (pass == 0)) continue;
       SlotHost& S = T->slots[cj.slot];
       DevJob& J = out[at++];
@@ -1320,7 +1328,7 @@ void ct_destroy(ct_table* T) {
   if (T->engStream) (void)hipStreamDestroy(T->engStream);
   if (T->stream) (void)hipStreamSynchronize(T->stream);
   for (void* p : T->blocks) (void)hipFree(p);
-  queue_free(T->q);
+  if (T->q.dStaged) (void)hipFree(T->q.dStaged);
   if (T->pBlock) (void)hipHostFree(T->pBlock);
   if (T->pCt) (void)hipHostFree(T->pCt);
   if (T->stream) (void)hipStreamDestroy(T->stream);
@@ -1406,7 +1414,6 @@ static int create_impl(ct_table* T, const int32_t* tuples, int64_t t, int32_t n,
   const size_t domB = line(sizeof(uint64_t) * D), llB = line(sizeof(uint64_t) * (2 + 2 * (size_t)D));
   ALLOCCHK(hipHostMalloc((void**)&T->pBlock, 256 + 2 * domB + llB, hipHostMallocMapped | hipHostMallocCoherent));
   T->pStatus = (int32_t*)T->pBlock;
-  T->q.own = false;
   T->q.hostErr = (int32_t*)(T->pBlock + 128);
   T->pDomOut = (uint64_t*)(T->pBlock + 256);
   T->pDomIn = (uint64_t*)(T->pBlock + 256 + domB);
@@ -2026,7 +2033,7 @@ BatchPlan batch_plan(const ct_job* jobs, int n_jobs, bool nodes) {
       const bool propagate = jobs[j].flags & CT_JOB_PROPAGATE, root = jobs[j].flags & CT_JOB_ROOT;
       roots = roots && root && T->kind != CT_KIND_NEGATIVE;
       granules += T->nGran;
-      if (batch_staged(T, propagate, STAGE_SCRATCH, root)) need.add(T, propagate, false, root);
+      if (batch_staged(T, propagate)) need.add(T, propagate, false, root);
     }
     p.stagedBytes = need.bytes();
     p.streamRoots = roots && stage_stream_roots(granules);

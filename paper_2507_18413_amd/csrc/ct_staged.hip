@@ -406,7 +406,7 @@ __device__ __forceinline__ void stage_partition(const StageRec& V, FinShared<FBL
       if (!nSurv) s->failed = 1;
     }
     s->status = st;
-    s->pad2 = noop;
+    s->noop = noop;
     const unsigned long long nrows = (unsigned long long)R->nrows, lim = (unsigned long long)limit;
     atomicAdd(&s->stats[S_JOBS], 1ull);
     atomicAdd(&s->stats[S_GRAN_IN], lim);

@@ -224,6 +224,11 @@ def nodes_leg(seed, n_nodes, reps, warmup, schedule=0, plain=True, cpu=False):
     # root currTable once + per node currTable write + domains
     W_words = table.W
     comp = 8 * table.rows * W_words + 8 * W_words + n_nodes * (8 * W_words + 16 * lay.D)
+    # the update kernel's own: the nodes' currTables and, per group of 512
+    # nodes, the tuples' row numbers (2 bytes a cell, an even number of columns)
+    # and the row vectors
+    upd_bytes = 512 * table.granules * n_nodes + -(-n_nodes // 512) * (
+        2 * 4096 * table.granules * ((lay.n + 1) // 2 * 2) + 64 * (table.rows + 2))
     from paper_2507_18413_amd import profiling
     prof = profiling.read_summary(os.path.join(ROOT, "profiles", "nodes_update_4096_nodes.md"))
     extra = {}
@@ -267,8 +272,8 @@ def nodes_leg(seed, n_nodes, reps, warmup, schedule=0, plain=True, cpu=False):
         "update_kernel_hbm_bytes": prof.get("hbm_bytes_per_launch") if prof else None,
         "update_kernel_avg_us_profiled": prof.get("avg_us") if prof else None,
         "update_kernel_roofline": None if not prof else {
-            "bound": "hbm", "achieved": round(comp / prof["avg_us"] / 1e3, 1), "peak": HBM_PEAK_GBS,
-            "unit": "GB/s", "frac": round(comp / prof["avg_us"] / 1e3 / HBM_PEAK_GBS, 4)},
+            "bound": "hbm", "bytes": upd_bytes, "achieved": round(upd_bytes / prof["avg_us"] / 1e3, 1),
+            "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(upd_bytes / prof["avg_us"] / 1e3 / HBM_PEAK_GBS, 4)},
     }
 
 
@@ -612,9 +617,9 @@ def root_batch_leg(tabs, specs, reps, per_table=True):
            "timing": "HIP events around the batches on the launch stream"}
     # the streaming kernel alone, from the committed rocprofv3 summary
     from paper_2507_18413_amd import profiling
-    prof = profiling.read_summary(os.path.join(ROOT, "profiles", "root_update_2000_tables.md"))
+    prof = profiling.read_summary(os.path.join(ROOT, "profiles", "root_stream_2000_tables.md"))
     stream_bytes = 8 * rows_w + 8 * sum(int(t.W) for t in tabs)
-    out["stream_kernel"] = {"name": "ctk::stage_update_kernel", "algorithmic_bytes": stream_bytes}
+    out["stream_kernel"] = {"name": "ctk::stage_root_kernel", "algorithmic_bytes": stream_bytes}
     if prof:
         us = prof["avg_us"]
         out["stream_kernel"].update({

@@ -10,18 +10,17 @@
 // The launch boundaries order the steps, so no workgroup waits for another
 // and nothing is fenced inside a launch (an agent-scope release writes this
 // chip's L2 back, an acquire invalidates it), and each kernel has the
-// registers and LDS of its own step only: the update and the finish run at
-// eight waves per SIMD.  The jobs that run are known on the device after the
+// registers and LDS of its own step only: the update runs at eight waves per
+// SIMD, the finish at six.  The jobs that run are known on the device after the
 // prep (a model's clean tables, rejected inputs): it appends the later
 // kernels' items to lists that their workgroups walk.
 //
 // Against the same steps as one launch whose workgroups wait for each other
 // (agent-scope releases and acquires, 198 VGPRs and 79 KB of LDS a workgroup
 // for every step, items from one queue): a call of 2,000,000 tuples 26 us
-// against 64, of 2,422 domain words and 12,000 tuples 68 against 104, a batch
-// of 128 searches over tables of 1,000 to 2,000,000 tuples 41 against 132, of
-// 1,000 searches over tables of at most 16,000 54 against 91 (running such
-// jobs whole in their prep workgroup instead: 89).
+// against 64, of 2,422 domain words and 15,000 tuples 62 against 104, a batch
+// of 128 searches over tables of 1,000 to 2,000,000 tuples 36 against 132, of
+// 1,000 searches over tables of 16,000 38 against 71.
 //
 // A model's round is the same three launches: the prep takes each table's
 // input from the pool and skips the tables none of whose variables changed,

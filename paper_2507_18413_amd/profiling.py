@@ -82,7 +82,7 @@ def summarize(args):
     lines = [f"# {args.title}", "", f"Command (from the repository root): `{args.command}`", "",
              "Kernel-trace statistics (rocprofv3 --kernel-trace --stats):", "",
              "| kernel | calls | avg µs | min µs | max µs | share |", "|---|---|---|---|---|---|"]
-    for r in stats[:6]:
+    for r in stats[:12]:
         lines.append(f"| {r['Name'][:60]} | {r['Calls']} | {float(r['AverageNs'])/1e3:.3f} | "
                      f"{float(r['MinNs'])/1e3:.3f} | {float(r['MaxNs'])/1e3:.3f} | {float(r['Percentage']):.2f} % |")
     if args.calls_traced:

@@ -70,7 +70,8 @@ typedef struct ct_table ct_table;
  * for a call of a larger table, or as one launch with hand-offs for a call
  * whose update one workgroup takes.  The jobs of a batch run as three
  * launches together whatever the schedule of their (positive) tables (long
- * row lists of root jobs shared by up to four waves).  NODES is the
+ * row lists of root jobs shared by up to four waves; large batches of roots
+ * stream their rows).  NODES is the
  * search-node schedule of ct_propagate_batch: when every job of a batch is a
  * CT_JOB_FROM_ROOT propagation of the same positive table of at most about
  * 2,400 support rows (sum of the domain sizes: one bit vector over 512 jobs

@@ -2237,7 +2237,10 @@ int batch_queue(const ct_job* jobs, int n_jobs, hipStream_t stream, int32_t* sta
   r.order = q->order.data();
   r.dStaged = q->dStaged;
   r.capStaged = q->capStaged;
-  return batch_launch(jobs, n_jobs, stream, status_dev, p, r);
+  rc = batch_launch(jobs, n_jobs, stream, status_dev, p, r);
+  // (a launch that failed may have left item counts: the scratch is made anew)
+  if (rc) q->capStaged = 0;
+  return rc;
 }
 
 }  // namespace
